@@ -177,6 +177,50 @@ def run(st):
     return [st["cache"].k_cache, st["cache"].v_cache]
 
 
+def _exact_attention(st, case):
+    """Outputs, frame attention scores [H, 3] and log-sum-exp [H, Nq] of the queries in `st`, in 64 bits."""
+    Nq, sink, win = _sizes(case)
+    H, d, scale = len(sink), case["d"], st["scale"]
+    if "cache" in st:
+        k_hist, v_hist, off = st["cache"].k_cache, st["cache"].v_cache, list(st["cache"].head_row_off)
+    else:
+        k_hist, v_hist, off = st["k_hist"], st.get("v_hist"), st["off"]
+    q, values = st["q"][:: case["stride"]], v_hist is not None
+    n = q.shape[0]
+    out = torch.empty(n, H, d, dtype=torch.float64, device=_DEVICE)
+    F = torch.zeros(H, 3, dtype=torch.float64, device=_DEVICE)
+    lse = torch.empty(H, n, dtype=torch.float64, device=_DEVICE)
+    for h in range(H):
+        keys = torch.cat([k_hist[off[h]:off[h] + sink[h] + win[h]], st["k_cur"][:, h]]).double()
+        vals = torch.cat([v_hist[off[h]:off[h] + sink[h] + win[h]], st["v_cur"][:, h]]).double() if values else None
+        rows = max(1, 100_000_000 // keys.shape[0])
+        for r in range(0, n, rows):
+            logits = (q[r:r + rows, h].double() @ keys.t()).mul_(scale)
+            lse[h, r:r + rows] = torch.logsumexp(logits, 1)
+            p = logits.sub_(lse[h, r:r + rows, None]).exp_()
+            for i, part in enumerate((p[:, :sink[h]], p[:, sink[h]:sink[h] + win[h]], p[:, sink[h] + win[h]:])):
+                F[h, i] += part.sum()
+            if values:
+                out[r:r + rows, h] = p @ vals
+    return out, F / n, lse
+
+
+def exact(case, seed):
+    """What run returns, by plain torch in 64 bits; the copies (pack, append, the cache of a step) have no sums to compare."""
+    kind = case["kind"]
+    if kind in ("pack", "append"):
+        return None
+    st = prepare(case, seed)
+    out, F, lse = _exact_attention(st, case)
+    if kind == "attn":
+        return [out] + [F] * case["score"] + [lse] * case["lse"]
+    if kind == "step":
+        return [out, None, None]
+    if kind == "score":
+        return F
+    return [F, None, F[:, 0] + F[:, 1]]
+
+
 def work(case):
     Nq, sink, win = _sizes(case)
     H, d, kind = len(sink), case["d"], case["kind"]
