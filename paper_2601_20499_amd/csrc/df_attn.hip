@@ -19,8 +19,8 @@
 // that does not end its unit is done early - its sums (m, l, region sums,
 // unnormalised O in fp32) go to the workspace and a flag goes up - and the
 // piece that ends a unit is the last thing a workgroup does: it waits for the
-// flags of the earlier pieces, folds their sums and its own in key order and
-// writes the result.  This
+// flags of the earlier pieces, folds their sums into its own from the nearest
+// piece back to the unit's first and writes the result.  This
 // needs every workgroup of the launch on the device at once; when the device
 // cannot hold them all, the pieces are left in the workspace and a second kernel
 // puts them together in the same order with the same arithmetic.  Teams are laid
@@ -211,19 +211,7 @@ __device__ __forceinline__ void store4_through(float *ptr, float a, float b, flo
   const f32x4 v = {a, b, c, d};
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(ptr), "v"(v) : "memory");
 }
-// Four 16-byte loads at ptr + i * stride floats; returns when the data is in the registers.
-__device__ __forceinline__ void load4x4_through(const float *ptr, int stride, f32x4 (&v)[4]) {
-  const float *p1 = ptr + stride, *p2 = ptr + 2 * stride, *p3 = ptr + 3 * stride;
-  asm volatile(
-      "global_load_dwordx4 %0, %4, off sc0 sc1\n\t"
-      "global_load_dwordx4 %1, %5, off sc0 sc1\n\t"
-      "global_load_dwordx4 %2, %6, off sc0 sc1\n\t"
-      "global_load_dwordx4 %3, %7, off sc0 sc1\n\t"
-      "s_waitcnt vmcnt(0)"
-      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-      : "v"(ptr), "v"(p1), "v"(p2), "v"(p3)
-      : "memory");
-}
+// One 16-byte load; returns when the data is in the registers.
 __device__ __forceinline__ f32x4 load4_through(const float *ptr) {
   f32x4 v;
   asm volatile("global_load_dwordx4 %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(ptr) : "memory");
@@ -307,7 +295,7 @@ __device__ __forceinline__ void load_slot_through<8>(const float *slot, int tid,
       : "memory");
 }
 
-// Weighted sum of the earlier pieces' value and a later piece's, written out so that both places that
+// Weighted sum of an earlier piece's value and the later pieces', written out so that both places that
 // put pieces together (in the main kernel and in the merge kernel) round in the same way.
 __device__ __forceinline__ float fold(float earlier, float w_earlier, float later, float w_later) {
   return __fmaf_rn(earlier, w_earlier, __fmul_rn(later, w_later));
@@ -767,92 +755,50 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // device: the rows then come out as NaN.
       int s_first = span - 1;                      // span that holds the unit's first tile
       while (s_first > 0 && span_begin(s_first, p.line_len, p.n_teams) > unit_lo) --s_first;
-      if (tid == 0) {
-        int all = 1;
-        for (int sp = s_first; sp < span; ++sp) {
+      if (wave == 0) {
+        // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
+        int ok = 1;
+        for (int sp = s_first + lane; sp < span; sp += 64) {
           unsigned long long *flag = p.flags + sp * p.team_size + member;
-          int ok = 0;
-          for (int spin = 0; spin < kSpinLimit && !ok; ++spin) {
-            ok = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
-            if (!ok) __builtin_amdgcn_s_sleep(16);
+          int up = 0;
+          for (int spin = 0; spin < kSpinLimit && !up; ++spin) {
+            up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
+            if (!up) __builtin_amdgcn_s_sleep(16);
           }
           // a flag has one reader: put it back, so that a replay of this launch (same epoch) starts clean
           __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-          all &= ok;
+          ok &= up;
         }
-        lds_ok = all;
+        if (lane == 0) lds_ok = __all(ok);
       }
       __syncthreads();
       const float poison = lds_ok ? 0.f : NAN;
-      // earlier pieces first, this one last: the same order and arithmetic as the merge kernel
-      if (s_first == span - 1) {
-        // the common case, one earlier piece: all of it is loaded with one wait (folding it into an empty sum
-        // would give back the same numbers)
-        const int which = unit_lo > span_begin(s_first, p.line_len, p.n_teams) ? 1 : 0;
-        const float *slot = p.slots + slot_index(p, s_first, which, member) * Slot<D>::kFloats;
+      // From this piece back to the unit's first, the order and arithmetic of the merge kernel: every earlier piece is
+      // folded into this one's registers, all of it loaded with one wait.  (Front to back the sum so far needs
+      // registers of its own, and the loads had to go out four at a time: with 6 pieces to a unit that was most of
+      // a small launch.)
+#pragma unroll 1
+      for (int sp = span - 1; sp >= s_first; --sp) {
+        const int which = unit_lo > span_begin(sp, p.line_len, p.n_teams) ? 1 : 0;
+        const float *slot = p.slots + slot_index(p, sp, which, member) * Slot<D>::kFloats;
         f32x4 st, v[D / 8];
         if constexpr (SCORE_ONLY) st = load4_through(Slot<D>::stats(const_cast<float *>(slot), tid));
         else load_slot_through<D / 8>(slot, tid, st, v);
-        const float m_new = fmaxf(st[0], m);
+        const float m_new = fmaxf(st[0], m_u);
         const float w_h = (st[0] == m_new) ? 1.f : fast_exp2((st[0] - m_new) * p.c);
-        const float w_t = (m == m_new) ? 1.f : fast_exp2((m - m_new) * p.c);
-        m_u = m_new + poison;
-        lt_u = fold(st[1], w_h, lt, w_t);
-        l1_u = fold(st[2], w_h, l1, w_t);
-        l2_u = fold(st[3], w_h, l2, w_t);
+        const float w_t = (m_u == m_new) ? 1.f : fast_exp2((m_u - m_new) * p.c);
+        m_u = m_new;
+        lt_u = fold(st[1], w_h, lt_u, w_t);
+        l1_u = fold(st[2], w_h, l1_u, w_t);
+        l2_u = fold(st[3], w_h, l2_u, w_t);
         if (!SCORE_ONLY) {
 #pragma unroll
           for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int cq = 0; cq < 4; ++cq)
-#pragma unroll
-              for (int e = 0; e < 4; ++e) o[db][4 * cq + e] = fold(v[db * 4 + cq][e], w_h, o[db][4 * cq + e], w_t);
-        }
-      } else {
-        float M = -INFINITY, Lt = 0.f, La = 0.f, Lb = 0.f;
-        f32x16 acc[DB];
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[db][v] = 0.f;
-#pragma unroll 1
-        for (int sp = s_first; sp < span; ++sp) {
-          const int which = unit_lo > span_begin(sp, p.line_len, p.n_teams) ? 1 : 0;
-          const float *slot = p.slots + slot_index(p, sp, which, member) * Slot<D>::kFloats;
-          const f32x4 st = load4_through(Slot<D>::stats(const_cast<float *>(slot), tid));
-          const float m_new = fmaxf(M, st[0]);
-          const float w_old = (M == m_new) ? 1.f : fast_exp2((M - m_new) * p.c);
-          const float w_new = (st[0] == m_new) ? 1.f : fast_exp2((st[0] - m_new) * p.c);
-          M = m_new;
-          Lt = fold(Lt, w_old, st[1], w_new);
-          La = fold(La, w_old, st[2], w_new);
-          Lb = fold(Lb, w_old, st[3], w_new);
-          if (!SCORE_ONLY) {
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-              f32x4 v[4];
-              load4x4_through(Slot<D>::ovec(const_cast<float *>(slot), tid, db * 4), kThreads * 4, v);
-#pragma unroll
-              for (int cq = 0; cq < 4; ++cq)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[db][4 * cq + e] = fold(acc[db][4 * cq + e], w_old, v[cq][e], w_new);
-            }
-          }
-        }
-        const float m_new = fmaxf(M, m);
-        const float w_h = (M == m_new) ? 1.f : fast_exp2((M - m_new) * p.c);
-        const float w_t = (m == m_new) ? 1.f : fast_exp2((m - m_new) * p.c);
-        m_u = m_new + poison;
-        lt_u = fold(Lt, w_h, lt, w_t);
-        l1_u = fold(La, w_h, l1, w_t);
-        l2_u = fold(Lb, w_h, l2, w_t);
-        if (!SCORE_ONLY) {
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[db][v] = fold(acc[db][v], w_h, o[db][v], w_t);
+            for (int e = 0; e < 16; ++e) o[db][e] = fold(v[db * 4 + e / 4][e % 4], w_h, o[db][e], w_t);
         }
       }
+      m_u += poison;
       __syncthreads();                             // lds_ok is free again
     }
     if (t_end == n_tiles && (t_begin == 0 || take)) {
@@ -889,7 +835,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 
 // Second kernel.  Workgroup (k, member; db) looks at the boundary between spans k-1 and k: if it falls
 // inside a head (not on its first column), the unit (group, head, member's query tile) was cut there
-// and is put together from the partial results of its pieces, in key order, with the usual
+// and is put together from the partial results of its pieces, last to first, with the usual
 // log-sum-exp weights; a unit cut by several boundaries is handled at the first of them.  blockIdx.y
 // = db selects 32 of the D output columns, so that a unit is spread over D/32 workgroups (the kernel
 // is a pure data mover and wants many loads in flight).  When scores are wanted, the db = 0 workgroup
@@ -928,26 +874,26 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
 #pragma unroll
   for (int v = 0; v < 16; ++v) o[v] = 0.f;
 #pragma unroll 1
-  for (int sp = s_lo; sp <= s_hi; ++sp) {
+  for (int sp = s_hi; sp >= s_lo; --sp) {          // last piece first, as in the main kernel
     const int64_t b = span_begin(sp, p.line_len, p.n_teams);
     const float *slot = p.slots + slot_index(p, sp, u_lo > b ? 1 : 0, member) * Slot<D>::kFloats;
     const float4 st = *reinterpret_cast<const float4 *>(Slot<D>::stats(const_cast<float *>(slot), tid));
-    const float m_new = fmaxf(M, st.x);
+    const float m_new = fmaxf(st.x, M);
     // a piece of a wave that computes nothing (rows past the last query) has m = -inf throughout
-    const float w_old = (M == m_new) ? 1.f : fast_exp2((M - m_new) * p.c);
-    const float w_new = (st.x == m_new) ? 1.f : fast_exp2((st.x - m_new) * p.c);
+    const float w_h = (st.x == m_new) ? 1.f : fast_exp2((st.x - m_new) * p.c);
+    const float w_t = (M == m_new) ? 1.f : fast_exp2((M - m_new) * p.c);
     M = m_new;
-    Lt = fold(Lt, w_old, st.y, w_new);
-    La = fold(La, w_old, st.z, w_new);
-    Lb = fold(Lb, w_old, st.w, w_new);
+    Lt = fold(st.y, w_h, Lt, w_t);
+    La = fold(st.z, w_h, La, w_t);
+    Lb = fold(st.w, w_h, Lb, w_t);
     if (!SCORE_ONLY) {
 #pragma unroll
       for (int cq = 0; cq < 4; ++cq) {
         const float4 v4 = *reinterpret_cast<const float4 *>(Slot<D>::ovec(const_cast<float *>(slot), tid, db * 4 + cq));
-        o[4 * cq] = fold(o[4 * cq], w_old, v4.x, w_new);
-        o[4 * cq + 1] = fold(o[4 * cq + 1], w_old, v4.y, w_new);
-        o[4 * cq + 2] = fold(o[4 * cq + 2], w_old, v4.z, w_new);
-        o[4 * cq + 3] = fold(o[4 * cq + 3], w_old, v4.w, w_new);
+        o[4 * cq] = fold(v4.x, w_h, o[4 * cq], w_t);
+        o[4 * cq + 1] = fold(v4.y, w_h, o[4 * cq + 1], w_t);
+        o[4 * cq + 2] = fold(v4.z, w_h, o[4 * cq + 2], w_t);
+        o[4 * cq + 3] = fold(v4.w, w_h, o[4 * cq + 3], w_t);
       }
     }
   }
