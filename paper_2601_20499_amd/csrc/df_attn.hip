@@ -105,6 +105,15 @@ constexpr int kNumCU = 256;        // MI355X: one workgroup per CU (LDS-bound oc
 constexpr int kMinSpan = 8;        // do not cut the work finer than this many key tiles per team
 constexpr int kSpinLimit = 1 << 22; // polls of a hand-over flag before a workgroup gives up (seconds; normally one poll)
 
+// One head as the kernels read it.  The table is sorted by descending key count.
+struct HeadRec {
+  int64_t off;         // first history row
+  int32_t len;         // history rows that hold keys (a prefix of the head's rows)
+  int32_t sink;        // of these, sink rows
+  int32_t head;        // index of the head
+  int32_t pad_;
+};
+
 struct AttnParams {
   const u16 *q, *k_cur, *v_cur, *k_hist, *v_hist;
   u16 *out;
@@ -122,15 +131,14 @@ struct AttnParams {
   int32_t total_cols;          // key tiles of all heads
   int64_t line_len;            // n_groups * total_cols: positions of the line the teams share out
   int16_t n_cut_units[kMaxHeads];   // units of a head that span boundaries cut (put together by the merge kernel)
+  int64_t span_base;           // positions per span: line_len / n_teams ...
+  int32_t span_rem;            // ... and line_len % n_teams, spread evenly over the spans
   int32_t cum[kMaxHeads + 1];  // first column of the hh-th longest head
   uint32_t cur_bytes;  // addressable bytes of one head's current-chunk rows: ((Nc-1)*kc_st + d) * 2
   float c;             // softmax_scale * log2(e)
   float inv_c;         // 1 / c
   float scale;         // softmax_scale
-  int64_t hist_off[kMaxHeads + 1];
-  int32_t hist_len[kMaxHeads];   // rows of each head that hold keys (a prefix of its rows)
-  int32_t sink_len[kMaxHeads];
-  uint8_t order[kMaxHeads];    // heads sorted by descending key count
+  HeadRec rec[kMaxHeads];      // heads sorted by descending key count
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -307,9 +315,12 @@ __device__ __forceinline__ int64_t slot_index(const AttnParams &p, int span, int
 }
 
 // Where the work is cut.  The line has one position per (group of query tiles, column); span s covers
-// positions [span_begin(s), span_begin(s+1)).  Host and device use the same arithmetic.
-__host__ __device__ __forceinline__ int64_t span_begin(int64_t s, int64_t line_len, int64_t n_spans) {
-  return (s * line_len) / n_spans;
+// positions [span_begin(s), span_begin(s+1)), span_begin(s) = floor(s * line_len / n_teams).  Host and device
+// use the same arithmetic: with line_len = n_teams * span_base + span_rem only s * span_rem is left to divide,
+// which is less than kNumCU^2 (a 64-bit division is over a hundred dependent instructions, and a workgroup
+// needs several before it can issue its first load).
+__host__ __device__ __forceinline__ int64_t span_begin(const AttnParams &p, int s) {
+  return s * p.span_base + unsigned(s * p.span_rem) / unsigned(p.n_teams);
 }
 
 // One piece of a span: the part of a unit (group of query tiles x head) that the span holds.  The same
@@ -327,15 +338,33 @@ __host__ __device__ __forceinline__ int head_of_column(const AttnParams &p, int 
   while (col >= p.cum[hh + 1]) ++hh;
   return hh;
 }
+// The two ways to look a column up: one after the other in the parameters (host, merge kernel) ...
+struct ColumnsInParams {
+  const AttnParams &p;
+  __host__ __device__ __forceinline__ int head_of(int col) const { return head_of_column(p, col); }
+  __host__ __device__ __forceinline__ int first(int hh) const { return p.cum[hh]; }
+};
+// ... or one head per lane in the main kernel's copy in LDS.
+struct ColumnsInLds {
+  const int *cum;      // [kMaxHeads + 1], INT32_MAX past the last head
+  __device__ __forceinline__ int head_of(int col) const {
+    return __popcll(__ballot(col >= cum[(threadIdx.x & 63) + 1]));
+  }
+  __device__ __forceinline__ int first(int hh) const { return __builtin_amdgcn_readfirstlane(cum[hh]); }
+};
 
 // The piece of span [span_lo, ...) that ends at line position pos_end (span_lo < pos_end <= the span's end).
-__host__ __device__ __forceinline__ Piece piece_ending_at(const AttnParams &p, int64_t span_lo, int64_t pos_end) {
+template <class Columns>
+__host__ __device__ __forceinline__ Piece piece_ending_at(const AttnParams &p, const Columns &columns, int64_t span_lo,
+                                                          int64_t pos_end) {
   Piece c;
-  c.grp = int((pos_end - 1) / p.total_cols);
-  const int col = int((pos_end - 1) - int64_t(c.grp) * p.total_cols);
-  c.hh = head_of_column(p, col);
-  c.n_tiles = p.cum[c.hh + 1] - p.cum[c.hh];
-  c.unit_lo = int64_t(c.grp) * p.total_cols + p.cum[c.hh];
+  const int64_t last = pos_end - 1;
+  c.grp = p.n_groups == 1 ? 0 : (p.line_len <= int64_t(UINT32_MAX) ? int(uint32_t(last) / uint32_t(p.total_cols))
+                                                                   : int(last / p.total_cols));
+  const int col = int(last - int64_t(c.grp) * p.total_cols);
+  c.hh = columns.head_of(col);
+  c.n_tiles = columns.first(c.hh + 1) - columns.first(c.hh);
+  c.unit_lo = int64_t(c.grp) * p.total_cols + columns.first(c.hh);
   c.pos = span_lo > c.unit_lo ? span_lo : c.unit_lo;
   c.t_begin = int(c.pos - c.unit_lo);
   c.t_end = int(pos_end - c.unit_lo);
@@ -409,6 +438,8 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char lds_v[SCORE_ONLY ? 16 : kNBuf * L::VTILE];
   __shared__ float lds_red[kWaves * 2];
   __shared__ int lds_ok;
+  __shared__ int lds_cum[kMaxHeads + 1];
+  __shared__ HeadRec lds_rec[kMaxHeads];
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -424,8 +455,19 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   const int wg = (gridDim.x % kXcd == 0) ? (blockIdx.x % kXcd) * n_slots_x + blockIdx.x / kXcd : blockIdx.x;
   const int span = wg / p.team_size, member = wg % p.team_size;
   if (span >= p.n_teams) return;
-  const int64_t span_lo = span_begin(span, p.line_len, p.n_teams);
-  const int64_t span_hi = span_begin(span + 1, p.line_len, p.n_teams);
+  const int64_t span_lo = span_begin(p, span);
+  const int64_t span_hi = span_begin(p, span + 1);
+
+  // The head tables, one head per thread: a single trip to memory, and a column is then found with one ballot.
+  // (Read where they are needed they were a chain of scalar loads, one per head up to the one sought and three
+  // more behind it, each a miss to memory at the start of a launch.)
+  if (tid < kMaxHeads) {
+    const bool present = tid < p.H;
+    if (present) lds_rec[tid] = p.rec[tid];
+    lds_cum[tid + 1] = present ? p.cum[tid + 1] : INT32_MAX;
+    if (tid == 0) lds_cum[0] = 0;
+  }
+  __syncthreads();
 
   // per-lane LDS byte addresses of the MFMA A operands (buffer 0); see TileLayout for the row placement
   const int g16 = lane >> 4, i16 = lane & 15;
@@ -451,12 +493,14 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 #pragma unroll 1
   for (int64_t pos_end = span_hi; pos_end > span_lo;) {
     // ---- the piece that ends at `pos_end`: group of query tiles, head, first and last tile of this team's share
-    const Piece piece = piece_ending_at(p, span_lo, pos_end);
-    const int grp = piece.grp, hh = piece.hh;      // hh: index into the length-sorted head order
-    const int h = p.order[hh];
-    const int64_t hoff = p.hist_off[h];
-    const int len_h = p.hist_len[h];
-    const int sink = p.sink_len[h];
+    const Piece piece = piece_ending_at(p, ColumnsInLds{lds_cum}, span_lo, pos_end);
+    const int grp = piece.grp;
+    const HeadRec &rec = lds_rec[piece.hh];
+    const int h = __builtin_amdgcn_readfirstlane(rec.head);
+    const int64_t hoff = int64_t(uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(rec.off)))) |
+                                 uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(rec.off >> 32)))) << 32);
+    const int len_h = __builtin_amdgcn_readfirstlane(rec.len);
+    const int sink = __builtin_amdgcn_readfirstlane(rec.sink);
     const int nt0 = (sink + kKT - 1) / kKT;
     const int nt1 = (len_h - sink + kKT - 1) / kKT;
     const int nt2 = (p.Nc + kKT - 1) / kKT;
@@ -568,20 +612,25 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(src + 16 * ks);
     }
 
-    // ---- piece prologue: its first three K tiles and first two V tiles on their way into LDS; the
-    // spare V buffer, which the first MFMA phase multiplies with P = 0, is cleared
-    dma_tile(t_begin, 0, false);
-    dma_tile(t_begin + 1, 1, false);
-    dma_tile(t_begin + 2, 2, false);
+    // ---- piece prologue: the spare V buffer, which the first MFMA phase multiplies with P = 0, is cleared; the
+    // first three K tiles and first two V tiles go on their way into LDS in the order in which they are read.
+    // Only Q and the first K tile are waited for: the rest are what two VALU phases leave in flight, so the
+    // waits of the tile loop cover them.  (All workgroups of a launch start here at once, and five tiles and Q
+    // for each are 37 MB: waiting for all of it took 2.5 to 3.7 us a piece.)
     if (!SCORE_ONLY) {
-      dma_tile(t_begin, 0, true);
-      dma_tile(t_begin + 1, 1, true);
       for (int i = tid; i < L::VTILE / 16; i += kThreads) {
         const u32x4 z = {0u, 0u, 0u, 0u};
         *reinterpret_cast<u32x4 *>(lds_v + (kNBuf - 1) * L::VTILE + 16 * i) = z;
       }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    dma_tile(t_begin, 0, false);
+    dma_tile(t_begin + 1, 1, false);
+    if (!SCORE_ONLY) dma_tile(t_begin, 0, true);
+    dma_tile(t_begin + 2, 2, false);
+    if (!SCORE_ONLY) dma_tile(t_begin + 1, 1, true);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kDmaPerPhase) : "memory");
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));   // the compiler's own wait for Q, here and not in the loop
     lds_barrier();
 
     f32x16 o[DB];
@@ -754,7 +803,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // its piece is in memory; the wait is bounded so that a workgroup that never runs cannot hang the
       // device: the rows then come out as NaN.
       int s_first = span - 1;                      // span that holds the unit's first tile
-      while (s_first > 0 && span_begin(s_first, p.line_len, p.n_teams) > unit_lo) --s_first;
+      while (s_first > 0 && span_begin(p, s_first) > unit_lo) --s_first;
       if (wave == 0) {
         // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
         int ok = 1;
@@ -779,7 +828,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // a small launch.)
 #pragma unroll 1
       for (int sp = span - 1; sp >= s_first; --sp) {
-        const int which = unit_lo > span_begin(sp, p.line_len, p.n_teams) ? 1 : 0;
+        const int which = unit_lo > span_begin(p, sp) ? 1 : 0;
         const float *slot = p.slots + slot_index(p, sp, which, member) * Slot<D>::kFloats;
         f32x4 st, v[D / 8];
         if constexpr (SCORE_ONLY) st = load4_through(Slot<D>::stats(const_cast<float *>(slot), tid));
@@ -855,19 +904,19 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
     return;
   }
   const int k = int(blockIdx.x) / p.team_size + 1, member = int(blockIdx.x) % p.team_size;
-  const int64_t cut = span_begin(k, p.line_len, p.n_teams);
+  const int64_t cut = span_begin(p, k);
   const int grp = int(cut / p.total_cols);
   const int col = int(cut - int64_t(grp) * p.total_cols);
   const int hh = head_of_column(p, col);
   if (col == p.cum[hh]) return;                    // the boundary coincides with the head's first column
   const int64_t u_lo = int64_t(grp) * p.total_cols + p.cum[hh], u_hi = u_lo + (p.cum[hh + 1] - p.cum[hh]);
-  if (k >= 2 && span_begin(k - 1, p.line_len, p.n_teams) > u_lo) return;   // an earlier boundary cuts the same unit
+  if (k >= 2 && span_begin(p, k - 1) > u_lo) return;   // an earlier boundary cuts the same unit
   const int qt = grp * p.team_size + member;
   if (qt >= p.n_qtiles) return;
-  const int h = p.order[hh];
+  const int h = p.rec[hh].head;
   const int s_lo = k - 1;                          // span that holds the unit's first column
   int s_hi = k;
-  while (span_begin(s_hi + 1, p.line_len, p.n_teams) < u_hi) ++s_hi;
+  while (span_begin(p, s_hi + 1) < u_hi) ++s_hi;
 
   float M = -INFINITY, Lt = 0.f, La = 0.f, Lb = 0.f;
   f32x16 o;
@@ -875,7 +924,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
   for (int v = 0; v < 16; ++v) o[v] = 0.f;
 #pragma unroll 1
   for (int sp = s_hi; sp >= s_lo; --sp) {          // last piece first, as in the main kernel
-    const int64_t b = span_begin(sp, p.line_len, p.n_teams);
+    const int64_t b = span_begin(p, sp);
     const float *slot = p.slots + slot_index(p, sp, u_lo > b ? 1 : 0, member) * Slot<D>::kFloats;
     const float4 st = *reinterpret_cast<const float4 *>(Slot<D>::stats(const_cast<float *>(slot), tid));
     const float m_new = fmaxf(st.x, M);
@@ -950,9 +999,8 @@ static df_status plan(AttnParams &p) {
   p.n_qtiles = (p.Nq + kBQ - 1) / kBQ;
   int64_t total = 0;
   for (int hh = 0; hh < p.H; ++hh) {
-    const int h = p.order[hh];
-    const int64_t len = p.hist_len[h];
-    const int64_t sink = p.sink_len[h];
+    const int64_t len = p.rec[hh].len;
+    const int64_t sink = p.rec[hh].sink;
     p.cum[hh] = int32_t(total);
     total += (sink + kKT - 1) / kKT + (len - sink + kKT - 1) / kKT + (p.Nc + kKT - 1) / kKT;
     if (total > INT32_MAX / 2) return DF_ERR_RANGE;
@@ -980,17 +1028,19 @@ static df_status plan(AttnParams &p) {
   p.n_groups = (p.n_qtiles + team - 1) / team;
   p.n_teams = int32_t(teams_of(team));
   p.line_len = int64_t(p.n_groups) * total;
+  p.span_base = p.line_len / p.n_teams;
+  p.span_rem = int32_t(p.line_len % p.n_teams);
   // units cut by a span boundary (the same walk as the merge kernel's); with hand-over none is left to it
   for (int h = 0; h < p.H; ++h) p.n_cut_units[h] = 0;
   for (int k = 1; k < p.n_teams && !p.handoff; ++k) {
-    const int64_t cut = span_begin(k, p.line_len, p.n_teams);
+    const int64_t cut = span_begin(p, k);
     const int grp = int(cut / total);
     const int col = int(cut - int64_t(grp) * total);
     const int hh = head_of_column(p, col);
     if (col == p.cum[hh]) continue;
     const int64_t u_lo = int64_t(grp) * total + p.cum[hh];
-    if (k >= 2 && span_begin(k - 1, p.line_len, p.n_teams) > u_lo) continue;
-    p.n_cut_units[p.order[hh]] += std::min(team, p.n_qtiles - grp * team);
+    if (k >= 2 && span_begin(p, k - 1) > u_lo) continue;
+    p.n_cut_units[p.rec[hh].head] += std::min(team, p.n_qtiles - grp * team);
   }
   return DF_OK;
 }
@@ -1061,6 +1111,17 @@ static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStr
   return DF_OK;
 }
 
+// The head table: longest history first, heads of equal length in their own order.
+static void sort_heads(AttnParams &p, int H, const int64_t *off, const int32_t *len, const int32_t *sink) {
+  int idx[kMaxHeads];
+  std::iota(idx, idx + H, 0);
+  std::stable_sort(idx, idx + H, [&](int a, int b) { return len[a] > len[b]; });
+  for (int i = 0; i < H; ++i) {
+    const int h = idx[i];
+    p.rec[i] = HeadRec{off ? off[h] : 0, len[h], sink ? sink[h] : 0, h, 0};
+  }
+}
+
 // Checks shared by both entry points; fills the per-head tables of `p`.
 static df_status fill_heads(AttnParams &p, int H, int d, int Nq, int Nc, const int64_t *hist_off,
                             const int32_t *sink_len, const int32_t *hist_len, bool need_sink, const void *k_hist,
@@ -1071,6 +1132,7 @@ static df_status fill_heads(AttnParams &p, int H, int d, int Nq, int Nc, const i
   if (need_sink && !sink_len) return DF_ERR_NULL;
   if (hist_off[0] != 0) return DF_ERR_RANGE;
   int64_t any = 0;
+  int32_t lens[kMaxHeads], sinks[kMaxHeads];
   for (int h = 0; h < H; ++h) {
     const int64_t rows = hist_off[h + 1] - hist_off[h];
     if (rows < 0 || rows * d * 2 >= kMaxBufferBytes) return DF_ERR_RANGE;
@@ -1078,20 +1140,15 @@ static df_status fill_heads(AttnParams &p, int H, int d, int Nq, int Nc, const i
     if (len < 0 || len > rows) return DF_ERR_RANGE;
     const int32_t sl = sink_len ? sink_len[h] : 0;
     if (sl < 0 || sl > len) return DF_ERR_RANGE;
-    p.hist_off[h] = hist_off[h];
-    p.hist_len[h] = int32_t(len);
-    p.sink_len[h] = sl;
+    lens[h] = int32_t(len);
+    sinks[h] = sl;
     any += len;
   }
-  p.hist_off[H] = hist_off[H];
   if (any > 0) {
     if (!k_hist || (need_v && !v_hist)) return DF_ERR_NULL;
     if (!aligned16(k_hist) || (need_v && !aligned16(v_hist))) return DF_ERR_ALIGN;
   }
-  int idx[kMaxHeads];
-  std::iota(idx, idx + H, 0);
-  std::stable_sort(idx, idx + H, [&](int a, int b) { return p.hist_len[a] > p.hist_len[b]; });
-  for (int h = 0; h < H; ++h) p.order[h] = uint8_t(idx[h]);
+  sort_heads(p, H, hist_off, lens, sinks);
   p.H = H;
   p.Nq = Nq;
   p.Nc = Nc;
@@ -1113,16 +1170,11 @@ extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32
   if (H <= 0 || Nq <= 0 || Nc <= 0) return DF_ERR_SHAPE;
   if (H > kMaxHeads) return DF_ERR_UNSUPPORTED;
   AttnParams p{};
-  int idx[kMaxHeads];
   for (int h = 0; h < H; ++h) {
     const int32_t sl = hist_sink_len ? hist_sink_len[h] : 0;
     if (hist_len[h] < 0 || sl < 0 || sl > hist_len[h]) return DF_ERR_RANGE;
-    p.hist_len[h] = hist_len[h];
-    p.sink_len[h] = sl;
-    idx[h] = h;
   }
-  std::stable_sort(idx, idx + H, [&](int a, int b) { return p.hist_len[a] > p.hist_len[b]; });
-  for (int h = 0; h < H; ++h) p.order[h] = uint8_t(idx[h]);
+  sort_heads(p, H, nullptr, hist_len, hist_sink_len);
   p.H = H;
   p.Nq = Nq;
   p.Nc = Nc;
@@ -1139,7 +1191,7 @@ extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32
   out->span_min = INT64_MAX;
   out->span_max = 0;
   for (int t = 0; t < p.n_teams; ++t) {
-    const int64_t len = span_begin(t + 1, p.line_len, p.n_teams) - span_begin(t, p.line_len, p.n_teams);
+    const int64_t len = span_begin(p, t + 1) - span_begin(p, t);
     out->span_min = std::min(out->span_min, len);
     out->span_max = std::max(out->span_max, len);
   }
@@ -1152,11 +1204,11 @@ extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32
   int64_t expect_unit = -1;        // unit_lo of the unit whose next piece the walk must meet, or -1
   int expect_t = 0, unit_pieces = 0, first_span = 0;
   for (int span = 0; span < p.n_teams; ++span) {
-    const int64_t lo = span_begin(span, p.line_len, p.n_teams), hi = span_begin(span + 1, p.line_len, p.n_teams);
+    const int64_t lo = span_begin(p, span), hi = span_begin(p, span + 1);
     // the kernel walks from the end; collect, then check in line order
     std::vector<Piece> list;
     for (int64_t pos_end = hi; pos_end > lo;) {
-      const Piece c = piece_ending_at(p, lo, pos_end);
+      const Piece c = piece_ending_at(p, ColumnsInParams{p}, lo, pos_end);
       if (c.pos >= pos_end || c.pos < lo) { out->consistent = 0; break; }
       list.push_back(c);
       pos_end = c.pos;
@@ -1187,7 +1239,7 @@ extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32
           ++takes;
           // the kernel finds the span of the unit's first piece by stepping back from its own
           int s_first = span - 1;
-          while (s_first > 0 && span_begin(s_first, p.line_len, p.n_teams) > c.unit_lo) --s_first;
+          while (s_first > 0 && span_begin(p, s_first) > c.unit_lo) --s_first;
           if (s_first != first_span || unit_pieces != span - first_span + 1) out->consistent = 0;
         }
         out->max_pieces_per_unit = std::max(out->max_pieces_per_unit, unit_pieces);
