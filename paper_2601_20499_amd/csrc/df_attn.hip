@@ -125,6 +125,8 @@ struct AttnParams {
   int32_t handoff;     // cut units are put together inside the main kernel (needs all workgroups on the device at once)
   float *slots;        // workspace: 2 partial-result slots per workgroup (see Slot)
   float *score;        // [H, 3] frame attention scores, or null
+  unsigned long long *done;    // one word per workgroup, = epoch once its units' score sums are in memory; null: the
+                               // second kernel sums the scores
   int64_t q_st, q_sh, kc_st, kc_sh, o_st, o_sh;
   int32_t Nq, Nc, H, n_qtiles;
   int32_t team_size, n_teams, n_groups;   // members of a team, teams (= spans), groups of team_size query tiles
@@ -311,7 +313,7 @@ __device__ __forceinline__ float fold(float earlier, float w_earlier, float late
 }
 
 // Partial-result slot of (span, first or later piece of the span, member of the team).
-__device__ __forceinline__ int64_t slot_index(const AttnParams &p, int span, int which, int member) {
+__host__ __device__ __forceinline__ int64_t slot_index(const AttnParams &p, int span, int which, int member) {
   return int64_t(2 * span + which) * p.team_size + member;
 }
 
@@ -433,22 +435,74 @@ __device__ __forceinline__ void reduce_masses(const AttnParams &p, float *lds_re
   if (tid < 2) {
     float acc = 0.f;
     for (int w = 0; w < kWaves; ++w) acc += lds_red[2 * w + tid];
-    p.part[(int64_t(h) * p.n_qtiles + qt) * 4 + tid] = acc;
+    // written through: the sums of all units may be read by another workgroup of this launch
+    __hip_atomic_store(p.part + (int64_t(h) * p.n_qtiles + qt) * 4 + tid, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   lds_barrier();
 }
 
 // F[h] = (sum_a, sum_b - sum_a, n - sum_b) / n over the head's query tiles, in tile order.
+__device__ __forceinline__ void store_score(const AttnParams &p, int h, float a, float b) {
+  const float inv = 1.f / float(p.Nq);
+  p.score[3 * h] = a * inv;
+  p.score[3 * h + 1] = (b - a) * inv;
+  p.score[3 * h + 2] = (float(p.Nq) - b) * inv;
+}
 __device__ __forceinline__ void finish_score(const AttnParams &p, int h) {
   float a = 0.f, b = 0.f;
   for (int t = 0; t < p.n_qtiles; ++t) {
     a += p.part[(int64_t(h) * p.n_qtiles + t) * 4];
     b += p.part[(int64_t(h) * p.n_qtiles + t) * 4 + 1];
   }
-  const float inv = 1.f / float(p.Nq);
-  p.score[3 * h] = a * inv;
-  p.score[3 * h + 1] = (b - a) * inv;
-  p.score[3 * h + 2] = (float(p.Nq) - b) * inv;
+  store_score(p, h, a, b);
+}
+
+// Wait, for a bounded time, until a flag word holds this launch's value, and put it back: a flag has one reader, and
+// a replay of the launch (same value) has to start clean.
+__device__ __forceinline__ int take_flag(unsigned long long *flag, unsigned long long epoch) {
+  int up = 0;
+  for (int spin = 0; spin < kSpinLimit && !up; ++spin) {
+    up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == epoch;
+    if (!up) __builtin_amdgcn_s_sleep(16);
+  }
+  __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return up;
+}
+
+// The frame attention scores of all heads, by the first workgroup at the end of its span: when every workgroup has
+// raised its flag, the units' sums come into LDS (`buf`, room for PAIRS of them) with all threads loading, and
+// one thread per head adds its tiles up in finish_score's order, so that both ways give the same bits.  A second
+// launch for these few sums cost 4 to 6 us a call (832x480 sampled scores, a 1170-query call); this costs two
+// trips to memory.  An atomic counter per head instead of the flags puts a trip on every unit's path.
+template <int PAIRS>
+__device__ __forceinline__ void finish_all_scores(const AttnParams &p, float2 *buf, int *all_up, int tid) {
+  const int n_wg = p.n_teams * p.team_size;
+  if (tid == 0) *all_up = 1;
+  __syncthreads();
+  if (tid < n_wg && !take_flag(p.done + tid, p.epoch)) *all_up = 0;
+  __syncthreads();
+  const float poison = *all_up ? 0.f : NAN;
+  static_assert(PAIRS >= kMaxHeads, "one tile of every head");
+  const int tiles_at_once = PAIRS / p.H;
+  float a = 0.f, b = 0.f;
+  for (int t0 = 0; t0 < p.n_qtiles; t0 += tiles_at_once) {
+    const int n = min(tiles_at_once, p.n_qtiles - t0);
+    for (int i = tid; i < p.H * n; i += kThreads) {
+      const int h = i / n, t = i - h * n;
+      const unsigned long long both =
+          __hip_atomic_load(reinterpret_cast<unsigned long long *>(p.part + (int64_t(h) * p.n_qtiles + t0 + t) * 4),
+                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      buf[i] = __builtin_bit_cast(float2, both);
+    }
+    __syncthreads();
+    if (tid < p.H)
+      for (int t = 0; t < n; ++t) {
+        a += buf[tid * n + t].x;
+        b += buf[tid * n + t].y;
+      }
+    __syncthreads();
+  }
+  if (tid < p.H) store_score(p, tid, a + poison, b + poison);
 }
 
 template <int D, bool SCORE_ONLY>
@@ -832,15 +886,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
         // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
         int ok = 1;
         for (int sp = s_first + lane; sp < span; sp += 64) {
-          unsigned long long *flag = p.flags + sp * p.team_size + member;
-          int up = 0;
-          for (int spin = 0; spin < kSpinLimit && !up; ++spin) {
-            up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
-            if (!up) __builtin_amdgcn_s_sleep(16);
-          }
-          // a flag has one reader: put it back, so that a replay of this launch (same epoch) starts clean
-          __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-          ok &= up;
+          ok &= take_flag(p.flags + sp * p.team_size + member, p.epoch);
         }
         if (lane == 0) lds_ok = __all(ok);
       }
@@ -905,6 +951,13 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       }
     }
   }
+  if (p.done != nullptr) {
+    if (wave == 0) {                               // the wave that wrote the units' sums: they are in memory, then the flag
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (lane == 0) __hip_atomic_store(p.done + wg, p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (wg == 0) finish_all_scores<kNBuf * L::KTILE / 8>(p, reinterpret_cast<float2 *>(lds_k), &lds_ok, tid);
+  }
 }
 
 // Second kernel.  Workgroup (k, member; db) looks at the boundary between spans k-1 and k: if it falls
@@ -922,7 +975,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, j = lane & 31, hf = lane >> 5;
   const int db = int(blockIdx.y);
-  const int n_merge = p.handoff ? 0 : (p.n_teams - 1) * p.team_size;
+  const int n_merge = (p.n_teams - 1) * p.team_size;
   if (int(blockIdx.x) >= n_merge) {                // score of a head no boundary cuts
     const int h = int(blockIdx.x) - n_merge;
     if (db == 0 && tid == 0 && p.n_cut_units[h] == 0) finish_score(p, h);
@@ -1111,10 +1164,11 @@ template <int D, bool SCORE_ONLY>
 static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStream_t st) {
   p.handoff = 0;
   if (df_status s = plan(p)) return s;
-  if (p.n_teams > 1 && handover_possible(p.n_teams * p.team_size)) {
+  const bool together = (p.n_teams > 1 || score_out) && handover_possible(p.n_teams * p.team_size);
+  if (together) p.epoch = next_epoch();
+  if (together && p.n_teams > 1) {
     p.handoff = 1;
     for (int h = 0; h < p.H; ++h) p.n_cut_units[h] = 0;
-    p.epoch = next_epoch();
   }
   char *ws = static_cast<char *>(workspace);
   p.part = score_out ? reinterpret_cast<float *>(ws) : nullptr;
@@ -1122,14 +1176,20 @@ static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStr
   p.flags = reinterpret_cast<unsigned long long *>(ws + part_bytes(p.H, p.Nq) + kTicketBytes);
   p.slots = reinterpret_cast<float *>(ws + part_bytes(p.H, p.Nq) + kTicketBytes + kFlagBytes);
   p.score = score_out;
+  // The last span ends where the line does and hands nothing on, so the slots of its later pieces are free: the
+  // flags of the score sums lie there.
+  p.done = together && score_out
+               ? reinterpret_cast<unsigned long long *>(p.slots + slot_index(p, p.n_teams - 1, 1, 0) * Slot<D>::kFloats)
+               : nullptr;
   const int n_wg = p.n_teams * p.team_size;
   const int grid = n_wg >= kXcd ? (n_wg + kXcd - 1) / kXcd * kXcd : n_wg;   // XCD-major numbering needs a multiple of 8
   hipLaunchKernelGGL((df_attn_kernel<D, SCORE_ONLY>), dim3(grid), dim3(kThreads), 0, st, p);
   if (df_status s = launch_status()) return s;
-  // second launch: units cut by span boundaries (unless they were handed over), and the per-head score sums
-  const int n_merge = (p.handoff ? 0 : (p.n_teams - 1) * p.team_size) + (score_out ? p.H : 0);
+  if (together) return DF_OK;
+  // second launch: the units that span boundaries cut, and the per-head score sums
+  const int n_merge = (p.n_teams - 1) * p.team_size + (score_out ? p.H : 0);
   if (n_merge > 0) {
-    hipLaunchKernelGGL((df_attn_merge_kernel<D, SCORE_ONLY>), dim3(n_merge, (SCORE_ONLY || p.handoff) ? 1 : D / 32),
+    hipLaunchKernelGGL((df_attn_merge_kernel<D, SCORE_ONLY>), dim3(n_merge, SCORE_ONLY ? 1 : D / 32),
                        dim3(kThreads), 0, st, p);
     if (df_status s = launch_status()) return s;
   }
