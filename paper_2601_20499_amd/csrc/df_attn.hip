@@ -102,7 +102,8 @@ constexpr int kNBuf = 4;           // LDS buffers per operand
 constexpr float kSumLimit = 0x1p100f; // the reference of the exponentials is raised when a row's running sum passes this
 constexpr int kXcd = 8;            // XCDs per device: consecutive workgroup ids go to consecutive XCDs
 constexpr int kNumCU = 256;        // MI355X: one workgroup per CU (LDS-bound occupancy)
-constexpr int kMinSpan = 8;        // do not cut the work finer than this many key tiles per team
+constexpr int kMinSpan = 8;        // do not cut the work finer than this many key tiles per team ...
+constexpr int kMinSmallSpan = 4;   // ... nor, where the spans are chosen by their cost, finer than this
 constexpr int kSpinLimit = 1 << 22; // polls of a hand-over flag before a workgroup gives up (seconds; normally one poll)
 
 // One head as the kernels read it.  The table is sorted by descending key count.
@@ -1066,6 +1067,67 @@ static size_t workspace_bytes(int H, int d, int Nq) {
   return part_bytes(H, Nq) + kTicketBytes + kFlagBytes + 2 * size_t(kNumCU) * slot_bytes(d);
 }
 
+// Spans for a launch that cannot give every compute unit a long one.  There, what a piece costs besides its tiles
+// decides: a workgroup that holds the end of one unit and the start of the next pays for two, and every
+// earlier piece of a unit is another trip to memory for the workgroup that finishes it.  span_cost is the time of
+// the slowest workgroup, counted in tile iterations (1.4 us at d = 128): reading a piece's first tiles, leaving sums
+// behind, finishing a unit, and the flags and sums of earlier pieces, as stamps inside the kernel gave them.
+constexpr float kPieceCost = 2.0f, kGiveCost = 2.0f, kFinishCost = 1.5f, kPollCost = 1.0f, kFoldCost = 1.4f;
+static float span_cost(const AttnParams &p, int n) {
+  const int line = p.n_groups * p.total_cols;
+  float worst = 0.f, ready = 0.f;          // ready: when the last of the current unit's pieces so far is in memory
+  int n_before = 0, hh = 0, group = 0;     // pieces of the unit that lie in earlier spans; the unit at the span's start
+  for (int k = 0; k < n; ++k) {
+    const int begin = int(unsigned(k * line) / unsigned(n)), hi = int(unsigned((k + 1) * line) / unsigned(n));
+    int lo = begin;
+    float t = 0.f, give_at = 0.f, fold = 0.f;
+    bool gives = false, takes = false;
+    while (lo < hi) {
+      while (lo >= group + p.cum[hh + 1])
+        if (++hh == p.H) { hh = 0; group += p.total_cols; }
+      const int unit_end = group + p.cum[hh + 1], end = std::min(hi, unit_end);
+      const float piece = kPieceCost + float(end - lo + 1);
+      t += piece;
+      if (end < unit_end) {                  // the first thing this workgroup does
+        gives = true;
+        t += kGiveCost;
+        give_at = piece + kGiveCost;
+      } else {
+        t += kFinishCost;
+        if (lo > group + p.cum[hh]) { takes = true; fold = kPollCost + kFoldCost * float(n_before); }
+      }
+      lo = end;
+    }
+    const float finish = takes ? std::max(t, ready) + fold : t;
+    worst = std::max(worst, finish);
+    if (gives) {
+      const bool goes_on = !takes && n_before > 0 && begin > group + p.cum[hh];   // a unit's middle piece
+      ready = goes_on ? std::max(ready, give_at) : give_at;
+      n_before = goes_on ? n_before + 1 : 1;
+    } else {
+      n_before = 0;
+    }
+  }
+  return worst;
+}
+// The cheapest of a few numbers of spans up to n_max: spans of the least length and up to six tiles longer, and the
+// largest two numbers that cut the units of equally long heads into equal parts.  Few, because the walk is paid on
+// every small call (about 10 ns a span).
+static int cheapest_spans(const AttnParams &p, int n_max) {
+  const int line = p.n_groups * p.total_cols;
+  int best = 1;
+  float best_cost = INFINITY;
+  auto consider = [&](int n) {
+    const float c = span_cost(p, n);
+    if (c < best_cost || (c == best_cost && n < best)) { best_cost = c; best = n; }
+  };
+  consider(n_max);
+  for (int longer : {1, 2, 4, 6}) consider(std::max(1, line / (line / n_max + longer)));
+  const int units = p.H * p.n_groups;
+  for (int n = n_max / units * units, i = 0; n >= 1 && i < 2; n -= units, ++i) consider(n);
+  return best;
+}
+
 // The decomposition of a launch (A4).  Columns = key tiles of all heads, longest head first.  Query tiles
 // are taken in groups of `team_size`; the line has one position per (group, column) and is cut into
 // equal spans, one per team.  A team has one workgroup per query tile of a group; its members walk the
@@ -1104,8 +1166,14 @@ static df_status plan(AttnParams &p) {
   while (team > 1 && busy(team) < want) --team;
   p.team_size = team;
   p.n_groups = (p.n_qtiles + team - 1) / team;
-  p.n_teams = int32_t(teams_of(team));
   p.line_len = int64_t(p.n_groups) * total;
+  p.n_teams = int32_t(teams_of(team));
+  // Launches that spans of kMinSpan tiles leave part of the machine without work.  Measured on 13 of them, 64 to 1170
+  // queries and 4 to 45 tiles a unit: a fixed least span of 8, 6, 4 or 3 tiles each was best for some and up to twice
+  // too slow for others.  One step further (1170 queries, 9 tiles a span) all spans are better kept: 43.4 against
+  // 44.0 us with the choice.
+  if (p.line_len < kMinSpan * (kNumCU / team))
+    p.n_teams = cheapest_spans(p, std::max(1, std::min(kNumCU / team, int(p.line_len) / kMinSmallSpan)));
   p.span_base = p.line_len / p.n_teams;
   p.span_rem = int32_t(p.line_len % p.n_teams);
   // units cut by a span boundary (the same walk as the merge kernel's); with hand-over none is left to it
