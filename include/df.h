@@ -95,7 +95,9 @@ df_status df_head_context(int32_t head_type, int32_t T, int32_t sink_frames,
  * (compute units taken away from the process), the rows concerned come out as
  * NaN after some seconds instead of hanging the device.  DF_ATTN_HANDOVER=0 in
  * the environment (read at every call) selects the other path, in which a
- * second kernel puts those units together; the results are the same bit for bit.
+ * second kernel puts those units together and sums the scores (otherwise the
+ * first workgroup does, behind the same kind of wait); the results are the same
+ * bit for bit.
  * Two calls that use the same workspace must not overlap on the device.
  *
  * Under HIP graph capture: the call records kernels only (no memset, no copy),
