@@ -126,6 +126,7 @@ struct AttnParams {
   unsigned long long *flags;   // workspace: one word per workgroup, = epoch once its hand-over sum is in memory
   unsigned long long epoch;    // this launch's flag value: random, so that memory never holds it by chance
   int32_t handoff;     // cut units are put together inside the main kernel (needs all workgroups on the device at once)
+  int32_t lost_flag;   // number of a flag that its reader gives up on without a poll, or -1 (see lost_flag())
   float *slots;        // workspace: 2 partial-result slots per workgroup (see Slot)
   float *score;        // [H, 3] frame attention scores, or null
   unsigned long long *done;    // one word per workgroup, = epoch once its units' score sums are in memory; null: the
@@ -461,11 +462,12 @@ __device__ __forceinline__ void finish_score(const AttnParams &p, int h) {
 }
 
 // Wait, for a bounded time, until a flag word holds this launch's value, and put it back: a flag has one reader, and
-// a replay of the launch (same value) has to start clean.
-__device__ __forceinline__ int take_flag(unsigned long long *flag, unsigned long long epoch) {
+// a replay of the launch (same value) has to start clean.  `number` is the flag's number as lost_flag() counts them.
+__device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int number) {
   int up = 0;
-  for (int spin = 0; spin < kSpinLimit && !up; ++spin) {
-    up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == epoch;
+  const int polls = number == p.lost_flag ? 0 : kSpinLimit;
+  for (int spin = 0; spin < polls && !up; ++spin) {
+    up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
     if (!up) __builtin_amdgcn_s_sleep(16);
   }
   __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -482,7 +484,7 @@ __device__ __forceinline__ void finish_all_scores(const AttnParams &p, float2 *b
   const int n_wg = p.n_teams * p.team_size;
   if (tid == 0) *all_up = 1;
   __syncthreads();
-  if (tid < n_wg && !take_flag(p.done + tid, p.epoch)) *all_up = 0;
+  if (tid < n_wg && !take_flag(p, p.done + tid, kNumCU + tid)) *all_up = 0;
   __syncthreads();
   const float poison = *all_up ? 0.f : NAN;
   static_assert(PAIRS >= kMaxHeads, "one tile of every head");
@@ -900,9 +902,11 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
         // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
         int ok = 1;
         for (int sp = s_first + lane; sp < span; sp += 64) {
-          ok &= take_flag(p.flags + sp * p.team_size + member, p.epoch);
+          const int number = sp * p.team_size + member;
+          ok &= take_flag(p, p.flags + number, number);
         }
-        if (lane == 0) lds_ok = __all(ok);
+        const int all_ok = __all(ok);              // the whole wave votes: inside `lane == 0` only that lane would
+        if (lane == 0) lds_ok = all_ok;
       }
       __syncthreads();
       const float poison = lds_ok ? 0.f : NAN;
@@ -1230,6 +1234,14 @@ static bool handover_possible(int n_wg) {
   return cus[dev] >= n_wg;
 }
 
+// For tests of what a call returns when one of its workgroups never runs: DF_ATTN_LOST_FLAG=n in the environment
+// (looked at on every call) lets the reader of flag n give up on it at once, as it would after kSpinLimit polls.  The
+// hand-over flags are numbered by workgroup, the flags of the score sums follow from kNumCU on.
+static int lost_flag() {
+  const char *e = std::getenv("DF_ATTN_LOST_FLAG");
+  return e && *e ? std::atoi(e) : -1;
+}
+
 // A flag value that neither stale workspace contents nor an earlier launch hold: a counter run through a
 // 64-bit mixer, never zero.
 static unsigned long long next_epoch() {
@@ -1246,7 +1258,10 @@ static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStr
   p.handoff = 0;
   if (df_status s = plan(p)) return s;
   const bool together = (p.n_teams > 1 || score_out) && handover_possible(p.n_teams * p.team_size);
-  if (together) p.epoch = next_epoch();
+  if (together) {
+    p.epoch = next_epoch();
+    p.lost_flag = lost_flag();
+  }
   if (together && p.n_teams > 1) {
     p.handoff = 1;
     for (int h = 0; h < p.H; ++h) p.n_cut_units[h] = 0;
