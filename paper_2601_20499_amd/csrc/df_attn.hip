@@ -895,7 +895,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // The earlier pieces were written when their workgroups began their spans (a piece that fills a whole
       // span: when that workgroup ended), i.e. long ago or at about this time.  Wait until every flag says
       // its piece is in memory; the wait is bounded so that a workgroup that never runs cannot hang the
-      // device: the rows then come out as NaN.
+      // device: the unit's rows, and through them the head's scores, then come out as NaN.
       int s_first = span - 1;                      // span that holds the unit's first tile
       while (s_first > 0 && span_begin(p, s_first) > unit_lo) --s_first;
       if (wave == 0) {
@@ -935,7 +935,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
             for (int e = 0; e < 16; ++e) o[db][e] = fold(v[db * 4 + e / 4][e % 4], w_h, o[db][e], w_t);
         }
       }
-      m_u += poison;
+      lt_u += poison;                              // every result divides by it: rows, log-sum-exp, score sums
       __syncthreads();                             // lds_ok is free again
     }
     if (t_end == n_tiles && (t_begin == 0 || take)) {

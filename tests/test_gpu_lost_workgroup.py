@@ -81,10 +81,13 @@ def test_rows_of_a_unit_with_a_lost_piece_are_nan(df, monkeypatch, d, shape, tea
     whole = call()
     monkeypatch.setenv("DF_ATTN_LOST_FLAG", str(span * team_size + member))
     out, lse, F, F2 = call()
-    assert torch.isnan(lse[h, rows]).all()
+    assert torch.isnan(lse[h, rows]).all() and torch.isnan(out[rows, h].float()).all()
+    assert torch.isnan(F[h]).all() and torch.isnan(F2[h]).all()
     rest = torch.ones_like(lse, dtype=torch.bool)
     rest[h, rows] = False
-    assert torch.equal(lse[rest], whole[1][rest])
+    assert torch.equal(lse[rest], whole[1][rest]) and torch.equal(out[rest.t()], whole[0][rest.t()])
+    others = [i for i in range(call.H) if i != h]
+    assert torch.equal(F[others], whole[2][others]) and torch.equal(F2[others], whole[3][others])
     monkeypatch.delenv("DF_ATTN_LOST_FLAG")        # what the launch left in the workspace does not touch the next one
     for a, b in zip(call(), whole):
         assert torch.equal(a, b)
