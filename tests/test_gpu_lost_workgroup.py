@@ -104,3 +104,15 @@ def test_scores_are_nan_when_a_workgroup_never_says_it_is_done(df, monkeypatch):
     monkeypatch.delenv("DF_ATTN_LOST_FLAG")
     for a, b in zip(call(), whole):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_single_team_waits_for_no_workgroup(df, monkeypatch, d):
+    """Two workgroups that share no unit: whatever compute units they get, and one after the other if need be."""
+    call = Call(df, d=d, H=1, Nq=300, Nc=40, lens=[100], sinks=[30])
+    assert call.plan["n_teams"] == 1 and call.plan["workgroups"] == 2 and call.plan["cut_units"] == 0
+    whole = call()
+    for flag in (0, 1, N_CU, N_CU + 1):
+        monkeypatch.setenv("DF_ATTN_LOST_FLAG", str(flag))
+        for a, b in zip(call(), whole):
+            assert torch.isfinite(a.float()).all() and torch.equal(a, b)
