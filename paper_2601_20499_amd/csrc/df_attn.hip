@@ -122,7 +122,7 @@ struct AttnParams {
   u16 *out;
   float *lse;          // [H, Nq] or null
   float *part;         // workspace: [H, n_qtiles, 4] partial score sums, or null
-  int32_t *tickets;    // workspace: [H] counters of the merged units of a head (zeroed by the main kernel)
+  int32_t *tickets;    // workspace: [H] counters of the merged units of a head (zeroed by the main kernel), or null
   unsigned long long *flags;   // workspace: one word per workgroup, = epoch once its hand-over sum is in memory
   unsigned long long epoch;    // this launch's flag value: random, so that memory never holds it by chance
   int32_t handoff;     // cut units are put together inside the main kernel (needs all workgroups on the device at once)
@@ -549,8 +549,8 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   }
   __syncthreads();
 
-  // the merge kernel counts the merged units of a head: its counters start at zero (this kernel ends
-  // before that one begins)
+  // the merge kernel, where there is one, counts the merged units of a head: its counters start at zero (this kernel
+  // ends before that one begins)
   if (blockIdx.x == 0 && p.tickets != nullptr && tid < p.H) p.tickets[tid] = 0;
 
   // ---- this workgroup's team (span of the line) and member index (query tile inside a group); XCD-major numbering
@@ -1197,19 +1197,22 @@ static df_status plan(AttnParams &p) {
     p.n_teams = cheapest_spans(p, std::max(1, std::min(kNumCU / team, int(p.line_len) / kMinSmallSpan)));
   p.span_base = p.line_len / p.n_teams;
   p.span_rem = int32_t(p.line_len % p.n_teams);
-  // units cut by a span boundary (the same walk as the merge kernel's); with hand-over none is left to it
-  for (int h = 0; h < p.H; ++h) p.n_cut_units[h] = 0;
-  for (int k = 1; k < p.n_teams && !p.handoff; ++k) {
+  return DF_OK;
+}
+
+// The units of each head that span boundaries cut (the same walk as the merge kernel's), for df_attn_plan and for the
+// two-kernel path; a launch that puts its units together itself has no use for them.
+static void count_cut_units(AttnParams &p) {
+  for (int k = 1; k < p.n_teams; ++k) {
     const int64_t cut = span_begin(p, k);
-    const int grp = int(cut / total);
-    const int col = int(cut - int64_t(grp) * total);
+    const int grp = int(cut / p.total_cols);
+    const int col = int(cut - int64_t(grp) * p.total_cols);
     const int hh = head_of_column(p, col);
     if (col == p.cum[hh]) continue;
-    const int64_t u_lo = int64_t(grp) * total + p.cum[hh];
+    const int64_t u_lo = int64_t(grp) * p.total_cols + p.cum[hh];
     if (k >= 2 && span_begin(p, k - 1) > u_lo) continue;
-    p.n_cut_units[p.rec[hh].head] += std::min(team, p.n_qtiles - grp * team);
+    p.n_cut_units[p.rec[hh].head] += std::min(p.team_size, p.n_qtiles - grp * p.team_size);
   }
-  return DF_OK;
 }
 
 // Whether the workgroups of a launch can hand partial results and score sums to each other while it runs: every one of
@@ -1259,7 +1262,6 @@ static unsigned long long next_epoch() {
 
 template <int D, bool SCORE_ONLY>
 static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStream_t st) {
-  p.handoff = 0;
   if (df_status s = plan(p)) return s;
   // One team of several workgroups has no cut unit: it waits for nothing and needs no two compute units at a time.  Its
   // scores are left to the second kernel, so that this stays so: 16.5 against 15.7 us with 2 workgroups, 19.6 against
@@ -1267,16 +1269,15 @@ static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStr
   const int n_wg = p.n_teams * p.team_size;
   const bool together = (p.n_teams > 1 || (score_out && n_wg == 1)) && handover_possible(n_wg);
   if (together) {
+    p.handoff = p.n_teams > 1;
     p.epoch = next_epoch();
     p.lost_flag = lost_flag();
-  }
-  if (together && p.n_teams > 1) {
-    p.handoff = 1;
-    for (int h = 0; h < p.H; ++h) p.n_cut_units[h] = 0;
+  } else {
+    count_cut_units(p);
   }
   char *ws = static_cast<char *>(workspace);
   p.part = score_out ? reinterpret_cast<float *>(ws) : nullptr;
-  p.tickets = score_out ? reinterpret_cast<int32_t *>(ws + part_bytes(p.H, p.Nq)) : nullptr;
+  p.tickets = score_out && !together ? reinterpret_cast<int32_t *>(ws + part_bytes(p.H, p.Nq)) : nullptr;
   p.flags = reinterpret_cast<unsigned long long *>(ws + part_bytes(p.H, p.Nq) + kTicketBytes);
   p.slots = reinterpret_cast<float *>(ws + part_bytes(p.H, p.Nq) + kTicketBytes + kFlagBytes);
   p.score = score_out;
@@ -1372,6 +1373,7 @@ extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32
   out->n_groups = p.n_groups;
   out->n_teams = p.n_teams;
   out->workgroups = p.n_teams * p.team_size;
+  count_cut_units(p);
   out->cut_units = 0;
   for (int h = 0; h < H; ++h) out->cut_units += p.n_cut_units[h];
   out->total_cols = p.total_cols;
