@@ -278,7 +278,7 @@ def run_config3(args, df, wl, torch, dev):
                    "history_frames": 21, "step": "per layer: head_score+classify(N=3), pack+attn(fused score)+append"},
         "stack_ms": {k: round(v, 3) for k, v in t_total.items()},
         "attn_ms_per_layer": stats(attn_ms),
-        "roofline": {"bound": "mfma", "kernel": "df_attn_fwd (df_attn_kernel + df_attn_merge_kernel), median over layers",
+        "roofline": {"bound": "mfma", "kernel": "df_attn_fwd (df_attn_kernel), median over layers",
                      "achieved": round(statistics.median(l["attn_TFLOPs"] for l in layers), 2), "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(statistics.median(l["attn_TFLOPs"] for l in layers) / PEAK_BF16_TFLOPS, 4),
                      "traffic": None},
@@ -357,7 +357,7 @@ def main():
                    "dummy_heads": n_dummy, "step": "head_score+classify, pack+attn(fused score)+append",
                    "value_is": "(attention + head_score algorithmic FLOP) / step time",
                    "classified_dummy": [h for h, t in enumerate(types) if t == df.DF_HEAD_DUMMY]},
-        "roofline": {"bound": "mfma", "kernel": "df_attn_fwd = df_attn_kernel + df_attn_merge_kernel",
+        "roofline": {"bound": "mfma", "kernel": "df_attn_fwd = df_attn_kernel",
                      "achieved": round(attn_tflops, 2),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(attn_tflops / PEAK_BF16_TFLOPS, 4),
                      "traffic": measured_traffic(w.name), "flop_per_launch": attn_flop,

@@ -86,18 +86,22 @@ df_status df_head_context(int32_t head_type, int32_t T, int32_t sink_frames,
  * the head's own visibility: the mean over all Nq queries of the attention
  * mass on (sink region, neighbour region, current chunk).
  *
- * Launches: one kernel, plus a small second one when score_out is given.  The
- * keys of a (head, query tile) unit may be split between workgroups; when the
- * device has a compute unit for every workgroup of the launch (it has on the
- * part this library is written for) the partial sums go through the workspace
- * while the kernel runs and the workgroup with a unit's last keys collects
- * them, with a bounded wait: should a workgroup never get to run
- * (compute units taken away from the process), the rows concerned come out as
- * NaN after some seconds instead of hanging the device.  DF_ATTN_HANDOVER=0 in
- * the environment (read at every call) selects the other path, in which a
- * second kernel puts those units together and sums the scores (otherwise the
- * first workgroup does, behind the same kind of wait); the results are the same
- * bit for bit.
+ * Launches: one kernel.  The keys of a (head, query tile) unit may be split
+ * between workgroups; when the device has a compute unit for every workgroup
+ * of the launch (it has on the part this library is written for) the partial
+ * sums go through the workspace while the kernel runs, the workgroup with a
+ * unit's last keys collects them, and the first workgroup sums the scores once
+ * all others are done, both with a bounded wait: should a workgroup never get
+ * to run (compute units taken away from the process), what depends on it comes
+ * out as NaN after some seconds instead of hanging the device - the unit's rows
+ * in out and lse_out, the head's or, where the first workgroup gave up, all
+ * heads' score_out.  A captured graph whose replay ended that way has to be
+ * captured again (the late workgroup's flag may still be up in the workspace).
+ * DF_ATTN_HANDOVER=0 in the environment (read at every call) selects the other
+ * path, which waits for nothing: a second kernel puts the split units together
+ * and sums the scores, the results are the same bit for bit.  A launch with
+ * score_out whose workgroups share no unit but are several (one span, more than
+ * one query tile) always leaves its scores to the second kernel.
  * Two calls that use the same workspace must not overlap on the device.
  *
  * Under HIP graph capture: the call records kernels only (no memset, no copy),
@@ -105,8 +109,8 @@ df_status df_head_context(int32_t head_type, int32_t T, int32_t sink_frames,
  * strides, pointers and the per-head tables hist_off / hist_sink_len /
  * hist_len.  A captured graph therefore stays valid only while the cache state
  * it was captured in holds (same head types, same per-head lengths, same
- * buffers); the data in the buffers may change.  After df_cache_append has
- * changed a length, or df_cache_pack has re-typed the heads, capture again.
+ * buffers); the data in the buffers may change.  After df_kv_append has
+ * changed a length, or heads have been re-typed, capture again.
  * ---------------------------------------------------------------------- */
 typedef struct df_attn_args {
   const void *q;            /* DEVICE bf16, element (u,h,c) at q[u*q_stride_tok + h*q_stride_head + c] */

@@ -73,7 +73,8 @@
 // and (m2,l2) after the window region give a row's region masses as
 // l1*2^(m1-m3)/l3, (l2*2^(m2-m3) - l1*2^(m1-m3))/l3 and the remainder.  Each unit
 // leaves the sums of its rows; the first workgroup adds them up per head when all
-// workgroups are on the device at once, else the second kernel does, in the same order.
+// workgroups are on the device at once, else (and for a single team of several
+// workgroups) the second kernel does, in the same order.
 #include <algorithm>
 #include <cmath>
 #include <atomic>
@@ -393,9 +394,12 @@ __device__ __forceinline__ void store_output_block(const AttnParams &p, int h, i
 // The same for a whole unit: a wave's 32 finished rows (first row row0) go through LDS, `buf` being the wave's own
 // 32 * D bf16 there, and out with 16 bytes per lane and whole rows side by side.  In the accumulator layout a lane
 // holds 8-byte bits of one row, and a store of those touches 32 rows: issuing 16 of them and draining them took
-// 5 to 6 us a unit; through LDS a 832x480 call went from 319 to 314 us, one of 1170 queries from 46.5 to
-// 44.7.  16-byte chunk c of row r lies at position c ^ (r mod chunks per
-// row), which keeps both directions free of bank conflicts without padding.
+// 5 to 6 us a unit.  Both ways on one box, direct -> through LDS: 1170 queries 44.1 -> 42.1 us, 832x480 308.0 -> 305.0,
+// packed-dummy step 234.8 -> 230.7, histories of 3 to 60 frames 610.0 -> 601.9; a launch of 64 queries 15.1 -> 15.8.
+// The price is registers: the d = 128 kernel spills 2 (12 bytes of scratch a lane), direct stores spill none.
+// 16-byte chunk c of row r lies at position c ^ (r mod chunks per row).  The reads are then free of bank conflicts;
+// the 8-byte writes are not: rows D / 8 apart share a position and the lanes of a half-wave have one 8-byte half, 4
+// cycles more a write at d = 128 (116,736 in an 832x480 launch, 0.1 % of the CU-busy cycles).
 template <int D>
 __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row0, unsigned char *buf, int lane,
                                              const f32x16 (&o)[D / 32], float inv) {
@@ -477,8 +481,9 @@ __device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long
 // The frame attention scores of all heads, by the first workgroup at the end of its span: when every workgroup has
 // raised its flag, the units' sums come into LDS (`buf`, room for PAIRS of them) with all threads loading, and
 // one thread per head adds its tiles up in finish_score's order, so that both ways give the same bits.  A second
-// launch for these few sums cost 4 to 6 us a call (832x480 sampled scores, a 1170-query call); this costs two
-// trips to memory.  An atomic counter per head instead of the flags puts a trip on every unit's path.
+// launch for these few sums took 4 to 6 us by the kernel trace; this costs two trips to memory (1170 queries 44.7 ->
+// 43.4 us, 832x480 sampled scores 67.4 -> 65.6).  An atomic counter per head instead of the flags puts a trip on every
+// unit's path.
 template <int PAIRS>
 __device__ __forceinline__ void finish_all_scores(const AttnParams &p, float2 *buf, int *all_up, int tid) {
   const int n_wg = p.n_teams * p.team_size;
@@ -916,8 +921,8 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       const float poison = lds_ok ? 0.f : NAN;
       // From this piece back to the unit's first, the order and arithmetic of the merge kernel: every earlier piece is
       // folded into this one's registers, all of it loaded with one wait.  (Front to back the sum so far needs
-      // registers of its own, and the loads had to go out four at a time: with 6 pieces to a unit that was most of
-      // a small launch.)
+      // registers of its own, and the loads had to go out four at a time: 1170 queries, 6 pieces to a unit, 54.8 us
+      // against 47.1.)
 #pragma unroll 1
       for (int sp = span - 1; sp >= s_first; --sp) {
         const int which = unit_lo > span_begin(p, sp) ? 1 : 0;
@@ -1073,7 +1078,8 @@ constexpr int kMinQTile = 128;   // smallest query tile any kernel variant uses 
 // Workspace layout: [score partials: H * ceil(Nq/128) * 4 floats, rounded up to 256 B]
 //                   [unit counters of the merge kernel: 256 B]
 //                   [hand-over flags: one 8-byte word per workgroup]
-//                   [partial-result slots: 2 per workgroup, kNumCU workgroups at most]
+//                   [partial-result slots: 2 per workgroup, kNumCU workgroups at most; the flags of the score sums, one
+//                    8-byte word per workgroup, lie in the last span's slot for later pieces, which stays empty]
 static size_t part_bytes(int H, int Nq) {
   const size_t tiles = (size_t(Nq) + kMinQTile - 1) / kMinQTile;
   return ((size_t(H) * tiles * 4 * sizeof(float) + 255) / 256) * 256;
@@ -1092,7 +1098,8 @@ static size_t workspace_bytes(int H, int d, int Nq) {
 // decides: a workgroup that holds the end of one unit and the start of the next pays for two, and every
 // earlier piece of a unit is another trip to memory for the workgroup that finishes it.  span_cost is the time of
 // the slowest workgroup, counted in tile iterations (1.4 us at d = 128): reading a piece's first tiles, leaving sums
-// behind, finishing a unit, and the flags and sums of earlier pieces, as stamps inside the kernel gave them.
+// behind, finishing a unit, and the flags and sums of earlier pieces, as stamps inside the kernel gave them.  d = 64 and
+// scoring, whose tiles are shorter and whose handed-on pieces are smaller, use the same numbers.
 constexpr float kPieceCost = 2.0f, kGiveCost = 2.0f, kFinishCost = 1.5f, kPollCost = 1.0f, kFoldCost = 1.4f;
 static float span_cost(const AttnParams &p, int n) {
   const int line = p.n_groups * p.total_cols;
@@ -1190,8 +1197,9 @@ static df_status plan(AttnParams &p) {
   p.line_len = int64_t(p.n_groups) * total;
   p.n_teams = int32_t(teams_of(team));
   // Launches that spans of kMinSpan tiles leave part of the machine without work.  Measured on 13 of them, 64 to 1170
-  // queries and 4 to 45 tiles a unit: a fixed least span of 8, 6, 4 or 3 tiles each was best for some and up to twice
-  // too slow for others.  One step further (1170 queries, 9 tiles a span) all spans are better kept: 43.4 against
+  // queries and 4 to 45 tiles a unit (three at d = 64, three of scores): a fixed least span of 8, 6, 4 or 3 tiles each was
+  // best for some and up to twice too slow for others; against spans of 4 the choice is between the same (64 queries 15.8
+  // us both) and 23 % faster (300 queries 29.2 -> 22.6; scores 25.5 -> 21.5, 16.9 -> 14.2, 12.8 -> 10.9).  One step further (1170 queries, 9 tiles a span) all spans are better kept: 43.4 against
   // 44.0 us with the choice.
   if (p.line_len < kMinSpan * (kNumCU / team))
     p.n_teams = cheapest_spans(p, std::max(1, std::min(kNumCU / team, int(p.line_len) / kMinSmallSpan)));

@@ -9,8 +9,8 @@ DIR is the -d directory of one rocprofv3 run (--output-format csv).  `kernels` p
 durations of a --kernel-trace --stats run as a markdown table; `counters` the median per dispatch of
 every counter of a --pmc run; `traffic` scales FETCH_SIZE / WRITE_SIZE (two runs) by what the same
 counters read for the one large device copy of known size in the same run, prints bytes per dispatch
-of every kernel, and with --update records the bytes of one attention call (main kernel + second
-kernel), with a hash of the kernel sources, in the JSON file bench.py reads its `roofline.traffic`
+of every kernel, and with --update records the bytes of one attention call (the main kernel and, on
+the two-kernel path, the second one), with a hash of the kernel sources, in the JSON file bench.py reads its `roofline.traffic`
 from.
 """
 from __future__ import annotations
@@ -115,7 +115,7 @@ def main():
             print("| `%s` | %.1f | %.1f |" % (k[:90], table[k][0] / 1e6, table[k][1] / 1e6))
             if "df_attn_kernel" in k and "false" in k or "df_attn_merge_kernel" in k and "false" in k:
                 call += table[k][0] + table[k][1]
-        print(f"\ndf_attn_fwd per call (main kernel + second kernel, fetched + written): {call / 1e6:.1f} MB; "
+        print(f"\ndf_attn_fwd per call (all its kernels, fetched + written): {call / 1e6:.1f} MB; "
               f"kernel sources {kernel_source_hash()}")
         if a.update:
             try:
