@@ -97,6 +97,9 @@ df_status df_head_context(int32_t head_type, int32_t T, int32_t sink_frames,
  * in out and lse_out, the head's or, where the first workgroup gave up, all
  * heads' score_out.  A captured graph whose replay ended that way has to be
  * captured again (the late workgroup's flag may still be up in the workspace).
+ * Two calls that run on the device at the same time (different streams) can
+ * bring that about for each other: workgroups of both that wait hold compute
+ * units which those they wait for need.  Order such calls, or use the other path.
  * DF_ATTN_HANDOVER=0 in the environment (read at every call) selects the other
  * path, which waits for nothing: a second kernel puts the split units together
  * and sums the scores, the results are the same bit for bit.  A launch with
