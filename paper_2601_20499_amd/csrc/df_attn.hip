@@ -76,6 +76,7 @@
 // workgroups are on the device at once, else (and for a single team of several
 // workgroups) the second kernel does, in the same order.
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <atomic>
 #include <cstdlib>
@@ -844,13 +845,12 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
             for (int v = 0; v < 16; ++v) a = fmaxf(a, s[kb][v]);
           const float mx = pair_max(a);       // exact row maximum of the tile: the new P are at most 1
           // the reference also absorbs the size of the sum so far (l becomes O(1)); -inf while l = 0
-          const float m_new = fmaxf(fmaxf(m, mx), m + __builtin_amdgcn_logf(pair_sum(l)) * p.inv_c);
-          // Every key so far scores minus infinity: there is nothing to refer to yet.  P is zero for the tile (taken
-          // against 0) and the row starts anew with the next one, whose sum is not finite against nmc = +inf.
-          const bool none = m_new == -INFINITY;
-          const float alpha = none ? 1.f : fast_exp2((m - m_new) * p.c);
+          // Finite also where every key so far scores minus infinity: P of such a tile is then zero, not the NaN of
+          // inf - inf, and the first key that scores anything takes the reference up here again.
+          const float m_new = fmaxf(fmaxf(fmaxf(m, mx), m + __builtin_amdgcn_logf(pair_sum(l)) * p.inv_c), -FLT_MAX);
+          const float alpha = fast_exp2((m - m_new) * p.c);
           m = m_new;
-          nmc = -m * p.c;
+          nmc = fminf(-m * p.c, FLT_MAX);
           l *= alpha;
           if (!SCORE_ONLY) {
 #pragma unroll
@@ -858,7 +858,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 #pragma unroll
               for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
           }
-          ts = exp_tile(none ? 0.f : nmc);
+          ts = exp_tile(nmc);
           l_new = l + ts;
         }
         l = l_new;
@@ -894,9 +894,8 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 
     // ---- piece epilogue
     const float lt = pair_sum(l_piece);
-    // (m may still be minus infinity, see `none` above)
-    const float l1 = pair_sum(snap_m0 == m ? snap_l0 : snap_l0 * fast_exp2((snap_m0 - m) * p.c));   // sink region, relative to m
-    const float l2 = pair_sum(snap_m1 == m ? snap_l1 : snap_l1 * fast_exp2((snap_m1 - m) * p.c));   // sink + window regions
+    const float l1 = pair_sum(snap_l0 * fast_exp2((snap_m0 - m) * p.c));   // sink region, relative to m
+    const float l2 = pair_sum(snap_l1 * fast_exp2((snap_m1 - m) * p.c));   // sink + window regions
     const int row = q0 + j;
     const bool valid = row < p.Nq;
     float m_u = m, lt_u = lt, l1_u = l1, l2_u = l2;
