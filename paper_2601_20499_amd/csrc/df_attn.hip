@@ -127,8 +127,9 @@ struct AttnParams {
   int32_t *tickets;    // workspace: [H] counters of the merged units of a head (zeroed by the main kernel), or null
   unsigned long long *flags;   // workspace: one word per workgroup, = epoch once its hand-over sum is in memory
   unsigned long long epoch;    // this launch's flag value: random, so that memory never holds it by chance
-  int32_t handoff;     // cut units are put together inside the main kernel (needs all workgroups on the device at once)
-  int32_t lost_flag;   // number of a flag that its reader gives up on without a poll, or -1 (see lost_flag())
+  int32_t handoff;     // cut units are put together inside the main kernel (needs all workgroups on the device at once);
+                       // 2 + n: and the reader of flag n gives up on it without a poll (see lost_flag(); a parameter of
+                       // its own cost a scored launch 0.4 us, by the scalar register that it holds)
   float *slots;        // workspace: 2 partial-result slots per workgroup (see Slot)
   float *score;        // [H, 3] frame attention scores, or null
   unsigned long long *done;    // one word per workgroup, = epoch once its units' score sums are in memory; null: the
@@ -470,8 +471,7 @@ __device__ __forceinline__ void finish_score(const AttnParams &p, int h) {
 // a replay of the launch (same value) has to start clean.  `number` is the flag's number as lost_flag() counts them.
 __device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int number) {
   int up = 0;
-  const int polls = number == p.lost_flag ? 0 : kSpinLimit;
-  for (int spin = 0; spin < polls && !up; ++spin) {
+  for (int spin = number == p.handoff - 2 ? kSpinLimit : 0; spin < kSpinLimit && !up; ++spin) {
     up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
     if (!up) __builtin_amdgcn_s_sleep(16);
   }
@@ -1253,7 +1253,7 @@ static bool handover_possible(int n_wg) {
 // hand-over flags are numbered by workgroup, the flags of the score sums follow from kNumCU on.
 static int lost_flag() {
   const char *e = std::getenv("DF_ATTN_LOST_FLAG");
-  return e && *e ? std::atoi(e) : -1;
+  return e && *e ? std::clamp(std::atoi(e), -1, 2 * kNumCU) : -1;
 }
 
 // A flag value that neither stale workspace contents nor an earlier launch hold: a counter run through a
@@ -1276,9 +1276,8 @@ static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStr
   const int n_wg = p.n_teams * p.team_size;
   const bool together = (p.n_teams > 1 || (score_out && n_wg == 1)) && handover_possible(n_wg);
   if (together) {
-    p.handoff = p.n_teams > 1;
+    p.handoff = 2 + lost_flag();
     p.epoch = next_epoch();
-    p.lost_flag = lost_flag();
   } else {
     count_cut_units(p);
   }
