@@ -28,14 +28,14 @@
 // two XCDs.
 //
 // MFMA mapping.  Scores are computed transposed, S^T = K Q^T, with
-// v_mfma_f32_32x32x16_bf16: the K tile is the A operand (ds_read_b128 from a
-// row-major LDS tile), the wave's Q fragment is the B operand (registers, loaded
-// once per unit).  In the 32x32 accumulator layout a lane owns ONE query
-// (column lane%32) and 16 of the 32 keys of a block, so the softmax row
-// reductions are in-lane except for one exchange with lane^32, and the
-// probabilities are already in the register layout the second product needs
-// as its B operand: O^T += V^T P^T.  V^T is the A operand and is read from a
-// row-major V tile in LDS with the transposing ds_read_b64_tr_b16.
+// v_mfma_f32_16x16x32_bf16: 16 keys of the K tile are the A operand (ds_read_b128 from a
+// row-major LDS tile), 16 queries of the wave's Q the B operand (registers, loaded
+// once per unit); an A operand feeds the wave's two blocks of 16 queries.  In the
+// 16x16 accumulator layout a lane owns TWO queries (lane%16 of each block) and 4 of the 16
+// keys of a block, so the softmax row reductions are in-lane except for the exchange between
+// the four lanes of a query at the end, and the probabilities are already in the register
+// layout the second product needs as its B operand: O^T += V^T P^T.  V^T is the A operand
+// and is read from a row-major V tile in LDS with the transposing ds_read_b64_tr_b16.
 //
 // Schedule.  The 8 waves form two groups of 4 (one wave of each group per
 // SIMD).  Every tile iteration of a wave has an MFMA phase (S = K Q^T of tile t
@@ -45,33 +45,31 @@
 // after its MFMA phase: between two barriers group 0 runs MFMA(t), VALU(t) and
 // group 1 runs VALU(t-1), MFMA(t), so on every SIMD one wave is in its MFMA
 // phase while the other is in its VALU phase: the matrix core and the vector
-// ALU overlap without relying on instruction scheduling.
+// ALU overlap without relying on instruction scheduling.  The loop over the tiles of a
+// piece is one generated asm statement (gen_attn_phase.py has the schedule and its reasons).
 //
 // Staging.  K and V tiles go from global memory straight into LDS with
 // buffer_load_dwordx4 ... lds (no registers, no LDS store instructions); rows
 // past the end of a head's buffer read as zero through the buffer range check.
 // One such instruction fills 1 KB of LDS contiguously, so a tile is stored as
 // groups of rows {g, g+NG, g+2NG, ...} (NG = 16 groups for d = 128), each group
-// 1 KB plus a small pad.  With 16 B of pad per K group the 32 rows a wavefront
-// reads per ds_read_b128 fall into distinct banks, with 64 B per V group the
-// four consecutive keys of a ds_read_b64_tr_b16 do, and every operand address
-// is still "lane base + compile-time offset".  Tiles rotate through four LDS
-// buffers each; loads are issued two to three iterations before their first use.
+// 1 KB plus a small pad, and every operand address is still "lane base + compile-time
+// offset".  Tiles rotate through four LDS buffers each; loads are issued two to three
+// iterations before their first use.
 //
-// Online softmax keeps a reference exponent m per row and per-lane partial row
-// sums l in fp32.  m is the maximum of the row's first tile and is NOT raised
-// tile by tile: exp2 of a logit above m simply exceeds one, which fp32 holds
+// Online softmax keeps a reference exponent per row (in units of log2) and per-lane partial row
+// sums l in fp32.  The reference is the maximum of the row's first tile and is NOT raised
+// tile by tile: exp2 of a logit above it simply exceeds one, which fp32 holds
 // with room to spare.  Only when a row's sum passes 2^100 (or is no longer
-// finite) is m raised to the row's current maximum plus the logarithm of the
+// finite) is it raised to the row's current maximum or the logarithm of the
 // sum and O, l rescaled, so the per-tile work has no row maximum, no
 // comparison against the old one and no rescaling; P is rounded to bf16 (RNE)
 // before the second product; l sums the unrounded fp32 values.  The output is
 // divided by l and rounded to bf16 once at the end.
 //
 // The frame attention score of Eq. 3 falls out of the same statistics: with the
-// keys ordered sink | window | current, snapshots (m1,l1) after the sink region
-// and (m2,l2) after the window region give a row's region masses as
-// l1*2^(m1-m3)/l3, (l2*2^(m2-m3) - l1*2^(m1-m3))/l3 and the remainder.  Each unit
+// keys ordered sink | window | current, the sums l1 after the sink region and l2 after the window region,
+// rescaled with l where the reference goes up, give a row's region masses as l1/l, (l2 - l1)/l and the remainder.  Each unit
 // leaves the sums of its rows; the first workgroup adds them up per head when all
 // workgroups are on the device at once, else (and for a single team of several
 // workgroups) the second kernel does, in the same order.
@@ -103,7 +101,7 @@ constexpr int kWaves = 8;
 constexpr int kBQ = kWaves * 32;   // queries per workgroup
 constexpr int kKT = 64;            // keys per LDS tile
 constexpr int kNBuf = 4;           // LDS buffers per operand
-constexpr float kSumLimit = 0x1p100f; // the reference of the exponentials is raised when a row's running sum passes this
+constexpr float kSumLimit = 0x1p100f; // the references are raised when the running sums of a lane's two rows pass this
 constexpr int kXcd = 8;            // XCDs per device: consecutive workgroup ids go to consecutive XCDs
 constexpr int kNumCU = 256;        // MI355X: one workgroup per CU (LDS-bound occupancy)
 constexpr int kMinSpan = 8;        // do not cut the work finer than this many key tiles per team ...
@@ -145,8 +143,7 @@ struct AttnParams {
   int32_t cum[kMaxHeads + 1];  // first column of the hh-th longest head
   uint32_t cur_bytes;  // addressable bytes of one head's current-chunk rows: ((Nc-1)*kc_st + d) * 2
   float c;             // softmax_scale * log2(e)
-  float inv_c;         // 1 / c
-  float scale;         // softmax_scale
+  float lse_unit;      // softmax_scale / c: natural logarithm of one unit of the references
   HeadRec rec[kMaxHeads];      // heads sorted by descending key count
 };
 
@@ -158,30 +155,29 @@ __device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
   return __builtin_bit_cast(unsigned, h);
 }
 
-// Both values of the lane pair (lane, lane^32): a = the lower lane's value, b = the upper lane's.
-// v_permlane32_swap_b32 exchanges lanes 32..63 of its first operand with lanes 0..31 of its second.
-__device__ __forceinline__ void pair_values(float x, float &a, float &b) {
-  a = x;
-  b = x;
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+// Sum over the four lanes (lane % 16 + 0, 16, 32, 48) that share a query.
+__device__ __forceinline__ float quad_sum(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
 }
-__device__ __forceinline__ float pair_max(float x) { float a, b; pair_values(x, a, b); return fmaxf(a, b); }
-__device__ __forceinline__ float pair_sum(float x) { float a, b; pair_values(x, a, b); return a + b; }
+
+// A lane's value for query block g % 2 (by value: an address that depends on the lane would put the pair into memory).
+__device__ __forceinline__ float of_block(int g, const float (&x)[2]) {
+  const float x0 = x[0], x1 = x[1];
+  return (g & 1) ? x1 : x0;
+}
 
 // Workgroup barrier that waits for this wave's LDS traffic only: global loads stay in flight.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Position, inside a 32-key block, of the key whose scores land in accumulator
-// row i: bits 2 and 3 of i are exchanged.  With it, accumulator registers
-// 8t..8t+7 of a lane in half hf hold the 8 consecutive keys 16t+8hf .. +7,
-// which is exactly the k-slice that lane feeds to the second product.
-__device__ __forceinline__ int key_of_row(int i) {
-  return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1);
+// Key, inside a block of 16, of row i of a product's A operand (row i of the first product's result, k index i of the
+// second's): rows 4..11 are the keys 0, 1, 4, 5, 8, 9, 12, 13, so that the reads of the operands are free of bank
+// conflicts (see TileLayout).  key_of_row(4 g + v) = key_of_row(4 g) + key_of_row(4 + v) for v < 4.
+__host__ __device__ constexpr int key_of_row(int i) {
+  return (i & 1) | ((i & 2) << 1) | ((((i >> 2) + 1) & 2) ? 0 : 2) | (i & 8);
 }
-
-
 
 // LDS layout of one 64-key tile (all sizes in bytes).  Row r lives in group r % NG at position
 // r / NG; a group is the 1 KB one buffer_load ... lds instruction writes, followed by a pad.
@@ -191,9 +187,15 @@ struct TileLayout {
   static constexpr int RPG = 1024 / ROWB;       // rows per group
   static constexpr int NG = kKT / RPG;          // groups per tile
   static constexpr int KGS = 1024 + 16;         // K group stride
-  static constexpr int VGS = 1024 + 64;         // V group stride
+  static constexpr int VGS = 1024 + 32;         // V group stride
   static constexpr int KTILE = NG * KGS, VTILE = NG * VGS;
   static_assert(kNBuf * KTILE >= kBQ * ROWB, "a unit's output rows pass through the K buffers");
+  // A lane of quarter g reads the 16-byte chunks first_chunk(g) + ks of its K row, ks = 0 .. D/32 - 1.  The hardware
+  // takes the lanes of a ds_read_b128 in the groups {0-3, 12-15, 20-27}, {4-11, 16-19, 28-31} and the same + 32;
+  // row r begins at bank slot (16 bytes) r, so a group reads slots {r of its rows in quarter 0 or 2} and
+  // {r + 4 of its rows in quarter 1 or 3}: with rows 4..11 on keys 0, 1 mod 4 and the others on 2, 3 mod 4 all 16
+  // differ.
+  static constexpr int first_chunk(int g) { return 4 * (g & 1) + (D == 128 ? 8 : 2) * (g >> 1); }
   static constexpr int k_row(int r) { return (r % NG) * KGS + (r / NG) * ROWB; }
   static constexpr int v_row(int r) { return (r % NG) * VGS + (r / NG) * ROWB; }
 };
@@ -202,20 +204,53 @@ __device__ __forceinline__ unsigned lds_address(const void *ptr) {
   return unsigned(reinterpret_cast<uintptr_t>(ptr));     // low half of a flat LDS address = LDS offset
 }
 
-// The MFMA phase of a wave (both products of one tile, LDS operand reads hand-ordered) as one asm block.
+// Buffer descriptor of `bytes` bytes from `base` on (loads past its end return zeros), as the four words themselves.
+__device__ __forceinline__ u32x4 buffer_descriptor(const u16 *base, uint32_t bytes) {
+  const uint64_t addr = reinterpret_cast<uint64_t>(base);
+  return u32x4{uint32_t(addr), uint32_t(addr >> 32) & 0xffffu, bytes, 0x00020000u};
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t as_buffer(const u32x4 &words) {
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(uint64_t(words[0]) | uint64_t(words[1]) << 32), 0,
+                                           int(words[2]), int(words[3]));
+}
+
+// What the tile loop of a piece needs besides the queries (uniform, or one value per lane where it says so) ...
+struct TileLoopArgs {
+  int t_begin, te;             // first tile of the piece, tile behind its last
+  int nt0, nt1;                // tile behind the sink region, tile behind the window region
+  int sink, win, nc;           // keys of the sink region, the window region, the current chunk
+  unsigned cs;                 // bytes between rows of the current chunk
+  int grp;                     // group of the wave
+  unsigned ldsk, ldsv;         // LDS addresses of the wave's first row group in the K and V buffers
+  float c, lim;                // scale of the logits in units of log2; row sum beyond which the reference is raised
+  unsigned ka, va;             // per lane: LDS addresses of the first K and V operand in buffer 0
+  unsigned offh, offc;         // per lane: byte offset of the lane's 16 bytes in the first tile, history and current chunk
+  int key0;                    // per lane: key of the first of the lane's four rows of a block
+  u32x4 kh, kc, vh, vc;        // buffer descriptors: history and current chunk of K and V
+};
+// ... and what it leaves for the lane's two queries besides O: reference of the exponentials in units of log2 (its
+// negative), the lane's share of the row sum relative to it, and of the sums up to the end of the sink and window region.
+struct RowSums {
+  float neg_ref[2], l[2], l_sink[2], l_hist[2];
+};
+template <int D, bool SCORE_ONLY, bool LIVE>
+__device__ __forceinline__ void tile_loop(const TileLoopArgs &a, const bf16x8 (&qf)[D / 32][2], f32x4 (&o)[D / 16][2], RowSums &r);
 #include "df_attn_phase.inc"
 
 typedef __attribute__((address_space(3))) void lds_void;
 
 // Partial result of one piece of a unit, as the main kernel leaves it in the workspace and the
 // merge kernel reads it back.  Both kernels use the same thread <-> element mapping, so the layout
-// is simply "in register order": per thread (m, l, l_sink, l_sink+window) and D/8 vectors of 4
-// consecutive output elements.
+// is simply "in register order": per thread 4 statistics (reference, l, l_sink, l_sink+window) and D/8 vectors of
+// 4 consecutive output elements.  A thread holds the same statistics as three other lanes for each of its two
+// queries: it writes those of query block (lane / 16) % 2 and reads its blocks' from lanes lane % 16 and
+// 16 + lane % 16 of its wave.
 template <int D>
 struct Slot {
   static constexpr int kStats = kThreads * 4;                   // floats
   static constexpr int kFloats = kStats + kThreads * (D / 8) * 4;
   __device__ static float *stats(float *slot, int tid) { return slot + 4 * tid; }
+  __device__ static int stats_reader(int tid, int qb) { return (tid & ~63) + 16 * qb + (tid & 15); }
   __device__ static float *ovec(float *slot, int tid, int i) { return slot + kStats + (i * kThreads + tid) * 4; }
 };
 
@@ -225,9 +260,11 @@ struct Slot {
 // sc1: stores write through to memory, loads are served from memory) - the same bits the compiler puts
 // on a relaxed system-scope atomic, here on 16-byte accesses - instead of cache maintenance, which
 // would also throw the K/V tiles the team shares out of L2.
-__device__ __forceinline__ void store4_through(float *ptr, float a, float b, float c, float d) {
-  const f32x4 v = {a, b, c, d};
-  asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(ptr), "v"(v) : "memory");
+// The idle cycles keep the next instruction off the data registers while the store still reads them (a store of more
+// than 8 bytes needs one wait state, which the compiler does not add to inline asm: without it the next address went
+// into the first statistics of the last four lanes of every 16).
+__device__ __forceinline__ void store4_through(float *ptr, const f32x4 &v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(ptr), "v"(v) : "memory");
 }
 // One 16-byte load; returns when the data is in the registers.
 __device__ __forceinline__ f32x4 load4_through(const float *ptr) {
@@ -236,17 +273,18 @@ __device__ __forceinline__ f32x4 load4_through(const float *ptr) {
   return v;
 }
 
-// A whole slot (the thread's statistics and its N = D/8 vectors of O) with every load in flight at once and one
-// wait: the slot's address is uniform, the thread's part of it is tid * 16 bytes, vectors are 8 KB apart.
+// A whole slot (the statistics of the thread's two queries and its N = D/8 vectors of O) with every load in flight at
+// once and one wait: the slot's address is uniform, the thread's part of it is tid * 16 bytes, vectors are 8 KB apart.
 template <int N>
-__device__ __forceinline__ void load_slot_through(const float *slot, int tid, f32x4 &st, f32x4 (&v)[N]);
+__device__ __forceinline__ void load_slot_through(const float *slot, int tid, f32x4 (&st)[2], f32x4 (&v)[N]);
 template <>
-__device__ __forceinline__ void load_slot_through<16>(const float *slot, int tid, f32x4 &st, f32x4 (&v)[16]) {
+__device__ __forceinline__ void load_slot_through<16>(const float *slot, int tid, f32x4 (&st)[2], f32x4 (&v)[16]) {
   static_assert(Slot<128>::kStats * 4 == 0x2000 && kThreads * 16 == 0x2000, "offsets of the asm below");
-  const unsigned vo = unsigned(tid) * 16u;
+  const unsigned vo = unsigned(tid) * 16u, so = unsigned(Slot<128>::stats_reader(tid, 0)) * 16u;
   unsigned t0, t1;
   asm volatile(
-      "global_load_dwordx4 %[st], %[vo], %[sb] sc0 sc1\n\t"
+      "global_load_dwordx4 %[s0], %[so], %[sb] sc0 sc1\n\t"
+      "global_load_dwordx4 %[s1], %[so], %[sb] offset:256 sc0 sc1\n\t"
       "v_add_u32 %[t0], 0x2000, %[vo]\n\t"
       "global_load_dwordx4 %[v0], %[t0], %[sb] sc0 sc1\n\t"
       "v_add_u32 %[t1], 0x4000, %[vo]\n\t"
@@ -280,17 +318,18 @@ __device__ __forceinline__ void load_slot_through<16>(const float *slot, int tid
       "v_add_u32 %[t1], 0x20000, %[vo]\n\t"
       "global_load_dwordx4 %[v15], %[t1], %[sb] sc0 sc1\n\t"
       "s_waitcnt vmcnt(0)"
-      : [st] "=&v"(st), [v0] "=&v"(v[0]), [v1] "=&v"(v[1]), [v2] "=&v"(v[2]), [v3] "=&v"(v[3]), [v4] "=&v"(v[4]), [v5] "=&v"(v[5]), [v6] "=&v"(v[6]), [v7] "=&v"(v[7]), [v8] "=&v"(v[8]), [v9] "=&v"(v[9]), [v10] "=&v"(v[10]), [v11] "=&v"(v[11]), [v12] "=&v"(v[12]), [v13] "=&v"(v[13]), [v14] "=&v"(v[14]), [v15] "=&v"(v[15]), [t0] "=&v"(t0), [t1] "=&v"(t1)
-      : [vo] "v"(vo), [sb] "s"(slot)
+      : [s0] "=&v"(st[0]), [s1] "=&v"(st[1]), [v0] "=&v"(v[0]), [v1] "=&v"(v[1]), [v2] "=&v"(v[2]), [v3] "=&v"(v[3]), [v4] "=&v"(v[4]), [v5] "=&v"(v[5]), [v6] "=&v"(v[6]), [v7] "=&v"(v[7]), [v8] "=&v"(v[8]), [v9] "=&v"(v[9]), [v10] "=&v"(v[10]), [v11] "=&v"(v[11]), [v12] "=&v"(v[12]), [v13] "=&v"(v[13]), [v14] "=&v"(v[14]), [v15] "=&v"(v[15]), [t0] "=&v"(t0), [t1] "=&v"(t1)
+      : [vo] "v"(vo), [so] "v"(so), [sb] "s"(slot)
       : "memory");
 }
 template <>
-__device__ __forceinline__ void load_slot_through<8>(const float *slot, int tid, f32x4 &st, f32x4 (&v)[8]) {
+__device__ __forceinline__ void load_slot_through<8>(const float *slot, int tid, f32x4 (&st)[2], f32x4 (&v)[8]) {
   static_assert(Slot<64>::kStats * 4 == 0x2000 && kThreads * 16 == 0x2000, "offsets of the asm below");
-  const unsigned vo = unsigned(tid) * 16u;
+  const unsigned vo = unsigned(tid) * 16u, so = unsigned(Slot<64>::stats_reader(tid, 0)) * 16u;
   unsigned t0, t1;
   asm volatile(
-      "global_load_dwordx4 %[st], %[vo], %[sb] sc0 sc1\n\t"
+      "global_load_dwordx4 %[s0], %[so], %[sb] sc0 sc1\n\t"
+      "global_load_dwordx4 %[s1], %[so], %[sb] offset:256 sc0 sc1\n\t"
       "v_add_u32 %[t0], 0x2000, %[vo]\n\t"
       "global_load_dwordx4 %[v0], %[t0], %[sb] sc0 sc1\n\t"
       "v_add_u32 %[t1], 0x4000, %[vo]\n\t"
@@ -308,8 +347,8 @@ __device__ __forceinline__ void load_slot_through<8>(const float *slot, int tid,
       "v_add_u32 %[t1], 0x10000, %[vo]\n\t"
       "global_load_dwordx4 %[v7], %[t1], %[sb] sc0 sc1\n\t"
       "s_waitcnt vmcnt(0)"
-      : [st] "=&v"(st), [v0] "=&v"(v[0]), [v1] "=&v"(v[1]), [v2] "=&v"(v[2]), [v3] "=&v"(v[3]), [v4] "=&v"(v[4]), [v5] "=&v"(v[5]), [v6] "=&v"(v[6]), [v7] "=&v"(v[7]), [t0] "=&v"(t0), [t1] "=&v"(t1)
-      : [vo] "v"(vo), [sb] "s"(slot)
+      : [s0] "=&v"(st[0]), [s1] "=&v"(st[1]), [v0] "=&v"(v[0]), [v1] "=&v"(v[1]), [v2] "=&v"(v[2]), [v3] "=&v"(v[3]), [v4] "=&v"(v[4]), [v5] "=&v"(v[5]), [v6] "=&v"(v[6]), [v7] "=&v"(v[7]), [t0] "=&v"(t0), [t1] "=&v"(t1)
+      : [vo] "v"(vo), [so] "v"(so), [sb] "s"(slot)
       : "memory");
 }
 
@@ -381,41 +420,34 @@ __host__ __device__ __forceinline__ Piece piece_ending_at(const AttnParams &p, c
   return c;
 }
 
-// Normalise, round and store one thread's share of 32 output columns (block db) of a finished unit.
-__device__ __forceinline__ void store_output_block(const AttnParams &p, int h, int row, int hf, int db, const f32x16 &o,
-                                                   float inv) {
-  u16 *dst = p.out + row * p.o_st + h * p.o_sh + 4 * hf + 32 * db;
-#pragma unroll
-  for (int cq = 0; cq < 4; ++cq) {
-    uint2 w;
-    w.x = pack_bf16x2(o[4 * cq] * inv, o[4 * cq + 1] * inv);
-    w.y = pack_bf16x2(o[4 * cq + 2] * inv, o[4 * cq + 3] * inv);
-    *reinterpret_cast<uint2 *>(dst + 8 * cq) = w;
-  }
+// Normalise and round four consecutive output elements.
+__device__ __forceinline__ uint2 output4(const f32x4 &o, float inv) {
+  uint2 w;
+  w.x = pack_bf16x2(o[0] * inv, o[1] * inv);
+  w.y = pack_bf16x2(o[2] * inv, o[3] * inv);
+  return w;
 }
-// The same for a whole unit: a wave's 32 finished rows (first row row0) go through LDS, `buf` being the wave's own
-// 32 * D bf16 there, and out with 16 bytes per lane and whole rows side by side.  In the accumulator layout a lane
-// holds 8-byte bits of one row, and a store of those touches 32 rows: issuing 16 of them and draining them took
-// 5 to 6 us a unit.  Both ways on one box, direct -> through LDS: 1170 queries 44.1 -> 42.1 us, 832x480 308.0 -> 305.0,
-// packed-dummy step 234.8 -> 230.7, histories of 3 to 60 frames 610.0 -> 601.9; a launch of 64 queries 15.1 -> 15.8.
-// The price is registers: the d = 128 kernel spills 2 (12 bytes of scratch a lane), direct stores spill none.
-// 16-byte chunk c of row r lies at position c ^ (r mod chunks per row).  The reads are then free of bank conflicts;
-// the 8-byte writes are not: rows D / 8 apart share a position and the lanes of a half-wave have one 8-byte half, 4
-// cycles more a write at d = 128 (116,736 in an 832x480 launch, 0.1 % of the CU-busy cycles).
+// A wave's 32 finished rows (first row row0) go through LDS, `buf` being the wave's own 32 * D bf16 there, and out with
+// 16 bytes per lane and whole rows side by side.  In the accumulator layout a lane holds 8-byte bits of two rows, and
+// a store of those touches 32 rows: with the 32x32 products of an earlier version, which held 8-byte bits of one row,
+// issuing 16 of them and draining them took 5 to 6 us a unit.  Both ways on one box at that time, direct -> through LDS:
+// 1170 queries 44.1 -> 42.1 us, 832x480 308.0 -> 305.0, packed-dummy step 234.8 -> 230.7, histories of 3 to 60 frames
+// 610.0 -> 601.9; a launch of 64 queries 15.1 -> 15.8.
+// 16-byte chunk c of row r lies at position c ^ (r mod chunks per row).  The reads are then free of bank conflicts; the
+// 8-byte writes are not: 4 cycles each (264,192 in a 1280x720 launch, 0.03 % of the CU-busy cycles).
 template <int D>
 __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row0, unsigned char *buf, int lane,
-                                             const f32x16 (&o)[D / 32], float inv) {
+                                             const f32x4 (&o)[D / 16][2], const float (&inv)[2]) {
   constexpr int kChunks = D / 8;                   // 16-byte chunks per row
-  const int j = lane & 31, hf = lane >> 5;
+  const int g = lane >> 4;
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+  for (int qb = 0; qb < 2; ++qb) {
+    const int r = 16 * qb + (lane & 15);
 #pragma unroll
-    for (int cq = 0; cq < 4; ++cq) {
-      uint2 w;
-      w.x = pack_bf16x2(o[db][4 * cq] * inv, o[db][4 * cq + 1] * inv);
-      w.y = pack_bf16x2(o[db][4 * cq + 2] * inv, o[db][4 * cq + 3] * inv);
-      *reinterpret_cast<uint2 *>(buf + j * 2 * D + 16 * ((4 * db + cq) ^ (j % kChunks)) + 8 * hf) = w;
-    }
+    for (int db = 0; db < D / 16; ++db)
+      *reinterpret_cast<uint2 *>(buf + r * 2 * D + 16 * ((2 * db + (g >> 1)) ^ (r % kChunks)) + 8 * (g & 1)) =
+          output4(o[db][qb], inv[qb]);
+  }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // lanes read what other lanes of the wave wrote
   const int c = lane % kChunks;
 #pragma unroll
@@ -426,14 +458,22 @@ __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row
   }
 }
 
+// Log-sum-exp of a wave's 32 finished rows: quarter qb of the wave writes those of query block qb.
+__device__ __forceinline__ void store_lse(const AttnParams &p, int h, int row0, int lane, const float (&ref)[2],
+                                          const float (&lt)[2]) {
+  const int row = row0 + (lane & 31);
+  if (p.lse != nullptr && lane < 32 && row < p.Nq)
+    p.lse[int64_t(h) * p.Nq + row] = of_block(lane >> 4, ref) * p.lse_unit + __logf(of_block(lane >> 4, lt));
+}
+
 // Sum of the two region masses over the 256 rows of a unit, in a fixed order (deterministic): a
-// butterfly over the 32 rows of every wave, then the 8 waves in order.  Both halves of a lane pair hold
-// the same masses, so the butterfly stays inside one half.
+// butterfly over the 32 rows of every wave, two to a lane, then the 8 waves in order.  The four lanes of a query hold
+// the same masses, so the butterfly stays inside 16 lanes.
 __device__ __forceinline__ void reduce_masses(const AttnParams &p, float *lds_red, int h, int qt, int tid,
                                               float mass_a, float mass_b) {
   const int wave = tid >> 6, lane = tid & 63;
 #pragma unroll
-  for (int m = 1; m < 32; m <<= 1) {
+  for (int m = 1; m < 16; m <<= 1) {
     mass_a += __shfl_xor(mass_a, m);
     mass_b += __shfl_xor(mass_b, m);
   }
@@ -518,8 +558,8 @@ __device__ __forceinline__ void finish_all_scores(const AttnParams &p, float2 *b
 
 template <int D, bool SCORE_ONLY>
 __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
-  constexpr int KS = D / 16;            // k-steps of the first product
-  constexpr int DB = D / 32;            // 32-row blocks of O^T
+  constexpr int KS = D / 32;            // k-steps of the first product
+  constexpr int DB = D / 16;            // 16-row blocks of O^T
   using L = TileLayout<D>;
   constexpr int GPW = L::NG / kWaves;   // row groups each wave loads per tile (2 for d=128, 1 for d=64)
   constexpr int kDmaPerPhase = GPW * (SCORE_ONLY ? 1 : 2);   // buffer loads a wave issues per VALU phase
@@ -533,7 +573,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int group = wave >> 2;
-  const int j = lane & 31, hf = lane >> 5;
+  const int j = lane & 15, g = lane >> 4;  // the lane's query in a block of 16; its quarter of the wave
 
   // The head tables, one head per thread: a single trip to memory, and a column is then found with one ballot.
   // (Read where they are needed they were a chain of scalar loads, one per head up to the one sought and three
@@ -545,7 +585,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
     const int i = tid < kMaxHeads ? tid : 0;
     const HeadRec rec = p.rec[i];
     const int cum = p.cum[i + 1];
-    asm volatile("" ::"s"(p.q), "s"(p.inv_c), "s"(p.part), "s"(p.slots), "s"(p.q_st), "s"(p.o_sh), "s"(p.n_teams), "s"(p.span_base),
+    asm volatile("" ::"s"(p.q), "s"(p.lse_unit), "s"(p.part), "s"(p.slots), "s"(p.q_st), "s"(p.o_sh), "s"(p.n_teams), "s"(p.span_base),
                  "s"(p.H), "v"(cum), "v"(rec.off), "v"(rec.len), "v"(rec.sink), "v"(rec.head));
     if (tid < kMaxHeads) {
       lds_rec[tid] = rec;
@@ -570,12 +610,9 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   const int64_t span_hi = span_begin(p, span + 1);
 
   // per-lane LDS byte addresses of the MFMA A operands (buffer 0); see TileLayout for the row placement
-  const int g16 = lane >> 4, i16 = lane & 15;
-  const int krow = key_of_row(j);
-  const int vrow = 8 * (g16 >> 1) + (i16 >> 2);
-  const unsigned k_lane_addr = lds_address(lds_k) + (krow % L::NG) * L::KGS + (krow / L::NG) * L::ROWB + 16 * hf;
-  const unsigned v_lane_addr = lds_address(lds_v) + (vrow % L::NG) * L::VGS + (vrow / L::NG) * L::ROWB +
-                               32 * (g16 & 1) + 8 * (i16 & 3);
+  const int krow = key_of_row(j), vrow = key_of_row(4 * g + (j >> 2));
+  const unsigned k_lane_addr = lds_address(lds_k) + (krow % L::NG) * L::KGS + (krow / L::NG) * L::ROWB + 16 * L::first_chunk(g);
+  const unsigned v_lane_addr = lds_address(lds_v) + (vrow % L::NG) * L::VGS + (vrow / L::NG) * L::ROWB + 8 * (j & 3);
   // lane -> (row position inside the group, 16-byte chunk of the row) in the 1 KB a load writes
   const int dma_pos = (16 * lane) / L::ROWB, dma_chunk = (16 * lane) % L::ROWB;
   const uint32_t cur_stride_b = uint32_t(p.kc_st) * 2u;
@@ -623,15 +660,11 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 
     // ---- global -> LDS: buffer descriptors of this head's history and current-chunk rows.  A load
     // past the end of the descriptor returns zeros, which is how partial and absent tiles are padded.
-    const int hist_bytes = len_h * L::ROWB;
-    const __amdgpu_buffer_rsrc_t rs_kh = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<u16 *>(p.k_hist) + hoff * D, 0, hist_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_kc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<u16 *>(p.k_cur) + h * p.kc_sh, 0, int(p.cur_bytes), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_vh = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<u16 *>(SCORE_ONLY ? p.k_hist : p.v_hist) + hoff * D, 0, hist_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_vc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<u16 *>(SCORE_ONLY ? p.k_cur : p.v_cur) + h * p.kc_sh, 0, int(p.cur_bytes), 0x00020000);
+    const uint32_t hist_bytes = uint32_t(len_h) * L::ROWB;
+    const u32x4 rs_kh = buffer_descriptor(p.k_hist + hoff * D, hist_bytes);
+    const u32x4 rs_kc = buffer_descriptor(p.k_cur + h * p.kc_sh, p.cur_bytes);
+    const u32x4 rs_vh = buffer_descriptor((SCORE_ONLY ? p.k_hist : p.v_hist) + hoff * D, hist_bytes);
+    const u32x4 rs_vc = buffer_descriptor((SCORE_ONLY ? p.k_cur : p.v_cur) + h * p.kc_sh, p.cur_bytes);
     // Issue this wave's share of tile t (zeros if the piece does not reach it) into LDS buffer `slot`.
     // The whole byte offset travels in the VGPR offset, the only part of a buffer address that the
     // hardware checks against the descriptor's size (the SGPR offset is not range-checked).
@@ -650,79 +683,27 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
         const int g = wave + kWaves * i;
         lds_void *d = (lds_void *)(dst + g * gs);
         const int vo = int(toff + uint32_t(g) * stride_b + uint32_t(cur ? voff_cur : voff_hist));
-        if (cur) __builtin_amdgcn_raw_ptr_buffer_load_lds(is_v ? rs_vc : rs_kc, d, 16, vo, 0, 0, 0);
-        else __builtin_amdgcn_raw_ptr_buffer_load_lds(is_v ? rs_vh : rs_kh, d, 16, vo, 0, 0, 0);
+        if (cur) __builtin_amdgcn_raw_ptr_buffer_load_lds(as_buffer(is_v ? rs_vc : rs_kc), d, 16, vo, 0, 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(as_buffer(is_v ? rs_vh : rs_kh), d, 16, vo, 0, 0, 0);
       }
     };
 
-    // Inside the tile loop the loads follow two cursors (K three tiles ahead, V two), advanced by one
-    // tile per iteration: byte offset += keys per tile * row stride, LDS buffer rotated, and only at
-    // the few tiles where a cursor enters the window region, the current chunk or the end of the piece
-    // are offset, step and descriptor worked out again.  That keeps the scalar work per iteration
-    // to a handful of instructions.
-    struct Cursor {
-      int t, next_event;            // tile under the cursor; first tile at which step/descriptor change
-      uint32_t vo;                  // per lane: byte offset of this lane's 16 bytes of the wave's first row group
-      uint32_t step, step_g;        // bytes per tile; bytes between the wave's row groups (kWaves rows apart)
-    };
-    // the descriptor each cursor currently reads through (the history's or the current chunk's); kept outside
-    // the struct and changed only where a cursor crosses into another region, not selected per tile
-    __amdgpu_buffer_rsrc_t rs_k_now = rs_kh, rs_v_now = rs_vh;
-    auto relocate = [&](Cursor &c, bool is_v) {
-      const int t = c.t;
-      bool cur = true;
-      if (t >= t_end) {             // absent tile: out of range for every lane, the loads write zeros
-        c.vo = kNoTile; c.step = 0; c.step_g = 0; c.next_event = INT32_MAX;
-      } else if (t < nt0 + nt1) {
-        const uint32_t row0 = t < nt0 ? uint32_t(t * kKT) : uint32_t(sink + (t - nt0) * kKT);
-        c.vo = lane_vo_hist + row0 * L::ROWB; c.step = kKT * L::ROWB; c.step_g = kWaves * L::ROWB;
-        c.next_event = min(t < nt0 ? nt0 : nt0 + nt1, t_end);
-        cur = false;
-      } else {
-        c.vo = lane_vo_cur + uint32_t((t - nt0 - nt1) * kKT) * cur_stride_b;
-        c.step = kKT * cur_stride_b; c.step_g = kWaves * cur_stride_b; c.next_event = t_end;
-      }
-      if (is_v) rs_v_now = cur ? rs_vc : rs_vh;
-      else rs_k_now = cur ? rs_kc : rs_kh;
-    };
-    // one tile on: next tile's bytes; then this wave's share of that tile goes out into LDS buffer `slot`
-    // (a compile-time number: the tile loop is unrolled over the four buffers)
-    auto advance_and_load = [&](Cursor &c, bool is_v, int slot) {
-      const unsigned tile_b = is_v ? L::VTILE : L::KTILE, gs = is_v ? L::VGS : L::KGS;
-      const unsigned dst = (is_v ? lds_address(lds_v) : lds_address(lds_k)) + wave * gs + slot * tile_b;
-      ++c.t;
-      c.vo += c.step;
-      if (c.t == c.next_event) relocate(c, is_v);
+    // ---- Q fragments: B operands of S^T = K Q^T.  Lane (j, g) holds, for queries j and 16 + j,
+    // chunk (8 elements) first_chunk(g) + ks of every k-step.
+    bf16x8 qf[KS][2];
 #pragma unroll
-      for (int i = 0; i < GPW; ++i) {
-        lds_void *d = (lds_void *)(uintptr_t)(dst + kWaves * i * gs);
-        const int vo = int(c.vo + uint32_t(i) * c.step_g);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(is_v ? rs_v_now : rs_k_now, d, 16, vo, 0, 0, 0);
-      }
-    };
-
-    // ---- Q fragment: B operand of S^T = K Q^T.  Lane (j, hf) holds, for query j,
-    // elements 16*ks + 8*hf .. +7 of every k-step.
-    bf16x8 qf[KS];
-    {
-      int row = q0 + j;
+    for (int qb = 0; qb < 2; ++qb) {
+      int row = q0 + 16 * qb + j;
       row = row < p.Nq ? row : p.Nq - 1;          // tail rows re-read the last query; never stored
-      const u16 *src = p.q + row * p.q_st + h * p.q_sh + 8 * hf;
+      const u16 *src = p.q + row * p.q_st + h * p.q_sh + 8 * L::first_chunk(g);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(src + 16 * ks);
+      for (int ks = 0; ks < KS; ++ks) qf[ks][qb] = *reinterpret_cast<const bf16x8 *>(src + 8 * ks);
     }
 
-    // ---- piece prologue: the spare V buffer, which the first MFMA phase multiplies with P = 0, is cleared; the
-    // first three K tiles and first two V tiles go on their way into LDS in the order in which they are read.
-    // Only Q and the first K tile are waited for: the rest are what two VALU phases leave in flight, so the
-    // waits of the tile loop cover them.  (All workgroups of a launch start here at once, and five tiles and Q
-    // for each are 37 MB: waiting for all of it took 2.5 to 3.7 us a piece.)
-    if (!SCORE_ONLY) {
-      for (int i = tid; i < L::VTILE / 16; i += kThreads) {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        *reinterpret_cast<u32x4 *>(lds_v + (kNBuf - 1) * L::VTILE + 16 * i) = z;
-      }
-    }
+    // ---- piece prologue: the first three K tiles and first two V tiles go on their way into LDS in the order in
+    // which they are read.  Only Q and the first K tile are waited for: the rest are what two VALU phases leave in
+    // flight, so the waits of the tile loop cover them.  (All workgroups of a launch start here at once, and five
+    // tiles and Q for each are 37 MB: waiting for all of it took 2.5 to 3.7 us a piece.)
     dma_tile(t_begin, 0, false);
     dma_tile(t_begin + 1, 1, false);
     if (!SCORE_ONLY) dma_tile(t_begin, 0, true);
@@ -730,175 +711,59 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
     if (!SCORE_ONLY) dma_tile(t_begin + 1, 1, true);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kDmaPerPhase) : "memory");
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));   // the compiler's own wait for Q, here and not in the loop
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks][0]), "+v"(qf[ks][1]));   // the compiler's own wait for Q, here and not in the loop
     lds_barrier();
 
-    f32x16 o[DB];
+    // ---- the tiles.  One workgroup barrier per iteration, taken by group 1 before its VALU phase and by group 0 after
+    // its: between two barriers group 0 runs MFMA(t), VALU(t) and group 1 runs VALU(t-1), MFMA(t), MFMA(t) being the
+    // products S(t) = K(t) Q and O += V(t-1) P(t-1), so the two waves of a SIMD are in opposite phases without
+    // being locked phase by phase.
+    // The loads of VALU phase t, K(t+3) and V(t+2), go where K(t-1) and V(t-2) were: behind barrier t every wave has
+    // finished MFMA(t-1).  (Barrier n = the one group 0 takes after VALU(n) and group 1 before it.)  They are first read
+    // in MFMA phase t+3, behind barrier t+2, and before a barrier a wave waits for those of its loads that the
+    // MFMA phases behind it read: group 0 issues them before barrier t and may leave the loads of its latest two
+    // phases in flight, group 1 issues them behind barrier t and may leave those of its latest phase in flight.  Either way
+    // a load has about two iterations to land.  Every wave issues the same number of loads in every VALU phase (absent
+    // tiles load zeros), so the counts hold.
+    TileLoopArgs a;
+    a.t_begin = t_begin; a.te = t_end;
+    a.nt0 = nt0; a.nt1 = nt0 + nt1;
+    a.sink = sink; a.win = len_h - sink; a.nc = p.Nc;
+    a.cs = cur_stride_b;
+    a.grp = group;
+    a.ldsk = lds_address(lds_k) + wave * L::KGS; a.ldsv = lds_address(lds_v) + wave * L::VGS;
+    a.c = p.c; a.lim = kSumLimit;
+    a.ka = k_lane_addr; a.va = v_lane_addr;
+    a.offh = lane_vo_hist; a.offc = lane_vo_cur;
+    a.key0 = key_of_row(4 * g);
+    a.kh = rs_kh; a.kc = rs_kc; a.vh = rs_vh; a.vc = rs_vc;
+    f32x4 o[DB][2];
+    RowSums sums;
+    if (wave_live) {
+      tile_loop<D, SCORE_ONLY, true>(a, qf, o, sums);
+    } else {
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+      for (int qb = 0; qb < 2; ++qb) {
+        sums.neg_ref[qb] = INFINITY;
+        sums.l[qb] = sums.l_sink[qb] = sums.l_hist[qb] = 0.f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-    float m = -INFINITY;
-    float l = 0.f;                           // this lane's share of the row sum, relative to m
-    float nmc = INFINITY;                    // -m * c
-    float snap_m0 = -INFINITY, snap_l0 = 0.f, snap_m1 = -INFINITY, snap_l1 = 0.f;
-    f32x16 s[2];
-    bf16x8 pb[2][2];                         // P^T of the previous tile, [key block][16-key step]
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int ts = 0; ts < 2; ++ts)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pb[kb][ts][e] = (__bf16)0.f;
-    // the cursors start on the last tiles the prologue has issued (K: t_begin + 2 in buffer 2, V: t_begin + 1 in buffer 1)
-    Cursor kc, vc;
-    kc.t = t_begin + 2;
-    relocate(kc, false);
-    vc.t = t_begin + 1;
-    relocate(vc, true);
-
-    const int seg_end0 = nt0 - 1, seg_end1 = nt0 + nt1 - 1;
-    // last tile of the segment that tile t lies in (empty segments have no tiles)
-    auto seg_end_from = [&](int t) { return t < nt0 ? seg_end0 : (t < nt0 + nt1 ? seg_end1 : n_tiles - 1); };
-    int next_seg_end = seg_end_from(t_begin);
-    // P^T of the tile in s against the reference -nmc/c: bf16 operands of the second product into pb, and
-    // the sum of the unrounded values over this lane's 32 keys (four independent chains)
-    auto exp_tile = [&](float nmc_) {
-      float c4[4];
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int ts = 0; ts < 2; ++ts) {
-          unsigned w[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float e0 = fast_exp2(__builtin_fmaf(s[kb][8 * ts + 2 * e], p.c, nmc_));
-            const float e1 = fast_exp2(__builtin_fmaf(s[kb][8 * ts + 2 * e + 1], p.c, nmc_));
-            w[e] = pack_bf16x2(e0, e1);
-            if (kb == 0 && ts == 0) c4[e] = e0 + e1;
-            else c4[e] += e0 + e1;   // plain adds: the dot-product instructions share the matrix core and stall its MFMAs
-          }
-          u32x4 u = {w[0], w[1], w[2], w[3]};
-          pb[kb][ts] = __builtin_bit_cast(bf16x8, u);
-        }
-      return (c4[0] + c4[1]) + (c4[2] + c4[3]);
-    };
-    // One tile iteration; SLOT = LDS buffer of K(t), a compile-time number (the loop below is unrolled over
-    // the four buffers, so no buffer address is computed at run time).  V(t-1) is in buffer SLOT + 3, the
-    // loads of this iteration fill K(t+3) into buffer SLOT + 3 and V(t+2) into buffer SLOT + 2 (mod 4).
-    int t = t_begin;
-    auto iteration = [&](auto slot_c) {
-      constexpr int SLOT = decltype(slot_c)::value;
-      int n_valid_t = kKT;                    // real keys in tile t: only a segment's last tile can be partial
-      bool seg_last = false;                  // tile t ends the sink or the window region (or the unit)
-      if (t == next_seg_end) {
-        seg_last = true;
-        if (t == seg_end0) n_valid_t = sink - (nt0 - 1) * kKT;
-        else if (t == seg_end1) n_valid_t = len_h - sink - (nt1 - 1) * kKT;
-        else n_valid_t = p.Nc - (nt2 - 1) * kKT;
-        next_seg_end = seg_end_from(t + 1);
+        for (int db = 0; db < DB; ++db) o[db][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      // ================= MFMA phase =================
-      // Always both products: at the first tile the second one multiplies P = 0 with the zero-filled
-      // spare V buffer, after the last tile the first one computes scores of a stale tile that nobody reads.
-      if (wave_live)
-        MfmaPhase<D, !SCORE_ONLY>::run(k_lane_addr + SLOT * L::KTILE, v_lane_addr + ((SLOT + 3) & 3) * L::VTILE, qf, pb, s, o);
-      // One workgroup barrier per iteration, taken by group 1 here and by group 0 after its VALU
-      // phase: between two barriers group 0 runs MFMA(t), VALU(t) and group 1 runs VALU(t-1), MFMA(t),
-      // so the two waves of a SIMD are in opposite phases without being locked phase by phase.
-      // Before a barrier a wave waits for those of its loads that the MFMA phases behind that barrier read.
-      // Tile K(t+3) / V(t+2), issued in VALU phase t, is first read in MFMA phase t+3, which begins behind
-      // barrier t+2 (barrier n = the one group 0 takes after VALU(n) and group 1 after MFMA(n)).  Group 0
-      // issues it before barrier t and may leave the loads of its latest two phases in flight; group 1
-      // issues it behind barrier t and may leave those of its latest phase in flight.  Either way a load has
-      // about two iterations to land.  Behind a barrier every wave has finished MFMA(t-1), whose tiles'
-      // buffers the next VALU phases overwrite.
-      if (group == 1) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kDmaPerPhase) : "memory");
-        lds_barrier();
-      }
-      // ================= VALU / memory phase =================
-      // every wave issues the same number of loads once per VALU phase (absent tiles load zeros), so
-      // the s_waitcnt counts hold
-      advance_and_load(kc, false, (SLOT + 3) & 3);
-      if (!SCORE_ONLY) advance_and_load(vc, true, (SLOT + 2) & 3);
-      if (t < t_end && wave_live) {
-        if (n_valid_t < kKT) {                // keys past the end of the segment
-          const int key0 = 8 * hf;
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)      // key = key0 + 32 kb + 16 (v / 8) + v % 8
-              if (key0 >= n_valid_t - (32 * kb + 16 * (v >> 3) + (v & 7))) s[kb][v] = -INFINITY;
-        }
-        // P = 2^(c s - c m) against the reference m the row already has, its sum in four chains
-        float ts = exp_tile(nmc);
-        float l_new = l + ts;
-        // No row maximum is taken on the common path.  m is only a reference: what has to hold is
-        // that nothing overflows, and any P beyond the limit (or infinite, or the NaN of an all-masked
-        // start) shows in the row's sum.  Rare: the first tile of a piece, and rows that outgrow 2^100.
-        if (__any(!(l_new <= kSumLimit))) {
-          float a = s[0][0];
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) a = fmaxf(a, s[kb][v]);
-          const float mx = pair_max(a);       // exact row maximum of the tile: the new P are at most 1
-          // the reference also absorbs the size of the sum so far (l becomes O(1)); -inf while l = 0
-          // Finite also where every key so far scores minus infinity: P of such a tile is then zero, not the NaN of
-          // inf - inf, and the first key that scores anything takes the reference up here again.
-          const float m_new = fmaxf(fmaxf(fmaxf(m, mx), m + __builtin_amdgcn_logf(pair_sum(l)) * p.inv_c), -FLT_MAX);
-          const float alpha = fast_exp2((m - m_new) * p.c);
-          m = m_new;
-          nmc = fminf(-m * p.c, FLT_MAX);
-          l *= alpha;
-          if (!SCORE_ONLY) {
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-              for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-          }
-          ts = exp_tile(nmc);
-          l_new = l + ts;
-        }
-        l = l_new;
-        if (seg_last) {                       // rare: keep the bookkeeping out of the common path
-          if (t == seg_end0) { snap_m0 = m; snap_l0 = l; }
-          if (t == seg_end1) { snap_m1 = m; snap_l1 = l; }
-        }
-      }
-      if (group == 0) {
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kDmaPerPhase) : "memory");
-        lds_barrier();
-      }
-    };
-#pragma unroll 1
-    for (;;) {
-      iteration(std::integral_constant<int, 0>{});
-      if (++t > t_end) break;
-      iteration(std::integral_constant<int, 1>{});
-      if (++t > t_end) break;
-      iteration(std::integral_constant<int, 2>{});
-      if (++t > t_end) break;
-      iteration(std::integral_constant<int, 3>{});
-      if (++t > t_end) break;
+      tile_loop<D, SCORE_ONLY, false>(a, qf, o, sums);
     }
     // no load of this piece may land in the next one's tiles, and no wave may still be reading them
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
-    // Region sums of this piece: a region that ended before the piece began contributes nothing, a
-    // region the piece ends in (or before) contains everything the piece has summed.
-    const float l_piece = l;
-    if (seg_end0 >= t_end) { snap_m0 = m; snap_l0 = l_piece; }
-    if (seg_end1 >= t_end) { snap_m1 = m; snap_l1 = l_piece; }
-
-    // ---- piece epilogue
-    const float lt = pair_sum(l_piece);
-    const float l1 = pair_sum(snap_l0 * fast_exp2((snap_m0 - m) * p.c));   // sink region, relative to m
-    const float l2 = pair_sum(snap_l1 * fast_exp2((snap_m1 - m) * p.c));   // sink + window regions
-    const int row = q0 + j;
-    const bool valid = row < p.Nq;
-    float m_u = m, lt_u = lt, l1_u = l1, l2_u = l2;
+    // ---- piece epilogue.  Region sums of this piece: a region that ended before the piece began contributes
+    // nothing, a region the piece ends in (or before) contains everything the piece has summed.
+    float ref_u[2], lt_u[2], l1_u[2], l2_u[2];     // reference; sums of all keys, the sink region, sink + window
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      ref_u[qb] = -sums.neg_ref[qb];
+      lt_u[qb] = quad_sum(sums.l[qb]);
+      l1_u[qb] = nt0 >= t_end ? lt_u[qb] : quad_sum(sums.l_sink[qb]);
+      l2_u[qb] = nt0 + nt1 >= t_end ? lt_u[qb] : quad_sum(sums.l_hist[qb]);
+    }
     if (take) {
       // The earlier pieces were written when their workgroups began their spans (a piece that fills a whole
       // span: when that workgroup ended), i.e. long ago or at about this time.  Wait until every flag says
@@ -926,47 +791,57 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       for (int sp = span - 1; sp >= s_first; --sp) {
         const int which = unit_lo > span_begin(p, sp) ? 1 : 0;
         const float *slot = p.slots + slot_index(p, sp, which, member) * Slot<D>::kFloats;
-        f32x4 st, v[D / 8];
-        if constexpr (SCORE_ONLY) st = load4_through(Slot<D>::stats(const_cast<float *>(slot), tid));
-        else load_slot_through<D / 8>(slot, tid, st, v);
-        const float m_new = fmaxf(st[0], m_u);
-        const float w_h = (st[0] == m_new) ? 1.f : fast_exp2((st[0] - m_new) * p.c);
-        const float w_t = (m_u == m_new) ? 1.f : fast_exp2((m_u - m_new) * p.c);
-        m_u = m_new;
-        lt_u = fold(st[1], w_h, lt_u, w_t);
-        l1_u = fold(st[2], w_h, l1_u, w_t);
-        l2_u = fold(st[3], w_h, l2_u, w_t);
-        if (!SCORE_ONLY) {
+        f32x4 st[2], v[D / 8];
+        if constexpr (SCORE_ONLY) {
+          st[0] = load4_through(Slot<D>::stats(const_cast<float *>(slot), Slot<D>::stats_reader(tid, 0)));
+          st[1] = load4_through(Slot<D>::stats(const_cast<float *>(slot), Slot<D>::stats_reader(tid, 1)));
+        } else {
+          load_slot_through<D / 8>(slot, tid, st, v);
+        }
 #pragma unroll
-          for (int db = 0; db < DB; ++db)
+        for (int qb = 0; qb < 2; ++qb) {
+          const float ref_new = fmaxf(st[qb][0], ref_u[qb]);
+          const float w_h = (st[qb][0] == ref_new) ? 1.f : fast_exp2(st[qb][0] - ref_new);
+          const float w_t = (ref_u[qb] == ref_new) ? 1.f : fast_exp2(ref_u[qb] - ref_new);
+          ref_u[qb] = ref_new;
+          lt_u[qb] = fold(st[qb][1], w_h, lt_u[qb], w_t);
+          l1_u[qb] = fold(st[qb][2], w_h, l1_u[qb], w_t);
+          l2_u[qb] = fold(st[qb][3], w_h, l2_u[qb], w_t);
+          if (!SCORE_ONLY) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) o[db][e] = fold(v[db * 4 + e / 4][e % 4], w_h, o[db][e], w_t);
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[db][qb][e] = fold(v[2 * db + qb][e], w_h, o[db][qb][e], w_t);
+          }
         }
       }
-      lt_u += poison;                              // every result divides by it: rows, log-sum-exp, score sums
+      lt_u[0] += poison;                           // every result divides by it: rows, log-sum-exp, score sums
+      lt_u[1] += poison;
       __syncthreads();                             // lds_ok is free again
     }
     if (t_end == n_tiles && (t_begin == 0 || take)) {
       // the unit is complete
-      const float inv = 1.f / lt_u;
+      const float inv[2] = {1.f / lt_u[0], 1.f / lt_u[1]};
       if (!SCORE_ONLY) {
         store_output<D>(p, h, q0, lds_k + wave * (32 * 2 * D), lane, o, inv);
-        if (valid && p.lse != nullptr && hf == 0) p.lse[int64_t(h) * p.Nq + row] = m_u * p.scale + __logf(lt_u);
+        store_lse(p, h, q0, lane, ref_u, lt_u);
       }
-      if (p.part != nullptr)
-        reduce_masses(p, lds_red, h, qt, tid, valid ? l1_u * inv : 0.f, valid ? l2_u * inv : 0.f);
+      if (p.part != nullptr) {
+        const bool in0 = q0 + j < p.Nq, in1 = q0 + 16 + j < p.Nq;
+        reduce_masses(p, lds_red, h, qt, tid, (in0 ? l1_u[0] * inv[0] : 0.f) + (in1 ? l1_u[1] * inv[1] : 0.f),
+                      (in0 ? l2_u[0] * inv[0] : 0.f) + (in1 ? l2_u[1] * inv[1] : 0.f));
+      }
       else if (!SCORE_ONLY) lds_barrier();         // the next piece's tiles go where the rows were
     } else {
       // a piece that starts at the span's first position uses the span's slot 0, a later one slot 1
       float *slot = p.slots + slot_index(p, span, piece_pos == span_lo ? 0 : 1, member) * Slot<D>::kFloats;
-      store4_through(Slot<D>::stats(slot, tid), m_u, lt_u, l1_u, l2_u);
+      store4_through(Slot<D>::stats(slot, tid),
+                     f32x4{of_block(g, ref_u), of_block(g, lt_u), of_block(g, l1_u), of_block(g, l2_u)});
       if (!SCORE_ONLY) {
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int cq = 0; cq < 4; ++cq)
-            store4_through(Slot<D>::ovec(slot, tid, db * 4 + cq), o[db][4 * cq], o[db][4 * cq + 1], o[db][4 * cq + 2],
-                           o[db][4 * cq + 3]);
+          for (int qb = 0; qb < 2; ++qb) store4_through(Slot<D>::ovec(slot, tid, 2 * db + qb), o[db][qb]);
       }
       if (give) {
         // each thread's stores are in memory when its counter reaches zero; after the barrier all are
@@ -999,12 +874,12 @@ template <int D, bool SCORE_ONLY>
 __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParams p) {
   __shared__ float lds_red[kWaves * 2];
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63, j = lane & 31, hf = lane >> 5;
-  const int db = int(blockIdx.y);
+  const int wave = tid >> 6, lane = tid & 63, j = lane & 15;
+  const int dq = int(blockIdx.y);                  // quarter (half at d = 64) of the output columns
   const int n_merge = (p.n_teams - 1) * p.team_size;
   if (int(blockIdx.x) >= n_merge) {                // score of a head no boundary cuts
     const int h = int(blockIdx.x) - n_merge;
-    if (db == 0 && tid == 0 && p.n_cut_units[h] == 0) finish_score(p, h);
+    if (dq == 0 && tid == 0 && p.n_cut_units[h] == 0) finish_score(p, h);
     return;
   }
   const int k = int(blockIdx.x) / p.team_size + 1, member = int(blockIdx.x) % p.team_size;
@@ -1022,43 +897,51 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
   int s_hi = k;
   while (span_begin(p, s_hi + 1) < u_hi) ++s_hi;
 
-  float M = -INFINITY, Lt = 0.f, La = 0.f, Lb = 0.f;
-  f32x16 o;
+  float M[2] = {-INFINITY, -INFINITY}, Lt[2] = {}, La[2] = {}, Lb[2] = {};
+  f32x4 o[2][2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) o[v] = 0.f;
+  for (int i = 0; i < 4; ++i) o[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
   for (int sp = s_hi; sp >= s_lo; --sp) {          // last piece first, as in the main kernel
     const int64_t b = span_begin(p, sp);
-    const float *slot = p.slots + slot_index(p, sp, u_lo > b ? 1 : 0, member) * Slot<D>::kFloats;
-    const float4 st = *reinterpret_cast<const float4 *>(Slot<D>::stats(const_cast<float *>(slot), tid));
-    const float m_new = fmaxf(st.x, M);
-    // a piece of a wave that computes nothing (rows past the last query) has m = -inf throughout
-    const float w_h = (st.x == m_new) ? 1.f : fast_exp2((st.x - m_new) * p.c);
-    const float w_t = (M == m_new) ? 1.f : fast_exp2((M - m_new) * p.c);
-    M = m_new;
-    Lt = fold(st.y, w_h, Lt, w_t);
-    La = fold(st.z, w_h, La, w_t);
-    Lb = fold(st.w, w_h, Lb, w_t);
-    if (!SCORE_ONLY) {
+    float *slot = p.slots + slot_index(p, sp, u_lo > b ? 1 : 0, member) * Slot<D>::kFloats;
 #pragma unroll
-      for (int cq = 0; cq < 4; ++cq) {
-        const float4 v4 = *reinterpret_cast<const float4 *>(Slot<D>::ovec(const_cast<float *>(slot), tid, db * 4 + cq));
-        o[4 * cq] = fold(v4.x, w_h, o[4 * cq], w_t);
-        o[4 * cq + 1] = fold(v4.y, w_h, o[4 * cq + 1], w_t);
-        o[4 * cq + 2] = fold(v4.z, w_h, o[4 * cq + 2], w_t);
-        o[4 * cq + 3] = fold(v4.w, w_h, o[4 * cq + 3], w_t);
+    for (int qb = 0; qb < 2; ++qb) {
+      const f32x4 st = *reinterpret_cast<const f32x4 *>(Slot<D>::stats(slot, Slot<D>::stats_reader(tid, qb)));
+      const float m_new = fmaxf(st[0], M[qb]);
+      // a piece of a wave that computes nothing (rows past the last query) has a reference of -inf throughout
+      const float w_h = (st[0] == m_new) ? 1.f : fast_exp2(st[0] - m_new);
+      const float w_t = (M[qb] == m_new) ? 1.f : fast_exp2(M[qb] - m_new);
+      M[qb] = m_new;
+      Lt[qb] = fold(st[1], w_h, Lt[qb], w_t);
+      La[qb] = fold(st[2], w_h, La[qb], w_t);
+      Lb[qb] = fold(st[3], w_h, Lb[qb], w_t);
+      if (!SCORE_ONLY) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const f32x4 v = *reinterpret_cast<const f32x4 *>(Slot<D>::ovec(slot, tid, 2 * (2 * dq + i) + qb));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[i][qb][e] = fold(v[e], w_h, o[i][qb][e], w_t);
+        }
       }
     }
   }
-  const float inv = 1.f / Lt;
-  const int row = qt * kBQ + wave * 32 + j;
-  const bool valid = row < p.Nq;
-  if (!SCORE_ONLY && valid) {
-    store_output_block(p, h, row, hf, db, o, inv);
-    if (db == 0 && p.lse != nullptr && hf == 0) p.lse[int64_t(h) * p.Nq + row] = M * p.scale + __logf(Lt);
+  const float inv[2] = {1.f / Lt[0], 1.f / Lt[1]};
+  const int row0 = qt * kBQ + wave * 32;
+  const bool in[2] = {row0 + j < p.Nq, row0 + 16 + j < p.Nq};
+  if (!SCORE_ONLY) {
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (in[qb])
+          *reinterpret_cast<uint2 *>(p.out + (row0 + 16 * qb + j) * p.o_st + h * p.o_sh + 32 * dq + 16 * i +
+                                     4 * (lane >> 4)) = output4(o[i][qb], inv[qb]);
+    if (dq == 0) store_lse(p, h, row0, lane, M, Lt);
   }
-  if (db == 0 && p.part != nullptr) {
-    reduce_masses(p, lds_red, h, qt, tid, valid ? La * inv : 0.f, valid ? Lb * inv : 0.f);
+  if (dq == 0 && p.part != nullptr) {
+    reduce_masses(p, lds_red, h, qt, tid, (in[0] ? La[0] * inv[0] : 0.f) + (in[1] ? La[1] * inv[1] : 0.f),
+                  (in[0] ? Lb[0] * inv[0] : 0.f) + (in[1] ? Lb[1] * inv[1] : 0.f));
     // the unit's masses are out; whoever completes the head's last merged unit sums the head
     if (tid == 0) {
       __threadfence();
@@ -1481,9 +1364,8 @@ static df_status attn_fwd(const df_attn_args *a, void *stream, void *workspace, 
   if ((int64_t(a->Nc - 1) * a->kc_stride_tok + a->d) * 2 >= kMaxBufferBytes || a->kc_stride_tok >= (1 << 24))
     return DF_ERR_RANGE;
   p.cur_bytes = uint32_t((int64_t(a->Nc - 1) * a->kc_stride_tok + a->d) * 2);
-  p.scale = a->softmax_scale;
   p.c = a->softmax_scale * 1.4426950408889634f;
-  p.inv_c = 1.f / p.c;
+  p.lse_unit = float(double(a->softmax_scale) / double(p.c));
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (a->d == 128) return launch<128, false>(p, workspace, a->score_out, st);
   return launch<64, false>(p, workspace, a->score_out, st);
@@ -1565,9 +1447,8 @@ extern "C" df_status df_head_score(const df_score_args *a, void *stream) {
   if ((int64_t(a->Nc - 1) * a->kc_stride_tok + a->d) * 2 >= kMaxBufferBytes || a->kc_stride_tok >= (1 << 24))
     return DF_ERR_RANGE;
   p.cur_bytes = uint32_t((int64_t(a->Nc - 1) * a->kc_stride_tok + a->d) * 2);
-  p.scale = a->softmax_scale;
   p.c = a->softmax_scale * 1.4426950408889634f;
-  p.inv_c = 1.f / p.c;
+  p.lse_unit = float(double(a->softmax_scale) / double(p.c));
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (a->d == 128) return launch<128, true>(p, a->workspace, a->score_out, st);
   return launch<64, true>(p, a->workspace, a->score_out, st);
