@@ -31,8 +31,7 @@ piece, a reference that has to go up) lies behind branches in two subroutines.
 The statement carries its own wait states (the compiler's hazard recogniser does not look into asm):
   * an accumulator is only reused eight MFMAs later (sixteen in the second product at d = 128): no
     dependent MFMAs back to back;
-  * an MFMA phase ends with 16 idle cycles, more than the 8 a vector instruction must keep
-    from a 4-pass MFMA whose result it reads or overwrites;
+  * a vector instruction keeps 8 wait states from a 4-pass MFMA whose result it reads or overwrites (mfma_phase);
   * no instruction uses the result of an exponential or logarithm issued right before it;
   * two idle cycles (s_nop 1) between a comparison and the selection that reads vcc, and around lane swaps;
   * one instruction between a write of m0 and the load into LDS that uses it.
@@ -105,7 +104,10 @@ def mfma_phase(D, do_qk, do_pv, koff, voff):
         lines.append(f"s_waitcnt lgkmcnt({pending})")
         lines += [m.replace("@", quad(slot(i))) for m in mfmas]
         issue(i + DEPTH)
-    return lines + ["s_nop 7", "s_nop 7"]
+    # 8 idle cycles (wait states) before a vector instruction touches what the last MFMAs wrote.  With both products that
+    # is O, which only the raise of a reference touches, a softmax phase later; S is long complete, and the first instruction
+    # that overwrites P comes 20 later.  (16 in every phase: 1920x1088 5692 -> 5629 us without, 1280x720 2193 -> 2173.)
+    return lines + (["s_nop 1"] if do_qk and do_pv else ["s_nop 7", "s_nop 1"])
 
 
 def softmax(with_p):
@@ -291,9 +293,15 @@ def tile_loop(D, score, live):
     lines.append("s_mov_b32 %[ev], %[t]")                # the first iteration sets the cursors
     if live:
         lines += mfma_phase(D, True, False, "0", "0")
-    lines += ["s_cmp_lg_u32 %[grp], 0", f"s_cbranch_scc1 {lab('g1_0')}"]
+    lines += ["s_cmp_lg_u32 %[grp], 0", f"s_cbranch_scc1 {lab('group1' if score and live else 'g1_0')}"]
     for g in range(2):
         at = lambda name, slot: lab(f"{name}_g{g}_{slot}")
+        # Scoring asks more of the issue port than of the matrix core (768 of 1536 cycles a tile and wave).  At equal
+        # priority the older waves of group 0 go first in both phases and the younger ones run when these wait at the
+        # barrier: 64.9 us for 832x480 sampled scores against 59.2 with group 1 first, 174 against 161 with 21 cached
+        # frames.  Attention gains nothing from it, nor from priority for one of the phases (under 0.3 %).
+        if score and live:
+            lines += [f"{lab(f'group{g}')}:", f"s_setprio {2 * g}"]
         for slot in range(NBUF):
             lines.append(f"{lab(f'g{g}_{slot}')}:")
             if g == 1:
@@ -339,6 +347,8 @@ def tile_loop(D, score, live):
     if live and not score:
         lines += mfma_phase(D, False, True, "0", "0")
     lines.append("s_mov_b32 m0, %[m0_was]")
+    if score and live:
+        lines.append("s_setprio 0")
     if live:
         lines += [".purgem df_mfma", ".purgem df_softmax"]
     return lines
