@@ -140,6 +140,7 @@ struct AttnParams {
   int16_t n_cut_units[kMaxHeads];   // units of a head that span boundaries cut (put together by the merge kernel)
   int64_t span_base;           // positions per span: line_len / n_teams ...
   int32_t span_rem;            // ... and line_len % n_teams, spread evenly over the spans
+  uint32_t by_n_teams, by_team_size;   // reciprocals: see divide_small
   int32_t cum[kMaxHeads + 1];  // first column of the hh-th longest head
   uint32_t cur_bytes;  // addressable bytes of one head's current-chunk rows: ((Nc-1)*kc_st + d) * 2
   float c;             // softmax_scale * log2(e)
@@ -266,11 +267,24 @@ struct Slot {
 __device__ __forceinline__ void store4_through(float *ptr, const f32x4 &v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(ptr), "v"(v) : "memory");
 }
-// One 16-byte load; returns when the data is in the registers.
-__device__ __forceinline__ f32x4 load4_through(const float *ptr) {
-  f32x4 v;
-  asm volatile("global_load_dwordx4 %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(ptr) : "memory");
-  return v;
+// The statistics of the thread's two queries from four slots, all loads in flight at once and one wait; `reader` is the
+// lane that wrote those of the first query (Slot::stats_reader), the second's lie 16 lanes on.
+__device__ __forceinline__ void load_stats_through(const float *s0, const float *s1, const float *s2, const float *s3,
+                                                   int reader, f32x4 (&st)[4][2]) {
+  asm volatile(
+      "global_load_dwordx4 %0, %8, %9 sc0 sc1\n\t"
+      "global_load_dwordx4 %1, %8, %9 offset:256 sc0 sc1\n\t"
+      "global_load_dwordx4 %2, %8, %10 sc0 sc1\n\t"
+      "global_load_dwordx4 %3, %8, %10 offset:256 sc0 sc1\n\t"
+      "global_load_dwordx4 %4, %8, %11 sc0 sc1\n\t"
+      "global_load_dwordx4 %5, %8, %11 offset:256 sc0 sc1\n\t"
+      "global_load_dwordx4 %6, %8, %12 sc0 sc1\n\t"
+      "global_load_dwordx4 %7, %8, %12 offset:256 sc0 sc1\n\t"
+      "s_waitcnt vmcnt(0)"
+      : "=&v"(st[0][0]), "=&v"(st[0][1]), "=&v"(st[1][0]), "=&v"(st[1][1]), "=&v"(st[2][0]), "=&v"(st[2][1]),
+        "=&v"(st[3][0]), "=&v"(st[3][1])
+      : "v"(unsigned(reader) * 16u), "s"(s0), "s"(s1), "s"(s2), "s"(s3)
+      : "memory");
 }
 
 // A whole slot (the statistics of the thread's two queries and its N = D/8 vectors of O) with every load in flight at
@@ -363,13 +377,19 @@ __host__ __device__ __forceinline__ int64_t slot_index(const AttnParams &p, int 
   return int64_t(2 * span + which) * p.team_size + member;
 }
 
+// x / n for x < 2^16 and n <= 2^8 with the reciprocal 2^32 / n, rounded up (2^32 - 1 for n = 1): it is too large by less
+// than n / 2^32 of itself, and x times that is less than 1 / n.
+__host__ __device__ __forceinline__ int divide_small(uint32_t x, uint32_t reciprocal) {
+  return int(uint32_t((uint64_t(x) * reciprocal + (reciprocal == UINT32_MAX ? x : 0u)) >> 32));
+}
+static uint32_t reciprocal_of(int n) { return n == 1 ? UINT32_MAX : uint32_t(((uint64_t(1) << 32) + n - 1) / n); }
+
 // Where the work is cut.  The line has one position per (group of query tiles, column); span s covers
 // positions [span_begin(s), span_begin(s+1)), span_begin(s) = floor(s * line_len / n_teams).  Host and device
 // use the same arithmetic: with line_len = n_teams * span_base + span_rem only s * span_rem is left to divide,
-// which is less than kNumCU^2 (a 64-bit division is over a hundred dependent instructions, and a workgroup
-// needs several before it can issue its first load).
+// which is less than kNumCU^2 (a workgroup needs several of them before it can issue its first load).
 __host__ __device__ __forceinline__ int64_t span_begin(const AttnParams &p, int s) {
-  return s * p.span_base + unsigned(s * p.span_rem) / unsigned(p.n_teams);
+  return s * p.span_base + divide_small(unsigned(s * p.span_rem), p.by_n_teams);
 }
 
 // One piece of a span: the part of a unit (group of query tiles x head) that the span holds.  The same
@@ -604,7 +624,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   // kernel's arguments, a miss of its own)
   const int n_wg = p.n_teams * p.team_size;
   const int wg = n_wg >= kXcd ? (blockIdx.x % kXcd) * ((n_wg + kXcd - 1) / kXcd) + blockIdx.x / kXcd : blockIdx.x;
-  const int span = wg / p.team_size, member = wg % p.team_size;
+  const int span = divide_small(wg, p.by_team_size), member = wg - span * p.team_size;
   if (span >= p.n_teams) return;
   const int64_t span_lo = span_begin(p, span);
   const int64_t span_hi = span_begin(p, span + 1);
@@ -751,9 +771,33 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       }
       tile_loop<D, SCORE_ONLY, false>(a, qf, o, sums);
     }
+    int s_first = span;                            // span that holds the unit's first tile
+    if (take) {
+      // The earlier pieces were written when their workgroups began their spans (a piece that fills a whole
+      // span: when that workgroup ended), i.e. long ago or at about this time.  Wait until every flag says
+      // its piece is in memory; the wait is bounded so that a workgroup that never runs cannot hang the
+      // device: the unit's rows, and through them the head's scores, then come out as NaN.  The first wave looks as soon
+      // as its own tiles are done: the other waves are up to half an iteration behind it.
+      do --s_first; while (s_first > 0 && span_begin(p, s_first) > unit_lo);
+      if (wave == 0) {
+        // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
+        int ok = 1;
+        for (int sp = s_first + lane; sp < span; sp += 64) {
+          const int number = sp * p.team_size + member;
+          ok &= take_flag(p, p.flags + number, number);
+        }
+        const int all_ok = __all(ok);              // the whole wave votes: inside `lane == 0` only that lane would
+        if (lane == 0) lds_ok = all_ok;
+      }
+    }
     // no load of this piece may land in the next one's tiles, and no wave may still be reading them
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
+    // What follows is worked out from here on: hoisted out of the loop over the pieces its addresses stood before a
+    // workgroup's first load, and in registers (2 spilled at d = 128, none now).
+    int tid_ = tid;
+    asm volatile("" : "+v"(tid_));
+    const int lane_ = tid_ & 63, g_ = lane_ >> 4, j_ = lane_ & 15;
     // ---- piece epilogue.  Region sums of this piece: a region that ended before the piece began contributes
     // nothing, a region the piece ends in (or before) contains everything the piece has summed.
     float ref_u[2], lt_u[2], l1_u[2], l2_u[2];     // reference; sums of all keys, the sink region, sink + window
@@ -765,49 +809,48 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       l2_u[qb] = nt0 + nt1 >= t_end ? lt_u[qb] : quad_sum(sums.l_hist[qb]);
     }
     if (take) {
-      // The earlier pieces were written when their workgroups began their spans (a piece that fills a whole
-      // span: when that workgroup ended), i.e. long ago or at about this time.  Wait until every flag says
-      // its piece is in memory; the wait is bounded so that a workgroup that never runs cannot hang the
-      // device: the unit's rows, and through them the head's scores, then come out as NaN.
-      int s_first = span - 1;                      // span that holds the unit's first tile
-      while (s_first > 0 && span_begin(p, s_first) > unit_lo) --s_first;
-      if (wave == 0) {
-        // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
-        int ok = 1;
-        for (int sp = s_first + lane; sp < span; sp += 64) {
-          const int number = sp * p.team_size + member;
-          ok &= take_flag(p, p.flags + number, number);
-        }
-        const int all_ok = __all(ok);              // the whole wave votes: inside `lane == 0` only that lane would
-        if (lane == 0) lds_ok = all_ok;
-      }
-      __syncthreads();
       const float poison = lds_ok ? 0.f : NAN;
       // From this piece back to the unit's first, the order and arithmetic of the merge kernel: every earlier piece is
       // folded into this one's registers, all of it loaded with one wait.  (Front to back the sum so far needs
       // registers of its own, and the loads had to go out four at a time: 1170 queries, 6 pieces to a unit, 54.8 us
       // against 47.1.)
+      auto slot_of = [&](int sp) {
+        return p.slots + slot_index(p, sp, unit_lo > span_begin(p, sp) ? 1 : 0, member) * Slot<D>::kFloats;
+      };
+      auto fold_sums = [&](int qb, const f32x4 &st, float &w_h, float &w_t) {
+        const float ref_new = fmaxf(st[0], ref_u[qb]);
+        w_h = (st[0] == ref_new) ? 1.f : fast_exp2(st[0] - ref_new);
+        w_t = (ref_u[qb] == ref_new) ? 1.f : fast_exp2(ref_u[qb] - ref_new);
+        ref_u[qb] = ref_new;
+        lt_u[qb] = fold(st[1], w_h, lt_u[qb], w_t);
+        l1_u[qb] = fold(st[2], w_h, l1_u[qb], w_t);
+        l2_u[qb] = fold(st[3], w_h, l2_u[qb], w_t);
+      };
+      if constexpr (SCORE_ONLY) {
+        // four pieces a trip (past the unit's first piece that one again, not looked at): 2.8 -> 1.2 us for 832x480
+        // sampled scores, whose units are cut four times
 #pragma unroll 1
-      for (int sp = span - 1; sp >= s_first; --sp) {
-        const int which = unit_lo > span_begin(p, sp) ? 1 : 0;
-        const float *slot = p.slots + slot_index(p, sp, which, member) * Slot<D>::kFloats;
-        f32x4 st[2], v[D / 8];
-        if constexpr (SCORE_ONLY) {
-          st[0] = load4_through(Slot<D>::stats(const_cast<float *>(slot), Slot<D>::stats_reader(tid, 0)));
-          st[1] = load4_through(Slot<D>::stats(const_cast<float *>(slot), Slot<D>::stats_reader(tid, 1)));
-        } else {
-          load_slot_through<D / 8>(slot, tid, st, v);
-        }
+        for (int sp = span - 1; sp >= s_first; sp -= 4) {
+          f32x4 st[4][2];
+          load_stats_through(slot_of(sp), slot_of(max(sp - 1, s_first)), slot_of(max(sp - 2, s_first)),
+                             slot_of(max(sp - 3, s_first)), Slot<D>::stats_reader(tid_, 0), st);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          const float ref_new = fmaxf(st[qb][0], ref_u[qb]);
-          const float w_h = (st[qb][0] == ref_new) ? 1.f : fast_exp2(st[qb][0] - ref_new);
-          const float w_t = (ref_u[qb] == ref_new) ? 1.f : fast_exp2(ref_u[qb] - ref_new);
-          ref_u[qb] = ref_new;
-          lt_u[qb] = fold(st[qb][1], w_h, lt_u[qb], w_t);
-          l1_u[qb] = fold(st[qb][2], w_h, l1_u[qb], w_t);
-          l2_u[qb] = fold(st[qb][3], w_h, l2_u[qb], w_t);
-          if (!SCORE_ONLY) {
+          for (int i = 0; i < 4; ++i)
+            if (sp - i >= s_first) {
+              float w_h, w_t;
+              fold_sums(0, st[i][0], w_h, w_t);
+              fold_sums(1, st[i][1], w_h, w_t);
+            }
+        }
+      } else {
+#pragma unroll 1
+        for (int sp = span - 1; sp >= s_first; --sp) {
+          f32x4 st[2], v[D / 8];
+          load_slot_through<D / 8>(slot_of(sp), tid_, st, v);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb) {
+            float w_h, w_t;
+            fold_sums(qb, st[qb], w_h, w_t);
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -817,31 +860,30 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       }
       lt_u[0] += poison;                           // every result divides by it: rows, log-sum-exp, score sums
       lt_u[1] += poison;
-      __syncthreads();                             // lds_ok is free again
     }
     if (t_end == n_tiles && (t_begin == 0 || take)) {
       // the unit is complete
       const float inv[2] = {1.f / lt_u[0], 1.f / lt_u[1]};
       if (!SCORE_ONLY) {
-        store_output<D>(p, h, q0, lds_k + wave * (32 * 2 * D), lane, o, inv);
-        store_lse(p, h, q0, lane, ref_u, lt_u);
+        store_output<D>(p, h, q0, lds_k + wave * (32 * 2 * D), lane_, o, inv);
+        store_lse(p, h, q0, lane_, ref_u, lt_u);
       }
       if (p.part != nullptr) {
-        const bool in0 = q0 + j < p.Nq, in1 = q0 + 16 + j < p.Nq;
-        reduce_masses(p, lds_red, h, qt, tid, (in0 ? l1_u[0] * inv[0] : 0.f) + (in1 ? l1_u[1] * inv[1] : 0.f),
+        const bool in0 = q0 + j_ < p.Nq, in1 = q0 + 16 + j_ < p.Nq;
+        reduce_masses(p, lds_red, h, qt, tid_, (in0 ? l1_u[0] * inv[0] : 0.f) + (in1 ? l1_u[1] * inv[1] : 0.f),
                       (in0 ? l2_u[0] * inv[0] : 0.f) + (in1 ? l2_u[1] * inv[1] : 0.f));
       }
       else if (!SCORE_ONLY) lds_barrier();         // the next piece's tiles go where the rows were
     } else {
       // a piece that starts at the span's first position uses the span's slot 0, a later one slot 1
       float *slot = p.slots + slot_index(p, span, piece_pos == span_lo ? 0 : 1, member) * Slot<D>::kFloats;
-      store4_through(Slot<D>::stats(slot, tid),
-                     f32x4{of_block(g, ref_u), of_block(g, lt_u), of_block(g, l1_u), of_block(g, l2_u)});
+      store4_through(Slot<D>::stats(slot, tid_),
+                     f32x4{of_block(g_, ref_u), of_block(g_, lt_u), of_block(g_, l1_u), of_block(g_, l2_u)});
       if (!SCORE_ONLY) {
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int qb = 0; qb < 2; ++qb) store4_through(Slot<D>::ovec(slot, tid, 2 * db + qb), o[db][qb]);
+          for (int qb = 0; qb < 2; ++qb) store4_through(Slot<D>::ovec(slot, tid_, 2 * db + qb), o[db][qb]);
       }
       if (give) {
         // each thread's stores are in memory when its counter reaches zero; after the barrier all are
@@ -1087,6 +1129,8 @@ static df_status plan(AttnParams &p) {
     p.n_teams = cheapest_spans(p, std::max(1, std::min(kNumCU / team, int(p.line_len) / kMinSmallSpan)));
   p.span_base = p.line_len / p.n_teams;
   p.span_rem = int32_t(p.line_len % p.n_teams);
+  p.by_n_teams = reciprocal_of(p.n_teams);
+  p.by_team_size = reciprocal_of(p.team_size);
   return DF_OK;
 }
 
