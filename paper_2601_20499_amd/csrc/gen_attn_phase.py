@@ -279,6 +279,7 @@ def loads(D, score, slot):
 def tile_loop(D, score, live):
     L = layout(D)
     dma = L["ng"] // WAVES * (1 if score else 2)         # loads a wave issues per VALU phase
+    prefer_group1 = live and (score or D == 64)          # see the loop over the groups
     lab = lambda name: f".Ldf_{name}_%="
     lines = [".macro df_mfma koff, voff"] + mfma_phase(D, True, not score, "\\\\koff", "\\\\voff") + [".endm"] if live else []
     if live:
@@ -293,14 +294,16 @@ def tile_loop(D, score, live):
     lines.append("s_mov_b32 %[ev], %[t]")                # the first iteration sets the cursors
     if live:
         lines += mfma_phase(D, True, False, "0", "0")
-    lines += ["s_cmp_lg_u32 %[grp], 0", f"s_cbranch_scc1 {lab('group1' if score and live else 'g1_0')}"]
+    lines += ["s_cmp_lg_u32 %[grp], 0", f"s_cbranch_scc1 {lab('group1' if prefer_group1 else 'g1_0')}"]
     for g in range(2):
         at = lambda name, slot: lab(f"{name}_g{g}_{slot}")
-        # Scoring asks more of the issue port than of the matrix core (768 of 1536 cycles a tile and wave).  At equal
-        # priority the older waves of group 0 go first in both phases and the younger ones run when these wait at the
-        # barrier: 64.9 us for 832x480 sampled scores against 59.2 with group 1 first, 174 against 161 with 21 cached
-        # frames.  Attention gains nothing from it, nor from priority for one of the phases (under 0.3 %).
-        if score and live:
+        # Scoring, and attention at d = 64, ask more of the issue port than of the matrix core (768 and 832 cycles a tile
+        # and wave of 8 an MFMA, 8 an exponential, 4 any other instruction, against 512).  At equal priority the older
+        # waves of group 0 go first in both phases and the younger ones run when these wait at the barrier: 64.9 us for
+        # 832x480 sampled scores against 59.2 with group 1 first, 174 against 161 with 21 cached frames, 186.9 against
+        # 167.6 for 832x480 attention at d = 64.  Attention at d = 128 (1168 against 1024) gains nothing from it, nor from
+        # priority for one of the phases (under 0.3 %).
+        if prefer_group1:
             lines += [f"{lab(f'group{g}')}:", f"s_setprio {2 * g}"]
         for slot in range(NBUF):
             lines.append(f"{lab(f'g{g}_{slot}')}:")
@@ -347,7 +350,7 @@ def tile_loop(D, score, live):
     if live and not score:
         lines += mfma_phase(D, False, True, "0", "0")
     lines.append("s_mov_b32 m0, %[m0_was]")
-    if score and live:
+    if prefer_group1:
         lines.append("s_setprio 0")
     if live:
         lines += [".purgem df_mfma", ".purgem df_softmax"]
