@@ -136,10 +136,12 @@ def softmax(with_p):
 
 
 def raise_reference(D, with_o):
-    """The references go up to the row's maximum so far, or to the size of its sum; l, the region sums and O follow.  Finite
-    also where every key so far scores minus infinity: P of such a tile is then zero, not the NaN of inf - inf, and the
-    first key that scores anything takes the reference up here again."""
-    t = [f"v{STAGE0 + i}" for i in range(4)]
+    """Subroutine: the references go up to the row's maximum so far, or to the size of its sum; l, the region sums and O
+    follow.  Finite also where every key so far scores minus infinity: P of such a tile is then zero, not the NaN of
+    inf - inf, and the first key that scores anything takes the reference up here again.  At a piece's first tile there is
+    nothing yet that could follow."""
+    t = [[f"v{STAGE0 + 4 * qb + i}" for i in range(4)] for qb in range(2)]
+    lab = lambda name: f".Ldf_{name}_%="
 
     def over_quad(x, y, op):                             # over the four lanes that share a query
         lines = []
@@ -147,30 +149,34 @@ def raise_reference(D, with_o):
             lines += [f"v_mov_b32 {y}, {x}", "s_nop 1", f"{swap} {x}, {y}", "s_nop 1", f"{op} {x}, {x}, {y}"]
         return lines
 
-    lines = []
+    lines = [f"{lab('raise')}:"]
     for qb in range(2):
         s = [f"v{REG_S[kb, qb] + v}" for kb in range(4) for v in range(4)]
-        lines.append(f"v_max3_f32 {t[0]}, {s[0]}, {s[1]}, {s[2]}")
-        lines += [f"v_max3_f32 {t[0]}, {t[0]}, {s[i]}, {s[i + 1]}" for i in range(3, 15, 2)]
-        lines.append(f"v_max_f32 {t[0]}, {t[0]}, {s[15]}")
-        lines += over_quad(t[0], t[1], "v_max_f32")
-        lines.append(f"v_mov_b32 {t[2]}, %[l{qb}]")
-        lines += over_quad(t[2], t[1], "v_add_f32")
-        lines += [f"v_log_f32 {t[2]}, {t[2]}",
-                  f"v_mul_f32 {t[0]}, %[c], {t[0]}",
+        m, y, sum_, alpha = t[qb]
+        lines.append(f"v_max3_f32 {m}, {s[0]}, {s[1]}, {s[2]}")
+        lines += [f"v_max3_f32 {m}, {m}, {s[i]}, {s[i + 1]}" for i in range(3, 15, 2)]
+        lines.append(f"v_max_f32 {m}, {m}, {s[15]}")
+        lines += over_quad(m, y, "v_max_f32")
+        lines.append(f"v_mov_b32 {sum_}, %[l{qb}]")
+        lines += over_quad(sum_, y, "v_add_f32")
+        lines += [f"v_log_f32 {sum_}, {sum_}",
+                  f"v_mul_f32 {m}, %[c], {m}",
                   "s_nop 0",
-                  f"v_sub_f32 {t[2]}, {t[2]}, %[nr{qb}]",
-                  f"v_max3_f32 {t[0]}, {t[0]}, {t[2]}, -%[nr{qb}]",
-                  f"v_max_f32 {t[0]}, 0xff7fffff, {t[0]}",
-                  f"v_add_f32_e64 {t[3]}, -%[nr{qb}], -{t[0]}",
-                  f"v_exp_f32 {t[3]}, {t[3]}",
-                  f"v_mul_f32 %[nr{qb}], -1.0, {t[0]}",
-                  "s_nop 0"]
+                  f"v_sub_f32 {sum_}, {sum_}, %[nr{qb}]",
+                  f"v_max3_f32 {m}, {m}, {sum_}, -%[nr{qb}]",
+                  f"v_max_f32 {m}, 0xff7fffff, {m}",
+                  f"v_add_f32_e64 {alpha}, -%[nr{qb}], -{m}",
+                  f"v_exp_f32 {alpha}, {alpha}",
+                  f"v_mul_f32 %[nr{qb}], -1.0, {m}"]
+    lines += ["s_cmp_lt_i32 %[again], 0",                # scc: first tile
+              "s_mov_b32 %[again], %[t]",
+              f"s_cbranch_scc1 {lab('raised')}"]
+    for qb in range(2):
         regs = [f"%[l{qb}]", f"%[ls{qb}]", f"%[lh{qb}]"]
         if with_o:
             regs += [f"v{REG_O[db, qb] + v}" for db in range(D // 16) for v in range(4)]
-        lines += [f"v_mul_f32 {r}, {r}, {t[3]}" for r in regs]
-    return lines
+        lines += [f"v_mul_f32 {r}, {r}, {t[qb][3]}" for r in regs]
+    return lines + [f"{lab('raised')}:", "s_setpc_b64 %[ret]"]
 
 
 def locate(D, which, ahead):
@@ -182,7 +188,14 @@ def locate(D, which, ahead):
         return [f"s_mov_b64 s[{RSRC[which] + i}:{RSRC[which] + i + 1}], s[{RSRC[which + region] + i}:{RSRC[which + region] + i + 1}]"
                 for i in (0, 2)]
 
+    crosses = []
+    for end in ("nt0", "nt1", "te"):
+        crosses += [f"s_cmp_eq_u32 %[x0], %[{end}]", f"s_cbranch_scc1 {lab('move')}"]
     return [f"s_add_i32 %[x0], %[t], {ahead}",
+            *crosses,
+            "s_cmp_ge_i32 %[first], 0",                  # not the first tile, nor one where a region begins: it goes on
+            f"s_cbranch_scc1 {lab('there')}",
+            f"{lab('move')}:",
             "s_cmp_ge_i32 %[x0], %[te]",
             f"s_cbranch_scc1 {lab('absent')}",
             "s_cmp_ge_i32 %[x0], %[nt1]",
@@ -253,7 +266,10 @@ def special(D, score, live):
                           "s_nop 1"]
                 lines += [f"v_cndmask_b32 v{REG_S[kb, qb] + v}, v{STAGE0}, v{REG_S[kb, qb] + v}, vcc" for qb in range(2)]
         lines.append(f"{lab('whole')}:")
-    return lines + ["s_setpc_b64 %[ret]"]
+    # A piece's first tile sets the references before it is scaled (with none every exponential would overflow, and the
+    # tile be done twice).
+    first = [f"s_cbranch_scc1 {lab('raise')}"] if live else []
+    return lines + ["s_cmp_lt_i32 %[first], 0", "s_mov_b32 %[first], 0", *first, "s_setpc_b64 %[ret]"]
 
 
 def next_boundary():
@@ -289,6 +305,7 @@ def tile_loop(D, score, live):
         if not score:
             lines += [f"v_mov_b32 v{REG_O[db, qb] + v}, 0" for db in range(D // 16) for qb in range(2) for v in range(4)]
         lines.append("s_mov_b32 %[again], -1")
+    lines.append("s_mov_b32 %[first], -1")
     lines += next_boundary()
     lines.append("s_mov_b32 %[m0_was], m0")
     lines.append("s_mov_b32 %[ev], %[t]")                # the first iteration sets the cursors
@@ -344,7 +361,7 @@ def tile_loop(D, score, live):
                 lines.append(f"v_add_u32 %[va], {slot * L['vtile']}, %[va]")
             lines.append(f"s_branch {lab('last')}")
     if live:
-        lines += [f"{lab('raise')}:", "s_mov_b32 %[again], %[t]"] + raise_reference(D, not score) + ["s_setpc_b64 %[ret]"]
+        lines += raise_reference(D, not score)
     lines += special(D, score, live)
     lines.append(f"{lab('last')}:")
     if live and not score:
@@ -364,7 +381,7 @@ def bound(how, regs, var, n):
 def function(D, score, live):
     L = layout(D)
     outs = ['[t] "+s"(t)', f'"=&{{s[{RSRC["k"]}:{RSRC["k"] + 3}]}}"(rk)', f'"=&{{s[{RSRC["v"]}:{RSRC["v"] + 3}]}}"(rv)']
-    outs += [f'[{n}] "=&s"({n})' for n in ("stk", "sgk", "bd", "ev", "x0", "x1", "x2", "ret", "m0_was")]
+    outs += [f'[{n}] "=&s"({n})' for n in ("stk", "sgk", "bd", "ev", "x0", "x1", "x2", "ret", "m0_was", "first")]
     outs += [f'[{n}] "=&v"({n})' for n in ("vok", "tmp")]
     ins = [f'[{n}] "s"(a.{n})' for n in ("te", "nt0", "nt1", "sink", "cs", "grp", "ldsk")]
     ins += [f'[{n}] "v"(a.{n})' for n in ("offh", "offc")]
@@ -390,7 +407,7 @@ __device__ __forceinline__ void tile_loop<{D}, {'true' if score else 'false'}, {
   static_assert(TileLayout<{D}>::NG == {L['ng']} && TileLayout<{D}>::KGS == {L['kgs']} && TileLayout<{D}>::VGS == {L['vgs']} &&
                 TileLayout<{D}>::ROWB == {L['rowb']} && kKT == {KT} && kNBuf == {NBUF} && kWaves == {WAVES}, "regenerate df_attn_phase.inc");
   u32x4 rk, rv;
-  int t = a.t_begin, bd, ev, again, x0, x1, x2, m0_was;
+  int t = a.t_begin, bd, ev, again, x0, x1, x2, m0_was, first;
   unsigned stk, sgk, stv, sgv, vok, vov, tmp, va = a.va;
   unsigned long long ret;
   float a_[2], b_[2];
