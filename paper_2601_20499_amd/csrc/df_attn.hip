@@ -105,7 +105,8 @@ constexpr float kSumLimit = 0x1p100f; // the references are raised when the runn
 constexpr int kXcd = 8;            // XCDs per device: consecutive workgroup ids go to consecutive XCDs
 constexpr int kNumCU = 256;        // MI355X: one workgroup per CU (LDS-bound occupancy)
 constexpr int kMinSpan = 8;        // do not cut the work finer than this many key tiles per team ...
-constexpr int kMinSmallSpan = 4;   // ... nor, where the spans are chosen by their cost, finer than this
+constexpr int kMinSmallSpan = 4;   // ... nor, where the spans are chosen by their cost, finer than this;
+constexpr int kMaxCostSpan = 64;   // which they are where all of them together would be shorter than this
 constexpr int kSpinLimit = 1 << 22; // polls of a hand-over flag before a workgroup gives up (seconds; normally one poll)
 
 // One head as the kernels read it.  The table is sorted by descending key count.
@@ -1021,16 +1022,22 @@ static size_t workspace_bytes(int H, int d, int Nq) {
 // Spans for a launch that cannot give every compute unit a long one.  There, what a piece costs besides its tiles
 // decides: a workgroup that holds the end of one unit and the start of the next pays for two, and every
 // earlier piece of a unit is another trip to memory for the workgroup that finishes it.  span_cost is the time of
-// the slowest workgroup, counted in tile iterations (1.4 us at d = 128): reading a piece's first tiles, leaving sums
-// behind, finishing a unit, and the flags and sums of earlier pieces, as stamps inside the kernel gave them.  d = 64 and
-// scoring, whose tiles are shorter and whose handed-on pieces are smaller, use the same numbers.
-constexpr float kPieceCost = 2.0f, kGiveCost = 2.0f, kFinishCost = 1.5f, kPollCost = 1.0f, kFoldCost = 1.4f;
-static float span_cost(const AttnParams &p, int n) {
-  const int line = p.n_groups * p.total_cols;
+// the slowest workgroup, counted in tile iterations: a piece's start and end, leaving its sums behind, and the flags and sums
+// of earlier pieces; kSpanCost is what each span more slows all of them.  The five numbers are fitted to up to 50
+// numbers of spans measured on each of 193 launches (64 to 8 000 queries, 1 to 40 heads, spans of 4 to 63 tiles, d = 64 and
+// 128, attention and scores): above the best number measured the launches take 1.1 % on average, where all spans that a device
+// holds (and for short ones the numbers that stamps inside the kernel had given) take 2.6 %.  Of 130 other launches 96 changed their
+// number: they take 4 % less on average, from 16 % less to 7 % more.  d = 64 and scoring use the same numbers.
+constexpr float kPieceCost = 2.9f, kGiveCost = 0.7f, kPollCost = 2.6f, kFoldCost = 0.9f, kSpanCost = 0.00024f;
+// Walks give up at `limit`.
+static float span_cost(const AttnParams &p, int n, float limit) {
+  const int line = int(p.line_len), span = line / n, rem = line % n;
   float worst = 0.f, ready = 0.f;          // ready: when the last of the current unit's pieces so far is in memory
   int n_before = 0, hh = 0, group = 0;     // pieces of the unit that lie in earlier spans; the unit at the span's start
+  int begin = 0, part = 0;                 // the span's first position, floor(k * line / n), and k * rem mod n
   for (int k = 0; k < n; ++k) {
-    const int begin = int(unsigned(k * line) / unsigned(n)), hi = int(unsigned((k + 1) * line) / unsigned(n));
+    int hi = begin + span;
+    if ((part += rem) >= n) { part -= n; ++hi; }
     int lo = begin;
     float t = 0.f, give_at = 0.f, fold = 0.f;
     bool gives = false, takes = false;
@@ -1038,20 +1045,20 @@ static float span_cost(const AttnParams &p, int n) {
       while (lo >= group + p.cum[hh + 1])
         if (++hh == p.H) { hh = 0; group += p.total_cols; }
       const int unit_end = group + p.cum[hh + 1], end = std::min(hi, unit_end);
-      const float piece = kPieceCost + float(end - lo + 1);
+      const float piece = kPieceCost + float(end - lo);
       t += piece;
       if (end < unit_end) {                  // the first thing this workgroup does
         gives = true;
         t += kGiveCost;
         give_at = piece + kGiveCost;
-      } else {
-        t += kFinishCost;
-        if (lo > group + p.cum[hh]) { takes = true; fold = kPollCost + kFoldCost * float(n_before); }
+      } else if (lo > group + p.cum[hh]) {
+        takes = true;
+        fold = kPollCost + kFoldCost * float(n_before);
       }
       lo = end;
     }
-    const float finish = takes ? std::max(t, ready) + fold : t;
-    worst = std::max(worst, finish);
+    worst = std::max(worst, takes ? std::max(t, ready) + fold : t);
+    if (worst >= limit) return worst;
     if (gives) {
       const bool goes_on = !takes && n_before > 0 && begin > group + p.cum[hh];   // a unit's middle piece
       ready = goes_on ? std::max(ready, give_at) : give_at;
@@ -1059,24 +1066,28 @@ static float span_cost(const AttnParams &p, int n) {
     } else {
       n_before = 0;
     }
+    begin = hi;
   }
   return worst;
 }
-// The cheapest of a few numbers of spans up to n_max: spans of the least length and up to six tiles longer, and the
-// largest two numbers that cut the units of equally long heads into equal parts.  Few, because the walk is paid on
-// every small call (about 10 ns a span).
+// The cheapest number of spans up to n_max.  A few first, so that the walks of the others give up early; numbers that must
+// be dearer than the best are not walked, and of more than 90 only every second, third, ... is looked at, with the
+// largest that cut the units of equally long heads into equal parts: 0 to 7 us on the host, 2 at most launches.
 static int cheapest_spans(const AttnParams &p, int n_max) {
-  const int line = p.n_groups * p.total_cols;
-  int best = 1;
+  int best = n_max;
   float best_cost = INFINITY;
   auto consider = [&](int n) {
-    const float c = span_cost(p, n);
-    if (c < best_cost || (c == best_cost && n < best)) { best_cost = c; best = n; }
+    const float slower = 1.f + kSpanCost * float(n);
+    const int span = int(p.line_len) / n, longest = span + 1, n_before = (p.cum[1] - 1) / longest;
+    // no less than this where the longest unit fills a span and lies in two more
+    if (n_before > 1 && slower * (float(span) + kPieceCost + kGiveCost + kPollCost + kFoldCost * float(n_before)) > best_cost) return;
+    const float c = slower * span_cost(p, n, best_cost / slower);
+    if (c < best_cost) { best_cost = c; best = n; }
   };
-  consider(n_max);
-  for (int longer : {1, 2, 4, 6}) consider(std::max(1, line / (line / n_max + longer)));
-  const int units = p.H * p.n_groups;
-  for (int n = n_max / units * units, i = 0; n >= 1 && i < 2; n -= units, ++i) consider(n);
+  for (int eighths = 8; eighths >= 4; --eighths) consider(std::max(1, n_max * eighths / 8));
+  const int units = p.H * p.n_groups, step = std::max(1, n_max * n_max / 8192);
+  for (int n = n_max / units * units, i = 0; n >= 1 && i < 8; n -= units, ++i) consider(n);
+  for (int n = n_max - 1; n >= 1 && float(p.line_len) / float(n) < best_cost; n -= step) consider(n);
   return best;
 }
 
@@ -1120,12 +1131,11 @@ static df_status plan(AttnParams &p) {
   p.n_groups = (p.n_qtiles + team - 1) / team;
   p.line_len = int64_t(p.n_groups) * total;
   p.n_teams = int32_t(teams_of(team));
-  // Launches that spans of kMinSpan tiles leave part of the machine without work.  Measured on 13 of them, 64 to 1170
-  // queries and 4 to 45 tiles a unit (three at d = 64, three of scores): a fixed least span of 8, 6, 4 or 3 tiles each was
-  // best for some and up to twice too slow for others; against spans of 4 the choice is between the same (64 queries 15.8
-  // us both) and 23 % faster (300 queries 29.2 -> 22.6; scores 25.5 -> 21.5, 16.9 -> 14.2, 12.8 -> 10.9).  One step further (1170 queries, 9 tiles a span) all spans are better kept: 43.4 against
-  // 44.0 us with the choice.
-  if (p.line_len < kMinSpan * (kNumCU / team))
+  // Where all the spans that the machine holds are shorter than kMaxCostSpan tiles their number is chosen by their cost (longer
+  // ones lose more by idle compute units than the cut saves: of 19 launches of 66 to 450 tiles a span one gains 1.8 %).
+  // All spans -> chosen, us: 1170 sampled queries 56.6 -> 55.0, 825 queries 107.7 -> 98.8, 1104 of two heads 54.3 -> 47.9, 98
+  // sampled ones of 24 heads 21.4 -> 18.9.
+  if (p.line_len < int64_t(kMaxCostSpan) * (kNumCU / team))
     p.n_teams = cheapest_spans(p, std::max(1, std::min(kNumCU / team, int(p.line_len) / kMinSmallSpan)));
   p.span_base = p.line_len / p.n_teams;
   p.span_rem = int32_t(p.line_len % p.n_teams);

@@ -31,3 +31,14 @@ def test_short_units_are_not_cut(b):
     one workgroup walk all four units."""
     r = b.df_attn_plan(64, 64, [192, 192, 192, 0], [64, 64, 64, 0])
     assert r["workgroups"] == 3 and r["gives"] == 0 and r["pieces"] == 4
+
+
+@pytest.mark.parametrize("Nq,Nc,lens,sinks,n_teams", [
+    (1170, 4680, [9360] * 12, [1560] * 12, 48),   # 12 equal units, 51 spans fit: four spans a unit
+    (237, 948, [4740] * 12, [316] * 12, 180),     # 256 fit: fifteen spans of six tiles a unit
+    (4680, 4680, [9360] * 12, [1560] * 12, 13),   # spans of more than 64 tiles: all that the machine holds
+])
+def test_spans_that_fit_the_units(b, Nq, Nc, lens, sinks, n_teams):
+    """Spans of less than 64 tiles are cut where the units end if a number near the largest does so."""
+    r = b.df_attn_plan(Nq, Nc, lens, sinks)
+    assert r["consistent"] == 1 and r["n_teams"] == n_teams, r
