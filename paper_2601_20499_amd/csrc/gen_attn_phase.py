@@ -180,7 +180,10 @@ def raise_reference(D, with_o):
 
 
 def locate(D, which, ahead):
-    """Cursor `which` (k or v) onto tile t + ahead: byte offset, bytes per tile, bytes between row groups, descriptor."""
+    """Cursor `which` (k or v) onto tile t + ahead: byte offset, bytes per tile, bytes between row groups, descriptor.  All
+    four also for an absent tile: its loads write zeros because the offset lies past the end that a descriptor states, and
+    at a piece's first tile, where K is absent in pieces of up to three tiles and V in those of up to two, no
+    descriptor has been set before."""
     rowb = layout(D)["rowb"]
     lab = lambda name: f".Ldf_{name}_{which}_%="
 
@@ -225,6 +228,7 @@ def locate(D, which, ahead):
             f"v_mov_b32 %[vo{which}], 0x{NO_TILE:x}",
             f"s_mov_b32 %[st{which}], 0",
             f"s_mov_b32 %[sg{which}], 0",
+            *through("h"),
             f"{lab('there')}:"]
 
 
@@ -308,7 +312,9 @@ def tile_loop(D, score, live):
     lines.append("s_mov_b32 %[first], -1")
     lines += next_boundary()
     lines.append("s_mov_b32 %[m0_was], m0")
-    lines.append("s_mov_b32 %[ev], %[t]")                # the first iteration sets the cursors
+    lines.append("s_mov_b32 %[ev], %[t]")                # the first iteration sets the cursors ...
+    for which in "k" if score else "kv":                 # ... after it has moved them on like any other
+        lines += [f"s_mov_b32 %[st{which}], 0", f"v_mov_b32 %[vo{which}], 0"]
     if live:
         lines += mfma_phase(D, True, False, "0", "0")
     lines += ["s_cmp_lg_u32 %[grp], 0", f"s_cbranch_scc1 {lab('group1' if prefer_group1 else 'g1_0')}"]
