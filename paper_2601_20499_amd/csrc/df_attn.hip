@@ -268,11 +268,15 @@ struct Slot {
 __device__ __forceinline__ void store4_through(float *ptr, const f32x4 &v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(ptr), "v"(v) : "memory");
 }
+// The loads below take their base from scalar registers.  A vector instruction that writes one - the compiler keeps scalars
+// in lanes of vector registers and reads them back with v_readlane - must lie five wait states before a vector memory
+// instruction that reads it, and the compiler does not look into asm for such an instruction: the statements begin with them.
 // The statistics of the thread's two queries from four slots, all loads in flight at once and one wait; `reader` is the
 // lane that wrote those of the first query (Slot::stats_reader), the second's lie 16 lanes on.
 __device__ __forceinline__ void load_stats_through(const float *s0, const float *s1, const float *s2, const float *s3,
                                                    int reader, f32x4 (&st)[4][2]) {
   asm volatile(
+      "s_nop 4\n\t"
       "global_load_dwordx4 %0, %8, %9 sc0 sc1\n\t"
       "global_load_dwordx4 %1, %8, %9 offset:256 sc0 sc1\n\t"
       "global_load_dwordx4 %2, %8, %10 sc0 sc1\n\t"
@@ -298,6 +302,7 @@ __device__ __forceinline__ void load_slot_through<16>(const float *slot, int tid
   const unsigned vo = unsigned(tid) * 16u, so = unsigned(Slot<128>::stats_reader(tid, 0)) * 16u;
   unsigned t0, t1;
   asm volatile(
+      "s_nop 4\n\t"
       "global_load_dwordx4 %[s0], %[so], %[sb] sc0 sc1\n\t"
       "global_load_dwordx4 %[s1], %[so], %[sb] offset:256 sc0 sc1\n\t"
       "v_add_u32 %[t0], 0x2000, %[vo]\n\t"
@@ -343,6 +348,7 @@ __device__ __forceinline__ void load_slot_through<8>(const float *slot, int tid,
   const unsigned vo = unsigned(tid) * 16u, so = unsigned(Slot<64>::stats_reader(tid, 0)) * 16u;
   unsigned t0, t1;
   asm volatile(
+      "s_nop 4\n\t"
       "global_load_dwordx4 %[s0], %[so], %[sb] sc0 sc1\n\t"
       "global_load_dwordx4 %[s1], %[so], %[sb] offset:256 sc0 sc1\n\t"
       "v_add_u32 %[t0], 0x2000, %[vo]\n\t"
