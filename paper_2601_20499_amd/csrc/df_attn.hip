@@ -89,8 +89,6 @@ namespace df {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -180,6 +178,17 @@ __device__ __forceinline__ void lds_barrier() {
 __host__ __device__ constexpr int key_of_row(int i) {
   return (i & 1) | ((i & 2) << 1) | ((((i >> 2) + 1) & 2) ? 0 : 2) | (i & 8);
 }
+// The tile loop adds the keys of rows 4..7 to that of a lane's first row when it masks a region's end, and takes the 16 rows
+// of a block as 16 keys.
+constexpr bool rows_are_as_the_tile_loop_masks_them() {
+  unsigned keys = 0;
+  for (int i = 0; i < 16; ++i) {
+    if (key_of_row(i) != key_of_row(i & ~3) + key_of_row(4 + (i & 3))) return false;
+    keys |= 1u << key_of_row(i);
+  }
+  return keys == 0xffffu;
+}
+static_assert(rows_are_as_the_tile_loop_masks_them(), "the tile loop's masks follow key_of_row");
 
 // LDS layout of one 64-key tile (all sizes in bytes).  Row r lives in group r % NG at position
 // r / NG; a group is the 1 KB one buffer_load ... lds instruction writes, followed by a pad.
@@ -198,6 +207,13 @@ struct TileLayout {
   // {r + 4 of its rows in quarter 1 or 3}: with rows 4..11 on keys 0, 1 mod 4 and the others on 2, 3 mod 4 all 16
   // differ.
   static constexpr int first_chunk(int g) { return 4 * (g & 1) + (D == 128 ? 8 : 2) * (g >> 1); }
+  // The four quarters' D / 32 chunks in a row are all chunks of the row: the tile loop reads first_chunk(g) + ks at offset 16 ks.
+  static constexpr bool quarters_share_a_row() {
+    unsigned chunks = 0;
+    for (int g = 0; g < 4; ++g)
+      for (int ks = 0; ks < D / 32; ++ks) chunks |= 1u << (first_chunk(g) + ks);
+    return chunks == (1u << (D / 8)) - 1u;
+  }
   static constexpr int k_row(int r) { return (r % NG) * KGS + (r / NG) * ROWB; }
   static constexpr int v_row(int r) { return (r % NG) * VGS + (r / NG) * ROWB; }
 };
@@ -205,6 +221,8 @@ struct TileLayout {
 __device__ __forceinline__ unsigned lds_address(const void *ptr) {
   return unsigned(reinterpret_cast<uintptr_t>(ptr));     // low half of a flat LDS address = LDS offset
 }
+
+static_assert(TileLayout<128>::quarters_share_a_row() && TileLayout<64>::quarters_share_a_row(), "the tile loop's K operands");
 
 // Buffer descriptor of `bytes` bytes from `base` on (loads past its end return zeros), as the four words themselves.
 __device__ __forceinline__ u32x4 buffer_descriptor(const u16 *base, uint32_t bytes) {

@@ -412,6 +412,7 @@ __device__ __forceinline__ void tile_loop<{D}, {'true' if score else 'false'}, {
     const TileLoopArgs &a, const bf16x8 (&qf)[{D // 32}][2], f32x4 (&o)[{D // 16}][2], RowSums &r) {{
   static_assert(TileLayout<{D}>::NG == {L['ng']} && TileLayout<{D}>::KGS == {L['kgs']} && TileLayout<{D}>::VGS == {L['vgs']} &&
                 TileLayout<{D}>::ROWB == {L['rowb']} && kKT == {KT} && kNBuf == {NBUF} && kWaves == {WAVES}, "regenerate df_attn_phase.inc");
+  static_assert({' && '.join(f"key_of_row({4 + v}) == {k}" for v, k in enumerate(KEY_OF_ROW))}, "the statement masks the keys {KEY_OF_ROW}");
   u32x4 rk, rv;
   int t = a.t_begin, bd, ev, again, x0, x1, x2, m0_was, first;
   unsigned stk, sgk, stv, sgv, vok, vov, tmp, va = a.va;

@@ -205,7 +205,7 @@ def check_piece(d, score, live, statement, nt, t_begin, te, ragged, quarter, out
     lds0 = dict(k=0x100, v=0x20000)
     lane_h, lane_c = 7 * ng * rowb + 16, 7 * ng * cs + 16          # some lane's bytes
     read0 = dict(k=0x100 + 48, v=0x20000 + 40)
-    key0 = (0, 2, 8, 10)[quarter]                                    # key of a quarter's first row of a block
+    key0 = (2, 0, 8, 10)[quarter]                                    # key of a quarter's first row of a block
     values = dict(t=t_begin, te=te, nt0=nt0, nt1=nt0 + nt1, sink=sink, win=win, nc=nc, cs=cs, ldsk=lds0["k"], ldsv=lds0["v"],
                   offh=lane_h, offc=lane_c, ka=read0["k"], va=read0["v"], key0=key0)
     for i, (w, x) in enumerate((w, x) for w in "kv" for x in "hc"):
