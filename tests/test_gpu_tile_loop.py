@@ -1,13 +1,15 @@
 """The tile loop of the attention kernel where its special cases meet: regions of one to five tiles whose ends are less
 than the load distance apart, ragged and whole last tiles, pieces of every length from one tile on, waves whose rows all
-lie past the last query, and rows whose reference has to go up in the middle of a region."""
+lie past the last query, and rows whose reference has to go up after a piece's first tile - by far, so that nothing of what
+was summed before is left, and by so little that it keeps its share."""
+import itertools
+import math
+
 import numpy as np
 import pytest
 import torch
 
 from tests import gpu_util as gu
-
-pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture(scope="module")
@@ -26,28 +28,101 @@ SHAPES = [
     (511, [(127, 64), (192, 1), (64, 257), (0, 0), (320, 63)], 130),
     (97, [(256, 320), (64, 64)], 256),
 ]
+# how the logits go on from a row's first keys: by noise of about a nat alone; up by 2 sqrt(d) nats every eight keys, 185 (d =
+# 64) or 261 bits a tile, past the limit of the sums (2^100) in every tile; up once, behind the unit's first tile, by 94 to 98 bits by
+# wave, after which the sums pass the limit with one tile or a few that all have a share in them
+GROWTH = ["none", "steep", "plateau"]
 
 
-@pytest.mark.parametrize("grows", [False, True])
-@pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("Nq,regions,Nc", SHAPES)
-def test_regions_of_few_tiles(df, d, Nq, regions, Nc, grows):
-    dev, H = gu.dev(), len(regions)
-    g = torch.Generator(device=dev).manual_seed(100 * Nq + Nc + d)
-    rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
-    sink = [s for s, _ in regions]
+def inputs(d, Nq, regions, Nc, growth):
+    """q, k_cur, v_cur, k_hist, v_hist (bf16, on the CPU) and the history offsets."""
+    H = len(regions)
+    g = torch.Generator().manual_seed(100 * Nq + Nc + d)
+    rnd = lambda *s: torch.randn(*s, generator=g).to(torch.bfloat16)
     off = [0] + np.cumsum([s + w for s, w in regions]).tolist()
     q, kc, vc, kh, vh = rnd(Nq, H, d), rnd(Nc, H, d), rnd(Nc, H, d), rnd(off[-1], d), rnd(off[-1], d)
-    if grows:
-        # every eighth key outscores those before it: logits climb by about 2 sqrt(d) / 8 nats a key, through the
-        # limit of the sums (2^100) several times in a region of a few hundred keys
-        up = torch.full((d,), 1.0, device=dev).to(torch.bfloat16)
-        q = (q.float() * 0.1 + up.float()).to(torch.bfloat16)
+    if growth != "none":
+        # q . (1, ..., 1) is about d: a lift of x is x sqrt(d) nats
+        if growth == "steep":
+            q = (q.float() * 0.1 + 1.0).to(torch.bfloat16)
+        else:
+            wave = (torch.arange(Nq) // 32)[:, None, None] + 3 * torch.arange(H)[:, None]
+            q = ((q.float() * 0.02 + 1.0) * (94.5 + 0.5 * (wave % 8)) / 97).to(torch.bfloat16)
+            kh, kc = kh * 0.25, kc * 0.25
         for h in range(H):
             n = off[h + 1] - off[h]
-            lift = lambda a, b: (0.25 * (torch.arange(a, b, device=dev) // 8)).to(torch.bfloat16)[:, None] * up
-            kh[off[h]:off[h + 1]] += lift(0, n)
-            kc[:, h] += lift(n, n + Nc)
+            i = torch.arange(n + Nc)
+            first = next(min(x, 64) for x in (*regions[h], Nc) if x)
+            lift = 2.0 * (i // 8) if growth == "steep" else (i >= first) * (97 * math.log(2) / d ** 0.5)
+            lift = lift.to(torch.float32)[:, None]
+            kh[off[h]:off[h + 1]] = (kh[off[h]:off[h + 1]].float() + lift[:n]).to(torch.bfloat16)
+            kc[:, h] = (kc[:, h].float() + lift[n:]).to(torch.bfloat16)
+    return q, kc, vc, kh, vh, off
+
+
+def raises(df, logits, regions, Nq, Nc):
+    """The rule for references on the pieces of the launch, from the logits of the heads in 64 bits: (raises after a piece's first
+    tile, of which some row's earlier tiles keep a hundredth of its sum, pieces of more than one tile)."""
+    tiles = [[(r0 + a, r0 + min(a + 64, n)) for r0, n in ((0, s), (s, w), (s + w, Nc)) for a in range(0, n, 64)] for s, w in regions]
+    plan = df.df_attn_plan(Nq, Nc, [s + w for s, w in regions], [s for s, _ in regions])
+    order = sorted(range(len(regions)), key=lambda h: -sum(regions[h]))
+    cuts = {k * plan["line_len"] // plan["n_teams"] for k in range(1, plan["n_teams"])}
+    n_raised = n_shared = n_long = at = 0
+    rows_of = lambda group: range(group * plan["team_size"] * 256, min(Nq, (group + 1) * plan["team_size"] * 256), 32)
+    for group, h in itertools.product(range(plan["n_groups"]), order):
+        starts = [0] + [c - at for c in sorted(cuts) if at < c < at + len(tiles[h])]
+        for begin, end in zip(starts, starts[1:] + [len(tiles[h])]):
+            n_long += end - begin > 1
+            for row0 in rows_of(group):
+                x = logits[h][row0:row0 + 32] * math.log2(math.e)
+                ref, l = None, None
+                for a, b in tiles[h][begin:end]:
+                    if ref is None:
+                        ref, l = x[:, a:b].amax(1), torch.zeros(len(x), 4, dtype=torch.float64)
+                    key = torch.arange(b - a) % 16              # quarter of the wave that holds a key of its block of 16
+                    quarter = (key // 8 * 2 + (key // 2 % 2 == 0) * 1)
+                    share = lambda r: torch.exp2(x[:, a:b] - r[:, None]) @ torch.nn.functional.one_hot(quarter, 4).double()
+                    new = l + share(ref)
+                    lanes = torch.zeros(32, 4, dtype=torch.float64)     # of the wave's two rows that a lane has
+                    lanes[:len(x)] = new
+                    if (lanes[:16] + lanes[16:]).max() > 2.0 ** 100:
+                        up = torch.maximum(torch.maximum(x[:, a:b].amax(1), ref), ref + torch.log2(l.sum(1)))
+                        l = l * torch.exp2(ref - up)[:, None]
+                        before, ref, new = l.sum(1), up, l + share(up)
+                        n_raised += 1
+                        n_shared += bool((before > 0.01 * new.sum(1)).any())
+                    l = new
+        at += len(tiles[h])
+    return n_raised, n_shared, n_long
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Nq,regions,Nc", SHAPES)
+def test_inputs_raise_references(df, d, Nq, regions, Nc):
+    """What the inputs of the GPU test below are made for: wherever a piece has a second tile, some reference goes up behind the
+    first; and where units have three or more tiles, some time with earlier tiles that count."""
+    for growth in GROWTH:
+        q, kc, _, kh, _, off = inputs(d, Nq, regions, Nc, growth)
+        logits = [q[:, h].double() @ torch.cat([kh[off[h]:off[h + 1]], kc[:, h]]).double().t() * d ** -0.5 for h in range(len(regions))]
+        n_raised, n_shared, n_long = raises(df, logits, regions, Nq, Nc)
+        print(growth, n_raised, n_shared, n_long)
+        if growth == "none":
+            assert n_raised == 0
+        elif growth == "steep":
+            assert (n_raised > 0) == (n_long > 0)
+        elif Nq > 33:
+            assert n_shared > 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("growth", GROWTH)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Nq,regions,Nc", SHAPES)
+def test_regions_of_few_tiles(df, d, Nq, regions, Nc, growth):
+    dev, H = gu.dev(), len(regions)
+    sink = [s for s, _ in regions]
+    *tensors, off = inputs(d, Nq, regions, Nc, growth)
+    q, kc, vc, kh, vh = (t.to(dev) for t in tensors)
     scale = d ** -0.5
     ws = torch.empty(df.df_attn_workspace_bytes(H, d, Nq), dtype=torch.uint8, device=dev)
     out = torch.full_like(q, float("nan"))
@@ -60,15 +135,17 @@ def test_regions_of_few_tiles(df, d, Nq, regions, Nc, grows):
         logits = q[:, h].double() @ torch.cat([kh[off[h]:off[h + 1]], kc[:, h]]).double().t() * scale
         p = torch.softmax(logits, 1)
         ref = p @ torch.cat([vh[off[h]:off[h + 1]], vc[:, h]]).double()
+        # products summed in fp32 (d roundings of 2^-24 in the worst case, half of that allowed); an error of a logit is one of
+        # its key's weight
+        logit_err = 4e-6 * logits.abs().max().item()
         # one key may hold almost all of a row: the output is then a bf16 value times a bf16 P, up to two roundings of
         # 2^-9 of |V| <= 5
         err = (out[:, h].double() - ref).abs().max().item()
-        assert np.isfinite(err) and err <= gu.MAX_ABS, (h, err)
+        assert np.isfinite(err) and err <= gu.MAX_ABS + 5 * logit_err, (h, err)
         R = torch.logsumexp(logits, 1)
-        # fp32 logits of up to |R|: products in fp32 (d roundings of 2^-24 in the worst case, a few in practice), c and the
-        # reference rounded once each
+        # fp32 logits of up to |R|, c and the reference rounded once each
         assert (lse[h] - R).abs().max() <= gu.LSE_ABS + 4e-6 * R.abs().max(), h
         s, n = sink[h], off[h + 1] - off[h]
         mass = torch.stack([p[:, :s].sum(), p[:, s:n].sum(), p[:, n:].sum()]) / Nq
-        tol = gu.F_ABS + 4e-6 * logits.abs().max()                     # an error of a logit is one of its weight
+        tol = gu.F_ABS + logit_err
         assert (F[h] - mass).abs().max() <= tol and (F2[h] - mass).abs().max() <= tol, h
