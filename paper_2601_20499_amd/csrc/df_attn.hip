@@ -1051,67 +1051,81 @@ static size_t workspace_bytes(int H, int d, int Nq) {
 // numbers of spans measured on each of 193 launches (64 to 8 000 queries, 1 to 40 heads, spans of 4 to 63 tiles, d = 64 and
 // 128, attention and scores): above the best number measured the launches take 1.1 % on average, where all spans that a device
 // holds (and for short ones the numbers that stamps inside the kernel had given) take 2.6 %.  Of 130 other launches 96 changed their
-// number: they take 4 % less on average, from 16 % less to 7 % more.  d = 64 and scoring use the same numbers.
+// number: they take 4 % less on average, from 16 % less to 7 % more.  d = 64 and scoring use the same numbers.  Choosing takes the host
+// 1.6 us on average and 6 at most (3 000 launches of 2 to 64 heads, 64 to 2048 tokens a frame, a 2.7 GHz Xeon; walked span by span and
+// without kMaxWalk 3.5 and 16; 64 heads of a few tiles each 7 against 42).
 constexpr float kPieceCost = 2.9f, kGiveCost = 0.7f, kPollCost = 2.6f, kFoldCost = 0.9f, kSpanCost = 0.00024f;
-// Walks give up at `limit`.
-static float span_cost(const AttnParams &p, int n, float limit) {
-  const int line = int(p.line_len), span = line / n, rem = line % n;
+constexpr int kMaxWalk = 1024;
+// The walk goes from unit to unit (the spans that lie inside one differ by a tile at most) and ends with infinity where the cost
+// reaches `limit`.
+static float span_cost(const AttnParams &p, int n, float limit, int &units_walked) {
+  const int line = int(p.line_len), base = line / n, rem = line % n;
+  const uint32_t by_n = reciprocal_of(n);
+  const uint64_t by_line = (uint64_t(1) << 40) / unsigned(line) + 1;   // of numbers below 2^22: line * n
+  auto begin_of = [&](int span) { return span * base + divide_small(unsigned(span * rem), by_n); };
   float worst = 0.f, ready = 0.f;          // ready: when the last of the current unit's pieces so far is in memory
-  int n_before = 0, hh = 0, group = 0;     // pieces of the unit that lie in earlier spans; the unit at the span's start
-  int begin = 0, part = 0;                 // the span's first position, floor(k * line / n), and k * rem mod n
-  for (int k = 0; k < n; ++k) {
-    int hi = begin + span;
-    if ((part += rem) >= n) { part -= n; ++hi; }
-    int lo = begin;
-    float t = 0.f, give_at = 0.f, fold = 0.f;
-    bool gives = false, takes = false;
-    while (lo < hi) {
-      while (lo >= group + p.cum[hh + 1])
-        if (++hh == p.H) { hh = 0; group += p.total_cols; }
-      const int unit_end = group + p.cum[hh + 1], end = std::min(hi, unit_end);
-      const float piece = kPieceCost + float(end - lo);
-      t += piece;
-      if (end < unit_end) {                  // the first thing this workgroup does
-        gives = true;
-        t += kGiveCost;
-        give_at = piece + kGiveCost;
-      } else if (lo > group + p.cum[hh]) {
-        takes = true;
-        fold = kPollCost + kFoldCost * float(n_before);
-      }
-      lo = end;
-    }
+  float t = 0.f, fold = 0.f;               // the current span: time of its pieces so far; of the earlier pieces it collects
+  bool takes = false;                      // ... if it does
+  int span = 0, hi = begin_of(1);          // the current span and its end
+  auto end_span = [&] {
     worst = std::max(worst, takes ? std::max(t, ready) + fold : t);
-    if (worst >= limit) return worst;
-    if (gives) {
-      const bool goes_on = !takes && n_before > 0 && begin > group + p.cum[hh];   // a unit's middle piece
-      ready = goes_on ? std::max(ready, give_at) : give_at;
-      n_before = goes_on ? n_before + 1 : 1;
-    } else {
-      n_before = 0;
+    t = 0.f;
+    takes = false;
+  };
+  for (int group = 0; group < line; group += p.total_cols)
+    for (int hh = 0; hh < p.H; ++hh) {
+      const int lo = group + p.cum[hh], end = group + p.cum[hh + 1];
+      ++units_walked;
+      if (end > hi) {                        // handed on: the first thing the workgroup does
+        const float give_at = kPieceCost + float(hi - lo) + kGiveCost;
+        t += kPieceCost + float(hi - lo);
+        t += kGiveCost;
+        end_span();
+        // the spans that the unit fills (`inside` of them, positions hi .. last), and the one that holds its end
+        const int last_span = int((uint64_t(unsigned(end) * unsigned(n) - 1u) * by_line) >> 40), inside = last_span - span - 1;
+        const int last = begin_of(last_span);
+        ready = give_at;
+        if (inside > 0) {
+          const float filled = kPieceCost + float(base + (last - hi > inside * base)) + kGiveCost;
+          worst = std::max(worst, filled);
+          ready = std::max(ready, filled);
+        }
+        if (worst >= limit) return INFINITY;
+        span = last_span;
+        hi = begin_of(span + 1);
+        takes = true;
+        fold = kPollCost + kFoldCost * float(inside + 1);
+        t = kPieceCost + float(end - last);
+      } else {
+        t += kPieceCost + float(end - lo);
+      }
+      if (end == hi) {
+        end_span();
+        if (worst >= limit) return INFINITY;
+        hi = begin_of(++span + 1);
+      }
     }
-    begin = hi;
-  }
-  return worst;
+  return worst < limit ? worst : INFINITY;
 }
-// The cheapest number of spans up to n_max.  A few first, so that the walks of the others give up early; numbers that must
-// be dearer than the best are not walked, and of more than 90 only every second, third, ... is looked at, with the
-// largest that cut the units of equally long heads into equal parts: 0 to 7 us on the host, 2 at most launches.
+// The cheapest number of spans up to n_max.  A few first, so that the walks of the others give up early; the largest that cut the
+// units of equally long heads into equal parts; then every number down to those whose spans alone cost more (every second, third, ... of
+// more than 90) until kMaxWalk units have been walked.  Numbers that must be dearer than the best are not walked.
 static int cheapest_spans(const AttnParams &p, int n_max) {
-  int best = n_max;
+  const int line = int(p.line_len), units = p.H * p.n_groups;
+  int best = n_max, walked = 0;
   float best_cost = INFINITY;
   auto consider = [&](int n) {
     const float slower = 1.f + kSpanCost * float(n);
-    const int span = int(p.line_len) / n, longest = span + 1, n_before = (p.cum[1] - 1) / longest;
+    const int span = line / n, longest = span + 1, n_before = (p.cum[1] - 1) / longest;
     // no less than this where the longest unit fills a span and lies in two more
     if (n_before > 1 && slower * (float(span) + kPieceCost + kGiveCost + kPollCost + kFoldCost * float(n_before)) > best_cost) return;
-    const float c = slower * span_cost(p, n, best_cost / slower);
+    const float c = slower * span_cost(p, n, best_cost / slower, walked);
     if (c < best_cost) { best_cost = c; best = n; }
   };
   for (int eighths = 8; eighths >= 4; --eighths) consider(std::max(1, n_max * eighths / 8));
-  const int units = p.H * p.n_groups, step = std::max(1, n_max * n_max / 8192);
   for (int n = n_max / units * units, i = 0; n >= 1 && i < 8; n -= units, ++i) consider(n);
-  for (int n = n_max - 1; n >= 1 && float(p.line_len) / float(n) < best_cost; n -= step) consider(n);
+  const int step = std::max(1, n_max * n_max / 8192);
+  for (int n = n_max - 1; n >= 1 && float(line) / float(n) < best_cost && walked < kMaxWalk; n -= step) consider(n);
   return best;
 }
 

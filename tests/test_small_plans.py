@@ -1,5 +1,7 @@
 """Launches too small to give every compute unit a long span: the number of spans is chosen by the cost of their pieces."""
+import os
 import random
+import re
 
 import pytest
 
@@ -42,3 +44,57 @@ def test_spans_that_fit_the_units(b, Nq, Nc, lens, sinks, n_teams):
     """Spans of less than 64 tiles are cut where the units end if a number near the largest does so."""
     r = b.df_attn_plan(Nq, Nc, lens, sinks)
     assert r["consistent"] == 1 and r["n_teams"] == n_teams, r
+
+
+def constant(name):
+    src = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2601_20499_amd", "csrc", "df_attn.hip")).read()
+    return float(re.search(name + r" = ([\d.]+)f?\b", src)[1])
+
+
+def cost(units, n):
+    """Time of the slowest workgroup for n spans over units of so many tiles, span by span: pieces and what they cost besides
+    their tiles; a unit's earlier pieces are there once the last of their workgroups has left its sums."""
+    piece_cost, give, poll, fold, span_cost = (constant(f"k{x}Cost") for x in ("Piece", "Give", "Poll", "Fold", "Span"))
+    line = sum(units)
+    starts = [sum(units[:i]) for i in range(len(units) + 1)]
+    cuts = [k * line // n for k in range(n + 1)]
+    given = [[] for _ in units]                # when the pieces of a unit that are handed on are in memory
+    worst = 0.0
+    for lo, hi in zip(cuts, cuts[1:]):
+        t, after = 0.0, None
+        for u, (a, b) in enumerate(zip(starts, starts[1:])):
+            if a < hi and b > lo:
+                piece = piece_cost + min(hi, b) - max(lo, a)
+                t += piece
+                if b > hi:
+                    t += give
+                    given[u].append(piece + give)
+                elif given[u]:
+                    after = u
+        worst = max(worst, t if after is None else max(t, max(given[after])) + poll + fold * len(given[after]))
+    return (1 + span_cost * n) * worst
+
+
+LAUNCHES = []                                  # queries, chunk, histories, sinks
+rng = random.Random(31)
+for _ in range(24):
+    H, T, F = rng.choice([2, 5, 12, 24, 40]), rng.randint(60, 500), rng.choice([1, 3, 9, 21])
+    frames = [rng.choice([0, 1, F, F]) for _ in range(H)]
+    LAUNCHES.append((rng.choice([T, T // 4]), T * rng.choice([1, 3]), [f * T for f in frames], [T if f else 0 for f in frames]))
+
+
+@pytest.mark.parametrize("Nq,Nc,lens,sinks", LAUNCHES)
+def test_number_of_spans_is_the_cheapest_of_those_looked_at(b, Nq, Nc, lens, sinks):
+    """No number that is always looked at costs less than the chosen one."""
+    r = b.df_attn_plan(Nq, Nc, lens, sinks)
+    tiles = lambda n: -(-n // 64)
+    units = sorted((tiles(s) + tiles(l - s) + tiles(Nc) for l, s in zip(lens, sinks)), reverse=True) * r["n_groups"]
+    line, most = r["line_len"], 256 // r["team_size"]
+    assert line == sum(units)
+    if line >= 64 * most:
+        assert r["n_teams"] == most
+        return
+    n_max = max(1, min(most, line // 4))
+    chosen = cost(units, r["n_teams"]) * (1 - 1e-5)        # the library counts in 32 bits
+    for n in {n_max * e // 8 or 1 for e in range(4, 9)} | {n for n in range(n_max // len(units) * len(units), 0, -len(units))[:8]}:
+        assert chosen <= cost(units, n), n
