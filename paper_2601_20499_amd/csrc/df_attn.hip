@@ -1050,11 +1050,13 @@ static size_t workspace_bytes(int H, int d, int Nq) {
 // of earlier pieces; kSpanCost is what each span more slows all of them.  The five numbers are fitted to up to 50
 // numbers of spans measured on each of 193 launches (64 to 8 000 queries, 1 to 40 heads, spans of 4 to 63 tiles, d = 64 and
 // 128, attention and scores): above the best number measured the launches take 1.1 % on average, where all spans that a device
-// holds (and for short ones the numbers that stamps inside the kernel had given) take 2.6 %.  Of 130 other launches 96 changed their
-// number: they take 4 % less on average, from 16 % less to 7 % more.  d = 64 and scoring use the same numbers.  Choosing takes the host
-// 1.6 us on average and 6 at most (3 000 launches of 2 to 64 heads, 64 to 2048 tokens a frame, a 2.7 GHz Xeon; walked span by span and
-// without kMaxWalk 3.5 and 16; 64 heads of a few tiles each 7 against 42).
+// holds (and for short ones the numbers that stamps inside the kernel had given) take 2.6 %.  Of 302 other launches (one query to 3 000,
+// 2 to 64 heads, 0.3 to 150 GFLOP) 216 get another number than all spans and take 7.5 % less on average, from 31 % less to 10 %
+// more.  d = 64 and scoring use the same numbers.  Choosing takes the host 1.6 us on average and 6 at most (3 000 launches of
+// 2 to 64 heads, 64 to 2048 tokens a frame, a 2.7 GHz Xeon; walked span by span and without kMaxWalk 3.5 and 16; 64 heads of a few
+// tiles each 7 against 42).
 constexpr float kPieceCost = 2.9f, kGiveCost = 0.7f, kPollCost = 2.6f, kFoldCost = 0.9f, kSpanCost = 0.00024f;
+constexpr float kSurelyCheaper = 0.92f;
 constexpr int kMaxWalk = 1024;
 // The walk goes from unit to unit (the spans that lie inside one differ by a tile at most) and ends with infinity where the cost
 // reaches `limit`.
@@ -1114,18 +1116,22 @@ static int cheapest_spans(const AttnParams &p, int n_max) {
   const int line = int(p.line_len), units = p.H * p.n_groups;
   int best = n_max, walked = 0;
   float best_cost = INFINITY;
-  auto consider = [&](int n) {
-    const float slower = 1.f + kSpanCost * float(n);
+  auto consider = [&](int n, float share = 1.f) {
+    const float slower = 1.f + kSpanCost * float(n), limit = share * best_cost;
     const int span = line / n, longest = span + 1, n_before = (p.cum[1] - 1) / longest;
     // no less than this where the longest unit fills a span and lies in two more
-    if (n_before > 1 && slower * (float(span) + kPieceCost + kGiveCost + kPollCost + kFoldCost * float(n_before)) > best_cost) return;
-    const float c = slower * span_cost(p, n, best_cost / slower, walked);
-    if (c < best_cost) { best_cost = c; best = n; }
+    if (n_before > 1 && slower * (float(span) + kPieceCost + kGiveCost + kPollCost + kFoldCost * float(n_before)) > limit) return;
+    const float c = slower * span_cost(p, n, limit / slower, walked);
+    if (c < limit) { best_cost = c; best = n; }
   };
   for (int eighths = 8; eighths >= 4; --eighths) consider(std::max(1, n_max * eighths / 8));
   for (int n = n_max / units * units, i = 0; n >= 1 && i < 8; n -= units, ++i) consider(n);
   const int step = std::max(1, n_max * n_max / 8192);
   for (int n = n_max - 1; n >= 1 && float(line) / float(n) < best_cost && walked < kMaxWalk; n -= step) consider(n);
+  // The fewest spans that are one to six tiles longer, which a step may have passed over: spans of even length cost less than their
+  // neighbours.  They have to be cheaper by more than the cost is wrong by.  92 launches that take one of them: 9 % less on
+  // average, from 16 % less to 6 % more.
+  for (int longer : {1, 2, 4, 6}) consider(std::max(1, line / (line / n_max + longer)), kSurelyCheaper);
   return best;
 }
 

@@ -75,7 +75,11 @@ def cost(units, n):
     return (1 + span_cost * n) * worst
 
 
-LAUNCHES = []                                  # queries, chunk, histories, sinks
+LAUNCHES = [    # queries, chunk, histories, sinks: the fewest spans of a length are much cheaper than their neighbours
+    (754, 754, [377] + [3393] * 4 + [0], [377] * 5 + [0]),
+    (362, 362, [3801] * 4 + [181] * 2 + [0] + [3801] * 3, [181] * 6 + [0] + [181] * 3),
+    (321, 321, [107, 0, 0, 0] + [2247] * 8 + [107, 107, 2247, 107, 2247, 107, 107] + [2247] * 5, [107, 0, 0, 0] + [107] * 20),
+]
 rng = random.Random(31)
 for _ in range(24):
     H, T, F = rng.choice([2, 5, 12, 24, 40]), rng.randint(60, 500), rng.choice([1, 3, 9, 21])
@@ -85,7 +89,7 @@ for _ in range(24):
 
 @pytest.mark.parametrize("Nq,Nc,lens,sinks", LAUNCHES)
 def test_number_of_spans_is_the_cheapest_of_those_looked_at(b, Nq, Nc, lens, sinks):
-    """No number that is always looked at costs less than the chosen one."""
+    """No number that is always looked at costs less than the chosen one (by a share, for the fewest spans of a length)."""
     r = b.df_attn_plan(Nq, Nc, lens, sinks)
     tiles = lambda n: -(-n // 64)
     units = sorted((tiles(s) + tiles(l - s) + tiles(Nc) for l, s in zip(lens, sinks)), reverse=True) * r["n_groups"]
@@ -98,3 +102,6 @@ def test_number_of_spans_is_the_cheapest_of_those_looked_at(b, Nq, Nc, lens, sin
     chosen = cost(units, r["n_teams"]) * (1 - 1e-5)        # the library counts in 32 bits
     for n in {n_max * e // 8 or 1 for e in range(4, 9)} | {n for n in range(n_max // len(units) * len(units), 0, -len(units))[:8]}:
         assert chosen <= cost(units, n), n
+    for longer in (1, 2, 4, 6):
+        n = max(1, line // (line // n_max + longer))
+        assert chosen * constant("kSurelyCheaper") <= cost(units, n), n
