@@ -175,7 +175,10 @@ def _stream_handle(stream) -> Optional[int]:
         return stream or None
     if stream is None:
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None   # without a Stream object
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # no Stream object, but not part of torch's interface
+        if raw is None:
+            return torch.cuda.current_stream().cuda_stream or None
+        return raw(torch.cuda.current_device()) or None
     return stream.cuda_stream or None
 
 

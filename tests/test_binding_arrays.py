@@ -1,4 +1,5 @@
-"""Host arrays on their way to the library: every kind of sequence of numbers gives the same C array."""
+"""Host arguments on their way to the library: every kind of sequence of numbers gives the same C array, every way to name a
+stream its handle."""
 import numpy as np
 import pytest
 import torch
@@ -36,3 +37,18 @@ def test_classify_takes_any_rows(b, make):
 def test_classify_refuses_rows_that_are_too_long(b):
     with pytest.raises(IndexError):
         b.df_classify([[0.5, 0.25, 0.25, 0.0]], 0, b.DF_CLASSIFY_TWO_CLASS)
+
+
+@pytest.mark.parametrize("fast", [True, False])
+def test_current_stream_with_and_without_the_raw_handle(b, monkeypatch, fast):
+    """The raw handle of the current stream comes from a function that torch need not have."""
+    class Stream:
+        cuda_stream = 0x1230
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    if fast:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x4560 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert b._stream_handle(None) == (0x4563 if fast else 0x1230)
+    assert b._stream_handle(Stream) == 0x1230 and b._stream_handle(7) == 7 and b._stream_handle(0) is None
