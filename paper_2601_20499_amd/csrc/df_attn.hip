@@ -763,12 +763,14 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
     // its: between two barriers group 0 runs MFMA(t), VALU(t) and group 1 runs VALU(t-1), MFMA(t), MFMA(t) being the
     // products S(t) = K(t) Q and O += V(t-1) P(t-1), so the two waves of a SIMD are in opposite phases without
     // being locked phase by phase.
-    // The loads of VALU phase t, K(t+3) and V(t+2), go where K(t-1) and V(t-2) were: behind barrier t every wave has
-    // finished MFMA(t-1).  (Barrier n = the one group 0 takes after VALU(n) and group 1 before it.)  They are first read
-    // in MFMA phase t+3, behind barrier t+2, and before a barrier a wave waits for those of its loads that the
-    // MFMA phases behind it read: group 0 issues them before barrier t and may leave the loads of its latest two
-    // phases in flight, group 1 issues them behind barrier t and may leave those of its latest phase in flight.  Either way
-    // a load has about two iterations to land.  Every wave issues the same number of loads in every VALU phase (absent
+    // Barrier n is the one group 0 takes after VALU(n) and group 1 before it, so behind barrier n both have finished MFMA(n),
+    // and group 0 its VALU(n).
+    // The loads of VALU phase t, K(t+3) and V(t+2), go where K(t-1) and V(t-2) were, which MFMA(t-1) reads last.  Behind
+    // barrier t-1 every wave has finished that: group 0 issues the loads between barriers t-1 and t, group 1 behind barrier t.
+    // They are first read in MFMA(t+3), which both groups run between barriers t+2 and t+3.  Before a barrier a wave waits for those of
+    // its loads that the MFMA phases behind it read, here before barrier t+2: group 0 has by then issued the loads of phases up to t+2 and
+    // may leave those of its latest two in flight, group 1, which issues phase t+2 behind that barrier, those of its latest one.  Either
+    // way a load has about two iterations to land.  Every wave issues the same number of loads in every VALU phase (absent
     // tiles load zeros), so the counts hold.
     TileLoopArgs a;
     a.t_begin = t_begin; a.te = t_end;
