@@ -386,7 +386,7 @@ def bound(how, regs, var, n):
 
 def function(D, score, live):
     L = layout(D)
-    outs = ['[t] "+s"(t)', f'"=&{{s[{RSRC["k"]}:{RSRC["k"] + 3}]}}"(rk)', f'"=&{{s[{RSRC["v"]}:{RSRC["v"] + 3}]}}"(rv)']
+    outs = ['[t] "+&s"(t)', f'"=&{{s[{RSRC["k"]}:{RSRC["k"] + 3}]}}"(rk)', f'"=&{{s[{RSRC["v"]}:{RSRC["v"] + 3}]}}"(rv)']
     outs += [f'[{n}] "=&s"({n})' for n in ("stk", "sgk", "bd", "ev", "x0", "x1", "x2", "ret", "m0_was", "first")]
     outs += [f'[{n}] "=&v"({n})' for n in ("vok", "tmp")]
     ins = [f'[{n}] "s"(a.{n})' for n in ("te", "nt0", "nt1", "sink", "cs", "grp", "ldsk")]
@@ -403,7 +403,7 @@ def function(D, score, live):
         ins += [f'[{n}] "s"(a.{n})' for n in ("win", "nc", "c", "lim")] + [f'[{n}] "v"(a.{n})' for n in ("ka", "key0")]
         ins += bound("", REG_Q, "qf", D // 32)
         if not score:
-            outs += ['[va] "+v"(va)'] + bound("=&", REG_P, "pb", 2) + bound("=&", REG_O, "o", D // 16)
+            outs += ['[va] "+&v"(va)'] + bound("=&", REG_P, "pb", 2) + bound("=&", REG_O, "o", D // 16)
     ins += [f'"{{s[{RSRC[n]}:{RSRC[n] + 3}]}}"(a.{n})' for n in regions]
     clob = ['"vcc"', '"scc"', '"memory"'] + ([f'"v{r}"' for r in range(STAGE0, 256)] if live else [])
     body = "\n".join(f'        "{ln}\\n\\t"' for ln in tile_loop(D, score, live))

@@ -36,8 +36,8 @@ def asm_statement(d, score, live):
             regs = {f"{fixed[1]}{i}" for i in range(int(fixed[2]), int(fixed[3]) + 1)} if fixed else {name}
             if is_out:
                 outputs |= regs
-                # an output is early-clobber, unless the statement begins with its value
-                assert how.startswith("+") or how.startswith("=&"), (name, how)
+                # written before the last input is read
+                assert "&" in how, (name, how)
             if not is_out or how.startswith("+"):
                 inputs |= regs
     macros, expanded, at = {}, [], None
