@@ -1,7 +1,8 @@
 """The generated tile-loop statements of the attention kernel, interpreted on the CPU one wave at a time.
 
 Scalar instructions and addresses are computed, everything else only counts as having written its result: no
-instruction may read a register that is neither an input of the statement nor written by it before.  Every load into LDS
+instruction may read a register that is neither an input of the statement nor written by it before, or touch one that a read of
+LDS is still to fill, or come too soon after what wrote it (the wait states that the generator lists).  Every load into LDS
 must go through a descriptor of its head, to the byte offset and the buffer that its tile belongs to (past the descriptor's
 end for a tile that the piece does not have), and the loads, waits, barriers and reads of the two groups must fit
 together."""
@@ -94,6 +95,9 @@ class Wave:
         self.r = {name: values.get(name, UNKNOWN) for name in inputs}
         self.r["m0"] = UNKNOWN                       # saved and restored
         self.events, self.outgrown = [], outgrown
+        self.state, self.vector = 0, False           # wait states so far; whether the instruction runs on the vector ALU
+        self.wrote = {}                              # register -> (what wrote it: "mfma", "trans", "swap", other; state)
+        self.in_flight = []                          # registers of the LDS reads not yet waited for
 
     def get(self, operand):
         regs = registers(operand)
@@ -101,21 +105,47 @@ class Wave:
             return int(operand, 0) & 0xFFFFFFFF if re.fullmatch(r"-?(0x[0-9a-f]+|\d+)", operand) else UNKNOWN
         for x in regs:
             assert x in self.r, f"{x} is read before anything is written to it"
+            self.check(x)
         return self.r[regs[0]]
 
     def put(self, operand, value=UNKNOWN):
         for x in registers(operand):
             assert x in self.outputs or x in self.clobbers or x == "m0", f"{x} is written but not declared"
+            self.check(x)
             self.r[x] = value
+            self.wrote[x] = self.kind, self.state
+
+    def check(self, x):
+        """Register x is touched by the present instruction."""
+        assert not any(x in regs for regs in self.in_flight), f"{x} is touched before the read that fills it is waited for"
+        kind, state = self.wrote.get(x, (None, 0))
+        between = self.state - state - 1
+        if self.vector and kind == "mfma" and self.kind != "mfma":
+            assert between >= 8, (x, between)
+        if self.vector and (kind == "trans" and self.kind != "trans"):
+            assert between >= 1, (x, between)
+        if kind == "swap" or self.kind == "swap" and kind or x == "vcc" and self.vector and kind:
+            assert between >= 2, (x, self.kind, kind, between)
+        if x == "m0" and self.kind == "load":
+            assert between >= 1
 
     def run(self, limit=100000):
         pc, r = 0, self.r
         for _ in range(limit):
             if pc >= len(self.program):
+                assert not self.in_flight
+                for x, (kind, state) in self.wrote.items():       # what follows may be a vector instruction
+                    assert kind != "mfma" or self.state - state >= 8, x
                 return self.events
             op, *a = self.program[pc]
             pc += 1
-            if op in ("label", "s_nop", "s_setprio"):
+            if op == "label":
+                continue
+            self.state += 1 + (int(a[0]) if op == "s_nop" else 0)
+            self.vector = op[0] == "v"
+            self.kind = ("mfma" if "mfma" in op else "trans" if op in ("v_exp_f32", "v_log_f32") else "swap" if "_swap_" in op else
+                         "load" if op.startswith("buffer") else "other")
+            if op in ("s_nop", "s_setprio"):
                 continue
             if op in ("s_add_i32", "s_add_u32", "s_sub_i32", "s_mul_i32", "s_lshl_b32", "s_min_i32", "v_add_u32"):
                 x, y = self.get(a[1]), self.get(a[2])
@@ -156,6 +186,9 @@ class Wave:
             elif op == "s_waitcnt":
                 if a[0].startswith("vmcnt"):
                     self.events.append(("wait", int(a[0][6:-1])))
+                else:
+                    left = int(re.fullmatch(r"lgkmcnt\((\d+)\)", a[0])[1])
+                    self.in_flight = self.in_flight[len(self.in_flight) - left:] if left else []
             elif op == "s_barrier":
                 self.events.append(("barrier",))
             elif op == "buffer_load_dwordx4":
@@ -166,6 +199,7 @@ class Wave:
                 addr, _, offset = a[1].partition(" offset:")
                 base = self.get(addr)
                 self.put(a[0])
+                self.in_flight.append(registers(a[0]))
                 self.events.append(("read", addr[2], base + sum(int(x) for x in offset.split("+")), 16 if "b128" in op else 8))
             elif op == "v_cmp_gt_i32":
                 self.put("vcc", signed(self.get(a[1])) > signed(self.get(a[2])))
