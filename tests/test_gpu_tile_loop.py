@@ -119,10 +119,31 @@ def test_inputs_raise_references(df, d, Nq, regions, Nc):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Nq,regions,Nc", SHAPES)
 def test_regions_of_few_tiles(df, d, Nq, regions, Nc, growth):
-    dev, H = gu.dev(), len(regions)
-    sink = [s for s, _ in regions]
+    dev, sink = gu.dev(), [s for s, _ in regions]
     *tensors, off = inputs(d, Nq, regions, Nc, growth)
     q, kc, vc, kh, vh = (t.to(dev) for t in tensors)
+    check_against_reference(df, q, kc, vc, kh, vh, off, sink)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("stride", [16384, 40000])
+@pytest.mark.parametrize("d", [64, 128])
+def test_pieces_of_one_to_three_tiles_of_a_chunk_with_wide_rows(df, d, stride):
+    """Rows of the current chunk 32 KB and more apart, in pieces so short that the loop's first loads are of tiles that they do not
+    have: offsets and descriptors of such tiles are not those of the chunk."""
+    dev, regions, Nc = gu.dev(), [(0, 0), (65, 1), (1, 64), (0, 63)], 65
+    q, kc, vc, kh, vh, off = inputs(d, 40, regions, Nc, "none")
+    wide = torch.zeros(2, Nc, stride, dtype=torch.bfloat16, device=dev)
+    rows = [x[:, :len(regions) * d].view(Nc, len(regions), d) for x in wide]
+    rows[0].copy_(kc)
+    rows[1].copy_(vc)
+    assert rows[0].stride(0) == stride
+    check_against_reference(df, q.to(dev), *rows, kh.to(dev), vh.to(dev), off, [s for s, _ in regions])
+
+
+def check_against_reference(df, q, kc, vc, kh, vh, off, sink):
+    """Outputs, log-sum-exp and both kinds of scores against 64 bits."""
+    (Nq, H, d), dev = q.shape, q.device
     scale = d ** -0.5
     ws = torch.empty(df.df_attn_workspace_bytes(H, d, Nq), dtype=torch.uint8, device=dev)
     out = torch.full_like(q, float("nan"))
