@@ -162,7 +162,8 @@ df_status df_attn_fwd(const df_attn_args *args, void *stream);
 #define DF_STATIC_SCRATCH_BYTES (70u << 20)
 df_status df_attn_fwd_static(const df_attn_args *args, void *stream);
 
-/* df_attn_plan: how df_attn_fwd / df_head_score share a launch out over the GPU's 256 compute units
+/* df_attn_plan: how df_attn_fwd / df_head_score share a launch out over the GPU's 256 compute units, unless
+ * df_attn_units says otherwise
  * (the head-type-driven scheduling: heads differ in context length by Eq. 5 / Eq. 8, so work is cut by
  * key tiles, not by heads).  Pure host code, launches nothing; for callers and tests that want to see
  * the decomposition.  Queries are taken in tiles of 256, keys in tiles of 64 per region (sink, window,
@@ -195,6 +196,15 @@ typedef struct df_attn_plan_info {
 
 df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32_t *hist_len,
                        const int32_t *hist_sink_len, df_attn_plan_info *out);
+
+/* df_attn_units: the other way to share a launch out, which is taken instead of df_attn_plan's spans where it
+ * costs less (launches of few key tiles; it depends on d and on whether only scores are wanted).  Queries are
+ * taken in tiles of 128, and every (head, query tile) unit of head h is cut into pieces[h] parts of equally
+ * many key tiles (give or take one), one workgroup to each.  score_only != 0: a df_head_score launch, Nq being
+ * the number of sampled queries.  Writes pieces[0 .. H-1] (HOST), all 0 if the launch is shared out in spans.
+ * Errors as df_attn_plan, and DF_ERR_UNSUPPORTED for other d than 64 and 128. */
+df_status df_attn_units(int32_t H, int32_t d, int32_t score_only, int32_t Nq, int32_t Nc, const int32_t *hist_len,
+                        const int32_t *hist_sink_len, int32_t *pieces);
 
 /* ------------------------------------------------------------------------
  * df_head_score: the global frame attention score F[h] = (alpha^sink,

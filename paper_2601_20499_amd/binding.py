@@ -23,7 +23,7 @@ DF_MAX_HEADS = 64
 DF_HEAD_FULL, DF_HEAD_SINK, DF_HEAD_NEIGHBOR, DF_HEAD_DUMMY, DF_HEAD_PACK_DUMMY = range(5)
 DF_CLASSIFY_TWO_CLASS, DF_CLASSIFY_DHP = 0, 1
 
-EXPORTS = ["df_status_string", "df_head_context", "df_attn_workspace_bytes", "df_attn_fwd", "df_attn_fwd_static", "df_attn_plan",
+EXPORTS = ["df_status_string", "df_head_context", "df_attn_workspace_bytes", "df_attn_fwd", "df_attn_fwd_static", "df_attn_plan", "df_attn_units",
            "df_head_score", "df_classify", "df_kv_append", "df_pack_context"]
 
 
@@ -109,6 +109,9 @@ def _load() -> C.CDLL:
     lib.df_attn_plan.restype = C.c_int32
     lib.df_attn_plan.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                  C.POINTER(df_attn_plan_info)]
+    lib.df_attn_units.restype = C.c_int32
+    lib.df_attn_units.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
+                                  C.POINTER(C.c_int32)]
     lib.df_head_score.restype = C.c_int32
     lib.df_head_score.argtypes = [C.POINTER(df_score_args), C.c_void_p]
     lib.df_classify.restype = C.c_int32
@@ -161,6 +164,15 @@ def df_attn_plan(Nq: int, Nc: int, hist_len: Sequence[int], hist_sink_len: Optio
     _check(lib.df_attn_plan(H, int(Nq), int(Nc), _i32(hist_len),
                             _i32(hist_sink_len) if hist_sink_len is not None else None, C.byref(info)), "df_attn_plan")
     return {name: getattr(info, name) for name, _ in df_attn_plan_info._fields_}
+
+
+def df_attn_units(d: int, score_only: bool, Nq: int, Nc: int, hist_len: Sequence[int],
+                  hist_sink_len: Optional[Sequence[int]] = None) -> list:
+    """Pieces that each head's units of 128 queries are cut into, all 0 where the launch is cut into df_attn_plan's spans (host only)."""
+    pieces = _i32([0] * len(hist_len))
+    _check(lib.df_attn_units(len(hist_len), int(d), int(score_only), int(Nq), int(Nc), _i32(hist_len),
+                             _i32(hist_sink_len) if hist_sink_len is not None else None, pieces), "df_attn_units")
+    return list(pieces)
 
 
 def _ptr(t) -> Optional[int]:

@@ -27,6 +27,16 @@
 // out XCD-major (workgroup id mod 8 selects the XCD), so a team sits on one or
 // two XCDs.
 //
+// Launches of few tiles are cut in another way where that costs less (cut_units): into units of 128
+// queries, each head's units into a number of equal pieces of its own, one workgroup to a
+// piece.  There the two groups of waves (see the schedule) have the same queries and take half of
+// every tile's keys each, and a workgroup puts the two together through LDS (exchange_halves).  What such
+// launches pay for is not tiles: a second piece in a span cost a workgroup 7 us besides its tiles, and those that
+// waited for its sums with it; a piece of 256 queries hands on 136 KB, one of 128 queries 72, and a unit needs
+// half as many pieces for the same number of workgroups; and the first load goes out 0.2 us earlier.  One box, spans -> units: 64
+// queries 14.4 -> 10.0 us, 1170 queries 38.1 -> 35.3, 393 queries and 5 heads 29.0 -> 20.0, 266 queries and long histories
+// 50.0 -> 31.9, 478 sampled queries 21.1 -> 18.1; 80 random launches 14 % less on average, the worst 1.2 % more.
+//
 // MFMA mapping.  Scores are computed transposed, S^T = K Q^T, with
 // v_mfma_f32_16x16x32_bf16: 16 keys of the K tile are the A operand (ds_read_b128 from a
 // row-major LDS tile), 16 queries of the wave's Q the B operand (registers, loaded
@@ -96,7 +106,8 @@ typedef unsigned short u16;
 
 constexpr int kThreads = 512;
 constexpr int kWaves = 8;
-constexpr int kBQ = kWaves * 32;   // queries per workgroup
+constexpr int kBQ = kWaves * 32;   // queries per workgroup ...
+constexpr int kHalfBQ = kBQ / 2;   // ... and where its two groups of waves share the queries and halve every tile's keys
 constexpr int kKT = 64;            // keys per LDS tile
 constexpr int kNBuf = 4;           // LDS buffers per operand
 constexpr float kSumLimit = 0x1p100f; // the references are raised when the running sums of a lane's two rows pass this
@@ -113,7 +124,7 @@ struct HeadRec {
   int32_t len;         // history rows that hold keys (a prefix of the head's rows)
   int32_t sink;        // of these, sink rows
   int32_t head;        // index of the head
-  int32_t pad_;
+  uint32_t cut;        // a launch that cuts unit by unit (see by_units): span behind the head's last one; tiles of its shortest pieces << 16
 };
 
 struct AttnParams {
@@ -166,6 +177,7 @@ __device__ __forceinline__ float of_block(int g, const float (&x)[2]) {
   const float x0 = x[0], x1 = x[1];
   return (g & 1) ? x1 : x0;
 }
+__device__ __forceinline__ float of_block(int, const float (&x)[1]) { return x[0]; }
 
 // Workgroup barrier that waits for this wave's LDS traffic only: global loads stay in flight.
 __device__ __forceinline__ void lds_barrier() {
@@ -255,20 +267,30 @@ struct RowSums {
 };
 template <int D, bool SCORE_ONLY, bool LIVE>
 __device__ __forceinline__ void tile_loop(const TileLoopArgs &a, const bf16x8 (&qf)[D / 32][2], f32x4 (&o)[D / 16][2], RowSums &r);
+// The same for 32 keys of every tile, from the addresses and keys in `a` on.
+template <int D, bool SCORE_ONLY>
+__device__ __forceinline__ void half_tile_loop(const TileLoopArgs &a, const bf16x8 (&qf)[D / 32][2], f32x4 (&o)[D / 16][2], RowSums &r);
 #include "df_attn_phase.inc"
 
 typedef __attribute__((address_space(3))) void lds_void;
+
+// First of the rows that a wave finishes: 32, or where the two groups share a workgroup's queries, the first or second 16 of the 32 it has
+// in common with a wave of the other group.
+template <int NQB>
+__device__ __forceinline__ int first_row(int qt, int wave) {
+  return NQB == 2 ? qt * kBQ + 32 * wave : qt * kHalfBQ + 32 * (wave & 3) + 16 * (wave >> 2);
+}
 
 // Partial result of one piece of a unit, as the main kernel leaves it in the workspace and the
 // merge kernel reads it back.  Both kernels use the same thread <-> element mapping, so the layout
 // is simply "in register order": per thread 4 statistics (reference, l, l_sink, l_sink+window) and D/8 vectors of
 // 4 consecutive output elements.  A thread holds the same statistics as three other lanes for each of its two
 // queries: it writes those of query block (lane / 16) % 2 and reads its blocks' from lanes lane % 16 and
-// 16 + lane % 16 of its wave.
-template <int D>
+// 16 + lane % 16 of its wave.  Where a workgroup has half the queries (NQB = 1) a wave ends up with one block of 16.
+template <int D, int NQB = 2>
 struct Slot {
   static constexpr int kStats = kThreads * 4;                   // floats
-  static constexpr int kFloats = kStats + kThreads * (D / 8) * 4;
+  static constexpr int kFloats = kStats + kThreads * (D / 16 * NQB) * 4;
   __device__ static float *stats(float *slot, int tid) { return slot + 4 * tid; }
   __device__ static int stats_reader(int tid, int qb) { return (tid & ~63) + 16 * qb + (tid & 15); }
   __device__ static float *ovec(float *slot, int tid, int i) { return slot + kStats + (i * kThreads + tid) * 4; }
@@ -472,7 +494,7 @@ __device__ __forceinline__ uint2 output4(const f32x4 &o, float inv) {
   w.y = pack_bf16x2(o[2] * inv, o[3] * inv);
   return w;
 }
-// A wave's 32 finished rows (first row row0) go through LDS, `buf` being the wave's own 32 * D bf16 there, and out with
+// A wave's 32 (16 * NQB) finished rows (first row row0) go through LDS, `buf` being the wave's own 32 * D bf16 there, and out with
 // 16 bytes per lane and whole rows side by side.  In the accumulator layout a lane holds 8-byte bits of two rows, and
 // a store of those touches 32 rows: with the 32x32 products of an earlier version, which held 8-byte bits of one row,
 // issuing 16 of them and draining them took 5 to 6 us a unit.  Both ways on one box at that time, direct -> through LDS:
@@ -480,13 +502,13 @@ __device__ __forceinline__ uint2 output4(const f32x4 &o, float inv) {
 // 610.0 -> 601.9; a launch of 64 queries 15.1 -> 15.8.
 // 16-byte chunk c of row r lies at position c ^ (r mod chunks per row).  The reads are then free of bank conflicts; the
 // 8-byte writes are not: 4 cycles each (264,192 in a 1280x720 launch, 0.03 % of the CU-busy cycles).
-template <int D>
+template <int D, int NQB>
 __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row0, unsigned char *buf, int lane,
-                                             const f32x4 (&o)[D / 16][2], const float (&inv)[2]) {
+                                             const f32x4 (&o)[D / 16][NQB], const float (&inv)[NQB]) {
   constexpr int kChunks = D / 8;                   // 16-byte chunks per row
   const int g = lane >> 4;
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
+  for (int qb = 0; qb < NQB; ++qb) {
     const int r = 16 * qb + (lane & 15);
 #pragma unroll
     for (int db = 0; db < D / 16; ++db)
@@ -496,23 +518,33 @@ __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // lanes read what other lanes of the wave wrote
   const int c = lane % kChunks;
 #pragma unroll
-  for (int i = 0; i < kChunks / 2; ++i) {
+  for (int i = 0; i < kChunks * NQB / 4; ++i) {
     const int r = i * (64 / kChunks) + lane / kChunks;
     const u32x4 v = *reinterpret_cast<const u32x4 *>(buf + r * 2 * D + 16 * (c ^ (r % kChunks)));
     if (row0 + r < p.Nq) *reinterpret_cast<u32x4 *>(p.out + (row0 + r) * p.o_st + h * p.o_sh + 8 * c) = v;
   }
 }
 
-// Log-sum-exp of a wave's 32 finished rows: quarter qb of the wave writes those of query block qb.
-__device__ __forceinline__ void store_lse(const AttnParams &p, int h, int row0, int lane, const float (&ref)[2],
-                                          const float (&lt)[2]) {
-  const int row = row0 + (lane & 31);
-  if (p.lse != nullptr && lane < 32 && row < p.Nq)
+// Log-sum-exp of a wave's 16 * NQB finished rows: quarter qb of the wave writes those of query block qb.
+template <int NQB>
+__device__ __forceinline__ void store_lse(const AttnParams &p, int h, int row0, int lane, const float (&ref)[NQB],
+                                          const float (&lt)[NQB]) {
+  const int row = row0 + lane;
+  if (p.lse != nullptr && lane < 16 * NQB && row < p.Nq)
     p.lse[int64_t(h) * p.Nq + row] = of_block(lane >> 4, ref) * p.lse_unit + __logf(of_block(lane >> 4, lt));
 }
 
-// Sum of the two region masses over the 256 rows of a unit, in a fixed order (deterministic): a
-// butterfly over the 32 rows of every wave, two to a lane, then the 8 waves in order.  The four lanes of a query hold
+// Region masses (sink, sink + window) of a lane's rows `row` and, of a second block, row + 16.
+template <int NQB>
+__device__ __forceinline__ void unit_masses(const AttnParams &p, int row, const float (&lt)[NQB], const float (&l1)[NQB],
+                                            const float (&l2)[NQB], float &mass_a, float &mass_b) {
+  const float inv0 = 1.f / lt[0], inv1 = 1.f / lt[NQB - 1];
+  const bool in0 = row < p.Nq, in1 = NQB == 2 && row + 16 < p.Nq;
+  mass_a = (in0 ? l1[0] * inv0 : 0.f) + (in1 ? l1[NQB - 1] * inv1 : 0.f);
+  mass_b = (in0 ? l2[0] * inv0 : 0.f) + (in1 ? l2[NQB - 1] * inv1 : 0.f);
+}
+// Sum of the two region masses over the 256 (128) rows of a unit, in a fixed order (deterministic): a
+// butterfly over the 32 rows of every wave, two to a lane (16, one to a lane), then the 8 waves in order.  The four lanes of a query hold
 // the same masses, so the butterfly stays inside 16 lanes.
 __device__ __forceinline__ void reduce_masses(const AttnParams &p, float *lds_red, int h, int qt, int tid,
                                               float mass_a, float mass_b) {
@@ -552,11 +584,22 @@ __device__ __forceinline__ void finish_score(const AttnParams &p, int h) {
   store_score(p, h, a, b);
 }
 
+template <int D>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t all_slots(const AttnParams &p) {
+  return __builtin_amdgcn_make_buffer_rsrc(p.slots, 0, int(2u * kNumCU * unsigned(sizeof(float) * Slot<D>::kFloats)), 0x00020000);
+}
+// A system-scope load (sc0 sc1, see store4_through) that the compiler waits for where it is used.
+__device__ __forceinline__ f32x4 slot_load4(const __amdgpu_buffer_rsrc_t &slots, unsigned lane_offset, unsigned offset) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slots, int(lane_offset), int(offset), 1 | 16));
+}
+
+// Code of the unit of sorted head hh whose rows lie in tile qt of kBQ queries, behind those of single flags (see lost_flag()).
+__host__ __device__ __forceinline__ int lost_unit(int hh, int qt) { return 2 * kNumCU + hh * kNumCU + qt; }
 // Wait, for a bounded time, until a flag word holds this launch's value, and put it back: a flag has one reader, and
-// a replay of the launch (same value) has to start clean.  `number` is the flag's number as lost_flag() counts them.
-__device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int number) {
+// a replay of the launch (same value) has to start clean.  `code` is the flag's (or its unit's) as lost_flag() gives it.
+__device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int code) {
   int up = 0;
-  for (int spin = number == p.handoff - 2 ? kSpinLimit : 0; spin < kSpinLimit && !up; ++spin) {
+  for (int spin = code == p.handoff - 2 ? kSpinLimit : 0; spin < kSpinLimit && !up; ++spin) {
     up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
     if (!up) __builtin_amdgcn_s_sleep(16);
   }
@@ -601,8 +644,51 @@ __device__ __forceinline__ void finish_all_scores(const AttnParams &p, float2 *b
   if (tid < p.H) store_score(p, tid, a + poison, b + poison);
 }
 
+template <bool FIRST, class A, class B>
+__device__ __forceinline__ auto &either(A &a, B &b) {
+  if constexpr (FIRST) return a;
+  else return b;
+}
+
+// Where the two groups of waves hold sums of the same queries over different keys: wave w of group 0 finishes the first block of 16 of their 32
+// queries and wave w + 4 of group 1 the second.  Each leaves the other's block in LDS (statistics, then O) and returns what it finds of its own.
 template <int D, bool SCORE_ONLY>
+__device__ __forceinline__ f32x4 exchange_halves(f32x4 *from_group0, f32x4 *from_group1, int group, int wave, int lane, const f32x4 &stats,
+                                                 const f32x4 (&o)[D / 16][2], f32x4 (&theirs)[D / 16][1]) {
+  constexpr int kVectors = SCORE_ONLY ? 1 : 1 + D / 16;
+  static_assert(SCORE_ONLY || 4 * kVectors * 1024 <= kNBuf * TileLayout<D>::KTILE, "four waves' vectors in the K or the V buffers");
+  f32x4 *mine = (group ? from_group1 : from_group0) + (wave & 3) * kVectors * 64 + lane;
+  const f32x4 *other = (group ? from_group0 : from_group1) + (wave & 3) * kVectors * 64 + lane;
+  mine[0] = stats;
+  if (!SCORE_ONLY) {
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) mine[(1 + db) * 64] = group ? o[db][0] : o[db][1];
+  }
+  lds_barrier();
+  const f32x4 st = other[0];
+  if (!SCORE_ONLY) {
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) theirs[db][0] = other[(1 + db) * 64];
+  }
+  lds_barrier();                                   // what follows goes where these lie
+  return st;
+}
+// A whole slot of a workgroup with half the queries, all loads in flight at once (as load_slot_through).
+template <int D>
+__device__ __forceinline__ void load_half_slot(const AttnParams &p, int64_t slot, int tid, f32x4 &st, f32x4 (&v)[D / 16]) {
+  const __amdgpu_buffer_rsrc_t slots = all_slots<D>(p);
+  const unsigned at = unsigned(slot) * unsigned(sizeof(float) * Slot<D, 1>::kFloats);
+  st = slot_load4(slots, unsigned(Slot<D, 1>::stats_reader(tid, 0)) * 16u, at);
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) v[i] = slot_load4(slots, unsigned(tid) * 16u, at + unsigned((Slot<D, 1>::kStats + i * kThreads * 4) * 4));
+  asm volatile("" : "+v"(st));
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) asm volatile("" : "+v"(v[i]));
+}
+
+template <int D, bool SCORE_ONLY, bool HALF>
 __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
+  constexpr int NQB = HALF ? 1 : 2;     // blocks of 16 finished queries per wave
   constexpr int KS = D / 32;            // k-steps of the first product
   constexpr int DB = D / 16;            // 16-row blocks of O^T
   using L = TileLayout<D>;
@@ -626,19 +712,24 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   // known, and one scalar load from each line of the other parameters goes out beside them: the loads that follow
   // where a value is needed then hit the scalar cache (64 queries 16.9 -> 15.9 us, 1170 queries 43.4 -> 41.5,
   // 832x480 1.5 % less).
+  // (By units there is one piece, whose head every wave finds in its own copy of the table, in registers.)
+  HeadRec lane_rec;
+  int lane_cum;
   {
-    const int i = tid < kMaxHeads ? tid : 0;
+    const int i = HALF ? lane : tid < kMaxHeads ? tid : 0;
     const HeadRec rec = p.rec[i];
     const int cum = p.cum[i + 1];
+    lane_rec = rec;
+    lane_cum = cum;
     asm volatile("" ::"s"(p.q), "s"(p.lse_unit), "s"(p.part), "s"(p.slots), "s"(p.q_st), "s"(p.o_sh), "s"(p.n_teams), "s"(p.span_base),
-                 "s"(p.H), "v"(cum), "v"(rec.off), "v"(rec.len), "v"(rec.sink), "v"(rec.head));
-    if (tid < kMaxHeads) {
+                 "s"(p.H), "v"(cum), "v"(rec.off), "v"(rec.len), "v"(rec.sink), "v"(rec.head), "v"(rec.cut));
+    if (!HALF && tid < kMaxHeads) {
       lds_rec[tid] = rec;
       lds_cum[tid + 1] = tid < p.H ? cum : INT32_MAX;
       if (tid == 0) lds_cum[0] = 0;
     }
   }
-  __syncthreads();
+  if (!HALF) __syncthreads();
 
   // the merge kernel, where there is one, counts the merged units of a head: its counters start at zero (this kernel
   // ends before that one begins)
@@ -651,8 +742,8 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   const int wg = n_wg >= kXcd ? (blockIdx.x % kXcd) * ((n_wg + kXcd - 1) / kXcd) + blockIdx.x / kXcd : blockIdx.x;
   const int span = divide_small(wg, p.by_team_size), member = wg - span * p.team_size;
   if (span >= p.n_teams) return;
-  const int64_t span_lo = span_begin(p, span);
-  const int64_t span_hi = span_begin(p, span + 1);
+  const int64_t span_lo = HALF ? 0 : span_begin(p, span);       // by units: one piece, whatever its place
+  const int64_t span_hi = HALF ? 1 : span_begin(p, span + 1);
 
   // per-lane LDS byte addresses of the MFMA A operands (buffer 0); see TileLayout for the row placement
   const int krow = key_of_row(j), vrow = key_of_row(4 * g + (j >> 2));
@@ -672,17 +763,38 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   // completed by the workgroup that has the rest at the start of its span as the LAST thing it does: by
   // then the first part has long been in memory, and the second workgroup finishes the unit itself
   // (hand-over) instead of leaving a partial result to a second kernel.
+  int s_unit = 0;                                  // by units: span of the unit's first piece
 #pragma unroll 1
   for (int64_t pos_end = span_hi; pos_end > span_lo;) {
     // ---- the piece that ends at `pos_end`: group of query tiles, head, first and last tile of this team's share
-    const Piece piece = piece_ending_at(p, ColumnsInLds{lds_cum}, span_lo, pos_end);
+    Piece piece;
+    int h, len_h, sink;
+    int64_t hoff;
+    if constexpr (HALF) {
+      auto of_head = [](int x, int hh) { return __builtin_amdgcn_readlane(x, hh); };
+      const int lane_end = lane < p.H ? int(lane_rec.cut & 0xffffu) : INT32_MAX;
+      const int hh = __popcll(__ballot(span >= lane_end));
+      const int before = max(hh - 1, 0), first_span = hh ? of_head(lane_end, before) : 0;
+      const int n = of_head(lane_cum, hh) - (hh ? of_head(lane_cum, before) : 0), nth = span - first_span;
+      const int shortest = int(unsigned(of_head(int(lane_rec.cut), hh)) >> 16);
+      const int longer = n - (of_head(lane_end, hh) - first_span) * shortest;       // the first so many pieces have a tile more
+      piece = {0, hh, n, nth * shortest + min(nth, longer), 0, 0, 0};
+      piece.t_end = piece.t_begin + shortest + (nth < longer ? 1 : 0);
+      h = of_head(lane_rec.head, hh);
+      len_h = of_head(lane_rec.len, hh);
+      sink = of_head(lane_rec.sink, hh);
+      hoff = int64_t(uint64_t(uint32_t(of_head(int(lane_rec.off), hh))) | uint64_t(uint32_t(of_head(int(lane_rec.off >> 32), hh))) << 32);
+      s_unit = first_span;
+    } else {
+      piece = piece_ending_at(p, ColumnsInLds{lds_cum}, span_lo, pos_end);
+      const HeadRec &rec = lds_rec[piece.hh];
+      h = __builtin_amdgcn_readfirstlane(rec.head);
+      hoff = int64_t(uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(rec.off)))) |
+                     uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(rec.off >> 32)))) << 32);
+      len_h = __builtin_amdgcn_readfirstlane(rec.len);
+      sink = __builtin_amdgcn_readfirstlane(rec.sink);
+    }
     const int grp = piece.grp;
-    const HeadRec &rec = lds_rec[piece.hh];
-    const int h = __builtin_amdgcn_readfirstlane(rec.head);
-    const int64_t hoff = int64_t(uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(rec.off)))) |
-                                 uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(rec.off >> 32)))) << 32);
-    const int len_h = __builtin_amdgcn_readfirstlane(rec.len);
-    const int sink = __builtin_amdgcn_readfirstlane(rec.sink);
     const int nt0 = (sink + kKT - 1) / kKT;
     const int nt1 = (len_h - sink + kKT - 1) / kKT;
     const int nt2 = (p.Nc + kKT - 1) / kKT;
@@ -698,7 +810,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
     const bool take = p.handoff && t_begin > 0 && t_end == n_tiles;
     const int qt = grp * p.team_size + member;     // this workgroup's query tile in this group
     if (qt >= p.n_qtiles) continue;                // the last group may have fewer tiles than the team has members
-    const int q0 = qt * kBQ + wave * 32;
+    const int q0 = HALF ? qt * kHalfBQ + (wave & 3) * 32 : qt * kBQ + wave * 32;
     // a wave whose 32 rows all lie past the last query (tail of the last query tile) moves tiles and keeps
     // the barriers, but computes nothing
     const bool wave_live = q0 < p.Nq;
@@ -780,14 +892,17 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
     a.grp = group;
     a.ldsk = lds_address(lds_k) + wave * L::KGS; a.ldsv = lds_address(lds_v) + wave * L::VGS;
     a.c = p.c; a.lim = kSumLimit;
-    a.ka = k_lane_addr; a.va = v_lane_addr;
+    // where the groups halve the keys, group 1 begins 32 rows into the tile: 32 / NG row positions on
+    const unsigned half = HALF ? group * (kKT / 2 / L::NG * L::ROWB) : 0;
+    a.ka = k_lane_addr + half; a.va = v_lane_addr + half;
     a.offh = lane_vo_hist; a.offc = lane_vo_cur;
-    a.key0 = key_of_row(4 * g);
+    a.key0 = key_of_row(4 * g) + (HALF ? group * (kKT / 2) : 0);
     a.kh = rs_kh; a.kc = rs_kc; a.vh = rs_vh; a.vc = rs_vc;
     f32x4 o[DB][2];
     RowSums sums;
     if (wave_live) {
-      tile_loop<D, SCORE_ONLY, true>(a, qf, o, sums);
+      if constexpr (HALF) half_tile_loop<D, SCORE_ONLY>(a, qf, o, sums);
+      else tile_loop<D, SCORE_ONLY, true>(a, qf, o, sums);
     } else {
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb) {
@@ -805,13 +920,14 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // its piece is in memory; the wait is bounded so that a workgroup that never runs cannot hang the
       // device: the unit's rows, and through them the head's scores, then come out as NaN.  The first wave looks as soon
       // as its own tiles are done: the other waves are up to half an iteration behind it.
-      do --s_first; while (s_first > 0 && span_begin(p, s_first) > unit_lo);
+      if (HALF) s_first = s_unit;
+      else do --s_first; while (s_first > 0 && span_begin(p, s_first) > unit_lo);
       if (wave == 0) {
         // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
         int ok = 1;
         for (int sp = s_first + lane; sp < span; sp += 64) {
           const int number = sp * p.team_size + member;
-          ok &= take_flag(p, p.flags + number, number);
+          ok &= take_flag(p, p.flags + number, HALF ? lost_unit(piece.hh, qt >> 1) : number);
         }
         const int all_ok = __all(ok);              // the whole wave votes: inside `lane == 0` only that lane would
         if (lane == 0) lds_ok = all_ok;
@@ -827,13 +943,38 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
     const int lane_ = tid_ & 63, g_ = lane_ >> 4, j_ = lane_ & 15;
     // ---- piece epilogue.  Region sums of this piece: a region that ended before the piece began contributes
     // nothing, a region the piece ends in (or before) contains everything the piece has summed.
-    float ref_u[2], lt_u[2], l1_u[2], l2_u[2];     // reference; sums of all keys, the sink region, sink + window
+    float ref_w[2], lt_w[2], l1_w[2], l2_w[2];     // reference; sums of all keys, the sink region, sink + window
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-      ref_u[qb] = -sums.neg_ref[qb];
-      lt_u[qb] = quad_sum(sums.l[qb]);
-      l1_u[qb] = nt0 >= t_end ? lt_u[qb] : quad_sum(sums.l_sink[qb]);
-      l2_u[qb] = nt0 + nt1 >= t_end ? lt_u[qb] : quad_sum(sums.l_hist[qb]);
+      ref_w[qb] = -sums.neg_ref[qb];
+      lt_w[qb] = quad_sum(sums.l[qb]);
+      l1_w[qb] = nt0 >= t_end ? lt_w[qb] : quad_sum(sums.l_sink[qb]);
+      l2_w[qb] = nt0 + nt1 >= t_end ? lt_w[qb] : quad_sum(sums.l_hist[qb]);
+    }
+    // What the wave finishes: its two blocks, or, where the groups halve the keys, block `group` of its own and its partner's sums.
+    float ref_h[1], lt_h[1], l1_h[1], l2_h[1];
+    f32x4 out_h[DB][1];
+    auto &ref_u = either<HALF>(ref_h, ref_w), &lt_u = either<HALF>(lt_h, lt_w);
+    auto &l1_u = either<HALF>(l1_h, l1_w), &l2_u = either<HALF>(l2_h, l2_w);
+    auto &out = either<HALF>(out_h, o);
+    if constexpr (HALF) {
+      const f32x4 theirs = exchange_halves<D, SCORE_ONLY>(
+          reinterpret_cast<f32x4 *>(lds_k), reinterpret_cast<f32x4 *>(SCORE_ONLY ? lds_k + 4 * 1024 : lds_v), group, wave, lane_,
+          group ? f32x4{ref_w[0], lt_w[0], l1_w[0], l2_w[0]} : f32x4{ref_w[1], lt_w[1], l1_w[1], l2_w[1]}, o, out);
+      const float mine_ref = group ? ref_w[1] : ref_w[0];
+      const float ref_new = fmaxf(theirs[0], mine_ref);
+      const float w_t = theirs[0] == ref_new ? 1.f : fast_exp2(theirs[0] - ref_new);
+      const float w_m = mine_ref == ref_new ? 1.f : fast_exp2(mine_ref - ref_new);
+      ref_u[0] = ref_new;
+      lt_u[0] = fold(theirs[1], w_t, group ? lt_w[1] : lt_w[0], w_m);
+      l1_u[0] = fold(theirs[2], w_t, group ? l1_w[1] : l1_w[0], w_m);
+      l2_u[0] = fold(theirs[3], w_t, group ? l2_w[1] : l2_w[0], w_m);
+      if (!SCORE_ONLY) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) out[db][0][e] = fold(out[db][0][e], w_t, (group ? o[db][1] : o[db][0])[e], w_m);
+      }
     }
     if (take) {
       const float poison = lds_ok ? 0.f : NAN;
@@ -841,8 +982,9 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // folded into this one's registers, all of it loaded with one wait.  (Front to back the sum so far needs
       // registers of its own, and the loads had to go out four at a time: 1170 queries, 6 pieces to a unit, 54.8 us
       // against 47.1.)
+      auto slot_of_piece = [&](int sp) { return slot_index(p, sp, !HALF && unit_lo > span_begin(p, sp) ? 1 : 0, member); };
       auto slot_of = [&](int sp) {
-        return p.slots + slot_index(p, sp, unit_lo > span_begin(p, sp) ? 1 : 0, member) * Slot<D>::kFloats;
+        return p.slots + slot_of_piece(sp) * Slot<D, NQB>::kFloats;
       };
       auto fold_sums = [&](int qb, const f32x4 &st, float &w_h, float &w_t) {
         const float ref_new = fmaxf(st[0], ref_u[qb]);
@@ -866,51 +1008,55 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
             if (sp - i >= s_first) {
               float w_h, w_t;
               fold_sums(0, st[i][0], w_h, w_t);
-              fold_sums(1, st[i][1], w_h, w_t);
+              if (NQB == 2) fold_sums(NQB - 1, st[i][1], w_h, w_t);
             }
         }
       } else {
 #pragma unroll 1
         for (int sp = span - 1; sp >= s_first; --sp) {
-          f32x4 st[2], v[D / 8];
-          load_slot_through<D / 8>(slot_of(sp), tid_, st, v);
+          f32x4 st[2], v[DB * NQB];
+          if constexpr (HALF) load_half_slot<D>(p, slot_of_piece(sp), tid_, st[0], v);
+          else load_slot_through<D / 8>(slot_of(sp), tid_, st, v);
 #pragma unroll
-          for (int qb = 0; qb < 2; ++qb) {
+          for (int qb = 0; qb < NQB; ++qb) {
             float w_h, w_t;
             fold_sums(qb, st[qb], w_h, w_t);
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) o[db][qb][e] = fold(v[2 * db + qb][e], w_h, o[db][qb][e], w_t);
+              for (int e = 0; e < 4; ++e) out[db][qb][e] = fold(v[NQB * db + qb][e], w_h, out[db][qb][e], w_t);
           }
         }
       }
-      lt_u[0] += poison;                           // every result divides by it: rows, log-sum-exp, score sums
-      lt_u[1] += poison;
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) lt_u[qb] += poison;   // every result divides by it: rows, log-sum-exp, score sums
     }
     if (t_end == n_tiles && (t_begin == 0 || take)) {
       // the unit is complete
-      const float inv[2] = {1.f / lt_u[0], 1.f / lt_u[1]};
+      const int row0 = first_row<NQB>(qt, wave);
       if (!SCORE_ONLY) {
-        store_output<D>(p, h, q0, lds_k + wave * (32 * 2 * D), lane_, o, inv);
-        store_lse(p, h, q0, lane_, ref_u, lt_u);
+        float inv[NQB];
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) inv[qb] = 1.f / lt_u[qb];
+        store_output<D, NQB>(p, h, row0, lds_k + wave * (32 * 2 * D), lane_, out, inv);
+        store_lse(p, h, row0, lane_, ref_u, lt_u);
       }
       if (p.part != nullptr) {
-        const bool in0 = q0 + j_ < p.Nq, in1 = q0 + 16 + j_ < p.Nq;
-        reduce_masses(p, lds_red, h, qt, tid_, (in0 ? l1_u[0] * inv[0] : 0.f) + (in1 ? l1_u[1] * inv[1] : 0.f),
-                      (in0 ? l2_u[0] * inv[0] : 0.f) + (in1 ? l2_u[1] * inv[1] : 0.f));
+        float mass_a, mass_b;
+        unit_masses(p, row0 + j_, lt_u, l1_u, l2_u, mass_a, mass_b);
+        reduce_masses(p, lds_red, h, qt, tid_, mass_a, mass_b);
       }
       else if (!SCORE_ONLY) lds_barrier();         // the next piece's tiles go where the rows were
     } else {
       // a piece that starts at the span's first position uses the span's slot 0, a later one slot 1
-      float *slot = p.slots + slot_index(p, span, piece_pos == span_lo ? 0 : 1, member) * Slot<D>::kFloats;
-      store4_through(Slot<D>::stats(slot, tid_),
+      float *slot = p.slots + slot_index(p, span, piece_pos == span_lo ? 0 : 1, member) * Slot<D, NQB>::kFloats;
+      store4_through(Slot<D, NQB>::stats(slot, tid_),
                      f32x4{of_block(g_, ref_u), of_block(g_, lt_u), of_block(g_, l1_u), of_block(g_, l2_u)});
       if (!SCORE_ONLY) {
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int qb = 0; qb < 2; ++qb) store4_through(Slot<D>::ovec(slot, tid_, 2 * db + qb), o[db][qb]);
+          for (int qb = 0; qb < NQB; ++qb) store4_through(Slot<D, NQB>::ovec(slot, tid_, NQB * db + qb), out[db][qb]);
       }
       if (give) {
         // each thread's stores are in memory when its counter reaches zero; after the barrier all are
@@ -939,8 +1085,9 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 // that completes the last unit of a head (counted per head) sums the head's per-tile masses in tile
 // order; heads that were not cut anywhere get a workgroup of their own for that
 // (blockIdx.x >= (n_teams - 1) * team_size).
-template <int D, bool SCORE_ONLY>
+template <int D, bool SCORE_ONLY, bool HALF>
 __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParams p) {
+  constexpr int NQB = HALF ? 1 : 2;
   __shared__ float lds_red[kWaves * 2];
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, j = lane & 15;
@@ -952,31 +1099,46 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
     return;
   }
   const int k = int(blockIdx.x) / p.team_size + 1, member = int(blockIdx.x) % p.team_size;
-  const int64_t cut = span_begin(p, k);
-  const int grp = int(cut / p.total_cols);
-  const int col = int(cut - int64_t(grp) * p.total_cols);
-  const int hh = head_of_column(p, col);
-  if (col == p.cum[hh]) return;                    // the boundary coincides with the head's first column
-  const int64_t u_lo = int64_t(grp) * p.total_cols + p.cum[hh], u_hi = u_lo + (p.cum[hh + 1] - p.cum[hh]);
-  if (k >= 2 && span_begin(p, k - 1) > u_lo) return;   // an earlier boundary cuts the same unit
-  const int qt = grp * p.team_size + member;
-  if (qt >= p.n_qtiles) return;
-  const int h = p.rec[hh].head;
-  const int s_lo = k - 1;                          // span that holds the unit's first column
-  int s_hi = k;
-  while (span_begin(p, s_hi + 1) < u_hi) ++s_hi;
+  int h, qt, s_lo, s_hi;                           // head, query tile, spans that hold the unit's first and last column
+  int64_t u_lo = 0;
+  if constexpr (HALF) {
+    int hh = 0, first = 0;
+    for (int end = int(p.rec[0].cut & 0xffffu); k >= end; end = int(p.rec[hh].cut & 0xffffu)) { first = end; ++hh; }
+    if (k != first + 1) return;                    // not the first boundary inside a unit
+    h = p.rec[hh].head;
+    qt = member;
+    s_lo = first;
+    s_hi = int(p.rec[hh].cut & 0xffffu) - 1;
+  } else {
+    const int64_t cut = span_begin(p, k);
+    const int grp = int(cut / p.total_cols);
+    const int col = int(cut - int64_t(grp) * p.total_cols);
+    const int hh = head_of_column(p, col);
+    if (col == p.cum[hh]) return;                  // the boundary coincides with the head's first column
+    u_lo = int64_t(grp) * p.total_cols + p.cum[hh];
+    const int64_t u_hi = u_lo + (p.cum[hh + 1] - p.cum[hh]);
+    if (k >= 2 && span_begin(p, k - 1) > u_lo) return;   // an earlier boundary cuts the same unit
+    qt = grp * p.team_size + member;
+    if (qt >= p.n_qtiles) return;
+    h = p.rec[hh].head;
+    s_lo = k - 1;
+    s_hi = k;
+    while (span_begin(p, s_hi + 1) < u_hi) ++s_hi;
+  }
 
-  float M[2] = {-INFINITY, -INFINITY}, Lt[2] = {}, La[2] = {}, Lb[2] = {};
-  f32x4 o[2][2];
+  float M[NQB], Lt[NQB] = {}, La[NQB] = {}, Lb[NQB] = {};
+  f32x4 o[2][NQB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) o[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int qb = 0; qb < NQB; ++qb) {
+    M[qb] = -INFINITY;
+    o[0][qb] = o[1][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 #pragma unroll 1
   for (int sp = s_hi; sp >= s_lo; --sp) {          // last piece first, as in the main kernel
-    const int64_t b = span_begin(p, sp);
-    float *slot = p.slots + slot_index(p, sp, u_lo > b ? 1 : 0, member) * Slot<D>::kFloats;
+    float *slot = p.slots + slot_index(p, sp, !HALF && u_lo > span_begin(p, sp) ? 1 : 0, member) * Slot<D, NQB>::kFloats;
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      const f32x4 st = *reinterpret_cast<const f32x4 *>(Slot<D>::stats(slot, Slot<D>::stats_reader(tid, qb)));
+    for (int qb = 0; qb < NQB; ++qb) {
+      const f32x4 st = *reinterpret_cast<const f32x4 *>(Slot<D, NQB>::stats(slot, Slot<D, NQB>::stats_reader(tid, qb)));
       const float m_new = fmaxf(st[0], M[qb]);
       // a piece of a wave that computes nothing (rows past the last query) has a reference of -inf throughout
       const float w_h = (st[0] == m_new) ? 1.f : fast_exp2(st[0] - m_new);
@@ -988,29 +1150,28 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
       if (!SCORE_ONLY) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const f32x4 v = *reinterpret_cast<const f32x4 *>(Slot<D>::ovec(slot, tid, 2 * (2 * dq + i) + qb));
+          const f32x4 v = *reinterpret_cast<const f32x4 *>(Slot<D, NQB>::ovec(slot, tid, NQB * (2 * dq + i) + qb));
 #pragma unroll
           for (int e = 0; e < 4; ++e) o[i][qb][e] = fold(v[e], w_h, o[i][qb][e], w_t);
         }
       }
     }
   }
-  const float inv[2] = {1.f / Lt[0], 1.f / Lt[1]};
-  const int row0 = qt * kBQ + wave * 32;
-  const bool in[2] = {row0 + j < p.Nq, row0 + 16 + j < p.Nq};
+  const int row0 = first_row<NQB>(qt, wave);
   if (!SCORE_ONLY) {
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
-        if (in[qb])
+        if (row0 + 16 * qb + j < p.Nq)
           *reinterpret_cast<uint2 *>(p.out + (row0 + 16 * qb + j) * p.o_st + h * p.o_sh + 32 * dq + 16 * i +
-                                     4 * (lane >> 4)) = output4(o[i][qb], inv[qb]);
+                                     4 * (lane >> 4)) = output4(o[i][qb], 1.f / Lt[qb]);
     if (dq == 0) store_lse(p, h, row0, lane, M, Lt);
   }
   if (dq == 0 && p.part != nullptr) {
-    reduce_masses(p, lds_red, h, qt, tid, (in[0] ? La[0] * inv[0] : 0.f) + (in[1] ? La[1] * inv[1] : 0.f),
-                  (in[0] ? Lb[0] * inv[0] : 0.f) + (in[1] ? Lb[1] * inv[1] : 0.f));
+    float mass_a, mass_b;
+    unit_masses(p, row0 + j, Lt, La, Lb, mass_a, mass_b);
+    reduce_masses(p, lds_red, h, qt, tid, mass_a, mass_b);
     // the unit's masses are out; whoever completes the head's last merged unit sums the head
     if (tid == 0) {
       __threadfence();
@@ -1137,6 +1298,14 @@ static int cheapest_spans(const AttnParams &p, int n_max) {
   return best;
 }
 
+static void set_spans(AttnParams &p, int n_teams) {
+  p.n_teams = n_teams;
+  p.span_base = p.line_len / p.n_teams;
+  p.span_rem = int32_t(p.line_len % p.n_teams);
+  p.by_n_teams = reciprocal_of(p.n_teams);
+  p.by_team_size = reciprocal_of(p.team_size);
+}
+
 // The decomposition of a launch (A4).  Columns = key tiles of all heads, longest head first.  Query tiles
 // are taken in groups of `team_size`; the line has one position per (group, column) and is cut into
 // equal spans, one per team.  A team has one workgroup per query tile of a group; its members walk the
@@ -1144,7 +1313,7 @@ static int cheapest_spans(const AttnParams &p, int n_max) {
 // possible have a query tile in every group: when the number of query tiles does not divide the
 // number of compute units, smaller teams (more groups) fill the machine better than one team member per
 // query tile.
-static df_status plan(AttnParams &p) {
+static df_status plan(AttnParams &p, float *spans_cost) {
   p.n_qtiles = (p.Nq + kBQ - 1) / kBQ;
   int64_t total = 0;
   for (int hh = 0; hh < p.H; ++hh) {
@@ -1183,16 +1352,84 @@ static df_status plan(AttnParams &p) {
   // sampled ones of 24 heads 21.4 -> 18.9.
   if (p.line_len < int64_t(kMaxCostSpan) * (kNumCU / team))
     p.n_teams = cheapest_spans(p, std::max(1, std::min(kNumCU / team, int(p.line_len) / kMinSmallSpan)));
-  p.span_base = p.line_len / p.n_teams;
-  p.span_rem = int32_t(p.line_len % p.n_teams);
-  p.by_n_teams = reciprocal_of(p.n_teams);
-  p.by_team_size = reciprocal_of(p.team_size);
+  set_spans(p, p.n_teams);
+  if (spans_cost) {
+    int walked = 0;
+    *spans_cost = p.line_len < int64_t(kMaxCostSpan) * (kNumCU / team)
+                      ? (1.f + kSpanCost * float(p.n_teams)) * span_cost(p, p.n_teams, INFINITY, walked) : 0.f;
+  }
   return DF_OK;
+}
+
+// The other way to cut a launch, for workgroups of half the queries: unit by unit, each head's into a number of equal pieces of its own, one
+// workgroup to a piece.  No workgroup then pays for a second piece, nor waits for one that does, and a short unit is left whole; it takes few
+// enough units to go round.  UnitCost is the time in us of a launch that is cut so: `start`, and for its slowest unit `tile` for each tile of its longest
+// piece and, where it is cut, `cut` and for each piece that is handed on `fold`; each workgroup more slows all of it by `crowd`.  With equal
+// spans it is `spans` + `span` times span_cost.  Fitted to 540 launches (1 to 8 000 queries, 2 to 61 heads, up to 300 GFLOP) with all spans that
+// span_cost chooses and up to 18 cuts by units measured on each; they meet the times to 3 to 4 % by units and 6 to 11 % in spans.
+struct UnitCost {
+  float start, tile, cut, fold, crowd, spans, span;
+};
+template <int D, bool SCORE_ONLY>
+constexpr UnitCost kUnitCost = D == 128 ? (SCORE_ONLY ? UnitCost{8.53f, 0.405f, 2.16f, 0.150f, 0.00037f, 2.96f, 0.772f}
+                                                      : UnitCost{10.10f, 0.581f, 3.49f, 0.595f, 0.00047f, 0.31f, 1.490f})
+                                        : (SCORE_ONLY ? UnitCost{7.62f, 0.351f, 2.25f, 0.154f, 0.00029f, 3.65f, 0.629f}
+                                                      : UnitCost{7.58f, 0.420f, 2.40f, 0.429f, 0.00039f, 1.12f, 0.994f});
+constexpr float kUnitsSurelyCheaper = 0.94f;
+constexpr int kMaxUnitWalk = 512;
+// Cuts the launch by units if that costs less than its spans do (`spans_cost` as plan gives it; 0 for spans that are too long to be chosen by
+// their cost, and for this).
+static bool cut_units(AttnParams &p, const UnitCost &cost, float spans_cost) {
+  const int m = (p.Nq + kHalfBQ - 1) / kHalfBQ, most = kNumCU / m;
+  if (spans_cost <= 0.f || most < p.H || p.cum[1] > 0xffff) return false;
+  struct { int n, heads; } runs[kMaxHeads];        // heads of the same length
+  int n_runs = 0;
+  for (int hh = 0; hh < p.H; ++hh) {
+    const int n = p.cum[hh + 1] - p.cum[hh];
+    if (n_runs == 0 || runs[n_runs - 1].n != n) runs[n_runs++] = {n, 0};
+    ++runs[n_runs - 1].heads;
+  }
+  float best = kUnitsSurelyCheaper * (cost.spans + cost.span * spans_cost);
+  int best_longest = 0, walked = 0;
+  // from whole units on: more and more pieces for the longest
+  for (int pieces = 1; pieces <= most && walked < kMaxUnitWalk; pieces += 1 + pieces / 16) {
+    const int longest = (runs[0].n + pieces - 1) / pieces;
+    int spans = 0;
+    float slowest = 0.f;
+    for (int r = 0; r < n_runs; ++r, ++walked) {
+      const int k = (runs[r].n + longest - 1) / longest;
+      spans += k * runs[r].heads;
+      slowest = std::max(slowest, cost.tile * float((runs[r].n + k - 1) / k) + (k > 1 ? cost.cut + cost.fold * float(k - 1) : 0.f));
+    }
+    if (spans > most) break;
+    const float t = (cost.start + slowest) * (1.f + cost.crowd * float(spans * m));
+    if (t < best) { best = t; best_longest = longest; }
+  }
+  if (best_longest == 0) return false;
+  int spans = 0;
+  for (int hh = 0; hh < p.H; ++hh) {
+    const int n = p.cum[hh + 1] - p.cum[hh], k = (n + best_longest - 1) / best_longest;
+    spans += k;
+    p.rec[hh].cut = uint32_t(spans) | uint32_t(n / k) << 16;
+  }
+  p.n_qtiles = p.team_size = m;
+  p.n_groups = 1;
+  p.line_len = p.total_cols;
+  set_spans(p, spans);
+  return true;
 }
 
 // The units of each head that span boundaries cut (the same walk as the merge kernel's), for df_attn_plan and for the
 // two-kernel path; a launch that puts its units together itself has no use for them.
-static void count_cut_units(AttnParams &p) {
+static void count_cut_units(AttnParams &p, bool by_units = false) {
+  if (by_units) {
+    for (int hh = 0, first = 0; hh < p.H; ++hh) {
+      const int end = int(p.rec[hh].cut & 0xffffu);
+      if (end - first > 1) p.n_cut_units[p.rec[hh].head] = int16_t(p.n_qtiles);
+      first = end;
+    }
+    return;
+  }
   for (int k = 1; k < p.n_teams; ++k) {
     const int64_t cut = span_begin(p, k);
     const int grp = int(cut / p.total_cols);
@@ -1238,6 +1475,16 @@ static int lost_flag() {
   const char *e = std::getenv("DF_ATTN_LOST_FLAG");
   return e && *e ? std::clamp(std::atoi(e), -1, 2 * kNumCU) : -1;
 }
+// The same for a launch that is cut by units, which has other workgroups: of a hand-over flag, given the plan of equal spans that it is a
+// number in, the units of the rows and the head that it is raised for; of a flag of the score sums its own or the last.
+static int lost_unit_of(const AttnParams &p, int flag) {
+  if (flag < 0 || flag >= kNumCU) return flag == 2 * kNumCU ? -1 : flag;
+  const int span = flag / p.team_size;
+  if (span >= p.n_teams) return -1;
+  const int64_t end = span_begin(p, span + 1);
+  const Piece c = piece_ending_at(p, ColumnsInParams{p}, span_begin(p, span), end);
+  return c.t_end < c.n_tiles ? lost_unit(c.hh, c.grp * p.team_size + flag % p.team_size) : -1;
+}
 
 // A flag value that neither stale workspace contents nor an earlier launch hold: a counter run through a
 // 64-bit mixer, never zero.
@@ -1250,19 +1497,19 @@ static unsigned long long next_epoch() {
   return z ? z : 1ull;
 }
 
-template <int D, bool SCORE_ONLY>
-static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStream_t st) {
-  if (df_status s = plan(p)) return s;
+template <int D, bool SCORE_ONLY, bool HALF>
+static df_status launch_planned(AttnParams &p, void *workspace, float *score_out, hipStream_t st, int lost) {
+  using S = Slot<D, HALF ? 1 : 2>;
   // One team of several workgroups has no cut unit: it waits for nothing and needs no two compute units at a time.  Its
   // scores are left to the second kernel, so that this stays so: 16.5 against 15.7 us with 2 workgroups, 19.6 against
   // 18.5 with 8.  (A lone workgroup waits for its own flag only.)
   const int n_wg = p.n_teams * p.team_size;
   const bool together = (p.n_teams > 1 || (score_out && n_wg == 1)) && handover_possible(n_wg);
   if (together) {
-    p.handoff = 2 + lost_flag();
+    p.handoff = 2 + (HALF && lost < 2 * kNumCU ? std::min(lost, kNumCU + n_wg - 1) : lost);
     p.epoch = next_epoch();
   } else {
-    count_cut_units(p);
+    count_cut_units(p, HALF);
   }
   char *ws = static_cast<char *>(workspace);
   p.part = score_out ? reinterpret_cast<float *>(ws) : nullptr;
@@ -1273,20 +1520,30 @@ static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStr
   // The last span ends where the line does and hands nothing on, so the slots of its later pieces are free: the
   // flags of the score sums lie there.
   p.done = together && score_out
-               ? reinterpret_cast<unsigned long long *>(p.slots + slot_index(p, p.n_teams - 1, 1, 0) * Slot<D>::kFloats)
+               ? reinterpret_cast<unsigned long long *>(p.slots + slot_index(p, p.n_teams - 1, 1, 0) * S::kFloats)
                : nullptr;
   const int grid = n_wg >= kXcd ? (n_wg + kXcd - 1) / kXcd * kXcd : n_wg;   // XCD-major numbering needs a multiple of 8
-  hipLaunchKernelGGL((df_attn_kernel<D, SCORE_ONLY>), dim3(grid), dim3(kThreads), 0, st, p);
+  hipLaunchKernelGGL((df_attn_kernel<D, SCORE_ONLY, HALF>), dim3(grid), dim3(kThreads), 0, st, p);
   if (df_status s = launch_status()) return s;
   if (together) return DF_OK;
   // second launch: the units that span boundaries cut, and the per-head score sums
   const int n_merge = (p.n_teams - 1) * p.team_size + (score_out ? p.H : 0);
   if (n_merge > 0) {
-    hipLaunchKernelGGL((df_attn_merge_kernel<D, SCORE_ONLY>), dim3(n_merge, SCORE_ONLY ? 1 : D / 32),
+    hipLaunchKernelGGL((df_attn_merge_kernel<D, SCORE_ONLY, HALF>), dim3(n_merge, SCORE_ONLY ? 1 : D / 32),
                        dim3(kThreads), 0, st, p);
     if (df_status s = launch_status()) return s;
   }
   return DF_OK;
+}
+
+template <int D, bool SCORE_ONLY>
+static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStream_t st) {
+  float spans_cost;
+  if (df_status s = plan(p, &spans_cost)) return s;
+  const int lost = lost_flag(), lost_unit = lost_unit_of(p, lost);
+  return cut_units(p, kUnitCost<D, SCORE_ONLY>, spans_cost)
+             ? launch_planned<D, SCORE_ONLY, true>(p, workspace, score_out, st, lost_unit)
+             : launch_planned<D, SCORE_ONLY, false>(p, workspace, score_out, st, lost);
 }
 
 // The head table: longest history first, heads of equal length in their own order.
@@ -1342,12 +1599,11 @@ extern "C" size_t df_attn_workspace_bytes(int32_t H, int32_t d, int32_t Nq) {
   return workspace_bytes(H, d, Nq);
 }
 
-extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32_t *hist_len,
-                                  const int32_t *hist_sink_len, df_attn_plan_info *out) {
-  if (!hist_len || !out) return DF_ERR_NULL;
+// The plan of a launch of which only sizes are given.
+static df_status plan_of_sizes(AttnParams &p, int32_t H, int32_t Nq, int32_t Nc, const int32_t *hist_len, const int32_t *hist_sink_len,
+                               float *spans_cost) {
   if (H <= 0 || Nq <= 0 || Nc <= 0) return DF_ERR_SHAPE;
   if (H > kMaxHeads) return DF_ERR_UNSUPPORTED;
-  AttnParams p{};
   for (int h = 0; h < H; ++h) {
     const int32_t sl = hist_sink_len ? hist_sink_len[h] : 0;
     if (hist_len[h] < 0 || sl < 0 || sl > hist_len[h]) return DF_ERR_RANGE;
@@ -1356,7 +1612,29 @@ extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32
   p.H = H;
   p.Nq = Nq;
   p.Nc = Nc;
-  if (df_status s = plan(p)) return s;
+  return plan(p, spans_cost);
+}
+
+extern "C" df_status df_attn_units(int32_t H, int32_t d, int32_t score_only, int32_t Nq, int32_t Nc, const int32_t *hist_len,
+                                   const int32_t *hist_sink_len, int32_t *pieces) {
+  if (!hist_len || !pieces) return DF_ERR_NULL;
+  if (d != 64 && d != 128) return DF_ERR_UNSUPPORTED;
+  AttnParams p{};
+  float spans_cost;
+  if (df_status s = plan_of_sizes(p, H, Nq, Nc, hist_len, hist_sink_len, &spans_cost)) return s;
+  const UnitCost cost = d == 128 ? (score_only ? kUnitCost<128, true> : kUnitCost<128, false>)
+                                 : (score_only ? kUnitCost<64, true> : kUnitCost<64, false>);
+  const bool by_units = cut_units(p, cost, spans_cost);
+  for (int hh = 0; hh < H; ++hh)
+    pieces[p.rec[hh].head] = by_units ? int32_t(p.rec[hh].cut & 0xffffu) - (hh ? int32_t(p.rec[hh - 1].cut & 0xffffu) : 0) : 0;
+  return DF_OK;
+}
+
+extern "C" df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32_t *hist_len,
+                                  const int32_t *hist_sink_len, df_attn_plan_info *out) {
+  if (!hist_len || !out) return DF_ERR_NULL;
+  AttnParams p{};
+  if (df_status s = plan_of_sizes(p, H, Nq, Nc, hist_len, hist_sink_len, nullptr)) return s;
   out->n_qtiles = p.n_qtiles;
   out->team_size = p.team_size;
   out->n_groups = p.n_groups;

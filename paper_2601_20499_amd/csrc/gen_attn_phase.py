@@ -18,6 +18,10 @@ a tile (2 waves per SIMD) against 1481.
 VALU phase: the loads of a later tile into LDS, then P^T = 2^(c S^T - reference) in bf16 and the sums of the
 unrounded values.
 
+Half a tile (`blocks` = 2 of its 4 blocks of 16 keys; P of 32 keys): in launches of few tiles the two groups of waves have the same
+queries and each takes 32 keys of every tile.  Which is in the addresses of the operands and the key of a lane's
+first row, the statement is the same for both.  An iteration takes 0.9 us there where a whole tile takes 1.6.
+
 Why asm: the LDS reads that feed the matrix core return asynchronously.  Between
 the read and the s_waitcnt that covers it the destination registers must not be touched, and
 the order "wait, MFMA, next read" must not change: nothing can be scheduled into an asm statement, and its registers are
@@ -73,17 +77,17 @@ def layout(D):
     return dict(rowb=rowb, ng=ng, kgs=kgs, vgs=vgs, ktile=ng * kgs, vtile=ng * vgs, k_row=k_row, v_row=v_row)
 
 
-def mfma_phase(D, do_qk, do_pv, koff, voff):
+def mfma_phase(D, do_qk, do_pv, koff, voff, blocks):
     """A operands in issue order (the LDS reads that fetch one, the two MFMAs it feeds), DEPTH of them in flight."""
     L = layout(D)
     mfma = "v_mfma_f32_16x16x32_bf16"
     ops = []
     for ks in range(D // 32 if do_qk else 0):
-        for kb in range(4):
+        for kb in range(blocks):
             acc = [quad(REG_S[kb, qb]) for qb in range(2)]
             ops.append(([f"ds_read_b128 @, %[ka] offset:{koff}+{L['k_row'](16 * kb) + 16 * ks}"],
                         [f"{mfma} {acc[qb]}, @, {quad(REG_Q[ks, qb])}, {acc[qb] if ks else 0}" for qb in range(2)]))
-    for ts in range(2 if do_pv else 0):
+    for ts in range(blocks // 2 if do_pv else 0):
         for db in range(D // 16):
             acc = [quad(REG_O[db, qb]) for qb in range(2)]
             ops.append(([f"ds_read_b64_tr_b16 @, %[va] offset:{voff}+{L['v_row'](32 * ts + r) + 32 * db}" for r in (0, 16)],
@@ -110,10 +114,10 @@ def mfma_phase(D, do_qk, do_pv, koff, voff):
     return lines + (["s_nop 1"] if do_qk and do_pv else ["s_nop 7", "s_nop 1"])
 
 
-def softmax(with_p):
+def softmax(with_p, blocks):
     """P and the row sums a0, a1, in groups of four values (one S register block each), three groups in flight: scale,
     exponential, sum and pack."""
-    groups = [(kb, qb) for kb in range(4) for qb in range(2)]
+    groups = [(kb, qb) for kb in range(blocks) for qb in range(2)]
     tmp = lambda i: STAGE0 + 4 * (i % 4)
     lines = []
     for i in range(len(groups) + 2):
@@ -135,7 +139,7 @@ def softmax(with_p):
     return lines + ["v_add_f32 %[a0], %[a0], %[b0]", "v_add_f32 %[a1], %[a1], %[b1]"]
 
 
-def raise_reference(D, with_o):
+def raise_reference(D, with_o, blocks):
     """Subroutine: the references go up to the row's maximum so far, or to the size of its sum; l, the region sums and O
     follow.  Finite also where every key so far scores minus infinity: P of such a tile is then zero, not the NaN of
     inf - inf, and the first key that scores anything takes the reference up here again.  At a piece's first tile there is
@@ -151,11 +155,11 @@ def raise_reference(D, with_o):
 
     lines = [f"{lab('raise')}:"]
     for qb in range(2):
-        s = [f"v{REG_S[kb, qb] + v}" for kb in range(4) for v in range(4)]
+        s = [f"v{REG_S[kb, qb] + v}" for kb in range(blocks) for v in range(4)]
         m, y, sum_, alpha = t[qb]
         lines.append(f"v_max3_f32 {m}, {s[0]}, {s[1]}, {s[2]}")
-        lines += [f"v_max3_f32 {m}, {m}, {s[i]}, {s[i + 1]}" for i in range(3, 15, 2)]
-        lines.append(f"v_max_f32 {m}, {m}, {s[15]}")
+        lines += [f"v_max3_f32 {m}, {m}, {s[i]}, {s[i + 1]}" for i in range(3, len(s) - 1, 2)]
+        lines.append(f"v_max_f32 {m}, {m}, {s[-1]}")
         lines += over_quad(m, y, "v_max_f32")
         lines.append(f"v_mov_b32 {sum_}, %[l{qb}]")
         lines += over_quad(sum_, y, "v_add_f32")
@@ -232,7 +236,7 @@ def locate(D, which, ahead):
             f"{lab('there')}:"]
 
 
-def special(D, score, live):
+def special(D, score, live, blocks):
     """Subroutine: what is not the same for every tile, from three tiles before a boundary (of a region or the piece) on."""
     lab = lambda name: f".Ldf_{name}_%="
     lines = [f"{lab('special')}:",
@@ -263,7 +267,7 @@ def special(D, score, live):
                   f"s_cmp_ge_i32 %[x0], {KT}",
                   f"s_cbranch_scc1 {lab('whole')}",
                   f"v_mov_b32 v{STAGE0}, 0xff800000"]
-        for kb in range(4):
+        for kb in range(blocks):
             for v in range(4):
                 lines += [f"s_sub_i32 %[x1], %[x0], {16 * kb + KEY_OF_ROW[v]}",
                           "v_cmp_gt_i32 vcc, %[x1], %[key0]",
@@ -296,14 +300,14 @@ def loads(D, score, slot):
     return lines
 
 
-def tile_loop(D, score, live):
+def tile_loop(D, score, live, blocks=4):
     L = layout(D)
     dma = L["ng"] // WAVES * (1 if score else 2)         # loads a wave issues per VALU phase
     prefer_group1 = live and (score or D == 64)          # see the loop over the groups
     lab = lambda name: f".Ldf_{name}_%="
-    lines = [".macro df_mfma koff, voff"] + mfma_phase(D, True, not score, "\\\\koff", "\\\\voff") + [".endm"] if live else []
+    lines = [".macro df_mfma koff, voff"] + mfma_phase(D, True, not score, "\\\\koff", "\\\\voff", blocks) + [".endm"] if live else []
     if live:
-        lines += [".macro df_softmax"] + softmax(not score) + [".endm"]
+        lines += [".macro df_softmax"] + softmax(not score, blocks) + [".endm"]
         for r, init in (("l", 0), ("ls", 0), ("lh", 0), ("nr", "0x7f800000")):
             lines += [f"v_mov_b32 %[{r}{qb}], {init}" for qb in range(2)]
         if not score:
@@ -316,7 +320,7 @@ def tile_loop(D, score, live):
     for which in "k" if score else "kv":                 # ... after it has moved them on like any other
         lines += [f"s_mov_b32 %[st{which}], 0", f"v_mov_b32 %[vo{which}], 0"]
     if live:
-        lines += mfma_phase(D, True, False, "0", "0")
+        lines += mfma_phase(D, True, False, "0", "0", blocks)
     lines += ["s_cmp_lg_u32 %[grp], 0", f"s_cbranch_scc1 {lab('group1' if prefer_group1 else 'g1_0')}"]
     for g in range(2):
         at = lambda name, slot: lab(f"{name}_g{g}_{slot}")
@@ -367,11 +371,11 @@ def tile_loop(D, score, live):
                 lines.append(f"v_add_u32 %[va], {slot * L['vtile']}, %[va]")
             lines.append(f"s_branch {lab('last')}")
     if live:
-        lines += raise_reference(D, not score)
-    lines += special(D, score, live)
+        lines += raise_reference(D, not score, blocks)
+    lines += special(D, score, live, blocks)
     lines.append(f"{lab('last')}:")
     if live and not score:
-        lines += mfma_phase(D, False, True, "0", "0")
+        lines += mfma_phase(D, False, True, "0", "0", blocks)
     lines.append("s_mov_b32 m0, %[m0_was]")
     if prefer_group1:
         lines.append("s_setprio 0")
@@ -384,7 +388,7 @@ def bound(how, regs, var, n):
     return [f'"{how}{{{quad(regs[i, qb])}}}"({var}[{i}][{qb}])' for i in range(n) for qb in range(2)]
 
 
-def function(D, score, live):
+def function(D, score, live, blocks=4):
     L = layout(D)
     outs = ['[t] "+&s"(t)', f'"=&{{s[{RSRC["k"]}:{RSRC["k"] + 3}]}}"(rk)', f'"=&{{s[{RSRC["v"]}:{RSRC["v"] + 3}]}}"(rv)']
     outs += [f'[{n}] "=&s"({n})' for n in ("stk", "sgk", "bd", "ev", "x0", "x1", "x2", "ret", "m0_was", "first")]
@@ -399,16 +403,19 @@ def function(D, score, live):
     if live:
         outs += ['[again] "=&s"(again)'] + [f'[{n}{qb}] "=&v"({n}[{qb}])' for n in "ab" for qb in range(2)]
         outs += [f'[{n}{qb}] "=&v"(r.{f}[{qb}])' for n, f in (("l", "l"), ("ls", "l_sink"), ("lh", "l_hist"), ("nr", "neg_ref")) for qb in range(2)]
-        outs += bound("=&", REG_S, "s", 4)
+        outs += bound("=&", REG_S, "s", blocks)
         ins += [f'[{n}] "s"(a.{n})' for n in ("win", "nc", "c", "lim")] + [f'[{n}] "v"(a.{n})' for n in ("ka", "key0")]
         ins += bound("", REG_Q, "qf", D // 32)
         if not score:
-            outs += ['[va] "+&v"(va)'] + bound("=&", REG_P, "pb", 2) + bound("=&", REG_O, "o", D // 16)
+            outs += ['[va] "+&v"(va)'] + bound("=&", REG_P, "pb", blocks // 2) + bound("=&", REG_O, "o", D // 16)
     ins += [f'"{{s[{RSRC[n]}:{RSRC[n] + 3}]}}"(a.{n})' for n in regions]
     clob = ['"vcc"', '"scc"', '"memory"'] + ([f'"v{r}"' for r in range(STAGE0, 256)] if live else [])
-    body = "\n".join(f'        "{ln}\\n\\t"' for ln in tile_loop(D, score, live))
+    body = "\n".join(f'        "{ln}\\n\\t"' for ln in tile_loop(D, score, live, blocks))
+    name = f"tile_loop<{D}, {'true' if score else 'false'}, {'true' if live else 'false'}>"
+    if blocks == 2:
+        name = f"half_tile_loop<{D}, {'true' if score else 'false'}>"
     return f"""template <>
-__device__ __forceinline__ void tile_loop<{D}, {'true' if score else 'false'}, {'true' if live else 'false'}>(
+__device__ __forceinline__ void {name}(
     const TileLoopArgs &a, const bf16x8 (&qf)[{D // 32}][2], f32x4 (&o)[{D // 16}][2], RowSums &r) {{
   static_assert(TileLayout<{D}>::NG == {L['ng']} && TileLayout<{D}>::KGS == {L['kgs']} && TileLayout<{D}>::VGS == {L['vgs']} &&
                 TileLayout<{D}>::ROWB == {L['rowb']} && kKT == {KT} && kNBuf == {NBUF} && kWaves == {WAVES}, "regenerate df_attn_phase.inc");
@@ -418,8 +425,8 @@ __device__ __forceinline__ void tile_loop<{D}, {'true' if score else 'false'}, {
   unsigned stk, sgk, stv, sgv, vok, vov, tmp, va = a.va;
   unsigned long long ret;
   float a_[2], b_[2];
-  f32x4 s[4][2];
-  bf16x8 pb[2][2];
+  f32x4 s[{blocks}][2];
+  bf16x8 pb[{blocks // 2}][2];
   asm volatile(
 {body}
         : {', '.join(x.replace('(a[', '(a_[').replace('(b[', '(b_[') for x in outs)}
@@ -432,9 +439,12 @@ __device__ __forceinline__ void tile_loop<{D}, {'true' if score else 'false'}, {
 def text():
     head = ("// Generated by gen_attn_phase.py - do not edit; see that script for the schedule and its reasons.\n"
             "// tile_loop<D, SCORE_ONLY, LIVE>: all tiles of a piece; a wave that is not LIVE (its rows lie past the last query)\n"
-            "// moves tiles and keeps the barriers, but computes nothing.\n"
+            "// moves tiles and keeps the barriers, but computes nothing.  half_tile_loop<D, SCORE_ONLY>: the same, live, for 32 keys of\n"
+            "// every tile.\n"
             f"// Staging registers v{STAGE0}..v255, {DEPTH} operands in flight.\n")
-    return head + "\n".join(function(D, score, live) for D in (128, 64) for score in (False, True) for live in (True, False))
+    every = [(D, score, live, 4) for D in (128, 64) for score in (False, True) for live in (True, False)]
+    every += [(D, score, True, 2) for D in (128, 64) for score in (False, True)]
+    return head + "\n".join(function(*x) for x in every)
 
 
 OUT = os.path.join(os.path.dirname(os.path.abspath(__file__)), "df_attn_phase.inc")

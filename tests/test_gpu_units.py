@@ -1,0 +1,69 @@
+"""Launches that are cut unit by unit (workgroups of 128 queries whose two groups of waves halve every tile's keys): ragged and
+single rows, tiles with keys for one half only, units in one piece and in many, every output, both ways to put pieces together."""
+import numpy as np
+import pytest
+import torch
+
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def df():
+    from paper_2601_20499_amd import binding
+    return binding
+
+
+# queries, keys of the chunk, (sink, window) keys of the heads
+CASES = [
+    (1, 1, [(0, 0), (1, 0), (0, 1), (0, 65), (64, 64)]),   # one query, few keys
+    (17, 31, [(1, 0), (0, 32), (33, 63), (0, 0)]),         # regions that end in a tile's first half, at it, behind it
+    (64, 64, [(64, 128), (64, 128), (64, 128), (0, 0)]),   # half of the waves have rows
+    (97, 65, [(0, 900), (64, 1700)]),                      # a wave with one row
+    (128, 33, [(0, 5000)]),                                # one whole query tile, many pieces
+    (129, 128, [(130, 1000), (0, 0), (0, 257)]),           # ... and one row more
+    (300, 97, [(97, 1300), (0, 97), (97, 0), (0, 0), (0, 1300)]),
+    (700, 350, [(0, 2000), (350, 0), (0, 0), (0, 350)] * 3),
+]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Nq,Nc,heads", CASES)
+def test_every_output_by_both_ways(df, monkeypatch, d, Nq, Nc, heads):
+    dev, H, scale = gu.dev(), len(heads), d ** -0.5
+    sinks, lens = [s for s, _ in heads], [s + w for s, w in heads]
+    pieces = df.df_attn_units(d, False, Nq, Nc, lens, sinks)
+    print(f"d {d} Nq {Nq} Nc {Nc} heads {heads}: pieces {pieces}, scores {df.df_attn_units(d, True, Nq, Nc, lens, sinks)}", flush=True)
+    assert min(pieces) >= 1
+    off = [0] + np.cumsum(lens).tolist()
+    g = torch.Generator(device=dev).manual_seed(Nq + d)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
+    kc, vc = rnd(Nc, H, d), rnd(Nc, H, d)
+    q = rnd(H, Nq, d).transpose(0, 1)                      # head-major rows
+    kh, vh = rnd(max(off[-1], 1), d), rnd(max(off[-1], 1), d)
+    ws = torch.full((df.df_attn_workspace_bytes(H, d, Nq),), 0xAB, dtype=torch.uint8, device=dev)
+
+    def launch():
+        out = torch.full((Nq + 1, H, d), float("nan"), dtype=torch.bfloat16, device=dev)     # one row that stays
+        lse, F, F2 = torch.full((H, Nq), float("nan"), device=dev), torch.full((H, 3), float("nan"), device=dev), torch.zeros(H, 3, device=dev)
+        df.df_attn_fwd(q, kc, vc, kh, vh, off, sinks, out[:Nq], scale, lse_out=lse, score_out=F, workspace=ws)
+        df.df_head_score(q, kc, kh, off, sinks, F2, scale, q_sample_stride=1, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.isnan(out[Nq].float()).all()
+        return out[:Nq], lse, F, F2
+
+    first, again = launch(), launch()
+    monkeypatch.setenv("DF_ATTN_HANDOVER", "0")
+    for a, b, c in zip(first, again, launch()):
+        assert torch.equal(a, b) and torch.equal(a, c)
+    out, lse, F, F2 = first
+    for h in range(H):
+        logits = q[:, h].double() @ torch.cat([kh[off[h]:off[h + 1]], kc[:, h]]).double().t() * scale
+        p = torch.softmax(logits, 1)
+        ref = p @ torch.cat([vh[off[h]:off[h + 1]], vc[:, h]]).double()
+        gu.check_out(out[:, h].double().cpu().numpy(), ref.cpu().numpy(), f"head {h}")
+        assert (lse[h] - torch.logsumexp(logits, 1)).abs().max() <= gu.LSE_ABS
+        s, n = sinks[h], lens[h]
+        R = torch.stack([p[:, :s].sum(), p[:, s:n].sum(), p[:, n:].sum()]) / Nq
+        assert (F[h] - R).abs().max() <= gu.F_ABS and (F2[h] - R).abs().max() <= gu.F_ABS
