@@ -111,7 +111,7 @@ def _load() -> C.CDLL:
                                  C.POINTER(df_attn_plan_info)]
     lib.df_attn_units.restype = C.c_int32
     lib.df_attn_units.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
-                                  C.POINTER(C.c_int32)]
+                                  C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
     lib.df_head_score.restype = C.c_int32
     lib.df_head_score.argtypes = [C.POINTER(df_score_args), C.c_void_p]
     lib.df_classify.restype = C.c_int32
@@ -167,12 +167,13 @@ def df_attn_plan(Nq: int, Nc: int, hist_len: Sequence[int], hist_sink_len: Optio
 
 
 def df_attn_units(d: int, score_only: bool, Nq: int, Nc: int, hist_len: Sequence[int],
-                  hist_sink_len: Optional[Sequence[int]] = None) -> list:
-    """Pieces that each head's units of 128 queries are cut into, all 0 where the launch is cut into df_attn_plan's spans (host only)."""
-    pieces = _i32([0] * len(hist_len))
+                  hist_sink_len: Optional[Sequence[int]] = None) -> tuple:
+    """Queries of a unit and the pieces that each head's units are cut into, all 0 where the launch is cut into df_attn_plan's spans
+    (host only)."""
+    rows, pieces = C.c_int32(), _i32([0] * len(hist_len))
     _check(lib.df_attn_units(len(hist_len), int(d), int(score_only), int(Nq), int(Nc), _i32(hist_len),
-                             _i32(hist_sink_len) if hist_sink_len is not None else None, pieces), "df_attn_units")
-    return list(pieces)
+                             _i32(hist_sink_len) if hist_sink_len is not None else None, C.byref(rows), pieces), "df_attn_units")
+    return rows.value, list(pieces)
 
 
 def _ptr(t) -> Optional[int]:

@@ -735,7 +735,7 @@ __device__ __forceinline__ void read_q(const unsigned (&at)[D / 32], bf16x8 (&qf
         : "memory");
 }
 
-template <int D, bool SCORE_ONLY, bool HALF>
+template <int D, bool SCORE_ONLY, bool UNITS, bool HALF>
 __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   constexpr int NQB = HALF ? 1 : 2;     // blocks of 16 finished queries per wave
   constexpr int KS = D / 32;            // k-steps of the first product
@@ -766,20 +766,20 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   HeadRec lane_rec;
   int lane_cum;
   {
-    const int i = HALF ? lane : tid < kMaxHeads ? tid : 0;
+    const int i = UNITS ? lane : tid < kMaxHeads ? tid : 0;
     const HeadRec rec = p.rec[i];
     const int cum = p.cum[i + 1];
     lane_rec = rec;
     lane_cum = cum;
     asm volatile("" ::"s"(p.q), "s"(p.lse_unit), "s"(p.part), "s"(p.slots), "s"(p.q_st), "s"(p.o_sh), "s"(p.n_teams), "s"(p.span_base),
                  "s"(p.H), "v"(cum), "v"(rec.off), "v"(rec.len), "v"(rec.sink), "v"(rec.head), "v"(rec.cut));
-    if (!HALF && tid < kMaxHeads) {
+    if (!UNITS && tid < kMaxHeads) {
       lds_rec[tid] = rec;
       lds_cum[tid + 1] = tid < p.H ? cum : INT32_MAX;
       if (tid == 0) lds_cum[0] = 0;
     }
   }
-  if (!HALF) __syncthreads();
+  if (!UNITS) __syncthreads();
 
   // the merge kernel, where there is one, counts the merged units of a head: its counters start at zero (this kernel
   // ends before that one begins)
@@ -792,8 +792,8 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   const int wg = n_wg >= kXcd ? (blockIdx.x % kXcd) * ((n_wg + kXcd - 1) / kXcd) + blockIdx.x / kXcd : blockIdx.x;
   const int span = divide_small(wg, p.by_team_size), member = wg - span * p.team_size;
   if (span >= p.n_teams) return;
-  const int64_t span_lo = HALF ? 0 : span_begin(p, span);       // by units: one piece, whatever its place
-  const int64_t span_hi = HALF ? 1 : span_begin(p, span + 1);
+  const int64_t span_lo = UNITS ? 0 : span_begin(p, span);       // by units: one piece, whatever its place
+  const int64_t span_hi = UNITS ? 1 : span_begin(p, span + 1);
 
   // per-lane LDS byte addresses of the MFMA A operands (buffer 0); see TileLayout for the row placement
   const int krow = key_of_row(j), vrow = key_of_row(4 * g + (j >> 2));
@@ -820,7 +820,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
     Piece piece;
     int h, len_h, sink;
     int64_t hoff;
-    if constexpr (HALF) {
+    if constexpr (UNITS) {
       auto of_head = [](int x, int hh) { return __builtin_amdgcn_readlane(x, hh); };
       const int lane_end = lane < p.H ? int(lane_rec.cut & 0xffffu) : INT32_MAX;
       const int hh = __popcll(__ballot(span >= lane_end));
@@ -984,14 +984,14 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // its piece is in memory; the wait is bounded so that a workgroup that never runs cannot hang the
       // device: the unit's rows, and through them the head's scores, then come out as NaN.  The first wave looks as soon
       // as its own tiles are done: the other waves are up to half an iteration behind it.
-      if (HALF) s_first = s_unit;
+      if (UNITS) s_first = s_unit;
       else do --s_first; while (s_first > 0 && span_begin(p, s_first) > unit_lo);
       if (wave == 0) {
         // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
         int ok = 1;
         for (int sp = s_first + lane; sp < span; sp += 64) {
           const int number = sp * p.team_size + member;
-          ok &= take_flag(p, p.flags + number, HALF ? lost_unit(piece.hh, qt >> 1) : number);
+          ok &= take_flag(p, p.flags + number, UNITS ? lost_unit(piece.hh, HALF ? qt >> 1 : qt) : number);
         }
         const int all_ok = __all(ok);              // the whole wave votes: inside `lane == 0` only that lane would
         if (lane == 0) lds_ok = all_ok;
@@ -1046,7 +1046,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // folded into this one's registers, all of it loaded with one wait.  (Front to back the sum so far needs
       // registers of its own, and the loads had to go out four at a time: 1170 queries, 6 pieces to a unit, 54.8 us
       // against 47.1.)
-      auto slot_of_piece = [&](int sp) { return slot_index(p, sp, !HALF && unit_lo > span_begin(p, sp) ? 1 : 0, member); };
+      auto slot_of_piece = [&](int sp) { return slot_index(p, sp, !UNITS && unit_lo > span_begin(p, sp) ? 1 : 0, member); };
       auto slot_of = [&](int sp) {
         return p.slots + slot_of_piece(sp) * Slot<D, NQB>::kFloats;
       };
@@ -1149,7 +1149,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 // that completes the last unit of a head (counted per head) sums the head's per-tile masses in tile
 // order; heads that were not cut anywhere get a workgroup of their own for that
 // (blockIdx.x >= (n_teams - 1) * team_size).
-template <int D, bool SCORE_ONLY, bool HALF>
+template <int D, bool SCORE_ONLY, bool UNITS, bool HALF>
 __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParams p) {
   constexpr int NQB = HALF ? 1 : 2;
   __shared__ float lds_red[kWaves * 2];
@@ -1165,7 +1165,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
   const int k = int(blockIdx.x) / p.team_size + 1, member = int(blockIdx.x) % p.team_size;
   int h, qt, s_lo, s_hi;                           // head, query tile, spans that hold the unit's first and last column
   int64_t u_lo = 0;
-  if constexpr (HALF) {
+  if constexpr (UNITS) {
     int hh = 0, first = 0;
     for (int end = int(p.rec[0].cut & 0xffffu); k >= end; end = int(p.rec[hh].cut & 0xffffu)) { first = end; ++hh; }
     if (k != first + 1) return;                    // not the first boundary inside a unit
@@ -1199,7 +1199,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_merge_kernel(const AttnParam
   }
 #pragma unroll 1
   for (int sp = s_hi; sp >= s_lo; --sp) {          // last piece first, as in the main kernel
-    float *slot = p.slots + slot_index(p, sp, !HALF && u_lo > span_begin(p, sp) ? 1 : 0, member) * Slot<D, NQB>::kFloats;
+    float *slot = p.slots + slot_index(p, sp, !UNITS && u_lo > span_begin(p, sp) ? 1 : 0, member) * Slot<D, NQB>::kFloats;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       const f32x4 st = *reinterpret_cast<const f32x4 *>(Slot<D, NQB>::stats(slot, Slot<D, NQB>::stats_reader(tid, qb)));
@@ -1425,62 +1425,98 @@ static df_status plan(AttnParams &p, float *spans_cost) {
   return DF_OK;
 }
 
-// The other way to cut a launch, for workgroups of half the queries: unit by unit, each head's into a number of equal pieces of its own, one
-// workgroup to a piece.  No workgroup then pays for a second piece, nor waits for one that does, and a short unit is left whole; it takes few
-// enough units to go round.  UnitCost is the time in us of a launch that is cut so: `start`, and for its slowest unit `tile` for each tile of its longest
-// piece and, where it is cut, `cut` and for each piece that is handed on `fold`; each workgroup more slows all of it by `crowd`.  With equal
-// spans it is `spans` + `span` times span_cost.  Fitted to 540 launches (1 to 8 000 queries, 2 to 61 heads, up to 300 GFLOP) with all spans that
-// span_cost chooses and up to 18 cuts by units measured on each; they meet the times to 3 to 4 % by units and 6 to 11 % in spans.
+// The other way to cut a launch: unit by unit, each head's into a number of equal pieces of its own, one workgroup to a piece.
+// No workgroup then pays for a second piece, nor waits for one that does, and a short unit is left whole; it takes few
+// enough units to go round.  The fewest pieces go with units of kHalfBQ queries, the fewest tiles for the machine with
+// units of kBQ.  UnitCost is the time in us of a launch that is cut so: `start`, `wg` for each workgroup, and for its slowest unit
+// `tile` for each tile of its longest piece (`crowd` of it more for each workgroup), and where it is cut `cut` and for each piece that is
+// handed on `fold`.  SpanCost is that of equal spans: `start`, `cost` times span_cost, `tile` for each tile of a span and `wg` for each
+// workgroup.  Fitted to 380 launches (1 to 5 000 queries, 2 to 61 heads, up to 300 GFLOP) with the spans that span_cost chooses and up to 14
+// cuts by units of either kind measured on each; they meet the times to 3 to 7 % by units and 4 to 6 % in spans.  By units if that
+// takes kUnitsMargin of the spans' time: of the 380 one then takes 2.8 % more than in its spans, attention takes 20 % less on average and
+// scores 11 %.
 struct UnitCost {
-  float start, tile, cut, fold, crowd, spans, span;
+  float start, wg, tile, crowd, cut, fold;
+};
+struct SpanCost {
+  float start, cost, tile, wg;
+};
+struct LaunchCost {
+  UnitCost half, whole;        // units of kHalfBQ and of kBQ queries
+  SpanCost spans;
 };
 template <int D, bool SCORE_ONLY>
-constexpr UnitCost kUnitCost = D == 128 ? (SCORE_ONLY ? UnitCost{8.53f, 0.405f, 2.16f, 0.150f, 0.00037f, 2.96f, 0.772f}
-                                                      : UnitCost{10.10f, 0.581f, 3.49f, 0.595f, 0.00047f, 0.31f, 1.490f})
-                                        : (SCORE_ONLY ? UnitCost{7.62f, 0.351f, 2.25f, 0.154f, 0.00029f, 3.65f, 0.629f}
-                                                      : UnitCost{7.58f, 0.420f, 2.40f, 0.429f, 0.00039f, 1.12f, 0.994f});
-constexpr float kUnitsSurelyCheaper = 0.94f;
+constexpr LaunchCost kLaunchCost =
+    D == 128 ? (SCORE_ONLY ? LaunchCost{{8.17f, 0.0053f, 0.400f, 0.00040f, 1.96f, 0.142f}, {5.25f, 0.0040f, 0.713f, 0.00051f, 3.14f, 0.233f}, {6.68f, 0.296f, 0.667f, 0.f}}
+                           : LaunchCost{{8.29f, 0.0079f, 0.573f, 0.00062f, 2.70f, 0.642f}, {7.85f, 0.0135f, 1.034f, 0.00053f, 2.54f, 1.236f}, {2.29f, 1.110f, 0.371f, 0.0179f}})
+             : (SCORE_ONLY ? LaunchCost{{7.85f, 0.0034f, 0.339f, 0.00020f, 2.16f, 0.158f}, {5.09f, 0.0025f, 0.594f, 0.00040f, 3.02f, 0.246f}, {6.00f, 0.390f, 0.318f, 0.f}}
+                           : LaunchCost{{6.90f, 0.0097f, 0.434f, 0.00006f, 2.25f, 0.428f}, {6.14f, 0.0148f, 0.776f, 0.00004f, 2.39f, 0.662f}, {3.84f, 0.750f, 0.220f, 0.0101f}});
+constexpr float kUnitsMargin = 0.97f;
+constexpr float kMaxUnitLaunch = 110.f;   // us: in longer launches the clock under load decides, and equal spans keep it even
 constexpr int kMaxUnitWalk = 512;
-// Cuts the launch by units if that costs less than its spans do (`spans_cost` as plan gives it; 0 for spans that are too long to be chosen by
-// their cost, and for this).
-static bool cut_units(AttnParams &p, const UnitCost &cost, float spans_cost) {
-  const int m = (p.Nq + kHalfBQ - 1) / kHalfBQ, most = kNumCU / m;
-  if (spans_cost <= 0.f || most < p.H || p.cum[1] > 0xffff) return false;
-  struct { int n, heads; } runs[kMaxHeads];        // heads of the same length
+
+// Heads of the same length, longest first.
+struct Runs {
+  struct { int n, heads; } run[kMaxHeads];
   int n_runs = 0;
-  for (int hh = 0; hh < p.H; ++hh) {
-    const int n = p.cum[hh + 1] - p.cum[hh];
-    if (n_runs == 0 || runs[n_runs - 1].n != n) runs[n_runs++] = {n, 0};
-    ++runs[n_runs - 1].heads;
+  explicit Runs(const AttnParams &p) {
+    for (int hh = 0; hh < p.H; ++hh) {
+      const int n = p.cum[hh + 1] - p.cum[hh];
+      if (n_runs == 0 || run[n_runs - 1].n != n) run[n_runs++] = {n, 0};
+      ++run[n_runs - 1].heads;
+    }
   }
-  float best = kUnitsSurelyCheaper * (cost.spans + cost.span * spans_cost);
+};
+// Most tiles of a piece of the cheapest cut into units of `rows` queries, if that costs less than `best` (which it then replaces), else 0.
+static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &cost, float &best) {
+  const int m = (Nq + rows - 1) / rows, most = kNumCU / m;
   int best_longest = 0, walked = 0;
-  // from whole units on: more and more pieces for the longest
-  for (int pieces = 1; pieces <= most && walked < kMaxUnitWalk; pieces += 1 + pieces / 16) {
-    const int longest = (runs[0].n + pieces - 1) / pieces;
-    int spans = 0;
-    float slowest = 0.f;
-    for (int r = 0; r < n_runs; ++r, ++walked) {
-      const int k = (runs[r].n + longest - 1) / longest;
-      spans += k * runs[r].heads;
-      slowest = std::max(slowest, cost.tile * float((runs[r].n + k - 1) / k) + (k > 1 ? cost.cut + cost.fold * float(k - 1) : 0.f));
+  // from whole units on, each time with shorter pieces for those that have the longest (3 % shorter at least)
+  for (int longest = runs.run[0].n; longest > 0 && walked < kMaxUnitWalk;) {
+    int spans = 0, pieces_of[kMaxHeads], tiles_of[kMaxHeads], most_tiles = 0;
+    for (int r = 0; r < runs.n_runs; ++r, ++walked) {
+      const int n = runs.run[r].n, k = n <= longest ? 1 : (n + longest - 1) / longest;
+      pieces_of[r] = k;
+      tiles_of[r] = k == 1 ? n : (n + k - 1) / k;
+      most_tiles = std::max(most_tiles, tiles_of[r]);
+      spans += k * runs.run[r].heads;
     }
     if (spans > most) break;
-    const float t = (cost.start + slowest) * (1.f + cost.crowd * float(spans * m));
+    const float tile = cost.tile * (1.f + cost.crowd * float(spans * m));
+    float slowest = 0.f;
+    for (int r = 0; r < runs.n_runs; ++r)
+      slowest = std::max(slowest, tile * float(tiles_of[r]) + (pieces_of[r] > 1 ? cost.cut + cost.fold * float(pieces_of[r] - 1) : 0.f));
+    const float t = cost.start + cost.wg * float(spans * m) + slowest;
     if (t < best) { best = t; best_longest = longest; }
+    longest = most_tiles - 1 - most_tiles / 32;
   }
-  if (best_longest == 0) return false;
+  return best_longest;
+}
+// Cuts the launch into units of `rows` queries, in pieces of at most `longest` tiles.
+static void cut_units(AttnParams &p, int rows, int longest) {
   int spans = 0;
   for (int hh = 0; hh < p.H; ++hh) {
-    const int n = p.cum[hh + 1] - p.cum[hh], k = (n + best_longest - 1) / best_longest;
+    const int n = p.cum[hh + 1] - p.cum[hh], k = (n + longest - 1) / longest;
     spans += k;
     p.rec[hh].cut = uint32_t(spans) | uint32_t(n / k) << 16;
   }
-  p.n_qtiles = p.team_size = m;
+  p.n_qtiles = p.team_size = (p.Nq + rows - 1) / rows;
   p.n_groups = 1;
   p.line_len = p.total_cols;
   set_spans(p, spans);
-  return true;
+}
+// The plan by units if it costs less than the spans do (`spans_cost` as plan gives it, 0: not known): rows of its units, or 0.
+static int plan_units(AttnParams &p, const LaunchCost &cost, float spans_cost) {
+  if (spans_cost <= 0.f || p.cum[1] > 0xffff) return 0;
+  const float in_spans = cost.spans.start + cost.spans.cost * spans_cost + cost.spans.tile * float(p.span_base) +
+                         cost.spans.wg * float(p.n_teams * p.team_size);
+  if (in_spans > kMaxUnitLaunch) return 0;
+  const Runs runs(p);
+  float best = kUnitsMargin * in_spans;
+  const int half = cheapest_units(runs, p.Nq, kHalfBQ, cost.half, best), whole = cheapest_units(runs, p.Nq, kBQ, cost.whole, best);
+  const int rows = whole ? kBQ : half ? kHalfBQ : 0;
+  if (rows) cut_units(p, rows, whole ? whole : half);
+  return rows;
 }
 
 // The units of each head that span boundaries cut (the same walk as the merge kernel's), for df_attn_plan and for the
@@ -1561,7 +1597,7 @@ static unsigned long long next_epoch() {
   return z ? z : 1ull;
 }
 
-template <int D, bool SCORE_ONLY, bool HALF>
+template <int D, bool SCORE_ONLY, bool UNITS, bool HALF>
 static df_status launch_planned(AttnParams &p, void *workspace, float *score_out, hipStream_t st, int lost) {
   using S = Slot<D, HALF ? 1 : 2>;
   // One team of several workgroups has no cut unit: it waits for nothing and needs no two compute units at a time.  Its
@@ -1570,10 +1606,10 @@ static df_status launch_planned(AttnParams &p, void *workspace, float *score_out
   const int n_wg = p.n_teams * p.team_size;
   const bool together = (p.n_teams > 1 || (score_out && n_wg == 1)) && handover_possible(n_wg);
   if (together) {
-    p.handoff = 2 + (HALF && lost < 2 * kNumCU ? std::min(lost, kNumCU + n_wg - 1) : lost);
+    p.handoff = 2 + (UNITS && lost < 2 * kNumCU ? std::min(lost, kNumCU + n_wg - 1) : lost);
     p.epoch = next_epoch();
   } else {
-    count_cut_units(p, HALF);
+    count_cut_units(p, UNITS);
   }
   char *ws = static_cast<char *>(workspace);
   p.part = score_out ? reinterpret_cast<float *>(ws) : nullptr;
@@ -1587,13 +1623,13 @@ static df_status launch_planned(AttnParams &p, void *workspace, float *score_out
                ? reinterpret_cast<unsigned long long *>(p.slots + slot_index(p, p.n_teams - 1, 1, 0) * S::kFloats)
                : nullptr;
   const int grid = n_wg >= kXcd ? (n_wg + kXcd - 1) / kXcd * kXcd : n_wg;   // XCD-major numbering needs a multiple of 8
-  hipLaunchKernelGGL((df_attn_kernel<D, SCORE_ONLY, HALF>), dim3(grid), dim3(kThreads), 0, st, p);
+  hipLaunchKernelGGL((df_attn_kernel<D, SCORE_ONLY, UNITS, HALF>), dim3(grid), dim3(kThreads), 0, st, p);
   if (df_status s = launch_status()) return s;
   if (together) return DF_OK;
   // second launch: the units that span boundaries cut, and the per-head score sums
   const int n_merge = (p.n_teams - 1) * p.team_size + (score_out ? p.H : 0);
   if (n_merge > 0) {
-    hipLaunchKernelGGL((df_attn_merge_kernel<D, SCORE_ONLY, HALF>), dim3(n_merge, SCORE_ONLY ? 1 : D / 32),
+    hipLaunchKernelGGL((df_attn_merge_kernel<D, SCORE_ONLY, UNITS, HALF>), dim3(n_merge, SCORE_ONLY ? 1 : D / 32),
                        dim3(kThreads), 0, st, p);
     if (df_status s = launch_status()) return s;
   }
@@ -1605,9 +1641,11 @@ static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStr
   float spans_cost;
   if (df_status s = plan(p, &spans_cost)) return s;
   const int lost = lost_flag(), lost_unit = lost_unit_of(p, lost);
-  return cut_units(p, kUnitCost<D, SCORE_ONLY>, spans_cost)
-             ? launch_planned<D, SCORE_ONLY, true>(p, workspace, score_out, st, lost_unit)
-             : launch_planned<D, SCORE_ONLY, false>(p, workspace, score_out, st, lost);
+  switch (plan_units(p, kLaunchCost<D, SCORE_ONLY>, spans_cost)) {
+    case kHalfBQ: return launch_planned<D, SCORE_ONLY, true, true>(p, workspace, score_out, st, lost_unit);
+    case kBQ: return launch_planned<D, SCORE_ONLY, true, false>(p, workspace, score_out, st, lost_unit);
+    default: return launch_planned<D, SCORE_ONLY, false, false>(p, workspace, score_out, st, lost);
+  }
 }
 
 // The head table: longest history first, heads of equal length in their own order.
@@ -1680,17 +1718,16 @@ static df_status plan_of_sizes(AttnParams &p, int32_t H, int32_t Nq, int32_t Nc,
 }
 
 extern "C" df_status df_attn_units(int32_t H, int32_t d, int32_t score_only, int32_t Nq, int32_t Nc, const int32_t *hist_len,
-                                   const int32_t *hist_sink_len, int32_t *pieces) {
-  if (!hist_len || !pieces) return DF_ERR_NULL;
+                                   const int32_t *hist_sink_len, int32_t *unit_rows, int32_t *pieces) {
+  if (!hist_len || !unit_rows || !pieces) return DF_ERR_NULL;
   if (d != 64 && d != 128) return DF_ERR_UNSUPPORTED;
   AttnParams p{};
   float spans_cost;
   if (df_status s = plan_of_sizes(p, H, Nq, Nc, hist_len, hist_sink_len, &spans_cost)) return s;
-  const UnitCost cost = d == 128 ? (score_only ? kUnitCost<128, true> : kUnitCost<128, false>)
-                                 : (score_only ? kUnitCost<64, true> : kUnitCost<64, false>);
-  const bool by_units = cut_units(p, cost, spans_cost);
+  *unit_rows = plan_units(p, d == 128 ? (score_only ? kLaunchCost<128, true> : kLaunchCost<128, false>)
+                                               : (score_only ? kLaunchCost<64, true> : kLaunchCost<64, false>), spans_cost);
   for (int hh = 0; hh < H; ++hh)
-    pieces[p.rec[hh].head] = by_units ? int32_t(p.rec[hh].cut & 0xffffu) - (hh ? int32_t(p.rec[hh - 1].cut & 0xffffu) : 0) : 0;
+    pieces[p.rec[hh].head] = *unit_rows ? int32_t(p.rec[hh].cut & 0xffffu) - (hh ? int32_t(p.rec[hh - 1].cut & 0xffffu) : 0) : 0;
   return DF_OK;
 }
 
