@@ -1429,14 +1429,15 @@ static df_status plan(AttnParams &p, float *spans_cost) {
 // No workgroup then pays for a second piece, nor waits for one that does, and a short unit is left whole; it takes few
 // enough units to go round.  The fewest pieces go with units of kHalfBQ queries, the fewest tiles for the machine with
 // units of kBQ.  UnitCost is the time in us of a launch that is cut so: `start`, `wg` for each workgroup, and for its slowest unit
-// `tile` for each tile of its longest piece (`crowd` of it more for each workgroup), and where it is cut `cut` and for each piece that is
+// `tile` for each tile of its longest piece (`crowd` of it more for each workgroup, `few` of it where half of the waves have no rows and the others
+// a SIMD to themselves, or, of units of kHalfBQ, half of its waves), and where it is cut `cut` and for each piece that is
 // handed on `fold`.  SpanCost is that of equal spans: `start`, `cost` times span_cost, `tile` for each tile of a span and `wg` for each
-// workgroup.  Fitted to 380 launches (1 to 5 000 queries, 2 to 61 heads, up to 300 GFLOP) with the spans that span_cost chooses and up to 14
-// cuts by units of either kind measured on each; they meet the times to 3 to 7 % by units and 4 to 6 % in spans.  By units if that
-// takes kUnitsMargin of the spans' time: of the 380 one then takes 2.8 % more than in its spans, attention takes 20 % less on average and
-// scores 11 %.
+// workgroup.  Fitted to 720 launches (1 to 5 000 queries, 2 to 61 heads, up to 300 GFLOP) with the spans that span_cost chooses and up to 14
+// cuts by units of either kind measured on each; they meet the times to 2 to 4 % by units and 4 to 6 % in spans.  By units if that
+// takes units_margin of the spans' time: of the 720, attention then takes 16 % less time on average and scores 9 %, from 45 % less to, in five of
+// them, 3 to 6 % more.
 struct UnitCost {
-  float start, wg, tile, crowd, cut, fold;
+  float start, wg, tile, crowd, few, cut, fold;
 };
 struct SpanCost {
   float start, cost, tile, wg;
@@ -1447,12 +1448,14 @@ struct LaunchCost {
 };
 template <int D, bool SCORE_ONLY>
 constexpr LaunchCost kLaunchCost =
-    D == 128 ? (SCORE_ONLY ? LaunchCost{{8.17f, 0.0053f, 0.400f, 0.00040f, 1.96f, 0.142f}, {5.25f, 0.0040f, 0.713f, 0.00051f, 3.14f, 0.233f}, {6.68f, 0.296f, 0.667f, 0.f}}
-                           : LaunchCost{{8.29f, 0.0079f, 0.573f, 0.00062f, 2.70f, 0.642f}, {7.85f, 0.0135f, 1.034f, 0.00053f, 2.54f, 1.236f}, {2.29f, 1.110f, 0.371f, 0.0179f}})
-             : (SCORE_ONLY ? LaunchCost{{7.85f, 0.0034f, 0.339f, 0.00020f, 2.16f, 0.158f}, {5.09f, 0.0025f, 0.594f, 0.00040f, 3.02f, 0.246f}, {6.00f, 0.390f, 0.318f, 0.f}}
-                           : LaunchCost{{6.90f, 0.0097f, 0.434f, 0.00006f, 2.25f, 0.428f}, {6.14f, 0.0148f, 0.776f, 0.00004f, 2.39f, 0.662f}, {3.84f, 0.750f, 0.220f, 0.0101f}});
-constexpr float kUnitsMargin = 0.97f;
-constexpr float kMaxUnitLaunch = 110.f;   // us: in longer launches the clock under load decides, and equal spans keep it even
+    D == 128 ? (SCORE_ONLY ? LaunchCost{{8.35f, 0.0062f, 0.397f, 0.00038f, 0.95f, 1.81f, 0.136f}, {7.93f, 0.0063f, 0.715f, 0.00032f, 0.77f, 1.14f, 0.208f}, {6.78f, 0.316f, 0.610f, 0.f}}
+                           : LaunchCost{{8.48f, 0.0084f, 0.560f, 0.00073f, 0.90f, 2.57f, 0.639f}, {8.26f, 0.0147f, 1.025f, 0.00051f, 0.72f, 2.22f, 1.238f}, {2.30f, 1.118f, 0.375f, 0.0163f}})
+             : (SCORE_ONLY ? LaunchCost{{8.39f, 0.0041f, 0.335f, 0.00013f, 0.88f, 1.80f, 0.145f}, {7.38f, 0.0033f, 0.608f, 0.00013f, 0.73f, 1.69f, 0.214f}, {6.28f, 0.380f, 0.317f, 0.f}}
+                           : LaunchCost{{7.02f, 0.0101f, 0.428f, 0.00010f, 0.90f, 2.15f, 0.427f}, {6.56f, 0.0143f, 0.770f, 0.00005f, 0.72f, 2.14f, 0.662f}, {4.60f, 0.696f, 0.269f, 0.0103f}});
+// Share of the spans' time `us` that units may take: less of longer launches, in which the clock under load and not these sums decides
+// and equal spans keep all compute units busy to the end; none from kMaxUnitLaunch on.
+constexpr float kMaxUnitLaunch = 110.f;
+static float units_margin(float us) { return us > kMaxUnitLaunch ? 0.f : 0.97f - 0.002f * std::max(0.f, us - 50.f); }
 constexpr int kMaxUnitWalk = 512;
 
 // Heads of the same length, longest first.
@@ -1482,7 +1485,7 @@ static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &co
       spans += k * runs.run[r].heads;
     }
     if (spans > most) break;
-    const float tile = cost.tile * (1.f + cost.crowd * float(spans * m));
+    const float tile = cost.tile * (1.f + cost.crowd * float(spans * m)) * (2 * Nq <= rows ? cost.few : 1.f);
     float slowest = 0.f;
     for (int r = 0; r < runs.n_runs; ++r)
       slowest = std::max(slowest, tile * float(tiles_of[r]) + (pieces_of[r] > 1 ? cost.cut + cost.fold * float(pieces_of[r] - 1) : 0.f));
@@ -1510,9 +1513,9 @@ static int plan_units(AttnParams &p, const LaunchCost &cost, float spans_cost) {
   if (spans_cost <= 0.f || p.cum[1] > 0xffff) return 0;
   const float in_spans = cost.spans.start + cost.spans.cost * spans_cost + cost.spans.tile * float(p.span_base) +
                          cost.spans.wg * float(p.n_teams * p.team_size);
-  if (in_spans > kMaxUnitLaunch) return 0;
+  float best = units_margin(in_spans) * in_spans;
+  if (best <= 0.f) return 0;
   const Runs runs(p);
-  float best = kUnitsMargin * in_spans;
   const int half = cheapest_units(runs, p.Nq, kHalfBQ, cost.half, best), whole = cheapest_units(runs, p.Nq, kBQ, cost.whole, best);
   const int rows = whole ? kBQ : half ? kHalfBQ : 0;
   if (rows) cut_units(p, rows, whole ? whole : half);
