@@ -171,7 +171,7 @@ df_status df_attn_fwd_static(const df_attn_args *args, void *stream);
  * walked in groups of team_size; the line of (group, column) positions is cut into n_teams equal spans;
  * team t's member m handles query tile group*team_size + m over span t.
  * hist_len[h] = history keys of head h (>= 0), hist_sink_len[h] = how many of them are the sink region
- * (NULL = 0).  Errors: DF_ERR_NULL, DF_ERR_SHAPE (H, Nq, Nc <= 0), DF_ERR_UNSUPPORTED (H > DF_MAX_HEADS),
+ * (NULL = 0, and as a call without score_out has it: its regions are one).  Errors: DF_ERR_NULL, DF_ERR_SHAPE (H, Nq, Nc <= 0), DF_ERR_UNSUPPORTED (H > DF_MAX_HEADS),
  * DF_ERR_RANGE (sink > len, or more than 2^30 key tiles). */
 typedef struct df_attn_plan_info {
   int32_t n_qtiles;    /* ceil(Nq / 256)                                                        */

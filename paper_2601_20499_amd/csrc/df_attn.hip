@@ -1681,7 +1681,9 @@ static df_status fill_heads(AttnParams &p, int H, int d, int Nq, int Nc, const i
     const int32_t sl = sink_len ? sink_len[h] : 0;
     if (sl < 0 || sl > len) return DF_ERR_RANGE;
     lens[h] = int32_t(len);
-    sinks[h] = sl;
+    // Without scores nobody asks where the sink region ends, and its rows and the window's lie side by side: one region has up to one
+    // ragged tile less than two (98 tokens a frame, one chunk of them, 5 heads of 1 + 21 frames: 18.9 -> 17.8 us).
+    sinks[h] = need_sink ? sl : 0;
     any += len;
   }
   if (any > 0) {

@@ -68,3 +68,23 @@ def test_every_output_by_both_ways(df, monkeypatch, d, Nq, Nc, heads):
         s, n = sinks[h], lens[h]
         R = torch.stack([p[:, :s].sum(), p[:, s:n].sum(), p[:, n:].sum()]) / Nq
         assert (F[h] - R).abs().max() <= gu.F_ABS and (F2[h] - R).abs().max() <= gu.F_ABS
+
+
+@pytest.mark.parametrize("Nq,lens,sinks", [(70, [70 + 210, 70, 0], [70, 70, 0]), (1300, [9000, 9000, 65], [63, 8937, 1])])
+def test_without_scores_the_regions_are_one(df, Nq, lens, sinks):
+    """Where the sink region ends does not matter then, down to the last bit."""
+    dev, H, d = gu.dev(), 3, 128
+    off = [0] + np.cumsum(lens).tolist()
+    g = torch.Generator(device=dev).manual_seed(Nq)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
+    q, kc, vc, kh, vh = rnd(Nq, H, d), rnd(Nq, H, d), rnd(Nq, H, d), rnd(off[-1], d), rnd(off[-1], d)
+    ws = torch.empty(df.df_attn_workspace_bytes(H, d, Nq), dtype=torch.uint8, device=dev)
+    outs, lses = [torch.empty_like(q) for _ in range(2)], [torch.empty(H, Nq, device=dev) for _ in range(2)]
+    for s, out, lse in zip((sinks, None), outs, lses):
+        df.df_attn_fwd(q, kc, vc, kh, vh, off, s, out, d ** -0.5, lse_out=lse, workspace=ws)
+    assert torch.equal(*outs) and torch.equal(*lses)
+    for h in range(H):
+        logits = q[:, h].double() @ torch.cat([kh[off[h]:off[h + 1]], kc[:, h]]).double().t() * d ** -0.5
+        ref = torch.softmax(logits, 1) @ torch.cat([vh[off[h]:off[h + 1]], vc[:, h]]).double()
+        gu.check_out(outs[0][:, h].double().cpu().numpy(), ref.cpu().numpy(), f"head {h}")
+        assert (lses[0][h] - torch.logsumexp(logits, 1)).abs().max() <= gu.LSE_ABS
