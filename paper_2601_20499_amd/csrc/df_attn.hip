@@ -34,7 +34,7 @@
 // launches pay for is not tiles: a second piece in a span cost a workgroup 7 us besides its tiles, and those that
 // waited for its sums with it; a piece of 256 queries hands on 136 KB, one of 128 queries 72, and a unit needs
 // half as many pieces for the same number of workgroups; and the first load goes out 0.2 us earlier.  One box, spans -> units: 64
-// queries 14.4 -> 10.0 us, 1170 queries 38.1 -> 35.3, 393 queries and 5 heads 29.0 -> 20.0, 266 queries and long histories
+// queries 14.4 -> 10.0 us, 1170 queries 38.1 -> 35.3 (with what came after 9.4 and 26.8), 393 queries and 5 heads 29.0 -> 20.0, 266 queries and long histories
 // 50.0 -> 31.9, 478 sampled queries 21.1 -> 18.1; 80 random launches 14 % less on average, the worst 1.2 % more.
 //
 // MFMA mapping.  Scores are computed transposed, S^T = K Q^T, with
@@ -124,7 +124,7 @@ struct HeadRec {
   int32_t len;         // history rows that hold keys (a prefix of the head's rows)
   int32_t sink;        // of these, sink rows
   int32_t head;        // index of the head
-  uint32_t cut;        // a launch that cuts unit by unit (see by_units): span behind the head's last one; tiles of its shortest pieces << 16
+  uint32_t cut;        // a launch that cuts unit by unit (see cut_units): span behind the head's last one; tiles of each of its pieces but the last << 16
 };
 
 struct AttnParams {
@@ -826,10 +826,10 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       const int hh = __popcll(__ballot(span >= lane_end));
       const int before = max(hh - 1, 0), first_span = hh ? of_head(lane_end, before) : 0;
       const int n = of_head(lane_cum, hh) - (hh ? of_head(lane_cum, before) : 0), nth = span - first_span;
-      const int shortest = int(unsigned(of_head(int(lane_rec.cut), hh)) >> 16);
-      const int longer = n - (of_head(lane_end, hh) - first_span) * shortest;       // the first so many pieces have a tile more
-      piece = {0, hh, n, nth * shortest + min(nth, longer), 0, 0, 0};
-      piece.t_end = piece.t_begin + shortest + (nth < longer ? 1 : 0);
+      const unsigned cut = unsigned(of_head(int(lane_rec.cut), hh));
+      const int length = int(cut >> 16);
+      piece = {0, hh, n, nth * length, 0, 0, 0};
+      piece.t_end = span + 1 < int(cut & 0xffffu) ? piece.t_begin + length : n;
       h = of_head(lane_rec.head, hh);
       len_h = of_head(lane_rec.len, hh);
       sink = of_head(lane_rec.sink, hh);
@@ -1438,6 +1438,10 @@ static df_status plan(AttnParams &p, float *spans_cost) {
 // them, 3 to 6 % more.
 struct UnitCost {
   float start, wg, tile, crowd, few, cut, fold;
+  // Tiles that the last piece of a unit has more than the others: those that its workgroup does while their sums are on the way to it, for
+  // most of `cut`.  Equal pieces -> so, one box: 1170 queries, every output 29.9 -> 26.8 us, 1170 sampled ones 54.7 -> 53.8; 60 random
+  // launches take 1.6 % less on average (with 0.4 of `cut` 0.3 %, 0.6 0.4 %, all of it 1.7 %), from 8 % less to 4 % more.
+  constexpr int ahead() const { return int(0.8f * cut / tile); }
 };
 struct SpanCost {
   float start, cost, tile, wg;
@@ -1457,6 +1461,7 @@ constexpr LaunchCost kLaunchCost =
 constexpr float kMaxUnitLaunch = 110.f;
 static float units_margin(float us) { return us > kMaxUnitLaunch ? 0.f : 0.97f - 0.002f * std::max(0.f, us - 50.f); }
 constexpr int kMaxUnitWalk = 512;
+constexpr int kMaxTiles = 0xffff;      // of a unit, for HeadRec::cut
 
 // Heads of the same length, longest first.
 struct Runs {
@@ -1470,18 +1475,26 @@ struct Runs {
     }
   }
 };
+// The pieces of a unit of `n` tiles, of at most `longest` each and the last of `ahead` more: how many, and tiles of all but the last.
+struct UnitPieces {
+  int count, length;
+};
+static UnitPieces pieces(int n, int longest, int ahead) {
+  const int m = std::max(1, n - ahead), k = (m + longest - 1) / longest;
+  return {k, (m + k - 1) / k};                     // the last: ahead + 1 tiles at least
+}
 // Most tiles of a piece of the cheapest cut into units of `rows` queries, if that costs less than `best` (which it then replaces), else 0.
 static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &cost, float &best) {
-  const int m = (Nq + rows - 1) / rows, most = kNumCU / m;
+  const int m = (Nq + rows - 1) / rows, most = kNumCU / m, ahead = cost.ahead();
   int best_longest = 0, walked = 0;
   // from whole units on, each time with shorter pieces for those that have the longest (3 % shorter at least)
-  for (int longest = runs.run[0].n; longest > 0 && walked < kMaxUnitWalk;) {
+  for (int longest = pieces(runs.run[0].n, kMaxTiles, ahead).length; longest > 0 && walked < kMaxUnitWalk;) {
     int spans = 0, pieces_of[kMaxHeads], tiles_of[kMaxHeads], most_tiles = 0;
     for (int r = 0; r < runs.n_runs; ++r, ++walked) {
-      const int n = runs.run[r].n, k = n <= longest ? 1 : (n + longest - 1) / longest;
+      const auto [k, length] = pieces(runs.run[r].n, longest, ahead);
       pieces_of[r] = k;
-      tiles_of[r] = k == 1 ? n : (n + k - 1) / k;
-      most_tiles = std::max(most_tiles, tiles_of[r]);
+      tiles_of[r] = k == 1 ? runs.run[r].n : length;
+      most_tiles = std::max(most_tiles, length);
       spans += k * runs.run[r].heads;
     }
     if (spans > most) break;
@@ -1496,12 +1509,12 @@ static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &co
   return best_longest;
 }
 // Cuts the launch into units of `rows` queries, in pieces of at most `longest` tiles.
-static void cut_units(AttnParams &p, int rows, int longest) {
+static void cut_units(AttnParams &p, int rows, int longest, int ahead) {
   int spans = 0;
   for (int hh = 0; hh < p.H; ++hh) {
-    const int n = p.cum[hh + 1] - p.cum[hh], k = (n + longest - 1) / longest;
+    const auto [k, length] = pieces(p.cum[hh + 1] - p.cum[hh], longest, ahead);
     spans += k;
-    p.rec[hh].cut = uint32_t(spans) | uint32_t(n / k) << 16;
+    p.rec[hh].cut = uint32_t(spans) | uint32_t(length) << 16;
   }
   p.n_qtiles = p.team_size = (p.Nq + rows - 1) / rows;
   p.n_groups = 1;
@@ -1510,7 +1523,7 @@ static void cut_units(AttnParams &p, int rows, int longest) {
 }
 // The plan by units if it costs less than the spans do (`spans_cost` as plan gives it, 0: not known): rows of its units, or 0.
 static int plan_units(AttnParams &p, const LaunchCost &cost, float spans_cost) {
-  if (spans_cost <= 0.f || p.cum[1] > 0xffff) return 0;
+  if (spans_cost <= 0.f || p.cum[1] > kMaxTiles) return 0;
   const float in_spans = cost.spans.start + cost.spans.cost * spans_cost + cost.spans.tile * float(p.span_base) +
                          cost.spans.wg * float(p.n_teams * p.team_size);
   float best = units_margin(in_spans) * in_spans;
@@ -1518,7 +1531,7 @@ static int plan_units(AttnParams &p, const LaunchCost &cost, float spans_cost) {
   const Runs runs(p);
   const int half = cheapest_units(runs, p.Nq, kHalfBQ, cost.half, best), whole = cheapest_units(runs, p.Nq, kBQ, cost.whole, best);
   const int rows = whole ? kBQ : half ? kHalfBQ : 0;
-  if (rows) cut_units(p, rows, whole ? whole : half);
+  if (rows) cut_units(p, rows, whole ? whole : half, (whole ? cost.whole : cost.half).ahead());
   return rows;
 }
 
