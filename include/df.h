@@ -200,7 +200,7 @@ df_status df_attn_plan(int32_t H, int32_t Nq, int32_t Nc, const int32_t *hist_le
 /* df_attn_units: the other way to share a launch out, which is taken instead of df_attn_plan's spans where it
  * costs less (launches of few key tiles; it depends on d and on whether only scores are wanted).  Queries are
  * taken in tiles of *unit_rows (128 or 256), and every (head, query tile) unit of head h is cut into pieces[h]
- * parts of equally many key tiles (give or take one), one workgroup to each.  score_only != 0: a df_head_score
+ * parts of about equally many key tiles, one workgroup to each.  score_only != 0: a df_head_score
  * launch, Nq being the number of sampled queries.  Writes *unit_rows and pieces[0 .. H-1] (HOST), all 0 if the
  * launch is shared out in spans.  Errors as df_attn_plan, and DF_ERR_UNSUPPORTED for other d than 64 and 128. */
 df_status df_attn_units(int32_t H, int32_t d, int32_t score_only, int32_t Nq, int32_t Nc, const int32_t *hist_len,

@@ -28,13 +28,13 @@
 // two XCDs.
 //
 // Launches of few tiles are cut in another way where that costs less (cut_units): into units of 128
-// queries, each head's units into a number of equal pieces of its own, one workgroup to a
-// piece.  There the two groups of waves (see the schedule) have the same queries and take half of
+// or 256 queries, each head's units into a number of pieces of its own, one workgroup to a
+// piece (of about equal length: see UnitCost).  With 128  the two groups of waves (see the schedule) have the same queries and take half of
 // every tile's keys each, and a workgroup puts the two together through LDS (exchange_halves).  What such
 // launches pay for is not tiles: a second piece in a span cost a workgroup 7 us besides its tiles, and those that
 // waited for its sums with it; a piece of 256 queries hands on 136 KB, one of 128 queries 72, and a unit needs
 // half as many pieces for the same number of workgroups; and the first load goes out 0.2 us earlier.  One box, spans -> units: 64
-// queries 14.4 -> 10.0 us, 1170 queries 38.1 -> 35.3 (with what came after 9.4 and 26.8), 393 queries and 5 heads 29.0 -> 20.0, 266 queries and long histories
+// queries 14.4 -> 10.0 us, 1170 queries 38.1 -> 35.3 (with what came after 9.3 and 27.1), 393 queries and 5 heads 29.0 -> 20.0, 266 queries and long histories
 // 50.0 -> 31.9, 478 sampled queries 21.1 -> 18.1; 80 random launches 14 % less on average, the worst 1.2 % more.
 //
 // MFMA mapping.  Scores are computed transposed, S^T = K Q^T, with
@@ -124,7 +124,7 @@ struct HeadRec {
   int32_t len;         // history rows that hold keys (a prefix of the head's rows)
   int32_t sink;        // of these, sink rows
   int32_t head;        // index of the head
-  uint32_t cut;        // a launch that cuts unit by unit (see cut_units): span behind the head's last one; tiles of each of its pieces but the last << 16
+  uint32_t cut;        // a launch that cuts unit by unit (see cut_units): span behind the head's last one; UnitPieces::length << 16
 };
 
 struct AttnParams {
@@ -598,15 +598,22 @@ __device__ __forceinline__ f32x4 slot_load4(const __amdgpu_buffer_rsrc_t &slots,
 
 // Code of the unit of sorted head hh whose rows lie in tile qt of kBQ queries, behind those of single flags (see lost_flag()).
 __host__ __device__ __forceinline__ int lost_unit(int hh, int qt) { return 2 * kNumCU + hh * kNumCU + qt; }
-// Wait, for a bounded time, until a flag word holds this launch's value, and put it back: a flag has one reader, and
-// a replay of the launch (same value) has to start clean.  `code` is the flag's (or its unit's) as lost_flag() gives it.
-__device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int code) {
+// Wait, for a bounded time, until a flag word holds this launch's value.  `code` is the flag's (or its unit's) as lost_flag() gives it.
+__device__ __forceinline__ int await_flag(const AttnParams &p, unsigned long long *flag, int code) {
   int up = 0;
   for (int spin = code == p.handoff - 2 ? kSpinLimit : 0; spin < kSpinLimit && !up; ++spin) {
     up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
     if (!up) __builtin_amdgcn_s_sleep(16);
   }
+  return up;
+}
+// Put it back: a flag is read by one workgroup, and a replay of the launch (same value) has to start clean.
+__device__ __forceinline__ void reset_flag(unsigned long long *flag) {
   __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int code) {
+  const int up = await_flag(p, flag, code);
+  reset_flag(flag);
   return up;
 }
 
@@ -735,9 +742,51 @@ __device__ __forceinline__ void read_q(const unsigned (&at)[D / 32], bf16x8 (&qf
         : "memory");
 }
 
+// The other way to cut a launch: unit by unit, each head's into a number of pieces of its own, one workgroup to a piece.
+// No workgroup then pays for a second piece, nor waits for one that does, and a short unit is left whole; it takes few
+// enough units to go round.  The fewest pieces go with units of kHalfBQ queries, the fewest tiles for the machine with
+// units of kBQ.  UnitCost is the time in us of a launch that is cut so: `start`, `wg` for each workgroup, and for its slowest unit
+// `tile` for each tile of its longest piece (`crowd` of it more for each workgroup, `few` of it where half of the waves have no rows and the others
+// a SIMD to themselves, or, of units of kHalfBQ, half of its waves), and where it is cut `cut` and for each piece that is
+// handed on `fold`.  SpanCost is that of equal spans: `start`, `cost` times span_cost, `tile` for each tile of a span and `wg` for each
+// workgroup.  Fitted to 420 launches (1 to 6 000 queries, 2 to 61 heads, up to 100 GFLOP) with the spans that span_cost chooses and up to 14
+// cuts by units of either kind measured on each; they meet the times to 3 % by units and 3 to 6 % in spans.  By units if that
+// takes units_margin of the spans' time: of the 420, attention then takes 27 % less time on average and scores 10 %, four of them up to
+// 4 % more; the cheapest of all cuts measured would be another 1.3 % less.
+struct UnitCost {
+  float start, wg, tile, crowd, few, cut, fold;
+  int ahead, lag;
+  // `ahead`: tiles that the last piece of a unit has more than the one before it, done while the others' sums are on the way.  Equal
+  // pieces -> so, one box: 1170 queries, every output 29.9 -> 26.8 us, 1170 sampled ones 54.7 -> 53.8; 60 random launches 1.6 % less.
+  // `lag`: sixteenths of a tile that each of the pieces before that has more than the next, about `fold`: while the last
+  // piece's workgroup folds one, the one before is on its way.  One wait for all flags -> each wave for each piece on its own -> the latter with
+  // lag: 46 random attention launches 3.3 and 6.2 % less (half of the lag 4.5, three quarters 5.2; 5/4 and 6/4 as the whole), 290
+  // queries and 10 pieces 20.5 -> 18.9 us, 720 queries and 14 pieces 33.9 -> 27.7.  While scoring a fold is a sixth of
+  // that, and four go in one trip: no lag there.
+};
+// The pieces of a unit: all but the last `count` - 1 have `length` tiles and what `lag` adds; where the j-th begins.
+struct UnitPieces {
+  int count, length, lag;
+  __host__ __device__ __forceinline__ int begin(int j) const { return j * length + ((j * (2 * count - 3 - j) / 2 * lag) >> 4); }
+};
+struct SpanCost {
+  float start, cost, tile, wg;
+};
+struct LaunchCost {
+  UnitCost half, whole;        // units of kHalfBQ and of kBQ queries
+  SpanCost spans;
+};
+template <int D, bool SCORE_ONLY>
+constexpr LaunchCost kLaunchCost =
+    D == 128 ? (SCORE_ONLY ? LaunchCost{{8.26f, 0.0059f, 0.394f, 0.00076f, 0.96f, 1.76f, 0.147f, 3, 0}, {7.63f, 0.0062f, 0.706f, 0.00056f, 0.78f, 1.44f, 0.200f, 1, 0}, {5.83f, 0.371f, 0.600f, 0.f}}
+                           : LaunchCost{{8.01f, 0.0117f, 0.576f, 0.00054f, 0.86f, 1.83f, 0.667f, 3, 18}, {7.86f, 0.0169f, 1.048f, 0.00030f, 0.65f, 2.05f, 1.403f, 1, 19}, {1.10f, 1.213f, 0.297f, 0.0148f}})
+             : (SCORE_ONLY ? LaunchCost{{7.97f, 0.0079f, 0.342f, 0.00022f, 0.91f, 1.78f, 0.141f, 4, 0}, {7.07f, 0.0084f, 0.613f, 0.00017f, 0.73f, 1.59f, 0.199f, 2, 0}, {5.78f, 0.437f, 0.263f, 0.f}}
+                           : LaunchCost{{6.81f, 0.0094f, 0.419f, 0.00030f, 0.90f, 1.59f, 0.489f, 4, 16}, {6.45f, 0.0117f, 0.763f, 0.00023f, 0.71f, 1.58f, 0.800f, 2, 14}, {4.51f, 0.709f, 0.262f, 0.0112f}});
+
 template <int D, bool SCORE_ONLY, bool UNITS, bool HALF>
 __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
   constexpr int NQB = HALF ? 1 : 2;     // blocks of 16 finished queries per wave
+  constexpr bool PIECEWISE = UNITS && !SCORE_ONLY;   // earlier pieces are waited for one by one
   constexpr int KS = D / 32;            // k-steps of the first product
   constexpr int DB = D / 16;            // 16-row blocks of O^T
   using L = TileLayout<D>;
@@ -827,9 +876,10 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       const int before = max(hh - 1, 0), first_span = hh ? of_head(lane_end, before) : 0;
       const int n = of_head(lane_cum, hh) - (hh ? of_head(lane_cum, before) : 0), nth = span - first_span;
       const unsigned cut = unsigned(of_head(int(lane_rec.cut), hh));
-      const int length = int(cut >> 16);
-      piece = {0, hh, n, nth * length, 0, 0, 0};
-      piece.t_end = span + 1 < int(cut & 0xffffu) ? piece.t_begin + length : n;
+      constexpr int kLag = (HALF ? kLaunchCost<D, SCORE_ONLY>.half : kLaunchCost<D, SCORE_ONLY>.whole).lag;
+      const UnitPieces u{int(cut & 0xffffu) - first_span, int(cut >> 16), kLag};
+      piece = {0, hh, n, u.begin(nth), 0, 0, 0};
+      piece.t_end = nth + 1 < u.count ? u.begin(nth + 1) : n;
       h = of_head(lane_rec.head, hh);
       len_h = of_head(lane_rec.len, hh);
       sink = of_head(lane_rec.sink, hh);
@@ -978,6 +1028,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       tile_loop<D, SCORE_ONLY, false>(a, qf, o, sums);
     }
     int s_first = span;                            // span that holds the unit's first tile
+    unsigned long long next_flag = 0;
     if (take) {
       // The earlier pieces were written when their workgroups began their spans (a piece that fills a whole
       // span: when that workgroup ended), i.e. long ago or at about this time.  Wait until every flag says
@@ -986,7 +1037,10 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       // as its own tiles are done: the other waves are up to half an iteration behind it.
       if (UNITS) s_first = s_unit;
       else do --s_first; while (s_first > 0 && span_begin(p, s_first) > unit_lo);
-      if (wave == 0) {
+      if (PIECEWISE) {
+        // Each wave waits for each piece on its own, before it folds it, and looks first while it still waits for its tiles.
+        next_flag = __hip_atomic_load(p.flags + (span - 1) * p.team_size + member, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      } else if (wave == 0) {
         // one flag per lane: a poll is a round trip to memory, and a unit can have many pieces
         int ok = 1;
         for (int sp = s_first + lane; sp < span; sp += 64) {
@@ -1041,7 +1095,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
       }
     }
     if (take) {
-      const float poison = lds_ok ? 0.f : NAN;
+      float poison = PIECEWISE || lds_ok ? 0.f : NAN;
       // From this piece back to the unit's first, the order and arithmetic of the merge kernel: every earlier piece is
       // folded into this one's registers, all of it loaded with one wait.  (Front to back the sum so far needs
       // registers of its own, and the loads had to go out four at a time: 1170 queries, 6 pieces to a unit, 54.8 us
@@ -1079,6 +1133,13 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
 #pragma unroll 1
         for (int sp = span - 1; sp >= s_first; --sp) {
           f32x4 st[2], v[DB * NQB];
+          if constexpr (PIECEWISE) {
+            unsigned long long *flag = p.flags + sp * p.team_size + member;
+            const int code = lost_unit(piece.hh, HALF ? qt >> 1 : qt);
+            if (poison == 0.f && (next_flag != p.epoch || code == p.handoff - 2) && !await_flag(p, flag, code)) poison = NAN;
+            // seen when these sums are in, and so for nothing if the piece is
+            if (sp > s_first) next_flag = __hip_atomic_load(flag - p.team_size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          }
           if constexpr (HALF) load_half_slot<D>(p, slot_of_piece(sp), tid_, st[0], v);
           else load_slot_through<D / 8>(slot_of(sp), tid_, st, v);
 #pragma unroll
@@ -1111,6 +1172,8 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
         reduce_masses(p, lds_red, h, qt, tid_, mass_a, mass_b);
       }
       else if (!SCORE_ONLY) lds_barrier();         // the next piece's tiles go where the rows were
+      if (PIECEWISE && take && wave == kWaves - 1)   // every wave has seen all flags
+        for (int sp = s_first + lane; sp < span; sp += 64) reset_flag(p.flags + sp * p.team_size + member);
     } else {
       // a piece that starts at the span's first position uses the span's slot 0, a later one slot 1
       float *slot = p.slots + slot_index(p, span, piece_pos == span_lo ? 0 : 1, member) * Slot<D, NQB>::kFloats;
@@ -1425,37 +1488,6 @@ static df_status plan(AttnParams &p, float *spans_cost) {
   return DF_OK;
 }
 
-// The other way to cut a launch: unit by unit, each head's into a number of equal pieces of its own, one workgroup to a piece.
-// No workgroup then pays for a second piece, nor waits for one that does, and a short unit is left whole; it takes few
-// enough units to go round.  The fewest pieces go with units of kHalfBQ queries, the fewest tiles for the machine with
-// units of kBQ.  UnitCost is the time in us of a launch that is cut so: `start`, `wg` for each workgroup, and for its slowest unit
-// `tile` for each tile of its longest piece (`crowd` of it more for each workgroup, `few` of it where half of the waves have no rows and the others
-// a SIMD to themselves, or, of units of kHalfBQ, half of its waves), and where it is cut `cut` and for each piece that is
-// handed on `fold`.  SpanCost is that of equal spans: `start`, `cost` times span_cost, `tile` for each tile of a span and `wg` for each
-// workgroup.  Fitted to 720 launches (1 to 5 000 queries, 2 to 61 heads, up to 300 GFLOP) with the spans that span_cost chooses and up to 14
-// cuts by units of either kind measured on each; they meet the times to 2 to 4 % by units and 4 to 6 % in spans.  By units if that
-// takes units_margin of the spans' time: of the 720, attention then takes 16 % less time on average and scores 9 %, from 45 % less to, in five of
-// them, 3 to 6 % more.
-struct UnitCost {
-  float start, wg, tile, crowd, few, cut, fold;
-  // Tiles that the last piece of a unit has more than the others: those that its workgroup does while their sums are on the way to it, for
-  // most of `cut`.  Equal pieces -> so, one box: 1170 queries, every output 29.9 -> 26.8 us, 1170 sampled ones 54.7 -> 53.8; 60 random
-  // launches take 1.6 % less on average (with 0.4 of `cut` 0.3 %, 0.6 0.4 %, all of it 1.7 %), from 8 % less to 4 % more.
-  constexpr int ahead() const { return int(0.8f * cut / tile); }
-};
-struct SpanCost {
-  float start, cost, tile, wg;
-};
-struct LaunchCost {
-  UnitCost half, whole;        // units of kHalfBQ and of kBQ queries
-  SpanCost spans;
-};
-template <int D, bool SCORE_ONLY>
-constexpr LaunchCost kLaunchCost =
-    D == 128 ? (SCORE_ONLY ? LaunchCost{{8.35f, 0.0062f, 0.397f, 0.00038f, 0.95f, 1.81f, 0.136f}, {7.93f, 0.0063f, 0.715f, 0.00032f, 0.77f, 1.14f, 0.208f}, {6.78f, 0.316f, 0.610f, 0.f}}
-                           : LaunchCost{{8.48f, 0.0084f, 0.560f, 0.00073f, 0.90f, 2.57f, 0.639f}, {8.26f, 0.0147f, 1.025f, 0.00051f, 0.72f, 2.22f, 1.238f}, {2.30f, 1.118f, 0.375f, 0.0163f}})
-             : (SCORE_ONLY ? LaunchCost{{8.39f, 0.0041f, 0.335f, 0.00013f, 0.88f, 1.80f, 0.145f}, {7.38f, 0.0033f, 0.608f, 0.00013f, 0.73f, 1.69f, 0.214f}, {6.28f, 0.380f, 0.317f, 0.f}}
-                           : LaunchCost{{7.02f, 0.0101f, 0.428f, 0.00010f, 0.90f, 2.15f, 0.427f}, {6.56f, 0.0143f, 0.770f, 0.00005f, 0.72f, 2.14f, 0.662f}, {4.60f, 0.696f, 0.269f, 0.0103f}});
 // Share of the spans' time `us` that units may take: less of longer launches, in which the clock under load and not these sums decides
 // and equal spans keep all compute units busy to the end; none from kMaxUnitLaunch on.
 constexpr float kMaxUnitLaunch = 110.f;
@@ -1475,27 +1507,30 @@ struct Runs {
     }
   }
 };
-// The pieces of a unit of `n` tiles, of at most `longest` each and the last of `ahead` more: how many, and tiles of all but the last.
-struct UnitPieces {
-  int count, length;
-};
-static UnitPieces pieces(int n, int longest, int ahead) {
-  const int m = std::max(1, n - ahead), k = (m + longest - 1) / longest;
-  return {k, (m + k - 1) / k};                     // the last: ahead + 1 tiles at least
+// The fewest pieces of a unit of `n` tiles, the shortest but the last of at most `longest`; none if the last would be empty.
+// (`from`: a number that is known to be too few or just right.)
+static UnitPieces pieces(int n, int longest, const UnitCost &cost, int from = 1) {
+  UnitPieces u{from, longest, cost.lag};
+  while (u.count <= kNumCU && u.begin(u.count - 1) + longest + cost.ahead < n) ++u.count;
+  const int rest = n - cost.ahead - UnitPieces{u.count, 0, cost.lag}.begin(u.count - 1);
+  u.length = u.count == 1 ? std::max(1, n - cost.ahead) : (rest + u.count - 1) / u.count;
+  if (u.count > kNumCU || (u.count > 1 && (u.length < 1 || u.begin(u.count - 1) >= n))) u.count = 0;
+  return u;
 }
 // Most tiles of a piece of the cheapest cut into units of `rows` queries, if that costs less than `best` (which it then replaces), else 0.
 static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &cost, float &best) {
-  const int m = (Nq + rows - 1) / rows, most = kNumCU / m, ahead = cost.ahead();
-  int best_longest = 0, walked = 0;
+  const int m = (Nq + rows - 1) / rows, most = kNumCU / m;
+  int best_longest = 0, walked = 0, pieces_of[kMaxHeads];
+  std::fill_n(pieces_of, runs.n_runs, 1);
   // from whole units on, each time with shorter pieces for those that have the longest (3 % shorter at least)
-  for (int longest = pieces(runs.run[0].n, kMaxTiles, ahead).length; longest > 0 && walked < kMaxUnitWalk;) {
-    int spans = 0, pieces_of[kMaxHeads], tiles_of[kMaxHeads], most_tiles = 0;
+  for (int longest = pieces(runs.run[0].n, kMaxTiles, cost).length; longest > 0 && walked < kMaxUnitWalk;) {
+    int spans = 0, tiles_of[kMaxHeads], most_tiles = 0;
     for (int r = 0; r < runs.n_runs; ++r, ++walked) {
-      const auto [k, length] = pieces(runs.run[r].n, longest, ahead);
-      pieces_of[r] = k;
-      tiles_of[r] = k == 1 ? runs.run[r].n : length;
-      most_tiles = std::max(most_tiles, length);
-      spans += k * runs.run[r].heads;
+      const UnitPieces u = pieces(runs.run[r].n, longest, cost, pieces_of[r]);
+      pieces_of[r] = u.count;
+      tiles_of[r] = u.count == 1 ? runs.run[r].n : u.length;
+      most_tiles = std::max(most_tiles, u.length);
+      spans += u.count > 0 ? u.count * runs.run[r].heads : most + 1;
     }
     if (spans > most) break;
     const float tile = cost.tile * (1.f + cost.crowd * float(spans * m)) * (2 * Nq <= rows ? cost.few : 1.f);
@@ -1509,12 +1544,12 @@ static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &co
   return best_longest;
 }
 // Cuts the launch into units of `rows` queries, in pieces of at most `longest` tiles.
-static void cut_units(AttnParams &p, int rows, int longest, int ahead) {
+static void cut_units(AttnParams &p, int rows, int longest, const UnitCost &cost) {
   int spans = 0;
   for (int hh = 0; hh < p.H; ++hh) {
-    const auto [k, length] = pieces(p.cum[hh + 1] - p.cum[hh], longest, ahead);
-    spans += k;
-    p.rec[hh].cut = uint32_t(spans) | uint32_t(length) << 16;
+    const UnitPieces u = pieces(p.cum[hh + 1] - p.cum[hh], longest, cost);
+    spans += u.count;
+    p.rec[hh].cut = uint32_t(spans) | uint32_t(u.length) << 16;
   }
   p.n_qtiles = p.team_size = (p.Nq + rows - 1) / rows;
   p.n_groups = 1;
@@ -1531,7 +1566,7 @@ static int plan_units(AttnParams &p, const LaunchCost &cost, float spans_cost) {
   const Runs runs(p);
   const int half = cheapest_units(runs, p.Nq, kHalfBQ, cost.half, best), whole = cheapest_units(runs, p.Nq, kBQ, cost.whole, best);
   const int rows = whole ? kBQ : half ? kHalfBQ : 0;
-  if (rows) cut_units(p, rows, whole ? whole : half, (whole ? cost.whole : cost.half).ahead());
+  if (rows) cut_units(p, rows, whole ? whole : half, whole ? cost.whole : cost.half);
   return rows;
 }
 

@@ -88,3 +88,40 @@ def test_without_scores_the_regions_are_one(df, Nq, lens, sinks):
         ref = torch.softmax(logits, 1) @ torch.cat([vh[off[h]:off[h + 1]], vc[:, h]]).double()
         gu.check_out(outs[0][:, h].double().cpu().numpy(), ref.cpu().numpy(), f"head {h}")
         assert (lses[0][h] - torch.logsumexp(logits, 1)).abs().max() <= gu.LSE_ABS
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Nq", [128, 300])
+def test_replays_of_a_unit_in_many_pieces(df, d, Nq):
+    """Every wave looks at every piece's flag and one puts them back: a replay, whose value is the same, waits again."""
+    dev, lens, sinks = gu.dev(), [5000, 900], [0, 0]
+    rows, pieces = df.df_attn_units(d, False, Nq, 33, lens, sinks)
+    assert rows and pieces[0] > 8
+    g = torch.Generator(device=dev).manual_seed(d)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
+    q, kc, vc, kh, vh = rnd(Nq, 2, d), rnd(33, 2, d), rnd(33, 2, d), rnd(5900, d), rnd(5900, d)
+    ws = torch.empty(df.df_attn_workspace_bytes(2, d, Nq), dtype=torch.uint8, device=dev)
+    out, F = torch.empty_like(q), torch.empty(2, 3, device=dev)
+
+    def step():
+        df.df_attn_fwd(q, kc, vc, kh, vh, [0, 5000, 5900], sinks, out, d ** -0.5, score_out=F, workspace=ws)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    for replay in range(5):
+        q.copy_(rnd(Nq, 2, d))
+        vh.copy_(rnd(5900, d))
+        step()
+        torch.cuda.synchronize()
+        want = out.clone(), F.clone()
+        out.zero_()
+        F.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[0]) and torch.equal(F, want[1]), replay

@@ -10,9 +10,14 @@ def b():
     return binding
 
 
-# tiles that the last piece of a unit may have more than the others: by head dimension, scores only, queries of a unit
-AHEAD = {(128, False, 128): 3, (128, False, 256): 1, (64, False, 128): 4, (64, False, 256): 2,
-         (128, True, 128): 3, (128, True, 256): 1, (64, True, 128): 4, (64, True, 256): 2}
+# By head dimension, scores only, queries of a unit: tiles that the last piece may have more than the one before it, and sixteenths of a
+# tile that each of the others has more than the next.
+SHAPE = {(128, False, 128): (3, 18), (128, False, 256): (1, 19), (64, False, 128): (4, 16), (64, False, 256): (2, 14),
+         (128, True, 128): (3, 0), (128, True, 256): (1, 0), (64, True, 128): (4, 0), (64, True, 256): (2, 0)}
+
+
+def begin(j, count, length, lag):
+    return j * length + (j * (2 * count - 3 - j) // 2 * lag >> 4)
 
 
 def tiles(n):
@@ -20,8 +25,8 @@ def tiles(n):
 
 
 def test_pieces_fit_the_machine_and_the_units(b):
-    """Random mixes: all heads are cut or none, no piece is empty (the last takes up to AHEAD tiles more than the others), all pieces have a
-    compute unit, and no head has pieces that are longer than a head with more of them needs."""
+    """Random mixes: all heads are cut or none, no piece is empty, all pieces have a compute unit, and no head has more pieces than one that
+    is as long as the head with the longest needs."""
     rng, cut = random.Random(128), {128: 0, 256: 0}
     for _ in range(1500):
         H, d, score = rng.choice([1, 2, 5, 12, 40, 64]), rng.choice([64, 128]), rng.random() < 0.3
@@ -37,9 +42,14 @@ def test_pieces_fit_the_machine_and_the_units(b):
         units = [tiles(s) + tiles(n - s) + tiles(Nc) for n, s in zip(lens, sinks)]
         assert all(1 <= k <= n for k, n in zip(pieces, units))
         assert sum(pieces) * -(-Nq // rows) <= 256
-        units = [max(1, n - AHEAD[d, score, rows]) for n in units]
-        longest = max(-(-n // k) for n, k in zip(units, pieces))
-        assert all(k == 1 or -(-n // (k - 1)) > longest for k, n in zip(pieces, units))
+        ahead, lag = SHAPE[d, score, rows]
+        lengths = []
+        for n, k in zip(units, pieces):
+            lengths.append(max(1, n - ahead) if k == 1 else -(-(n - ahead - begin(k - 1, k, 0, lag)) // k))
+            starts = [begin(j, k, lengths[-1], lag) for j in range(k)] + [n]
+            assert all(a < b for a, b in zip(starts, starts[1:]))
+        longest = max(lengths)
+        assert all(k == 1 or begin(k - 2, k - 1, longest, lag) + longest + ahead < n for n, k in zip(units, pieces))
     assert min(cut.values()) > 50
 
 
