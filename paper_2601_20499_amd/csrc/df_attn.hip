@@ -29,8 +29,8 @@
 //
 // Launches of few tiles are cut in another way where that costs less (cut_units): into units of 128
 // or 256 queries, each head's units into a number of pieces of its own, one workgroup to a
-// piece (of about equal length: see UnitCost).  With 128  the two groups of waves (see the schedule) have the same queries and take half of
-// every tile's keys each, and a workgroup puts the two together through LDS (exchange_halves).  What such
+// piece (of about equal length: see UnitCost).  With 128 the two groups of waves (see the schedule)
+// have the same queries and take half of every tile's keys each, and a workgroup puts the two together through LDS (exchange_halves).  What such
 // launches pay for is not tiles: a second piece in a span cost a workgroup 7 us besides its tiles, and those that
 // waited for its sums with it; a piece of 256 queries hands on 136 KB, one of 128 queries 72, and a unit needs
 // half as many pieces for the same number of workgroups; and the first load goes out 0.2 us earlier.  One box, spans -> units: 64

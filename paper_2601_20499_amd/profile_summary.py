@@ -22,6 +22,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 import statistics
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -113,7 +114,7 @@ def main():
         call = 0.0
         for k in sorted(table):
             print("| `%s` | %.1f | %.1f |" % (k[:90], table[k][0] / 1e6, table[k][1] / 1e6))
-            if "df_attn_kernel" in k and "false" in k or "df_attn_merge_kernel" in k and "false" in k:
+            if re.search(r"df_attn_(merge_)?kernel<\d+, false", k):   # <d, scores only, ...>
                 call += table[k][0] + table[k][1]
         print(f"\ndf_attn_fwd per call (all its kernels, fetched + written): {call / 1e6:.1f} MB; "
               f"kernel sources {kernel_source_hash()}")
