@@ -308,7 +308,9 @@ struct Slot {
 // The idle cycles keep the next instruction off the data registers while the store still reads them (a store of more
 // than 8 bytes needs one wait state, which the compiler does not add to inline asm: without it the next address went
 // into the first statistics of the last four lanes of every 16).
-__device__ __forceinline__ void store4_through(float *ptr, const f32x4 &v) {
+template <class T, class V>
+__device__ __forceinline__ void store4_through(T *ptr, const V &v) {
+  static_assert(sizeof(V) == 16, "four registers");
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(ptr), "v"(v) : "memory");
 }
 // The loads below take their base from scalar registers.  A vector instruction that writes one - the compiler keeps scalars
@@ -505,6 +507,9 @@ __device__ __forceinline__ uint2 output4(const f32x4 &o, float inv) {
 // 610.0 -> 601.9; a launch of 64 queries 15.1 -> 15.8.
 // 16-byte chunk c of row r lies at position c ^ (r mod chunks per row).  The reads are then free of bank conflicts; the
 // 8-byte writes are not: 4 cycles each (264,192 in a 1280x720 launch, 0.03 % of the CU-busy cycles).
+// Units of 256 queries write them through to memory, so that a launch does not end with writing its rows back from L2.  In L2 -> through, one box:
+// 832x480 278.8 -> 276.6 us, with an elementwise kernel that reads the rows behind it 283.4 -> 281.8; 909 queries of 40 heads 32.0 -> 31.5.
+// The rows of units of 128, the smaller launches, stay in L2, where the next kernel finds them: 200 queries and that kernel 13.0 us, through 13.15.
 template <int D, int NQB>
 __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row0, unsigned char *buf, int lane,
                                              const f32x4 (&o)[D / 16][NQB], const float (&inv)[NQB]) {
@@ -524,7 +529,11 @@ __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row
   for (int i = 0; i < kChunks * NQB / 4; ++i) {
     const int r = i * (64 / kChunks) + lane / kChunks;
     const u32x4 v = *reinterpret_cast<const u32x4 *>(buf + r * 2 * D + 16 * (c ^ (r % kChunks)));
-    if (row0 + r < p.Nq) *reinterpret_cast<u32x4 *>(p.out + (row0 + r) * p.o_st + h * p.o_sh + 8 * c) = v;
+    if (row0 + r < p.Nq) {
+      u16 *to = p.out + (row0 + r) * p.o_st + h * p.o_sh + 8 * c;
+      if constexpr (NQB == 2) store4_through(to, v);
+      else *reinterpret_cast<u32x4 *>(to) = v;
+    }
   }
 }
 
