@@ -171,12 +171,19 @@ def _array(code: str, ctype, xs):
     return (ctype * len(xs))(*[number(x) for x in xs])
 
 
-def _i64(xs: Sequence[int]):
-    return _array("q", C.c_int64, xs)
+def _i64(xs: Sequence[int], at_least: int = 0):
+    return _at_least(_array("q", C.c_int64, xs), at_least)
 
 
-def _i32(xs: Sequence[int]):
-    return _array("i", C.c_int32, xs)
+def _i32(xs: Sequence[int], at_least: int = 0):
+    return _at_least(_array("i", C.c_int32, xs), at_least)
+
+
+def _at_least(numbers, n: int):
+    """The library reads one number per head (an offset more) whatever the length of the array is."""
+    if len(numbers) < n:
+        raise ValueError(f"{len(numbers)} numbers where the heads need {n}")
+    return numbers
 
 
 def df_attn_plan(Nq: int, Nc: int, hist_len: Sequence[int], hist_sink_len: Optional[Sequence[int]] = None) -> dict:
@@ -184,7 +191,7 @@ def df_attn_plan(Nq: int, Nc: int, hist_len: Sequence[int], hist_sink_len: Optio
     info = df_attn_plan_info()
     H = len(hist_len)
     _check(lib.df_attn_plan(H, int(Nq), int(Nc), _i32(hist_len),
-                            _i32(hist_sink_len) if hist_sink_len is not None else None, C.byref(info)), "df_attn_plan")
+                            _i32(hist_sink_len, H) if hist_sink_len is not None else None, C.byref(info)), "df_attn_plan")
     return {name: getattr(info, name) for name, _ in df_attn_plan_info._fields_}
 
 
@@ -192,9 +199,10 @@ def df_attn_units(d: int, score_only: bool, Nq: int, Nc: int, hist_len: Sequence
                   hist_sink_len: Optional[Sequence[int]] = None) -> tuple:
     """Queries of a unit and the pieces that each head's units are cut into, all 0 where the launch is cut into df_attn_plan's spans
     (host only)."""
-    rows, pieces = C.c_int32(), _i32([0] * len(hist_len))
-    _check(lib.df_attn_units(len(hist_len), int(d), int(score_only), int(Nq), int(Nc), _i32(hist_len),
-                             _i32(hist_sink_len) if hist_sink_len is not None else None, C.byref(rows), pieces), "df_attn_units")
+    H = len(hist_len)
+    rows, pieces = C.c_int32(), _i32([0] * H)
+    _check(lib.df_attn_units(H, int(d), int(score_only), int(Nq), int(Nc), _i32(hist_len),
+                             _i32(hist_sink_len, H) if hist_sink_len is not None else None, C.byref(rows), pieces), "df_attn_units")
     return rows.value, list(pieces)
 
 
@@ -254,15 +262,16 @@ def df_attn_fwd(q, k_cur, v_cur, k_hist, v_hist, hist_off, hist_sink_len, out, s
     a.kc_stride_tok, a.kc_stride_head = k_cur.stride(0), k_cur.stride(1)
     assert v_cur.stride() == k_cur.stride()
     a.k_hist, a.v_hist = _ptr(k_hist), _ptr(v_hist)
-    off = _i64(hist_off)
+    H = q.shape[1]
+    off = _i64(hist_off, H + 1)
     a.hist_off = off
-    sl = _i32(hist_sink_len) if hist_sink_len is not None else None
+    sl = _i32(hist_sink_len, H) if hist_sink_len is not None else None
     a.hist_sink_len = sl
-    hl = _i32(hist_len) if hist_len is not None else None
+    hl = _i32(hist_len, H) if hist_len is not None else None
     a.hist_len = hl
     a.out, a.o_stride_tok, a.o_stride_head = _ptr(out), out.stride(0), out.stride(1)
     a.lse_out, a.score_out = _ptr(lse_out), _ptr(score_out)
-    a.H, a.d, a.Nq, a.Nc = q.shape[1], q.shape[2], q.shape[0], k_cur.shape[0]
+    a.H, a.d, a.Nq, a.Nc = H, q.shape[2], q.shape[0], k_cur.shape[0]
     a.softmax_scale = softmax_scale
     a.workspace = _ptr(workspace)
     a.workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
@@ -281,12 +290,13 @@ def df_head_score(q, k_cur, k_hist, hist_off, hist_sink_len, score_out, softmax_
     a.q, a.q_stride_tok, a.q_stride_head = _ptr(q), q.stride(0), q.stride(1)
     a.k_cur, a.kc_stride_tok, a.kc_stride_head = _ptr(k_cur), k_cur.stride(0), k_cur.stride(1)
     a.k_hist = _ptr(k_hist)
-    off, sl = _i64(hist_off), _i32(hist_sink_len)
+    H = q.shape[1]
+    off, sl = _i64(hist_off, H + 1), _i32(hist_sink_len, H)
     a.hist_off, a.hist_sink_len = off, sl
-    hl = _i32(hist_len) if hist_len is not None else None
+    hl = _i32(hist_len, H) if hist_len is not None else None
     a.hist_len = hl
     a.score_out = _ptr(score_out)
-    a.H, a.d, a.Nq, a.Nc = q.shape[1], q.shape[2], q.shape[0], k_cur.shape[0]
+    a.H, a.d, a.Nq, a.Nc = H, q.shape[2], q.shape[0], k_cur.shape[0]
     a.q_sample_stride, a.q_offset = q_sample_stride, q_offset
     a.softmax_scale = softmax_scale
     a.workspace = _ptr(workspace)
@@ -312,8 +322,8 @@ class Cache:
     def __init__(self, k_cache, v_cache, head_row_off, sink_cap, win_cap, d: int):
         H = len(sink_cap)
         self.k_cache, self.v_cache = k_cache, v_cache
-        self.head_row_off = _i64(head_row_off)
-        self.sink_cap, self.win_cap = _i32(sink_cap), _i32(win_cap)
+        self.head_row_off = _i64(head_row_off, H + 1)
+        self.sink_cap, self.win_cap = _i32(sink_cap), _i32(win_cap, H)
         self.sink_len, self.win_len, self.win_pos = _i32([0] * H), _i32([0] * H), _i32([0] * H)
         self.c = df_cache()
         self.c.k_cache, self.c.v_cache = _ptr(k_cache), _ptr(v_cache)
@@ -357,7 +367,7 @@ def df_pack_context(cache: Cache, take_sink, take_win, k_out, v_out, stream=None
             return done[1:]
     a = df_pack_args()
     a.cache = C.pointer(cache.c)
-    ts, tw = _i32(take_sink), _i32(take_win)
+    ts, tw = _i32(take_sink, cache.H), _i32(take_win, cache.H)
     a.take_sink, a.take_win = ts, tw
     a.k_out, a.v_out = _ptr(k_out), _ptr(v_out)
     a.out_capacity_rows = k_out.shape[0]
@@ -373,7 +383,7 @@ def prepared_pack(cache: Cache, take_sink, take_win, k_out, v_out, stream=None):
     For loops in which the Python-side marshalling would otherwise be the slower part."""
     a = df_pack_args()
     a.cache = C.pointer(cache.c)
-    ts, tw = _i32(take_sink), _i32(take_win)
+    ts, tw = _i32(take_sink, cache.H), _i32(take_win, cache.H)
     a.take_sink, a.take_win = ts, tw
     a.k_out, a.v_out = _ptr(k_out), _ptr(v_out)
     a.out_capacity_rows = k_out.shape[0]

@@ -25,6 +25,31 @@ def test_what_is_not_ordinary_is_left_to_python(b):
         native.setup(1)
 
 
+def test_lists_shorter_than_the_heads_are_refused(b):
+    """The library reads a number per head (hist_off and head_row_off one more); no call reads past the end of a list."""
+    q, ws = torch.zeros(2, 3, 64, dtype=torch.bfloat16), torch.zeros(1, dtype=torch.uint8)
+    off, heads, short = [0] * 4, [0] * 3, [0] * 2
+    cache = b.Cache(None, None, off, heads, heads, d=64)
+    calls = [lambda **k: b.df_attn_fwd(q, q, q, q, q, k.get("off", off), k.get("sink", heads), q, 0.125, workspace=ws, hist_len=k.get("len")),
+             lambda **k: b.df_attn_fwd_static(q, q, q, q, q, k.get("off", off), k.get("sink", heads), q, 0.125, hist_len=k.get("len")),
+             lambda **k: b.df_head_score(q, q, q, k.get("off", off), k.get("sink", heads), ws, 0.125, workspace=ws, hist_len=k.get("len"))]
+    for call in calls:
+        for wrong in (dict(off=heads), dict(off=tuple(heads)), dict(sink=short), dict(len=short)):
+            with pytest.raises(ValueError):
+                call(**wrong)
+    for wrong in ((short, heads), (heads, short)):
+        for pack in (b.df_pack_context, b.prepared_pack):
+            with pytest.raises(ValueError):
+                pack(cache, *wrong, q, q)
+    for wrong in ((heads, heads, heads), (off, heads, short)):
+        with pytest.raises(ValueError):
+            b.Cache(None, None, *wrong, d=64)
+    with pytest.raises(ValueError):
+        b.df_attn_plan(1, 1, heads, short)
+    with pytest.raises(ValueError):
+        b.df_attn_units(64, False, 1, 1, heads, short)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [64, 128])
 def test_native_and_python_marshalling_make_the_same_calls(b, monkeypatch, d):
