@@ -88,6 +88,7 @@
 #include <cmath>
 #include <atomic>
 #include <cstdlib>
+#include <cstring>
 #include <mutex>
 #include <numeric>
 #include <type_traits>
@@ -1570,9 +1571,25 @@ static void cut_units(AttnParams &p, int rows, int longest, const UnitCost &cost
   p.line_len = p.total_cols;
   set_spans(p, spans);
 }
+// For tests of each way to cut a launch at sizes where another would be chosen: DF_ATTN_CUT=spans, 128 or 256 in the environment (looked
+// at on every call) cuts into spans, or by units of so many queries where the machine holds them.  0, the queries, or -1: what costs least.
+static int forced_cut() {
+  const char *e = std::getenv("DF_ATTN_CUT");
+  if (!e) return -1;
+  return !std::strcmp(e, "spans") ? 0 : !std::strcmp(e, "128") ? kHalfBQ : !std::strcmp(e, "256") ? kBQ : -1;
+}
 // The plan by units if it costs less than the spans do (`spans_cost` as plan gives it, 0: not known): rows of its units, or 0.
 static int plan_units(AttnParams &p, const LaunchCost &cost, float spans_cost) {
-  if (spans_cost <= 0.f || p.cum[1] > kMaxTiles) return 0;
+  const int forced = forced_cut();
+  if (forced == 0 || p.cum[1] > kMaxTiles) return 0;
+  if (forced > 0) {
+    const UnitCost &unit = forced == kBQ ? cost.whole : cost.half;
+    float any = INFINITY;
+    const int longest = cheapest_units(Runs(p), p.Nq, forced, unit, any);
+    if (longest) cut_units(p, forced, longest, unit);
+    return longest ? forced : 0;
+  }
+  if (spans_cost <= 0.f) return 0;
   const float in_spans = cost.spans.start + cost.spans.cost * spans_cost + cost.spans.tile * float(p.span_base) +
                          cost.spans.wg * float(p.n_teams * p.team_size);
   float best = units_margin(in_spans) * in_spans;

@@ -12,6 +12,13 @@ def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (run with -m gpu)")
 
 
+@pytest.fixture(params=["spans", "128", "256"])
+def cut(request, monkeypatch):
+    """The three ways to cut a launch, whichever is chosen at its size: queries of its units, 0 in spans."""
+    monkeypatch.setenv("DF_ATTN_CUT", request.param)
+    return 0 if request.param == "spans" else int(request.param)
+
+
 def pytest_collection_modifyitems(config, items):
     # GPU tests are skipped, not failed, when no device is present and -m gpu was not asked for.
     try:

@@ -1,4 +1,6 @@
 """Parity of df_attn_fwd (through the C ABI) with the fp64 oracle on identical seeded inputs."""
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -151,14 +153,20 @@ def test_config5_long_context_sampled_rows(df):
     _sampled_parity(df, w, 64, seed=5)
 
 
-def test_two_kernel_path_without_hand_over(df, monkeypatch):
-    """DF_ATTN_HANDOVER=0 leaves the units that span boundaries cut to the second kernel instead of handing
+def test_two_kernel_path_without_hand_over(df, monkeypatch, cut):
+    """DF_ATTN_HANDOVER=0 leaves the units that are cut to the second kernel instead of handing
     their partial sums from workgroup to workgroup.  Same pieces, same order of the same arithmetic: the
     two paths agree to the last bit, and both meet the oracle (multi-tile heads cut once and several times)."""
     w = wl.small_ragged(31, H=5, d=128, T=300, hist_frames=6,
                         types=[wl.HEAD_FULL, wl.HEAD_SINK, wl.HEAD_NEIGHBOR, wl.HEAD_DUMMY, wl.HEAD_FULL], planted=[0])
-    plan = df.df_attn_plan(w.Nq, w.Nq, [w.visible_len(h) for h in range(w.H)])
-    assert plan["n_teams"] > 2 and plan["cut_units"] > 0, plan
+    lens, sinks = [w.visible_len(h) for h in range(w.H)], w.n_sink
+    rows, pieces = df.df_attn_units(w.d, False, w.Nq, w.Nq, lens, sinks)
+    assert rows == cut
+    if cut:
+        assert max(pieces) > 2, pieces
+    else:
+        plan = df.df_attn_plan(w.Nq, w.Nq, lens, sinks)
+        assert plan["n_teams"] > 2 and plan["cut_units"] > 0 and plan["max_pieces_per_unit"] > 2, plan
     out_a, score_a, lse_a = gu.run_attn(df, w)
     monkeypatch.setenv("DF_ATTN_HANDOVER", "0")
     out_b, score_b, lse_b = gu.run_attn(df, w)
@@ -246,8 +254,9 @@ def _random_case(rng):
     return H, d, Nq, Nc, lens, sinks
 
 
-@pytest.mark.parametrize("seed", range(16))
-def test_random_shapes_against_the_oracle(df, seed):
+@functools.lru_cache(maxsize=None)
+def _random_inputs(seed):
+    """A random case, its tensors, and what the oracle makes of them."""
     rng = np.random.default_rng(3000 + seed)
     H, d, Nq, Nc, lens, sinks = _random_case(rng)
     g = torch.Generator().manual_seed(3000 + seed)
@@ -261,22 +270,32 @@ def test_random_shapes_against_the_oracle(df, seed):
         off.append(off[-1] + n)
     k_p = torch.cat(kh) if off[-1] else torch.zeros(0, d, dtype=torch.bfloat16)
     v_p = torch.cat(vh) if off[-1] else torch.zeros(0, d, dtype=torch.bfloat16)
-    print(f"seed {seed}: H={H} d={d} Nq={Nq} Nc={Nc} lens={lens} sinks={sinks} plan={df.df_attn_plan(Nq, Nc, lens, sinks)}",
-          flush=True)
-    out, score = _direct(df, q, kc, vc, k_p, v_p, off, sinks, d ** -0.5)
     # the packed rows of a head are its sink rows followed by its window rows: the oracle sees them as a history
     # of exactly that length with n_sink sink keys and the rest as window
     ref, mass, _ = _oracle_direct(q, kc, vc, kh, vh, sinks, [n - s for n, s in zip(lens, sinks)], d ** -0.5)
+    return (H, d, Nq, Nc, lens, sinks), (q, kc, vc, k_p, v_p, off), ref, mass
+
+
+@pytest.mark.parametrize("seed", range(16))
+def test_random_shapes_against_the_oracle(df, cut, seed):
+    (H, d, Nq, Nc, lens, sinks), tensors, ref, mass = _random_inputs(seed)
+    units = df.df_attn_units(d, False, Nq, Nc, lens, sinks)
+    print(f"seed {seed}: H={H} d={d} Nq={Nq} Nc={Nc} lens={lens} sinks={sinks} plan={df.df_attn_plan(Nq, Nc, lens, sinks)} "
+          f"units={units}", flush=True)
+    assert units[0] == cut
+    out, score = _direct(df, *tensors, sinks, d ** -0.5)
     gu.check_out(out, ref, f"random shape {seed}")
     np.testing.assert_allclose(score, mass.mean(axis=1), atol=gu.F_ABS)
 
 
-def test_query_tiles_in_several_groups_with_cut_units(df):
+def test_query_tiles_in_several_groups_with_cut_units(df, monkeypatch):
     """43 query tiles on 256 workgroup slots run as teams of 15 in 3 groups; with short histories of unequal
     length the spans cut units in every group.  Every row against the oracle."""
     g = torch.Generator().manual_seed(43)
     H, d, Nq, Nc = 4, 64, 256 * 42 + 100, 200
     lens, sinks = [2000, 900, 0, 1300], [64, 0, 0, 1300]
+    monkeypatch.setenv("DF_ATTN_CUT", "spans")                 # units have one group
+    assert df.df_attn_units(d, False, Nq, Nc, lens, sinks)[0] == 0
     plan = df.df_attn_plan(Nq, Nc, lens, sinks)
     assert plan["n_groups"] > 1 and plan["takes"] > 0 and plan["consistent"] == 1, plan
     mk = lambda *s: torch.randn(*s, generator=g).to(torch.bfloat16)

@@ -17,13 +17,14 @@ def df():
     return binding
 
 
-def test_pack_attention_append_in_a_graph(df):
+def test_pack_attention_append_in_a_graph(df, cut):
     d = gu.dev()
     w = wl.small_ragged(55, H=5, d=128, T=70, hist_frames=5,
                         types=[wl.HEAD_FULL, wl.HEAD_SINK, wl.HEAD_NEIGHBOR, wl.HEAD_PACK_DUMMY, wl.HEAD_DUMMY], planted=[3, 4])
     H, dd = w.H, w.d
     sink_cap = [min(w.n_sink[h], w.Nh) for h in range(H)]
     win_cap = [w.visible_len(h) - sink_cap[h] for h in range(H)]
+    assert df.df_attn_units(dd, False, w.Nq, w.Nq, [w.visible_len(h) for h in range(H)], sink_cap)[0] == cut
     off = np.concatenate([[0], np.cumsum([s + x for s, x in zip(sink_cap, win_cap)])]).tolist()
 
     def fresh_cache():

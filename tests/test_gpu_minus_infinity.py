@@ -16,13 +16,18 @@ def df():
     return binding
 
 
-# tiles of the history (one head, 64 queries): a unit of 14 tiles cut twice, one of 4 in one piece
+# tiles of the history (one head, 64 queries): a unit of 14 tiles cut twice in spans, one of 4 in one piece
 @pytest.mark.parametrize("d,tiles,n_teams", [(128, 13, 3), (64, 13, 3), (128, 3, 1)])
 @pytest.mark.parametrize("hand_over", ["1", "0"])
-def test_a_tile_of_minus_infinity_scores(df, monkeypatch, d, tiles, n_teams, hand_over):
+def test_a_tile_of_minus_infinity_scores(df, monkeypatch, cut, d, tiles, n_teams, hand_over):
     monkeypatch.setenv("DF_ATTN_HANDOVER", hand_over)
     dev, Nq, n = gu.dev(), 64, TILE * tiles
-    assert df.df_attn_plan(Nq, TILE, [n], [TILE])["n_teams"] == n_teams
+    rows, pieces = df.df_attn_units(d, False, Nq, TILE, [n], [TILE])
+    assert rows == cut
+    if cut:
+        assert (pieces[0] > 1) == (tiles == 13), pieces
+    else:
+        assert df.df_attn_plan(Nq, TILE, [n], [TILE])["n_teams"] == n_teams
     g = torch.Generator(device=dev).manual_seed(d + tiles)
     rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
     q, kc, vc, k, vh = rnd(Nq, 1, d), rnd(TILE, 1, d), rnd(TILE, 1, d), rnd(n, d), rnd(n, d)

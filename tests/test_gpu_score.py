@@ -123,7 +123,7 @@ def test_config3_all_thirty_layers_and_the_global_classification(df):
 
 
 @pytest.mark.parametrize("seed", range(8))
-def test_scores_on_random_shapes(df, seed):
+def test_scores_on_random_shapes(df, cut, seed):
     """Seeded random head mixes, query counts, sample strides and offsets: scores to 1e-4 against the oracle."""
     rng = np.random.default_rng(4000 + seed)
     H = int(rng.choice([1, 3, 6, 12]))
@@ -143,6 +143,7 @@ def test_scores_on_random_shapes(df, seed):
         off.append(off[-1] + n)
     k_p = torch.cat(kh) if off[-1] else torch.zeros(0, dd, dtype=torch.bfloat16)
     d = gu.dev()
+    assert df.df_attn_units(dd, True, -(-(Nq - offset) // stride), Nc, lens, sinks)[0] == cut
     F = torch.full((H, 3), float("nan"), dtype=torch.float32, device=d)
     ws = torch.empty(df.df_attn_workspace_bytes(H, dd, Nq), dtype=torch.uint8, device=d)
     print(f"seed {seed}: H={H} d={dd} Nq={Nq} Nc={Nc} lens={lens} sinks={sinks} stride={stride} offset={offset}", flush=True)

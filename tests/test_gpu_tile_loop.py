@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from tests import gpu_util as gu
+from tests import test_units
 
 
 @pytest.fixture(scope="module")
@@ -60,56 +61,78 @@ def inputs(d, Nq, regions, Nc, growth):
     return q, kc, vc, kh, vh, off
 
 
-def raises(df, logits, regions, Nq, Nc):
-    """The rule for references on the pieces of the launch, from the logits of the heads in 64 bits: (raises after a piece's first
-    tile, of which some row's earlier tiles keep a hundredth of its sum, pieces of more than one tile)."""
-    tiles = [[(r0 + a, r0 + min(a + 64, n)) for r0, n in ((0, s), (s, w), (s + w, Nc)) for a in range(0, n, 64)] for s, w in regions]
-    plan = df.df_attn_plan(Nq, Nc, [s + w for s, w in regions], [s for s, _ in regions])
+def pieces_of(df, d, tiles, regions, Nq, Nc, cut):
+    """Pieces of the launch: (head, queries, first tile, tile behind the last)."""
+    lens, sinks = [s + w for s, w in regions], [s for s, _ in regions]
+    rows, count = df.df_attn_units(d, False, Nq, Nc, lens, sinks)
+    assert rows == cut
+    if cut:
+        ahead, lag = test_units.SHAPE[d, False, cut]
+        for h, k in enumerate(count):
+            n = len(tiles[h])
+            length = -(-(n - ahead - test_units.begin(k - 1, k, 0, lag)) // k)
+            starts = [test_units.begin(j, k, length, lag) for j in range(k)] + [n]
+            yield from ((h, range(Nq), begin, end) for begin, end in zip(starts, starts[1:]))
+        return
+    plan = df.df_attn_plan(Nq, Nc, lens, sinks)
     order = sorted(range(len(regions)), key=lambda h: -sum(regions[h]))
     cuts = {k * plan["line_len"] // plan["n_teams"] for k in range(1, plan["n_teams"])}
-    n_raised = n_shared = n_long = at = 0
-    rows_of = lambda group: range(group * plan["team_size"] * 256, min(Nq, (group + 1) * plan["team_size"] * 256), 32)
+    group_rows, at = plan["team_size"] * 256, 0
     for group, h in itertools.product(range(plan["n_groups"]), order):
         starts = [0] + [c - at for c in sorted(cuts) if at < c < at + len(tiles[h])]
-        for begin, end in zip(starts, starts[1:] + [len(tiles[h])]):
-            n_long += end - begin > 1
-            for row0 in rows_of(group):
-                x = logits[h][row0:row0 + 32] * math.log2(math.e)
-                ref, l = None, None
-                for a, b in tiles[h][begin:end]:
-                    if ref is None:
-                        ref, l = x[:, a:b].amax(1), torch.zeros(len(x), 4, dtype=torch.float64)
-                    key = torch.arange(b - a) % 16              # quarter of the wave that holds a key of its block of 16
-                    quarter = (key // 8 * 2 + (key // 2 % 2 == 0) * 1)
-                    share = lambda r: torch.exp2(x[:, a:b] - r[:, None]) @ torch.nn.functional.one_hot(quarter, 4).double()
-                    new = l + share(ref)
-                    lanes = torch.zeros(32, 4, dtype=torch.float64)     # of the wave's two rows that a lane has
-                    lanes[:len(x)] = new
-                    if (lanes[:16] + lanes[16:]).max() > 2.0 ** 100:
-                        up = torch.maximum(torch.maximum(x[:, a:b].amax(1), ref), ref + torch.log2(l.sum(1)))
-                        l = l * torch.exp2(ref - up)[:, None]
-                        before, ref, new = l.sum(1), up, l + share(up)
-                        n_raised += 1
-                        n_shared += bool((before > 0.01 * new.sum(1)).any())
-                    l = new
+        queries = range(group * group_rows, min(Nq, (group + 1) * group_rows))
+        yield from ((h, queries, begin, end) for begin, end in zip(starts, starts[1:] + [len(tiles[h])]))
         at += len(tiles[h])
+
+
+def raises(df, logits, regions, Nq, Nc, d, cut):
+    """The rule for references on the pieces of the launch, from the logits of the heads in 64 bits: (raises after the first tile in which
+    a wave has a key, of which some row's earlier tiles keep a hundredth of its sum, pieces of more than one tile)."""
+    tiles = [[(r0 + a, r0 + min(a + 64, n)) for r0, n in ((0, s), (s, w), (s + w, Nc)) for a in range(0, n, 64)] for s, w in regions]
+    n_raised = n_shared = n_long = 0
+    for h, queries, begin, end in pieces_of(df, d, tiles, regions, Nq, Nc, cut):
+        n_long += end - begin > 1
+        for row0, first in itertools.product(queries[::32], (0, 32) if cut == 128 else (0,)):
+            x = logits[h][row0:row0 + 32] * math.log2(math.e)
+            ref, l = None, None
+            for a, b in tiles[h][begin:end]:
+                # where the two groups of waves halve the keys, a wave has 32 of a tile
+                a, b = a + first, min(b, a + first + 32) if cut == 128 else b
+                if a >= b:
+                    continue
+                if ref is None:
+                    ref, l = x[:, a:b].amax(1), torch.zeros(len(x), 4, dtype=torch.float64)
+                key = torch.arange(b - a) % 16              # quarter of the wave that holds a key of its block of 16
+                quarter = (key // 8 * 2 + (key // 2 % 2 == 0) * 1)
+                share = lambda r: torch.exp2(x[:, a:b] - r[:, None]) @ torch.nn.functional.one_hot(quarter, 4).double()
+                new = l + share(ref)
+                lanes = torch.zeros(32, 4, dtype=torch.float64)     # of the wave's two rows that a lane has
+                lanes[:len(x)] = new
+                if (lanes[:16] + lanes[16:]).max() > 2.0 ** 100:
+                    up = torch.maximum(torch.maximum(x[:, a:b].amax(1), ref), ref + torch.log2(l.sum(1)))
+                    l = l * torch.exp2(ref - up)[:, None]
+                    before, ref, new = l.sum(1), up, l + share(up)
+                    n_raised += 1
+                    n_shared += bool((before > 0.01 * new.sum(1)).any())
+                l = new
     return n_raised, n_shared, n_long
 
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Nq,regions,Nc", SHAPES)
-def test_inputs_raise_references(df, d, Nq, regions, Nc):
-    """What the inputs of the GPU test below are made for: wherever a piece has a second tile, some reference goes up behind the
-    first; and where units have three or more tiles, some time with earlier tiles that count."""
+def test_inputs_raise_references(df, cut, d, Nq, regions, Nc):
+    """What the inputs of the GPU test below are made for, however the launch is cut: wherever a piece has a second tile, some reference
+    goes up behind the first; and where units have three or more tiles, some time with earlier tiles that count."""
     for growth in GROWTH:
         q, kc, _, kh, _, off = inputs(d, Nq, regions, Nc, growth)
         logits = [q[:, h].double() @ torch.cat([kh[off[h]:off[h + 1]], kc[:, h]]).double().t() * d ** -0.5 for h in range(len(regions))]
-        n_raised, n_shared, n_long = raises(df, logits, regions, Nq, Nc)
+        n_raised, n_shared, n_long = raises(df, logits, regions, Nq, Nc, d, cut)
         print(growth, n_raised, n_shared, n_long)
         if growth == "none":
             assert n_raised == 0
         elif growth == "steep":
-            assert (n_raised > 0) == (n_long > 0)
+            # 33 keys go up by 92 bits at d = 64: a wave with half of the keys of a tile and one before it stays below the limit
+            assert (n_raised > 0) == (n_long > 0 and (cut, d, Nq) != (128, 64, 33))
         elif Nq > 33:
             assert n_shared > 1
 
@@ -118,17 +141,18 @@ def test_inputs_raise_references(df, d, Nq, regions, Nc):
 @pytest.mark.parametrize("growth", GROWTH)
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Nq,regions,Nc", SHAPES)
-def test_regions_of_few_tiles(df, d, Nq, regions, Nc, growth):
+def test_regions_of_few_tiles(df, cut, d, Nq, regions, Nc, growth):
     dev, sink = gu.dev(), [s for s, _ in regions]
     *tensors, off = inputs(d, Nq, regions, Nc, growth)
     q, kc, vc, kh, vh = (t.to(dev) for t in tensors)
+    assert df.df_attn_units(d, False, Nq, Nc, [s + w for s, w in regions], sink)[0] == cut
     check_against_reference(df, q, kc, vc, kh, vh, off, sink)
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("stride", [16384, 40000])
 @pytest.mark.parametrize("d", [64, 128])
-def test_pieces_of_one_to_three_tiles_of_a_chunk_with_wide_rows(df, d, stride):
+def test_pieces_of_one_to_three_tiles_of_a_chunk_with_wide_rows(df, cut, d, stride):
     """Rows of the current chunk 32 KB and more apart, in pieces so short that the loop's first loads are of tiles that they do not
     have: offsets and descriptors of such tiles are not those of the chunk."""
     dev, regions, Nc = gu.dev(), [(0, 0), (65, 1), (1, 64), (0, 63)], 65
@@ -138,6 +162,7 @@ def test_pieces_of_one_to_three_tiles_of_a_chunk_with_wide_rows(df, d, stride):
     rows[0].copy_(kc)
     rows[1].copy_(vc)
     assert rows[0].stride(0) == stride
+    assert df.df_attn_units(d, False, 40, Nc, [s + w for s, w in regions], [s for s, _ in regions])[0] == cut
     check_against_reference(df, q.to(dev), *rows, kh.to(dev), vh.to(dev), off, [s for s, _ in regions])
 
 

@@ -1,5 +1,6 @@
 """Launches that are cut unit by unit (workgroups of 256 queries, or of 128 whose two groups of waves halve every tile's keys): ragged and
-single rows, tiles with keys for one half only, units in one piece and in many, every output, both ways to put pieces together."""
+single rows, tiles with keys for one half only, units in one piece and in many, every output, both ways to put pieces together; and the
+same launches in spans."""
 import numpy as np
 import pytest
 import torch
@@ -29,14 +30,17 @@ CASES = [
 ]
 
 
+@pytest.mark.parametrize("spans", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Nq,Nc,heads", CASES)
-def test_every_output_by_both_ways(df, monkeypatch, d, Nq, Nc, heads):
+def test_every_output_by_both_ways(df, monkeypatch, d, Nq, Nc, heads, spans):
+    if spans:
+        monkeypatch.setenv("DF_ATTN_CUT", "spans")
     dev, H, scale = gu.dev(), len(heads), d ** -0.5
     sinks, lens = [s for s, _ in heads], [s + w for s, w in heads]
     units = df.df_attn_units(d, False, Nq, Nc, lens, sinks)
     print(f"d {d} Nq {Nq} Nc {Nc} heads {heads}: {units}, scores {df.df_attn_units(d, True, Nq, Nc, lens, sinks)}", flush=True)
-    assert units[0] > 0
+    assert (units[0] == 0) == spans
     off = [0] + np.cumsum(lens).tolist()
     g = torch.Generator(device=dev).manual_seed(Nq + d)
     rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
@@ -92,11 +96,13 @@ def test_without_scores_the_regions_are_one(df, Nq, lens, sinks):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Nq", [128, 300])
-def test_replays_of_a_unit_in_many_pieces(df, d, Nq):
-    """Every wave looks at every piece's flag and one puts them back: a replay, whose value is the same, waits again."""
+def test_replays_of_a_unit_in_many_pieces(df, cut, d, Nq):
+    """By units every wave looks at every piece's flag and one puts them back, in spans one wave looks at all and puts them back: a
+    replay, whose value is the same, waits again."""
     dev, lens, sinks = gu.dev(), [5000, 900], [0, 0]
     rows, pieces = df.df_attn_units(d, False, Nq, 33, lens, sinks)
-    assert rows and pieces[0] > 8
+    assert rows == cut
+    assert (pieces[0] if cut else df.df_attn_plan(Nq, 33, lens, sinks)["max_pieces_per_unit"]) > 4
     g = torch.Generator(device=dev).manual_seed(d)
     rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
     q, kc, vc, kh, vh = rnd(Nq, 2, d), rnd(33, 2, d), rnd(33, 2, d), rnd(5900, d), rnd(5900, d)
