@@ -611,12 +611,10 @@ __device__ __forceinline__ f32x4 slot_load4(const __amdgpu_buffer_rsrc_t &slots,
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slots, int(lane_offset), int(offset), 1 | 16));
 }
 
-// Code of the unit of sorted head hh whose rows lie in tile qt of kBQ queries, behind those of single flags (see lost_flag()).
-__host__ __device__ __forceinline__ int lost_unit(int hh, int qt) { return 2 * kNumCU + hh * kNumCU + qt; }
-// Wait, for a bounded time, until a flag word holds this launch's value.  `code` is the flag's (or its unit's) as lost_flag() gives it.
-__device__ __forceinline__ int await_flag(const AttnParams &p, unsigned long long *flag, int code) {
+// Wait, for a bounded time, until a flag word holds this launch's value.  `number` is the flag's in lost_flag()'s numbering.
+__device__ __forceinline__ int await_flag(const AttnParams &p, unsigned long long *flag, int number) {
   int up = 0;
-  for (int spin = code == p.handoff - 2 ? kSpinLimit : 0; spin < kSpinLimit && !up; ++spin) {
+  for (int spin = number == p.handoff - 2 ? kSpinLimit : 0; spin < kSpinLimit && !up; ++spin) {
     up = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == p.epoch;
     if (!up) __builtin_amdgcn_s_sleep(16);
   }
@@ -626,8 +624,8 @@ __device__ __forceinline__ int await_flag(const AttnParams &p, unsigned long lon
 __device__ __forceinline__ void reset_flag(unsigned long long *flag) {
   __hip_atomic_store(flag, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int code) {
-  const int up = await_flag(p, flag, code);
+__device__ __forceinline__ int take_flag(const AttnParams &p, unsigned long long *flag, int number) {
+  const int up = await_flag(p, flag, number);
   reset_flag(flag);
   return up;
 }
@@ -1060,7 +1058,7 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
         int ok = 1;
         for (int sp = s_first + lane; sp < span; sp += 64) {
           const int number = sp * p.team_size + member;
-          ok &= take_flag(p, p.flags + number, UNITS ? lost_unit(piece.hh, HALF ? qt >> 1 : qt) : number);
+          ok &= take_flag(p, p.flags + number, number);
         }
         const int all_ok = __all(ok);              // the whole wave votes: inside `lane == 0` only that lane would
         if (lane == 0) lds_ok = all_ok;
@@ -1149,9 +1147,9 @@ __global__ __launch_bounds__(kThreads) void df_attn_kernel(const AttnParams p) {
         for (int sp = span - 1; sp >= s_first; --sp) {
           f32x4 st[2], v[DB * NQB];
           if constexpr (PIECEWISE) {
-            unsigned long long *flag = p.flags + sp * p.team_size + member;
-            const int code = lost_unit(piece.hh, HALF ? qt >> 1 : qt);
-            if (poison == 0.f && (next_flag != p.epoch || code == p.handoff - 2) && !await_flag(p, flag, code)) poison = NAN;
+            const int number = sp * p.team_size + member;
+            unsigned long long *flag = p.flags + number;
+            if (poison == 0.f && (next_flag != p.epoch || number == p.handoff - 2) && !await_flag(p, flag, number)) poison = NAN;
             // seen when these sums are in, and so for nothing if the piece is
             if (sp > s_first) next_flag = __hip_atomic_load(flag - p.team_size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
           }
@@ -1652,20 +1650,11 @@ static bool handover_possible(int n_wg) {
 
 // For tests of what a call returns when one of its workgroups never runs: DF_ATTN_LOST_FLAG=n in the environment
 // (looked at on every call) lets the reader of flag n give up on it at once, as it would after kSpinLimit polls.  The
-// hand-over flags are numbered by workgroup, the flags of the score sums follow from kNumCU on.
+// hand-over flags are numbered by workgroup (span * team_size + member; by units a head's pieces are as many spans, longest head
+// first, and team_size is the number of query tiles), the flags of the score sums follow from kNumCU on.
 static int lost_flag() {
   const char *e = std::getenv("DF_ATTN_LOST_FLAG");
   return e && *e ? std::clamp(std::atoi(e), -1, 2 * kNumCU) : -1;
-}
-// The same for a launch that is cut by units, which has other workgroups: of a hand-over flag, given the plan of equal spans that it is a
-// number in, the units of the rows and the head that it is raised for; of a flag of the score sums its own or the last.
-static int lost_unit_of(const AttnParams &p, int flag) {
-  if (flag < 0 || flag >= kNumCU) return flag == 2 * kNumCU ? -1 : flag;
-  const int span = flag / p.team_size;
-  if (span >= p.n_teams) return -1;
-  const int64_t end = span_begin(p, span + 1);
-  const Piece c = piece_ending_at(p, ColumnsInParams{p}, span_begin(p, span), end);
-  return c.t_end < c.n_tiles ? lost_unit(c.hh, c.grp * p.team_size + flag % p.team_size) : -1;
 }
 
 // A flag value that neither stale workspace contents nor an earlier launch hold: a counter run through a
@@ -1680,7 +1669,7 @@ static unsigned long long next_epoch() {
 }
 
 template <int D, bool SCORE_ONLY, bool UNITS, bool HALF>
-static df_status launch_planned(AttnParams &p, void *workspace, float *score_out, hipStream_t st, int lost) {
+static df_status launch_planned(AttnParams &p, void *workspace, float *score_out, hipStream_t st) {
   using S = Slot<D, HALF ? 1 : 2>;
   // One team of several workgroups has no cut unit: it waits for nothing and needs no two compute units at a time.  Its
   // scores are left to the second kernel, so that this stays so: 16.5 against 15.7 us with 2 workgroups, 19.6 against
@@ -1688,7 +1677,7 @@ static df_status launch_planned(AttnParams &p, void *workspace, float *score_out
   const int n_wg = p.n_teams * p.team_size;
   const bool together = (p.n_teams > 1 || (score_out && n_wg == 1)) && handover_possible(n_wg);
   if (together) {
-    p.handoff = 2 + (UNITS && lost < 2 * kNumCU ? std::min(lost, kNumCU + n_wg - 1) : lost);
+    p.handoff = 2 + lost_flag();
     p.epoch = next_epoch();
   } else {
     count_cut_units(p, UNITS);
@@ -1722,11 +1711,10 @@ template <int D, bool SCORE_ONLY>
 static df_status launch(AttnParams &p, void *workspace, float *score_out, hipStream_t st) {
   float spans_cost;
   if (df_status s = plan(p, &spans_cost)) return s;
-  const int lost = lost_flag(), lost_unit = lost_unit_of(p, lost);
   switch (plan_units(p, kLaunchCost<D, SCORE_ONLY>, spans_cost)) {
-    case kHalfBQ: return launch_planned<D, SCORE_ONLY, true, true>(p, workspace, score_out, st, lost_unit);
-    case kBQ: return launch_planned<D, SCORE_ONLY, true, false>(p, workspace, score_out, st, lost_unit);
-    default: return launch_planned<D, SCORE_ONLY, false, false>(p, workspace, score_out, st, lost);
+    case kHalfBQ: return launch_planned<D, SCORE_ONLY, true, true>(p, workspace, score_out, st);
+    case kBQ: return launch_planned<D, SCORE_ONLY, true, false>(p, workspace, score_out, st);
+    default: return launch_planned<D, SCORE_ONLY, false, false>(p, workspace, score_out, st);
   }
 }
 
