@@ -696,9 +696,11 @@ __device__ __forceinline__ f32x4 exchange_halves(f32x4 *from_group0, f32x4 *from
   lds_barrier();                                   // what follows goes where these lie
   return st;
 }
-// A whole slot of a workgroup with half the queries, all loads in flight at once (as load_slot_through).
+// A whole slot of a workgroup with half the queries, all loads in flight at once (as load_slot_through).  Nothing in the loads says that
+// they may not go out before the look at the flag that the sums are there; the empty statement does.
 template <int D>
 __device__ __forceinline__ void load_half_slot(const AttnParams &p, int64_t slot, int tid, f32x4 &st, f32x4 (&v)[D / 16]) {
+  asm volatile("" ::: "memory");
   const __amdgpu_buffer_rsrc_t slots = all_slots<D>(p);
   const unsigned at = unsigned(slot) * unsigned(sizeof(float) * Slot<D, 1>::kFloats);
   st = slot_load4(slots, unsigned(Slot<D, 1>::stats_reader(tid, 0)) * 16u, at);

@@ -40,3 +40,13 @@ def test_wait_states_before_a_scalar_base_is_read(file, code, names):
             assert states >= 5, (file, x)
             break
         states += 1 + int(x.split()[1]) if x.startswith("s_nop") else 1
+
+
+def test_slots_are_loaded_behind_the_look_at_their_flag():
+    """Every function that loads a whole slot either does so in one statement that clobbers memory or begins with one."""
+    text = open(os.path.join(CSRC, "df_attn.hip")).read()
+    bodies = re.findall(r"void (load_(?:half_)?(?:slot|stats)\w*)(?:<\d+>)?\([^;{]*\{\n(.*?)\n\}", text, flags=re.S)
+    assert sorted(name for name, _ in bodies) == ["load_half_slot", "load_slot_through", "load_slot_through", "load_stats_through"]
+    for name, body in bodies:
+        before = body.index('"memory"')
+        assert "slot_load4" not in body[:before], name
