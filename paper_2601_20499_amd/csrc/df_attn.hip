@@ -1357,7 +1357,7 @@ static size_t workspace_bytes(int H, int d, int Nq) {
 // 128, attention and scores): above the best number measured the launches take 1.1 % on average, where all spans that a device
 // holds (and for short ones the numbers that stamps inside the kernel had given) take 2.6 %.  Of 302 other launches (one query to 3 000,
 // 2 to 64 heads, 0.3 to 150 GFLOP) 216 get another number than all spans and take 7.5 % less on average, from 31 % less to 10 %
-// more.  d = 64 and scoring use the same numbers.  Choosing takes the host 1.6 us on average and 6 at most (3 000 launches of
+// more.  d = 64 and scoring use the same numbers.  Choosing the spans (not planning by units: see cheapest_units) takes the host 1.6 us on average and 6 at most (3 000 launches of
 // 2 to 64 heads, 64 to 2048 tokens a frame, a 2.7 GHz Xeon; walked span by span and without kMaxWalk 3.5 and 16; 64 heads of a few
 // tiles each 7 against 42).
 constexpr float kPieceCost = 2.9f, kGiveCost = 0.7f, kPollCost = 2.6f, kFoldCost = 0.9f, kSpanCost = 0.00024f;
@@ -1507,56 +1507,83 @@ static df_status plan(AttnParams &p, float *spans_cost) {
 // and equal spans keep all compute units busy to the end; none from kMaxUnitLaunch on.
 constexpr float kMaxUnitLaunch = 110.f;
 static float units_margin(float us) { return us > kMaxUnitLaunch ? 0.f : 0.97f - 0.002f * std::max(0.f, us - 50.f); }
-constexpr int kMaxUnitWalk = 512;
 constexpr int kMaxTiles = 0xffff;      // of a unit, for HeadRec::cut
 
-// Heads of the same length, longest first.
+// Heads whose units have the same number of tiles, longest first (heads are sorted by keys: a ragged sink region can make a unit a tile
+// longer than the one before).
 struct Runs {
   struct { int n, heads; } run[kMaxHeads];
-  int n_runs = 0;
-  explicit Runs(const AttnParams &p) {
+  int n_runs = 0, heads, first_n;        // first_n: tiles of a unit of the head with the most keys
+  explicit Runs(const AttnParams &p) : heads(p.H), first_n(p.cum[1]) {
     for (int hh = 0; hh < p.H; ++hh) {
       const int n = p.cum[hh + 1] - p.cum[hh];
-      if (n_runs == 0 || run[n_runs - 1].n != n) run[n_runs++] = {n, 0};
-      ++run[n_runs - 1].heads;
+      int r = n_runs;
+      while (r > 0 && run[r - 1].n < n) --r;
+      if (r > 0 && run[r - 1].n == n) {
+        ++run[r - 1].heads;
+        continue;
+      }
+      std::copy_backward(run + r, run + n_runs, run + n_runs + 1);
+      run[r] = {n, 1};
+      ++n_runs;
     }
   }
 };
+// Tiles of the shortest piece but the last of `count` > 1 that a unit of `n` is cut into (less than one: there are too many).
+static int piece_length(int n, int count, const UnitCost &cost) {
+  return (n - cost.ahead - UnitPieces{count, 0, cost.lag}.begin(count - 1) + count - 1) / count;
+}
 // The fewest pieces of a unit of `n` tiles, the shortest but the last of at most `longest`; none if the last would be empty.
 // (`from`: a number that is known to be too few or just right.)
 static UnitPieces pieces(int n, int longest, const UnitCost &cost, int from = 1) {
   UnitPieces u{from, longest, cost.lag};
   while (u.count <= kNumCU && u.begin(u.count - 1) + longest + cost.ahead < n) ++u.count;
-  const int rest = n - cost.ahead - UnitPieces{u.count, 0, cost.lag}.begin(u.count - 1);
-  u.length = u.count == 1 ? std::max(1, n - cost.ahead) : (rest + u.count - 1) / u.count;
+  u.length = u.count == 1 ? std::max(1, n - cost.ahead) : piece_length(n, u.count, cost);
   if (u.count > kNumCU || (u.count > 1 && (u.length < 1 || u.begin(u.count - 1) >= n))) u.count = 0;
   return u;
 }
 // Most tiles of a piece of the cheapest cut into units of `rows` queries, if that costs less than `best` (which it then replaces), else 0.
+// From whole units on, each time with the longest pieces with which the unit that was the slowest can be part of a cheaper cut: what lies in
+// between leaves it too slow.  Of the units that are whole only the longest can be the slowest.  Whole units are those of the head with the
+// most keys: where others are a tile longer, to leave these whole too is a little cheaper by the model but takes 3 to 5 % longer in launches of
+// few tiles (58 queries and 40 heads 14.1 -> 15.7 us; 14 launches of one or two lengths 1.02 on average while attending).
+// Walked so, planning by units takes the host 0.9 us with one length, 2.2 with 12 and 5.3 with 64 on average (2, 6 and 12 at most) besides the
+// 1.5 to 2.5 for the spans (400 launches each, a 2.7 GHz Xeon); with all heads walked for each length of piece, 3 % apart, and given up after 512
+// of them it took 2, 14 and 15 (12, 26 and 28), and where heads have 20 to 64 lengths the cuts that it found took 13 to 29 % more time.
 static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &cost, float &best) {
   const int m = (Nq + rows - 1) / rows, most = kNumCU / m;
-  int best_longest = 0, walked = 0, pieces_of[kMaxHeads];
-  std::fill_n(pieces_of, runs.n_runs, 1);
-  // from whole units on, each time with shorter pieces for those that have the longest (3 % shorter at least)
-  for (int longest = pieces(runs.run[0].n, kMaxTiles, cost).length; longest > 0 && walked < kMaxUnitWalk;) {
-    int spans = 0, tiles_of[kMaxHeads], most_tiles = 0;
-    for (int r = 0; r < runs.n_runs; ++r, ++walked) {
-      const UnitPieces u = pieces(runs.run[r].n, longest, cost, pieces_of[r]);
-      pieces_of[r] = u.count;
-      tiles_of[r] = u.count == 1 ? runs.run[r].n : u.length;
-      most_tiles = std::max(most_tiles, u.length);
-      spans += u.count > 0 ? u.count * runs.run[r].heads : most + 1;
-    }
-    if (spans > most) break;
+  struct { int count, length; float fold; } cut[kMaxHeads];      // of the first n_cut runs; the others are whole
+  int best_longest = 0, n_cut = 0, spans = runs.heads;
+  for (int longest = std::max(1, runs.first_n - cost.ahead);;) {
+    for (; n_cut < runs.n_runs && runs.run[n_cut].n - cost.ahead > longest; ++n_cut) cut[n_cut] = {1, INT32_MAX, 0.f};
+    for (int r = 0; r < n_cut; ++r)
+      if (cut[r].length > longest) {
+        const UnitPieces u = pieces(runs.run[r].n, longest, cost, cut[r].count);
+        if (u.count == 0) return best_longest;
+        spans += (u.count - cut[r].count) * runs.run[r].heads;
+        cut[r] = {u.count, u.length, cost.cut + cost.fold * float(u.count - 1)};
+      }
+    if (spans > most) return best_longest;
     const float tile = cost.tile * (1.f + cost.crowd * float(spans * m)) * (2 * Nq <= rows ? cost.few : 1.f);
-    float slowest = 0.f;
-    for (int r = 0; r < runs.n_runs; ++r)
-      slowest = std::max(slowest, tile * float(tiles_of[r]) + (pieces_of[r] > 1 ? cost.cut + cost.fold * float(pieces_of[r] - 1) : 0.f));
-    const float t = cost.start + cost.wg * float(spans * m) + slowest;
-    if (t < best) { best = t; best_longest = longest; }
-    longest = most_tiles - 1 - most_tiles / 32;
+    const float others = cost.start + cost.wg * float(spans * m);
+    int slowest = n_cut;                                         // a run that is cut, or the first one that is not
+    float t = n_cut < runs.n_runs ? tile * float(runs.run[n_cut].n) : 0.f;
+    for (int r = 0; r < n_cut; ++r) {
+      const float t_r = tile * float(cut[r].length) + cut[r].fold;
+      if (t_r > t) { t = t_r; slowest = r; }
+    }
+    if (others + t < best) { best = others + t; best_longest = longest; }
+    // the fewest pieces with which that unit alone would leave a cheaper cut possible, and the longest pieces that take as many
+    int count = slowest < n_cut ? cut[slowest].count : 1;
+    int length = slowest < n_cut ? cut[slowest].length : runs.run[slowest].n - cost.ahead;
+    for (float t_slowest = INFINITY; others + t_slowest >= best;) {
+      longest = length - 1;
+      const float fold = cost.cut + cost.fold * float(count++);
+      length = piece_length(runs.run[slowest].n, count, cost);
+      if (length < 1 || others + tile + fold >= best) return best_longest;
+      t_slowest = tile * float(length) + fold;
+    }
   }
-  return best_longest;
 }
 // Cuts the launch into units of `rows` queries, in pieces of at most `longest` tiles.
 static void cut_units(AttnParams &p, int rows, int longest, const UnitCost &cost) {
