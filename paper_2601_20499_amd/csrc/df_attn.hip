@@ -578,26 +578,26 @@ __device__ __forceinline__ void reduce_masses(const AttnParams &p, float *lds_re
   }
   lds_barrier();
   if (tid < 2) {
-    float acc = 0.f;
-    for (int w = 0; w < kWaves; ++w) acc += lds_red[2 * w + tid];
+    double acc = 0.0;
+    for (int w = 0; w < kWaves; ++w) acc += double(lds_red[2 * w + tid]);
     // written through: the sums of all units may be read by another workgroup of this launch
-    __hip_atomic_store(p.part + (int64_t(h) * p.n_qtiles + qt) * 4 + tid, acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(p.part + (int64_t(h) * p.n_qtiles + qt) * 4 + tid, float(acc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   lds_barrier();
 }
 
-// F[h] = (sum_a, sum_b - sum_a, n - sum_b) / n over the head's query tiles, in tile order.
-__device__ __forceinline__ void store_score(const AttnParams &p, int h, float a, float b) {
-  const float n = float(p.Nq);                     // quotients are rounded once, products with 1 / n twice (5.5e-8 -> 4.5e-8 over 80 launches)
-  p.score[3 * h] = a / n;
-  p.score[3 * h + 1] = (b - a) / n;
-  p.score[3 * h + 2] = (n - b) / n;
+// F[h] = (sum_a, sum_b - sum_a, n - sum_b) / n over the head's query tiles, in tile order: in 64 bits, so that all of it is rounded once.
+__device__ __forceinline__ void store_score(const AttnParams &p, int h, double a, double b) {
+  const double n = double(p.Nq), inv = 1.0 / n;
+  p.score[3 * h] = float(a * inv);
+  p.score[3 * h + 1] = float((b - a) * inv);
+  p.score[3 * h + 2] = float((n - b) * inv);
 }
 __device__ __forceinline__ void finish_score(const AttnParams &p, int h) {
-  float a = 0.f, b = 0.f;
+  double a = 0.0, b = 0.0;
   for (int t = 0; t < p.n_qtiles; ++t) {
-    a += p.part[(int64_t(h) * p.n_qtiles + t) * 4];
-    b += p.part[(int64_t(h) * p.n_qtiles + t) * 4 + 1];
+    a += double(p.part[(int64_t(h) * p.n_qtiles + t) * 4]);
+    b += double(p.part[(int64_t(h) * p.n_qtiles + t) * 4 + 1]);
   }
   store_score(p, h, a, b);
 }
@@ -643,10 +643,10 @@ __device__ __forceinline__ void finish_all_scores(const AttnParams &p, float2 *b
   __syncthreads();
   if (tid < n_wg && !take_flag(p, p.done + tid, kNumCU + tid)) *all_up = 0;
   __syncthreads();
-  const float poison = *all_up ? 0.f : NAN;
+  const double poison = *all_up ? 0.0 : double(NAN);
   static_assert(PAIRS >= kMaxHeads, "one tile of every head");
   const int tiles_at_once = PAIRS / p.H;
-  float a = 0.f, b = 0.f;
+  double a = 0.0, b = 0.0;
   for (int t0 = 0; t0 < p.n_qtiles; t0 += tiles_at_once) {
     const int n = min(tiles_at_once, p.n_qtiles - t0);
     for (int i = tid; i < p.H * n; i += kThreads) {
@@ -659,8 +659,8 @@ __device__ __forceinline__ void finish_all_scores(const AttnParams &p, float2 *b
     __syncthreads();
     if (tid < p.H)
       for (int t = 0; t < n; ++t) {
-        a += buf[tid * n + t].x;
-        b += buf[tid * n + t].y;
+        a += double(buf[tid * n + t].x);
+        b += double(buf[tid * n + t].y);
       }
     __syncthreads();
   }

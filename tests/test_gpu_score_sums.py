@@ -54,3 +54,28 @@ def test_scores_and_rows_by_both_ways(df, monkeypatch, H, d, Nq, Nc):
         s, n = sink[h], lens[h]
         R = torch.stack([p[:, :s].sum(), p[:, s:n].sum(), p[:, n:].sum()]) / Nq
         assert (F[h] - R).abs().max() <= gu.F_ABS and (F2[h] - R).abs().max() <= gu.F_ABS
+
+
+@pytest.mark.parametrize("hand_over", ["1", "0"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_sums_over_query_tiles_are_rounded_once(df, monkeypatch, d, hand_over):
+    """The scores are those of the units' sums, which the launch leaves in the workspace ([H, query tiles, 4] floats), added up in 64 bits and
+    rounded to 32 once: 131 of them in 32 bits are off by several times that."""
+    monkeypatch.setenv("DF_ATTN_HANDOVER", hand_over)
+    dev, H, tiles, Nc = gu.dev(), 5, 131, 33
+    Nq, lens, sinks = 256 * (tiles - 1) + 7, [110, 0, 90, 300, 64], [40, 0, 90, 0, 1]
+    off = [0] + np.cumsum(lens).tolist()
+    g = torch.Generator(device=dev).manual_seed(d)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
+    q, kc, kh = rnd(Nq, H, d), rnd(Nc, H, d), rnd(off[-1], d)
+    ws = torch.empty(df.df_attn_workspace_bytes(H, d, Nq), dtype=torch.uint8, device=dev)
+    assert df.df_attn_units(d, True, Nq, Nc, lens, sinks)[0] == 0 and df.df_attn_units(d, False, Nq, Nc, lens, sinks)[0] == 0
+    out, F, F2 = torch.empty_like(q), torch.empty(H, 3, device=dev), torch.empty(H, 3, device=dev)
+    for score, launch in ((F, lambda: df.df_attn_fwd(q, kc, kc, kh, kh, off, sinks, out, d ** -0.5, score_out=F, workspace=ws)),
+                          (F2, lambda: df.df_head_score(q, kc, kh, off, sinks, F2, d ** -0.5, q_sample_stride=1, workspace=ws))):
+        launch()
+        torch.cuda.synchronize()
+        sums = ws[:H * tiles * 16].view(torch.float32).view(H, tiles, 4)[..., :2].double().sum(1)
+        want = torch.stack([sums[:, 0], sums[:, 1] - sums[:, 0], Nq - sums[:, 1]], 1) / Nq
+        # half a unit in the last place, and what 64 bits lose in differences
+        assert ((score.double() - want).abs() <= 2.0 ** -24 * want.abs() + 1e-14).all(), ((score.double() - want) / want).abs().max()
