@@ -1,8 +1,13 @@
 """The extension that marshals the frequent calls: for ordinary arguments it makes the same call as the Python code does, and
 it leaves everything else to that code."""
+import os
+import sys
+import sysconfig
+
 import pytest
 import torch
 
+from paper_2601_20499_amd import build
 from tests import gpu_util as gu
 
 
@@ -23,6 +28,32 @@ def test_what_is_not_ordinary_is_left_to_python(b):
     assert native.attn(q) is None and native.append() is None
     with pytest.raises(TypeError):
         native.setup(1)
+
+
+def test_the_extension_is_this_interpreters(b):
+    assert b._marshal().__file__ == build.MARSHAL and build.MARSHAL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+@pytest.mark.parametrize("lacking", ["torch", "g++", "headers", "nothing"])
+def test_the_library_is_built_where_the_extension_cannot_be(monkeypatch, tmp_path, capsys, lacking):
+    """Only hipcc is needed for the library; what is missing for the extension is told, and none of an earlier build stays."""
+    commands = []
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **_: commands.append(cmd[0]))
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.x.so"))
+    for old in ("_marshal.x.so", "_marshal.so"):
+        (tmp_path / old).write_text("")
+    if lacking == "torch":
+        monkeypatch.setitem(sys.modules, "torch", None)
+    elif lacking == "g++":
+        monkeypatch.setattr(build.shutil, "which", lambda _: None)
+    elif lacking == "headers":
+        monkeypatch.setattr(build, "marshal_includes", lambda _: [str(tmp_path)])
+    assert build.build_library(verbose=False) == build.LIB
+    assert [os.path.basename(c) for c in commands] == ["hipcc"] + ["g++"] * (lacking == "nothing")
+    assert os.listdir(tmp_path) == []
+    told = capsys.readouterr().out
+    assert (told == "") == (lacking == "nothing") and (lacking in ("nothing", "headers") or lacking in told)
 
 
 def test_lists_shorter_than_the_heads_are_refused(b):
