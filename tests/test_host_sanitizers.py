@@ -12,7 +12,7 @@ import pytest
 from paper_2601_20499_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-HOST_TESTS = ["tests/test_abi.py", "tests/test_workloads_vs_oracle.py"]
+HOST_TESTS = ["tests/test_abi.py", "tests/test_workloads_vs_oracle.py", "tests/test_units.py", "tests/test_small_plans.py"]
 SANITIZE = ["-g", "-fno-omit-frame-pointer", "-shared-libsan",
             "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
             "-Xarch_host", "-fno-sanitize-recover=undefined"]
