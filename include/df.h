@@ -94,8 +94,9 @@ df_status df_head_context(int32_t head_type, int32_t T, int32_t sink_frames,
  * all others are done, both with a bounded wait: should a workgroup never get
  * to run (compute units taken away from the process), what depends on it comes
  * out as NaN after some seconds instead of hanging the device - the unit's rows
- * in out and lse_out, the head's or, where the first workgroup gave up, all
- * heads' score_out.  A captured graph whose replay ended that way has to be
+ * in out and lse_out (where several waves wait for a piece and it comes between
+ * two of them giving up, the rows of some; what is not NaN is right), the head's
+ * or, where the first workgroup gave up, all heads' score_out.  A captured graph whose replay ended that way has to be
  * captured again (the late workgroup's flag may still be up in the workspace).
  * Two calls that run on the device at the same time (different streams) can
  * bring that about for each other: workgroups of both that wait hold compute

@@ -4,8 +4,8 @@ Every function here has the name of the C entry point it calls and does no
 arithmetic of its own: tensors are passed as raw device pointers plus sizes,
 host bookkeeping arrays as ctypes arrays.  There is no CPU fallback: if the
 HIP library is missing the import of this module fails.  The calls of a generation loop go through a small extension
-(csrc/df_marshal.cpp) that marshals the ordinary kinds of arguments in native code: an attention call is issued in 5.0 us
-instead of 9.4, a small append in 4.1 instead of 6.1, a small pack in 3.8 instead of 7.5.
+(csrc/df_marshal.cpp) that marshals the ordinary kinds of arguments in native code: attention of 64 queries is issued in 3.7 us
+instead of 8.8, of 1170 in 4.7 instead of 9.4, a small append in 3.1 instead of 5.2, a small pack in 3.3 instead of 6.9.
 """
 from __future__ import annotations
 

@@ -34,7 +34,7 @@
 // launches pay for is not tiles: a second piece in a span cost a workgroup 7 us besides its tiles, and those that
 // waited for its sums with it; a piece of 256 queries hands on 136 KB, one of 128 queries 72, and a unit needs
 // half as many pieces for the same number of workgroups; and the first load goes out 0.2 us earlier.  One box, spans -> units: 64
-// queries 14.4 -> 10.0 us, 1170 queries 38.1 -> 35.3 (with what came after 9.3 and 27.1), 393 queries and 5 heads 29.0 -> 20.0, 266 queries and long histories
+// queries 14.4 -> 10.0 us, 1170 queries 38.1 -> 35.3 (with what came after 9.4 and 27.8), 393 queries and 5 heads 29.0 -> 20.0, 266 queries and long histories
 // 50.0 -> 31.9, 478 sampled queries 21.1 -> 18.1; 80 random launches 14 % less on average, the worst 1.2 % more.
 //
 // MFMA mapping.  Scores are computed transposed, S^T = K Q^T, with
@@ -508,8 +508,9 @@ __device__ __forceinline__ uint2 output4(const f32x4 &o, float inv) {
 // 610.0 -> 601.9; a launch of 64 queries 15.1 -> 15.8.
 // 16-byte chunk c of row r lies at position c ^ (r mod chunks per row).  The reads are then free of bank conflicts; the
 // 8-byte writes are not: 4 cycles each (264,192 in a 1280x720 launch, 0.03 % of the CU-busy cycles).
-// Units of 256 queries write them through to memory, so that a launch does not end with writing its rows back from L2.  In L2 -> through, one box:
-// 832x480 278.8 -> 276.6 us, with an elementwise kernel that reads the rows behind it 283.4 -> 281.8; 909 queries of 40 heads 32.0 -> 31.5.
+// Units of 256 queries write them through to memory, so that a launch does not end with writing its rows back from L2.  In L2 -> through, medians of
+// 40 turns on one box: 909 queries of 40 heads 38.6 -> 37.8 us, with an elementwise kernel that reads the rows behind it 43.9 -> 43.3; 2340 of 12
+// heads 82.1 -> 81.6; 832x480 258.5 -> 257.1 and 261.5 -> 261.0, which the turns' own spread (quartiles 0.8 apart) hardly tells apart.
 // The rows of units of 128, the smaller launches, stay in L2, where the next kernel finds them: 200 queries and that kernel 13.0 us, through 13.15.
 template <int D, int NQB>
 __device__ __forceinline__ void store_output(const AttnParams &p, int h, int row0, unsigned char *buf, int lane,
@@ -1504,7 +1505,9 @@ static df_status plan(AttnParams &p, float *spans_cost) {
 }
 
 // Share of the spans' time `us` that units may take: less of longer launches, in which the clock under load and not these sums decides
-// and equal spans keep all compute units busy to the end; none from kMaxUnitLaunch on.
+// and equal spans keep all compute units busy to the end; none from kMaxUnitLaunch on.  Scoring, which the issue of instructions bounds, has
+// nothing to gain there either: 1170 sampled queries of 12 heads, 8 cached frames (spans of 64 tiles) 65.8 us in spans and 65.1 by units, 12 85.1 and
+// 84.3, 21 (139 tiles) 128.8 and 128.1, 32 181.9 and 183.3.
 constexpr float kMaxUnitLaunch = 110.f;
 static float units_margin(float us) { return us > kMaxUnitLaunch ? 0.f : 0.97f - 0.002f * std::max(0.f, us - 50.f); }
 constexpr int kMaxTiles = 0xffff;      // of a unit, for HeadRec::cut

@@ -33,8 +33,9 @@ cached frames, 32x32x16 with such a loop -> 16x16x32 with such a loop -> this: 2
 piece, a reference that has to go up) lies behind branches in two subroutines.
 
 The statement carries its own wait states (the compiler's hazard recogniser does not look into asm):
-  * an accumulator is only reused eight MFMAs later (sixteen in the second product at d = 128): no
-    dependent MFMAs back to back;
+  * an accumulator is only reused eight MFMAs later (sixteen in the second product at d = 128), with half a tile four later in the
+    first product and once a tile in the second: no dependent MFMAs back to back (the three in between hold the
+    matrix core for 12 passes, and what a 4-pass MFMA writes is there after 8 wait states);
   * a vector instruction keeps 8 wait states from a 4-pass MFMA whose result it reads or overwrites (mfma_phase);
   * no instruction uses the result of an exponential or logarithm issued right before it;
   * two idle cycles (s_nop 1) between a comparison and the selection that reads vcc, and around lane swaps;
