@@ -345,7 +345,8 @@ def main():
     app_tokens = sum(min(w.Nc, st["win_cap"][h]) for h in range(H))
     append_bytes = 2 * 2 * app_tokens * w.d * 2
     pack_ms, append_ms = statistics.fmean(per["pack"]), statistics.fmean(per["append"])
-    plan = df.df_attn_plan(w.Nq, w.Nc, [w.visible_len(h) for h in range(H)], [min(w.n_sink[h], w.Nh) for h in range(H)])
+    lens, sinks = [w.visible_len(h) for h in range(H)], [min(w.n_sink[h], w.Nh) for h in range(H)]
+    plan, units = df.df_attn_plan(w.Nq, w.Nc, lens, sinks), df.df_attn_units(w.d, False, w.Nq, w.Nc, lens, sinks)
 
     result = {
         "metric": "head-heterogeneous attention TFLOP/s + ms per chunk-layer; % bf16 MFMA peak",
@@ -369,6 +370,7 @@ def main():
         "breakdown_ms": {k: stats(v) for k, v in per.items()},
         "attn_ms_per_chunk_layer": round(attn_ms, 4),
         "attn_plan": {k: plan[k] for k in ("n_qtiles", "team_size", "n_groups", "n_teams", "workgroups", "cut_units", "busy")},
+        "attn_units": {"queries": units[0], "pieces": units[1]} if units[0] else None,     # by units, and attn_plan is not what runs
         "pack_GBps": round(pack_bytes / (pack_ms * 1e-3) / 1e9, 1) if pack_bytes else None,
         "append_GBps": round(append_bytes / (append_ms * 1e-3) / 1e9, 1) if append_bytes else None,
         "pack_frac_hbm": round(pack_bytes / (pack_ms * 1e-3) / 1e9 / PEAK_HBM_GBS, 4) if pack_bytes else None,
