@@ -1550,9 +1550,9 @@ static UnitPieces pieces(int n, int longest, const UnitCost &cost, int from = 1)
 // between leaves it too slow.  Of the units that are whole only the longest can be the slowest.  Whole units are those of the head with the
 // most keys: where others are a tile longer, to leave these whole too is a little cheaper by the model but takes 3 to 5 % longer in launches of
 // few tiles (58 queries and 40 heads 14.1 -> 15.7 us; 14 launches of one or two lengths 1.02 on average while attending).
-// Walked so, planning by units takes the host 0.9 us with one length, 2.2 with 12 and 5.3 with 64 on average (2, 6 and 12 at most) besides the
-// 1.5 to 2.5 for the spans (400 launches each, a 2.7 GHz Xeon); with all heads walked for each length of piece, 3 % apart, and given up after 512
-// of them it took 2, 14 and 15 (12, 26 and 28), and where heads have 20 to 64 lengths the cuts that it found took 13 to 29 % more time.
+// Walked so, planning by units takes the host 0.8 us with heads of one length, 2.2 with 12 and 5.9 with 64 on average (3, 7 and 17 at most) besides
+// the 1.5 to 2.5 for the spans (400 launches each, a 2.7 GHz Xeon); with all heads walked for each length of piece, 3 % apart, and given up after 512
+// of them it took 2.1, 16 and 17 (14, 41 and 40), and where heads have 20 to 64 lengths the cuts that it found took 13 to 29 % more time.
 static int cheapest_units(const Runs &runs, int Nq, int rows, const UnitCost &cost, float &best) {
   const int m = (Nq + rows - 1) / rows, most = kNumCU / m;
   struct { int count, length; float fold; } cut[kMaxHeads];      // of the first n_cut runs; the others are whole

@@ -17,15 +17,20 @@ def df():
 
 
 # (heads, d, queries, keys of the chunk): one query, one team; a ragged last tile; one tile more than a chunk of the
-# sums holds at 64 heads (130 tiles at d = 128, 65 at d = 64, so two and three chunks); more units than workgroups
+# sums holds at 64 heads (130 tiles at d = 128, 65 at d = 64, so two and three chunks); more units than workgroups, which are always
+# cut into spans, the others as they are and in spans
+@pytest.mark.parametrize("spans", [False, True])
 @pytest.mark.parametrize("H,d,Nq,Nc", [(1, 128, 1, 1), (3, 64, 300, 65), (5, 128, 511, 200), (64, 128, 130 * 256 + 1, 33),
                                        (64, 64, 130 * 256 + 31, 33)])
-def test_scores_and_rows_by_both_ways(df, monkeypatch, H, d, Nq, Nc):
+def test_scores_and_rows_by_both_ways(df, monkeypatch, H, d, Nq, Nc, spans):
+    if spans:
+        monkeypatch.setenv("DF_ATTN_CUT", "spans")
     dev, n_sink, n_win = gu.dev(), 40, 70
     g = torch.Generator(device=dev).manual_seed(H * d + Nq)
     rnd = lambda *s: torch.randn(*s, generator=g, device=dev).to(torch.bfloat16)
     lens = [n_sink + n_win if h % 3 != 1 else 0 for h in range(H)]
     sink = [n_sink if n else 0 for n in lens]
+    assert (df.df_attn_units(d, False, Nq, Nc, lens, sink)[0] == 0) == (spans or H == 64)
     off = [0] + np.cumsum(lens).tolist()
     q, kc, vc = rnd(Nq, H, d), rnd(Nc, H, d), rnd(Nc, H, d)
     kh, vh = rnd(off[-1], d), rnd(off[-1], d)
